@@ -13,7 +13,8 @@
 //     32 KB, four LDS stages, filled by direct global->LDS loads three chunks ahead;
 //   - the wave's rows of the hidden block come from the fragment-ordered copy (one MFMA B operand =
 //     1 KB contiguous, already multiplied by log2 e) straight into registers by loads the compiler
-//     does not track, one chunk (four operands) ahead; nothing of them touches LDS;
+//     does not track, each into the registers its MFMAs read, right behind the last MFMA that reads
+//     the operand before it (24 MFMAs ahead of its use); nothing of them touches LDS;
 //   - one barrier per chunk, in the MIDDLE of its 32 MFMAs (it publishes the next chunk and frees
 //     the stage of the one before); the loads are issued one by one between the MFMAs; every wave
 //     issues the same loads in the same order, so all vmcnt immediates are compile-time figures
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void outproj_rowstream_kernel(ModelDev m,
         };
 
         // ---- prologue: chunks 0 and 1, the B operands of chunk 0, chunk 2
-        bf16x8 dop[kDOperands], dnext[kDOperands];
+        bf16x8 dop[kDOperands];
         next_request();
 #pragma unroll
         for (int q = 0; q < kDmaPerChunk; ++q) request_piece(q);
@@ -200,14 +201,19 @@ __global__ __launch_bounds__(kThreads) void outproj_rowstream_kernel(ModelDev m,
         // through exp-and-add and the block restarts from the tile's constants.
         //
         // Loads of a wave per chunk, in program order (the slot is the MFMA they follow):
-        //   d0'@1  d1'@5  d2'@9  d3'@13  [barrier before MFMA 16]  w0@17  w1@20  w2@23  w3@26  c@29
-        // dk' = B operand k of the NEXT chunk into a second set of registers (moved over at the end of
-        // the chunk: a full chunk of time to arrive), w0..w3, c = weights and constants of chunk c+3 into
-        // the stage of chunk c-1.  Nine loads.  The barrier waits for chunk c+1, whose last load (c@29 of
-        // chunk c-2) is followed by the nine of chunk c-1 and four of this one: 13.  At the end of the
-        // chunk the next operands have landed once only this chunk's five direct-to-LDS loads are
-        // outstanding.  The prologue's order and its wait (everything but chunk 2 landed) give chunk 0
-        // counts that are no larger.
+        //   d0'@7  d1'@15  [barrier before MFMA 16]  w0@16  w1@17  w2@18  w3@19  c@20  d2'@23  d3'@31
+        // dk' = B operand k of the NEXT chunk, requested into its registers right behind the last MFMA that
+        // reads operand k of this one; w0..w3, c = weights and constants of chunk c+3 into the stage of
+        // chunk c-1.  Nine loads.  Loads younger than the one awaited, in front of
+        //   MFMA 0   d0' of chunk c-1: d1' w0..w3 c d2' d3'           8
+        //   MFMA 8   d1' of chunk c-1: w0..w3 c d2' d3', d0'          8
+        //   MFMA 16  d2' of chunk c-1: d3', d0' d1'                   3  (its weights of chunk c+2 are older: the
+        //                                                               barrier publishes chunk c+1 and more)
+        //   MFMA 24  d3' of chunk c-1: d0' d1' w0..w3 c d2'           8
+        // The prologue waits for all operands of chunk 0 and for chunk 1, and has fewer loads in flight
+        // than these figures allow, so chunk 0 needs no counts of its own.
+        // An operand is loaded into the very registers its MFMAs read: nothing may be copied between the
+        // request and the wait, because the compiler does not know that the data is not there yet.
         auto chunk = [&](bool first) __attribute__((always_inline)) {
             const char *stage = lds + (c & (kStages - 1)) * kStageBytes;
             const char *next_stage = lds + ((c + 1) & (kStages - 1)) * kStageBytes;
@@ -215,8 +221,11 @@ __global__ __launch_bounds__(kThreads) void outproj_rowstream_kernel(ModelDev m,
             const bf16_t *dnext_ptr = dfr + (size_t)kc_next * 2048;
             static_for<0, kMfmaPerChunk>([&](auto step) __attribute__((always_inline)) {
                 constexpr int i = decltype(step)::value, blk = i % kBlocks, ks = i / kBlocks;
+                if constexpr (i == 0) await_operand<8>(dop[0]);
+                if constexpr (i == 8) await_operand<8>(dop[1]);
+                if constexpr (i == 24) await_operand<8>(dop[3]);
                 if constexpr (i == 16) {
-                    wait_vmcnt<13>();
+                    await_operand<3>(dop[2]);
                     asm volatile("" ::: "memory");
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");
@@ -238,16 +247,12 @@ __global__ __launch_bounds__(kThreads) void outproj_rowstream_kernel(ModelDev m,
                     }
                 }
                 acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, dop[ks], acc[blk], 0, 0, 0);
-                if constexpr (i == 1) load_operand<0>(dnext[0], dnext_ptr);
-                if constexpr (i == 5) load_operand<1024>(dnext[1], dnext_ptr);
-                if constexpr (i == 9) load_operand<2048>(dnext[2], dnext_ptr);
-                if constexpr (i == 13) load_operand<3072>(dnext[3], dnext_ptr);
-                if constexpr (i >= 17 && i <= 29 && (i - 17) % 3 == 0) request_piece((i - 17) / 3);
+                if constexpr (i == 7) load_operand<0>(dop[0], dnext_ptr);
+                if constexpr (i == 15) load_operand<1024>(dop[1], dnext_ptr);
+                if constexpr (i == 23) load_operand<2048>(dop[2], dnext_ptr);
+                if constexpr (i == 31) load_operand<3072>(dop[3], dnext_ptr);
+                if constexpr (i >= 16 && i < 16 + kDmaPerChunk) request_piece(i - 16);
                 __builtin_amdgcn_sched_barrier(0);             // keep the LDS reads ahead of their MFMAs
-            });
-            static_for<0, kDOperands>([&](auto j) __attribute__((always_inline)) {
-                await_operand<kDmaPerChunk>(dnext[decltype(j)::value]);
-                dop[decltype(j)::value] = dnext[decltype(j)::value];
             });
             next_request();
             ++c;
@@ -268,9 +273,11 @@ __global__ __launch_bounds__(kThreads) void outproj_rowstream_kernel(ModelDev m,
         for (int blk = 0; blk < kBlocks; ++blk)
 #pragma unroll
             for (int e = 0; e < 16; ++e) srun += fast_exp2(acc[blk][e]);
+        // The last chunk's operand and dummy loads may still be in flight: the operands' registers stay
+        // taken, and the stages untouched, until they have landed.
+        static_for<0, kDOperands>([&](auto j) __attribute__((always_inline)) { await_operand<0>(dop[decltype(j)::value]); });
         srun += __shfl_xor(srun, 32, 64);                     // lanes l and l+32 hold the two halves of a row
         if (g == 0 && b < B) m.part[(size_t)b * kMaxSplits + split] = make_float2(m.m2_fixed, srun);
-        wait_vmcnt<0>();                                      // dummy loads may still be in flight
         __syncthreads();                                      // LDS is reused by the next item
     }
 }
