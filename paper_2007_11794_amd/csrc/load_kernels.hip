@@ -25,6 +25,14 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ O,
     }
 }
 
+// A workgroup per row at a time; bound by the host copy in front of it.
+template <typename T>
+__global__ __launch_bounds__(256) void pad_rows_kernel(const T *__restrict__ src, T *__restrict__ dst, size_t rows, int H,
+                                                       int Hp) {
+    for (size_t r = blockIdx.x; r < rows; r += gridDim.x)
+        for (int j = threadIdx.x; j < Hp; j += 256) dst[r * Hp + j] = j < H ? src[r * H + j] : T(0);
+}
+
 __device__ __forceinline__ double widen(float x) { return (double)x; }
 __device__ __forceinline__ double widen(bf16_t x) { return (double)bf16_to_f32(x); }
 
@@ -111,6 +119,17 @@ __global__ __launch_bounds__(256) void frag_weights_f32_kernel(const u32x4 *__re
 }
 
 }  // namespace
+
+hipError_t launch_pad_rows(const void *src, void *dst, int dtype, size_t rows, int H, int Hp, hipStream_t stream) {
+    const dim3 grid((unsigned)(rows < 16384 ? rows : 16384));
+    if (dtype == RNNLM_BF16)
+        hipLaunchKernelGGL(pad_rows_kernel<bf16_t>, grid, dim3(256), 0, stream, static_cast<const bf16_t *>(src),
+                           static_cast<bf16_t *>(dst), rows, H, Hp);
+    else
+        hipLaunchKernelGGL(pad_rows_kernel<float>, grid, dim3(256), 0, stream, static_cast<const float *>(src),
+                           static_cast<float *>(dst), rows, H, Hp);
+    return hipGetLastError();
+}
 
 hipError_t launch_frag_weights(const void *Ot, int dtype, int Vp, int Hp, void *Ofrag, hipStream_t stream) {
     if (dtype == RNNLM_BF16) {

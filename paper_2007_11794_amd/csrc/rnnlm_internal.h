@@ -288,6 +288,8 @@ hipError_t launch_pack_ids(const uint32_t *ctx, const uint32_t *small_lm, int N,
                            hipStream_t stream);
 
 // Load-time helpers.
+// [rows][H] -> [rows][Hp], zero-padded
+hipError_t launch_pad_rows(const void *src, void *dst, int dtype, size_t rows, int H, int Hp, hipStream_t stream);
 hipError_t launch_transpose_O(const void *O_dev /*[H][V]*/, void *Ot /*[Vp][Hp]*/, int dtype,
                               int H, int V, int Hp, int Vp, hipStream_t stream);
 hipError_t launch_col_stats(const void *O_dev, const float *bias_or_null, int dtype, int H, int V,
