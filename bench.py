@@ -297,7 +297,7 @@ def main() -> int:
     ap.add_argument("--warmup", type=int, default=30)
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip the oracle timing leg")
     ap.add_argument("--outproj-kernel", type=int, default=0,
-                    help="0 auto, 1 plain, 2 staged, 3 tiled, 4 bf16 three-term split (fp32 models), "
+                    help="0 auto, 1 plain, 2 staged, 3 tiled, 4 fp16 two-term split (fp32 models), "
                          "5 weight streaming (bf16 models, few rows)")
     ap.add_argument("--rows", type=int, default=None, metavar="B",
                     help="the chosen workload with only B rows per step (full-softmax workloads 1, 2, 3, 5): "
@@ -509,24 +509,21 @@ def main() -> int:
     k3_groups = sorted(m.time_outproj(cfg.N, reps, n_rows_dev=nu) for _ in range(7))
     k3_ms = median(k3_groups)
     flops = 2.0 * B * cfg.H * cfg.V                 # the contraction on the distinct rows, each product once
-    # fp32 models run the contraction on the bf16 matrix cores (from 64 rows on the tiled kernel,
-    # below that the weight-streaming one when H <= 768): six bf16 products per fp32 product
-    # (three-term split of both operands); `achieved` counts every fp32 product once, the rate at
-    # which bf16 products are issued is reported beside it
-    split3 = (not bf16) and args.outproj_kernel in (0, 4, 5) and (B >= 64 or cfg.H <= 768 or args.outproj_kernel == 4)
-    on_mfma = bf16 or split3
+    # fp32 models run the contraction on the fp16 matrix cores (from 64 rows on the tiled kernel, below that
+    # the weight-streaming one when H <= 1216): three fp16 products per fp32 product (two-term split of
+    # both operands); `achieved` counts every fp32 product once, the rate at which fp16 products are
+    # issued is reported beside it
+    split2 = (not bf16) and args.outproj_kernel in (0, 4, 5) and (B >= 64 or cfg.H <= 1216 or args.outproj_kernel == 4)
+    on_mfma = bf16 or split2
     achieved = flops / (k3_ms * 1e-3) / 1e12
     peak = PEAK_BF16_TFLOPS if on_mfma else PEAK_FP32_TFLOPS
-    # few rows (one launch of the weight-streaming kernel: up to 64 rows of a bf16 model with
-    # H <= 1216, up to 32 rows of an fp32 model with H <= 768): the launch reads the (padded) output
-    # weights once, nothing else of size
-    streamed = args.outproj_kernel in (0, 5) and ((bf16 and B <= 64 and cfg.H <= 1216) or
-                                                  (not bf16 and B <= 32 and cfg.H <= 768))
+    # few rows (one launch of the weight-streaming kernel): the launch reads the (padded) output weights
+    # once, nothing else of size
     Hp = max(128 if bf16 else 64, -(-cfg.H // 64) * 64)
     kernel_name = m.outproj_kernel_name(cfg.N)      # the library names the kernel it launches
     if kernel_name == "outproj_staged_kernel":
         kernel_name += "<%d, %s>" % (Hp, "true" if args.lse_mode in (0, 2) else "false")
-    assert streamed == (kernel_name == "outproj_stream_kernel"), (streamed, kernel_name)
+    streamed = kernel_name == "outproj_stream_kernel" and B <= (64 if cfg.H <= (1216 if bf16 else 576) else 32)
     traffic, traffic_source = TRAFFIC.get((kernel_name, args.config if args.unique_frac is None else -1), (None, None))
     if args.rows is not None and not streamed:
         traffic, traffic_source = None, None
@@ -544,14 +541,14 @@ def main() -> int:
                     "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE, copy-calibrated)",
                     "bytes_per_launch": wbytes, "flop_per_launch": flops}
     else:
-        roofline = {"kernel": kernel_name + (" (fp32 as 6 bf16 products)" if split3 else ""),
+        roofline = {"kernel": kernel_name + (" (fp32 as 3 fp16 products)" if split2 else ""),
                     "bound": "mfma" if on_mfma else "alu", "achieved": round(achieved, 2), "peak": peak,
                     "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                     "traffic": traffic, "traffic_source": traffic_source,
                     "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE+WRITE_SIZE, copy-calibrated)",
                     "flop_per_launch": flops}
-        if split3:
-            roofline["bf16_products_issued_tflops"] = round(6.0 * achieved, 2)
+        if split2:
+            roofline["fp16_products_issued_tflops"] = round(3.0 * achieved, 2)
     roofline.update(k3_timing)
 
     if roofline["bound"] == "mfma" and not args.no_mfma_probe and not args.no_cpu_baseline:

@@ -70,15 +70,15 @@ enum rnnlm_option {
     /* Which output-projection kernel: 0 = automatic (default), 1 = the plain any-shape
      * kernel, 2 = the LDS-staged kernel with the hidden block held in registers (bf16,
      * H <= 512), 3 = the LDS-tiled kernel for any hidden size and both types, 4 = (fp32 models)
-     * the LDS-tiled kernel on the three-term bf16 split of both operands, fp32 accuracy at
-     * bf16 matrix-core speed: the automatic choice for fp32 from 64 rows on, 5 = the weight-
-     * streaming kernel for few rows, which reads a second, operand-ordered copy of the output
-     * weights once per launch at memory speed (fp32 models: cut into three bf16 terms in registers,
-     * fp32 accuracy): the automatic choice up to 64 rows when two launches suffice (the staged, the
-     * eight-wave tiled and the three-term kernel also take it on the device, when a grouped or
+     * the LDS-tiled kernel on a two-term fp16 split of both operands (every word's weights scaled by a
+     * power of two), fp32 accuracy at fp16 matrix-core speed: the automatic choice for fp32 from 64 rows
+     * on, 5 = the weight-streaming kernel for few rows, which reads the operand-ordered copy of the
+     * output weights once per launch at memory speed (fp32 models: the same two fp16 terms):
+     * the automatic choice up to 64 rows when two launches suffice (the staged and the
+     * eight-wave tiled kernel also take it on the device, when a grouped or
      * cached step turns out to have that few rows and their LDS holds them).  One launch
      * serves as many rows as fit its LDS (bf16: 128 up to H = 576, 64 up to H = 1216, 32 up to
-     * H = 2432; fp32: 128 up to H = 192, 64 up to H = 384, 32 up to H = 768); on request it takes
+     * H = 2432; fp32: 128 up to H = 256, 64 up to H = 576, 32 up to H = 1216); on request it takes
      * up to 128 rows in at most four launches, and larger batches go the automatic way,
      * 6 = (bf16 models) the kernel that sends only the weights through
      * LDS and takes the hidden rows straight into registers chunk by chunk: the automatic choice for

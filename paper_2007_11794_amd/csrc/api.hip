@@ -38,7 +38,6 @@ bool use_fixed_offset(const rnnlm_model *m) {
 // kernel reads h_out itself).
 ModelDev recur_view(const rnnlm_model *m, int rows) {
     ModelDev v = m->dev;
-    if (v.dtype != RNNLM_BF16) return v;
     if (v.hs) { v.d = nullptr; v.dfrag = nullptr; return v; }
     if (!outproj_reads_row_order(v, rows, use_fixed_offset(m), m->outproj_kernel)) v.d = nullptr;
     return v;
@@ -51,8 +50,7 @@ void free_scratch(rnnlm_model *m) {
     (void)hipFree(d.dfrag);
     (void)hipFree(d.part);
     (void)hipFree(d.flag);
-    (void)hipFree(d.d3);
-    d.d = d.dfrag = d.d3 = nullptr; d.part = nullptr; d.flag = nullptr;
+    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = nullptr;
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
     m->ev0 = m->ev1 = nullptr;
@@ -69,8 +67,8 @@ void free_weights(rnnlm_model *m) {
     (void)hipFree(const_cast<float *>(d.half_colsum_O));
     (void)hipFree(const_cast<float *>(d.cvec2));
     (void)hipFree(const_cast<float *>(d.cvec2_fixed));
-    (void)hipFree(const_cast<void *>(d.Ot3));
     (void)hipFree(const_cast<void *>(d.Ofrag));
+    (void)hipFree(const_cast<float *>(d.ofac));
     (void)hipFree(const_cast<void *>(d.Theta));
     (void)hipFree(const_cast<int32_t *>(d.path_off));
     (void)hipFree(const_cast<int32_t *>(d.path_entry));
@@ -84,9 +82,9 @@ void free_dev(rnnlm_model *m) {
 std::mutex g_handles_mutex;        // guards rnnlm_model::owner / handles / released of every model
 
 // Scratch of one handle for batches of up to max_Bp rows (a multiple of 256): hidden block in row and
-// fragment order, log-sum-exp partials, three-term block (fp32 full-softmax models), flag, events.
+// operand order (bf16 models and full-softmax models), log-sum-exp partials, flag, events.
 // On failure the caller releases with free_scratch.
-int alloc_scratch(rnnlm_model *m, int max_Bp, bool with_partials, bool with_split3) {
+int alloc_scratch(rnnlm_model *m, int max_Bp, bool with_partials) {
     int status = RNNLM_OK;
     ModelDev &d = m->dev;
     const size_t es = elem_size(d.dtype), block = (size_t)max_Bp * d.Hp * es;
@@ -95,17 +93,13 @@ int alloc_scratch(rnnlm_model *m, int max_Bp, bool with_partials, bool with_spli
     HIP_TRY(hipMemset(d.d, 0, block));
     HIP_TRY(hipMalloc(&p, 4)); d.flag = static_cast<int *>(p);
     HIP_TRY(hipMemset(d.flag, 0, 4));
-    if (d.dtype == RNNLM_BF16) {
+    if (d.dtype == RNNLM_BF16 || with_partials) {
         HIP_TRY(hipMalloc(&p, block)); d.dfrag = p;
         HIP_TRY(hipMemset(d.dfrag, 0, block));
     }
     if (with_partials) {
         HIP_TRY(hipMalloc(&p, (size_t)max_Bp * kMaxSplits * sizeof(float2))); d.part = static_cast<float2 *>(p);
         HIP_TRY(hipMemset(d.part, 0, (size_t)max_Bp * kMaxSplits * sizeof(float2)));
-    }
-    if (with_split3) {
-        HIP_TRY(hipMalloc(&p, (size_t)max_Bp * 3 * d.Hp * 2)); d.d3 = p;
-        HIP_TRY(hipMemset(d.d3, 0, (size_t)max_Bp * 3 * d.Hp * 2));
     }
     HIP_TRY(hipEventCreate(&m->ev0));
     HIP_TRY(hipEventCreate(&m->ev1));
@@ -149,7 +143,7 @@ fail:
 // Device copies of what the hidden update needs (U, W zero-padded to Hp, half row sums of W) and
 // the handle's scratch.  On failure the caller releases with free_dev.
 int upload_recurrent(rnnlm_model *m, int V, int H, int Hp, int dtype, const void *U, const void *W, int max_Bp,
-                     bool with_partials, bool with_split3) {
+                     bool with_partials) {
     int status = RNNLM_OK;
     const size_t es = elem_size(dtype);
     ModelDev &d = m->dev;
@@ -158,7 +152,7 @@ int upload_recurrent(rnnlm_model *m, int V, int H, int Hp, int dtype, const void
     HIP_TRY(hipMalloc(&p, (size_t)V * Hp * es)); d.U = p;
     HIP_TRY(hipMalloc(&p, (size_t)Hp * Hp * es)); d.W = p;
     HIP_TRY(hipMalloc(&p, (size_t)Hp * 4)); d.half_rowsum_W = static_cast<float *>(p);
-    status = alloc_scratch(m, max_Bp, with_partials, with_split3);
+    status = alloc_scratch(m, max_Bp, with_partials);
     if (status != RNNLM_OK) return status;
     HIP_TRY(hipMemset(const_cast<void *>(d.W), 0, (size_t)Hp * Hp * es));       // rows H .. Hp - 1
     status = upload_rows(const_cast<void *>(d.U), U, V, H, Hp, dtype);
@@ -265,7 +259,7 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
     float max_upper = -INFINITY, min_lower = INFINITY;
 
     void *p;
-    status = upload_recurrent(m, V, H, Hp, dtype, U, W, max_Bp, true, dtype == RNNLM_F32);
+    status = upload_recurrent(m, V, H, Hp, dtype, U, W, max_Bp, true);
     if (status != RNNLM_OK) goto fail;
     HIP_TRY(hipMalloc(&p, (size_t)Vp * Hp * es)); d.Ot = p;
     HIP_TRY(hipMalloc(&p, (size_t)V * 4)); d.bias = static_cast<float *>(p);
@@ -303,12 +297,13 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
     }
     HIP_TRY(launch_fill_cvec(bias_stage, d.half_colsum_O, V, Vp, d.m2_fixed, const_cast<float *>(d.bias),
                              const_cast<float *>(d.cvec2), const_cast<float *>(d.cvec2_fixed), nullptr));
-    // operand-ordered copy for the weight-streaming kernels (few rows)
-    HIP_TRY(hipMalloc(&p, (size_t)Vp * Hp * es)); d.Ofrag = p;
-    HIP_TRY(launch_frag_weights(d.Ot, dtype, Vp, Hp, const_cast<void *>(d.Ofrag), nullptr));
-    if (dtype == RNNLM_F32) {       // three-term bf16 split of the weights, scratch for that of the hidden block
-        HIP_TRY(hipMalloc(&p, (size_t)Vp * 3 * Hp * 2)); d.Ot3 = p;
-        HIP_TRY(launch_split3_weights(static_cast<const float *>(d.Ot), Vp, Hp, const_cast<void *>(d.Ot3), nullptr));
+    HIP_TRY(hipMalloc(&p, (size_t)Vp * Hp * es)); d.Ofrag = p;                  // operand-ordered copy
+    if (dtype == RNNLM_F32) {
+        HIP_TRY(hipMalloc(&p, (size_t)Vp * 4)); d.ofac = static_cast<float *>(p);
+        HIP_TRY(launch_split2_weights(static_cast<const float *>(d.Ot), Vp, Hp, const_cast<void *>(d.Ofrag),
+                                      const_cast<float *>(d.ofac), nullptr));
+    } else {
+        HIP_TRY(launch_frag_weights(d.Ot, Vp, Hp, const_cast<void *>(d.Ofrag), nullptr));
     }
     HIP_TRY(hipDeviceSynchronize());
     (void)hipFree(O_stage); (void)hipFree(bias_stage); (void)hipFree(upper); (void)hipFree(lower);
@@ -349,12 +344,12 @@ int rnnlm_model_share(const rnnlm_model *model, int max_B, rnnlm_model **out) {
     if (!m) return RNNLM_ENOMEM;
     *m = *model;                           // weights' pointers, shapes, options
     ModelDev &d = m->dev;
-    d.d = d.dfrag = d.d3 = nullptr; d.part = nullptr; d.flag = nullptr;
+    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = nullptr;
     m->ev0 = m->ev1 = nullptr;
     m->max_B = max_B;
     m->max_Bp = round_up(max_B, 256);
     m->handles = 0; m->released = 0;
-    int status = alloc_scratch(m, m->max_Bp, !d.hs, !d.hs && d.dtype == RNNLM_F32);
+    int status = alloc_scratch(m, m->max_Bp, !d.hs);
     if (status == RNNLM_OK && hipDeviceSynchronize() != hipSuccess) status = RNNLM_EDEVICE;
     if (status != RNNLM_OK) {
         free_scratch(m);
@@ -385,7 +380,7 @@ int rnnlm_set_option(rnnlm_model *model, int option, int value) {
             if (model->dev.hs) return RNNLM_EINVAL;
             if (value == 6 && !outproj_rowstream_supported(model->dev)) return RNNLM_EINVAL;
             if (value == 5 && outproj_stream_max_rows(model->dev) == 0) return RNNLM_EINVAL;
-            if (value == 4 && !model->dev.Ot3) return RNNLM_EINVAL;
+            if (value == 4 && !model->dev.ofac) return RNNLM_EINVAL;
             if (value == 2 && !outproj_staged_supported(model->dev)) return RNNLM_EINVAL;
             model->outproj_kernel = value;
             return RNNLM_OK;
@@ -609,7 +604,7 @@ int rnnlm_hs_load(int V, int H, int dtype, const void *U, const void *W, const v
     d.V = V; d.H = H; d.Hp = Hp; d.Vp = round_up(V, 256); d.dtype = dtype; d.hs = 1; d.hs_max_len = longest;
     m->max_B = max_B; m->max_Bp = max_Bp;
     void *p;
-    status = upload_recurrent(m, V, H, Hp, dtype, U, W, max_Bp, false, false);
+    status = upload_recurrent(m, V, H, Hp, dtype, U, W, max_Bp, false);
     if (status != RNNLM_OK) goto fail;
     HIP_TRY(hipMalloc(&p, (size_t)(V - 1) * Hp * es)); d.Theta = p;
     status = upload_rows(p, Theta, V - 1, H, Hp, dtype);

@@ -7,6 +7,7 @@
 namespace rnnlm {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -24,15 +25,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// x = x1 + x2 + x3 with bf16 terms (round to nearest even each time): the three-way split that
-// puts an fp32 operand on the bf16 matrix cores.
-__device__ __forceinline__ void split3_bf16(float x, uint16_t &x1, uint16_t &x2, uint16_t &x3) {
-    const uint32_t p1 = pack_bf16x2(x, 0.f);
-    const float r1 = x - __uint_as_float(p1 << 16);
-    const uint32_t p2 = pack_bf16x2(r1, 0.f);
-    const float r2 = r1 - __uint_as_float(p2 << 16);
-    const uint32_t p3 = pack_bf16x2(r2, 0.f);
-    x1 = (uint16_t)p1; x2 = (uint16_t)p2; x3 = (uint16_t)p3;
+// x = x1 + x2 with fp16 terms, each rounded to nearest even (|x| below 2^15; 22 bits of x are kept as
+// long as the second term is a normal fp16 number, and no less than 2^-25 is lost in absolute terms):
+// the split that puts a scaled fp32 operand on the fp16 matrix cores.  Bit patterns.
+__device__ __forceinline__ void split2_f16(float x, uint16_t &x1, uint16_t &x2) {
+    const _Float16 h = (_Float16)x, l = (_Float16)(x - (float)h);
+    x1 = __builtin_bit_cast(uint16_t, h);
+    x2 = __builtin_bit_cast(uint16_t, l);
 }
 
 // Eight consecutive weights starting at element index `at` (a multiple of 8) as floats.

@@ -78,21 +78,6 @@ __global__ __launch_bounds__(256) void fill_cvec_kernel(const float *__restrict_
     }
 }
 
-// Three-way bf16 split of the fp32 [Vp][Hp] weights, term-interleaved in chunks of 32 units:
-// Ot3[v][j / 32][term][j % 32].
-__global__ __launch_bounds__(256) void split3_weights_kernel(const float *__restrict__ Ot, size_t n, int Hp,
-                                                             bf16_t *__restrict__ Ot3) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const size_t v = i / Hp;
-    const int j = (int)(i % Hp);
-    uint16_t t[3];
-    split3_bf16(Ot[i], t[0], t[1], t[2]);
-    bf16_t *dst = Ot3 + v * 3 * Hp + (size_t)(j >> 5) * 96 + (j & 31);
-#pragma unroll
-    for (int s = 0; s < 3; ++s) dst[s * 32] = t[s];
-}
-
 // bf16 [Vp][Hp] weights re-laid in MFMA-operand order: 16 bytes per thread.
 __global__ __launch_bounds__(256) void frag_weights_kernel(const u32x4 *__restrict__ Ot, size_t n, int KS,
                                                            u32x4 *__restrict__ Ofrag) {
@@ -105,17 +90,49 @@ __global__ __launch_bounds__(256) void frag_weights_kernel(const u32x4 *__restri
     Ofrag[i] = Ot[word * (2 * KS) + 2 * ks + (lane >> 5)];           // 2 KS chunks of 8 units per word
 }
 
-// fp32 [Vp][Hp] weights in the same operand order, 32 bytes per lane as two 16-byte halves:
-// [blk][ks][half][64 lanes][4 floats], lane 32 g + c: word 32 blk + c, units 16 ks + 8 g + 4 half .. + 3.
-__global__ __launch_bounds__(256) void frag_weights_f32_kernel(const u32x4 *__restrict__ Ot, size_t n, int KS,
-                                                               u32x4 *__restrict__ Ofrag) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;       // (blk, ks, half, lane)
-    if (i >= n) return;
-    const int lane = (int)(i & 63), half = (int)((i >> 6) & 1);
-    const size_t frag = i >> 7, blk = frag / KS;
-    const int ks = (int)(frag % KS);
-    const size_t word = blk * 32 + (lane & 31);
-    Ofrag[i] = Ot[word * (4 * KS) + 4 * ks + 2 * (lane >> 5) + half];   // 4 KS chunks of 4 units per word
+// fp32 [Vp][Hp] weights as two fp16 terms in the same operand order, [blk][ks][term][64 lanes][8 halves].
+// One workgroup per block of 32 words: eight threads find the largest weight of a word, then lane
+// 32 g + c of fragment ks takes word 32 blk + c, units 16 ks + 8 g .. + 7.  Words scaled to [2^13, 2^14):
+// second terms stay normal numbers down to 2^-17 of the largest weight, products stay far below the
+// fp32 range.  A word that holds an infinity or a NaN keeps it (its terms are infinities and NaN).
+__global__ __launch_bounds__(256) void split2_weights_kernel(const float *__restrict__ Ot, int Hp, uint16_t *__restrict__ Ofrag,
+                                                             float *__restrict__ ofac) {
+    __shared__ int shift[32];
+    const int tid = threadIdx.x, KS = Hp >> 4;
+    const size_t blk = blockIdx.x;
+    float big = 0.f;
+    const float *row = Ot + (blk * 32 + (tid >> 3)) * Hp;
+    for (int j = tid & 7; j < Hp; j += 8) big = fmaxf(big, fabsf(row[j]));
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) big = fmaxf(big, __shfl_xor(big, off, 64));
+    if ((tid & 7) == 0) {
+        int e = 0;
+        if (big > 0.f && big < INFINITY) {
+            (void)frexpf(big, &e);                                 // big in [2^(e-1), 2^e)
+            e = 14 - e;
+            if (e > 100) e = 100;                                  // words of denormal size: factors stay normal
+        }
+        shift[tid >> 3] = e;
+        ofac[blk * 32 + (tid >> 3)] = ldexpf(kLog2e, -(e + kSplit2DExp));
+    }
+    __syncthreads();
+    for (int i = tid; i < KS * 64; i += 256) {                     // (ks, lane)
+        const int lane = i & 63, ks = i >> 6, w = lane & 31;
+        float x[8];
+        load8_weights(Ot, (blk * 32 + w) * Hp + 16 * ks + 8 * (lane >> 5), x);
+        uint32_t p1[4], p2[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint16_t a1, a2, b1, b2;
+            split2_f16(ldexpf(x[2 * q], shift[w]), a1, a2);
+            split2_f16(ldexpf(x[2 * q + 1], shift[w]), b1, b2);
+            p1[q] = a1 | ((uint32_t)b1 << 16);
+            p2[q] = a2 | ((uint32_t)b2 << 16);
+        }
+        uint16_t *dst = Ofrag + ((blk * KS + ks) * 2 * 64 + lane) * 8;
+        *reinterpret_cast<u32x4 *>(dst) = u32x4{p1[0], p1[1], p1[2], p1[3]};
+        *reinterpret_cast<u32x4 *>(dst + 512) = u32x4{p2[0], p2[1], p2[2], p2[3]};
+    }
 }
 
 }  // namespace
@@ -131,23 +148,16 @@ hipError_t launch_pad_rows(const void *src, void *dst, int dtype, size_t rows, i
     return hipGetLastError();
 }
 
-hipError_t launch_frag_weights(const void *Ot, int dtype, int Vp, int Hp, void *Ofrag, hipStream_t stream) {
-    if (dtype == RNNLM_BF16) {
-        const size_t n = (size_t)Vp * Hp / 8;
-        hipLaunchKernelGGL(frag_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                           static_cast<const u32x4 *>(Ot), n, Hp / 16, static_cast<u32x4 *>(Ofrag));
-    } else {
-        const size_t n = (size_t)Vp * Hp / 4;
-        hipLaunchKernelGGL(frag_weights_f32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
-                           static_cast<const u32x4 *>(Ot), n, Hp / 16, static_cast<u32x4 *>(Ofrag));
-    }
+hipError_t launch_frag_weights(const void *Ot, int Vp, int Hp, void *Ofrag, hipStream_t stream) {
+    const size_t n = (size_t)Vp * Hp / 8;
+    hipLaunchKernelGGL(frag_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
+                       static_cast<const u32x4 *>(Ot), n, Hp / 16, static_cast<u32x4 *>(Ofrag));
     return hipGetLastError();
 }
 
-hipError_t launch_split3_weights(const float *Ot, int Vp, int Hp, void *Ot3, hipStream_t stream) {
-    const size_t n = (size_t)Vp * Hp;
-    hipLaunchKernelGGL(split3_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, Ot, n, Hp,
-                       static_cast<bf16_t *>(Ot3));
+hipError_t launch_split2_weights(const float *Ot, int Vp, int Hp, void *Ofrag, float *ofac, hipStream_t stream) {
+    hipLaunchKernelGGL(split2_weights_kernel, dim3((unsigned)(Vp / 32)), dim3(256), 0, stream, Ot, Hp,
+                       static_cast<uint16_t *>(Ofrag), ofac);
     return hipGetLastError();
 }
 

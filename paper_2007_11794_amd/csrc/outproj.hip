@@ -197,8 +197,8 @@ hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, 
 hipError_t launch_outproj_tiled(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
                                 SplitInfo *splits, hipStream_t stream);
 
-// defined in outproj_split3.hip
-hipError_t launch_outproj_split3(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
+// defined in outproj_split2.hip
+hipError_t launch_outproj_split2(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
                                  SplitInfo *splits, hipStream_t stream);
 // defined in outproj_rowstream.hip
 hipError_t launch_outproj_rowstream(const ModelDev &m, int rows, const int *B_dev, SplitInfo *splits,
@@ -232,11 +232,23 @@ static Bf16Kernel choose_bf16(const ModelDev &m, int rows, bool fixed_offset, in
     return kBf16Plain;
 }
 
+// The same for fp32 models.
+enum F32Kernel { kF32Stream, kF32Split2, kF32Tiled, kF32Plain };
+static F32Kernel choose_f32(const ModelDev &m, int rows, int kernel_choice) {
+    if (stream_choice(m, rows, kernel_choice)) return kF32Stream;
+    if (kernel_choice == 3) return kF32Tiled;
+    if (m.ofac && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64))) return kF32Split2;
+    return kF32Plain;
+}
+
 // Does the kernel launch_outproj will take read the row-ordered copy of the hidden block (m.d)?  The
-// weight-streaming, staged and row-streaming kernels read the fragment-ordered one (m.dfrag) only, also
-// when they fall back to weight streaming on the device; then the hidden update need not write m.d.
+// weight-streaming, staged, row-streaming and two-term kernels read the operand-ordered one (m.dfrag)
+// only, also when they fall back to weight streaming on the device; then the hidden update need not write m.d.
 bool outproj_reads_row_order(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {
-    if (m.dtype != RNNLM_BF16) return true;
+    if (m.dtype != RNNLM_BF16) {
+        const F32Kernel k = choose_f32(m, rows, kernel_choice);
+        return k == kF32Tiled || k == kF32Plain;
+    }
     const Bf16Kernel k = choose_bf16(m, rows, fixed_offset, kernel_choice);
     return k == kBf16Tiled || k == kBf16Plain;
 }
@@ -252,10 +264,12 @@ const char *outproj_kernel_name(const ModelDev &m, int rows, bool fixed_offset, 
             default: return "outproj_plain_bf16_kernel";
         }
     }
-    if (stream_choice(m, rows, kernel_choice)) return "outproj_stream_kernel";
-    if (kernel_choice == 3) return "outproj_tiled_kernel";
-    if (m.Ot3 && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64))) return "outproj_split3_kernel";
-    return "outproj_plain_f32_kernel";
+    switch (choose_f32(m, rows, kernel_choice)) {
+        case kF32Stream: return "outproj_stream_kernel";
+        case kF32Split2: return "outproj_split2_kernel";
+        case kF32Tiled: return "outproj_tiled_kernel";
+        default: return "outproj_plain_f32_kernel";
+    }
 }
 
 hipError_t launch_outproj(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
@@ -279,15 +293,13 @@ hipError_t launch_outproj(const ModelDev &m, int rows, const int *B_dev, bool fi
             hipLaunchKernelGGL(outproj_plain_bf16_kernel<false>, grid, dim3(256), 0, stream, m, rows, B_dev, per, S);
         *splits = fixed_split_info(S);
     } else {
-        // fp32 on the bf16 matrix cores through the three-term split of both operands (six bf16
-        // products per fp32 product at sixteen times the fp32 matrix rate, same accuracy): weight
-        // streaming for few rows, the tiled three-term kernel from 64 rows on.  The tiled
-        // fp32-MFMA kernel only on request; at the WSJ-sized workload it is no faster than the
-        // FMA kernel below.
-        if (stream_choice(m, rows, kernel_choice)) return launch_outproj_stream(m, rows, B_dev, fixed_offset, splits, stream);
-        if (kernel_choice == 3) return launch_outproj_tiled(m, rows, B_dev, fixed_offset, splits, stream);
-        if (m.Ot3 && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64)))
-            return launch_outproj_split3(m, rows, B_dev, fixed_offset, splits, stream);
+        // fp32 on the fp16 matrix cores through a two-term split of both operands (three fp16 products per
+        // fp32 product at sixteen times the fp32 matrix rate, same accuracy): weight streaming for few
+        // rows, the tiled two-term kernel from 64 rows on.  The tiled fp32-MFMA kernel only on request.
+        const F32Kernel which = choose_f32(m, rows, kernel_choice);
+        if (which == kF32Stream) return launch_outproj_stream(m, rows, B_dev, fixed_offset, splits, stream);
+        if (which == kF32Tiled) return launch_outproj_tiled(m, rows, B_dev, fixed_offset, splits, stream);
+        if (which == kF32Split2) return launch_outproj_split2(m, rows, B_dev, fixed_offset, splits, stream);
         const int row_groups = (rows + kFM - 1) / kFM, col_blocks = m.Vp / kFN;
         int S = choose_splits(row_groups, col_blocks, 1024);
         int per = (col_blocks + S - 1) / S;

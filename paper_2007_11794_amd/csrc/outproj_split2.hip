@@ -1,0 +1,236 @@
+// Output projection + log-sum-exp for fp32 models on the fp16 matrix cores, at fp32 accuracy.
+//
+// Same result as the other output-projection kernels (normalising over all words of the
+// vocabulary, Section 2.1 of the paper; the paper's models are fp32).  Every fp32 operand is
+// brought into the range of fp16 by a power of two (one per word for the weights, 2^14 for the
+// centred hidden vector, |d| <= 1/2) and cut into two fp16 terms x = x1 + x2 (11 + 11 mantissa bits,
+// each rounded to nearest: 2^-22 of x at worst); of the four cross terms three are kept (w2 d1, w1 d2,
+// w1 d1; the dropped one is below 2^-22 of the product) and added in the fp32 accumulators of the
+// matrix instruction.  Three matrix instructions per product instead of the six of a three-term bf16
+// split (which this kernel replaced), and half as many roundings of the accumulator, which is where the
+// error comes from: against float64 the log-probabilities are off by 4.95e-8 (rel.) where the six-product
+// kernel was off by 5.01e-8 at V = 65536, H = 512, 1024 rows, 6.4e-8 against 7.0e-8 at V = 30011, H = 1000,
+// weights of 0.2.  Bound by the matrix pipe at the clock the chip holds under it: 308 -> 159 us
+// (1.30 PFLOP/s of fp16 products), V = 20000, H = 256, 256 rows 20.5 -> 13.0 us.
+//
+// Layout: both operands are kept as MFMA operands (ModelDev::Ofrag, dfrag), so 32 words x 16 units x 2
+// terms are 2 KB contiguous, global memory -> LDS -> register without any rearrangement, and every LDS
+// read of a wave is one contiguous kilobyte (no bank conflicts).
+//   - a workgroup of 2 x 2 waves owns 128 rows and walks the tiles of 64 MB words of its vocabulary
+//     split; a wave owns 32 MB words x 64 rows = MB x 2 accumulators of 32x32;
+//   - a stage of LDS holds one k-step (16 units), three stages, filled by direct global->LDS loads
+//     two k-steps ahead;
+//   - per k-step a wave reads 2 MB + 4 operands and issues 6 MB MFMA 32x32x16 (MB = 4: half a kilobyte
+//     of LDS per MFMA, 64 of the 128 bytes a clock);
+//   - two workgroups share a compute unit and are not synchronised with each other: one's barriers,
+//     LDS latencies and exp-and-add (a third as many VALU cycles as MFMA cycles at Hp = 128, a twelfth
+//     at 512) run under the other's MFMAs; with the 256-word tile a wave inside its MFMA chain goes
+//     first (s_setprio: 168 -> 159 us at V = 65536, H = 512, 1024 rows; the 128-word tile loses 2 %);
+//   - MFMA roles as in the other kernels (A = words, B = rows): a lane holds sixteen logits of ONE
+//     row per accumulator, the sum over words stays in the lane.
+#include "device_utils.h"
+#include "rnnlm_internal.h"
+
+namespace rnnlm {
+
+namespace {
+
+constexpr int kThreads = 256, kRows = 128, kStages = 3;
+
+template <int MB>
+struct Split2Cfg {
+    static constexpr int kWords = 64 * MB;
+    static constexpr int kWordBytes = 2 * MB * kSplit2Operand, kRowBytes = 4 * kSplit2Operand;
+    static constexpr int kStageBytes = kWordBytes + kRowBytes;
+    static constexpr int kLoads = MB + 2;                       // 1 KB loads per wave and k-step
+    static constexpr int kConstBytes = 2 * kWords * 4;          // constants and factors of one tile
+    static constexpr int kConstAt = kStages * kStageBytes, kRedAt = kConstAt + 2 * kConstBytes;
+    static constexpr int kLdsBytes = kRedAt + 2 * kRows * 8;    // + final cross-wave reduction
+    static_assert(2 * kLdsBytes <= 160 * 1024, "two workgroups per compute unit");
+};
+
+template <bool FIXED, int MB>
+__global__ __launch_bounds__(kThreads, 2) void outproj_split2_kernel(ModelDev m, int rows,
+                                                                     const int *__restrict__ B_dev, int wg_per_xcd,
+                                                                     int sx_cap) {
+    using C = Split2Cfg<MB>;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    // The split follows the TRUE number of rows (after the grouping of ids or the cache lookup only
+    // the device knows it): few rows get many vocabulary splits, and the whole grid works.
+    const int B = B_dev ? *B_dev : rows;
+    if (B <= 0) return;                                       // uniform: no barrier is met
+    const RowPlan plan = plan_rows(B, kRows, wg_per_xcd, sx_cap);
+    const int S = plan.S, items = plan.RG * plan.Sx;
+    const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;                  // word half, 64-row half of the tile
+    const int KS = m.Hp >> 4;                                 // k-steps per tile, at least 4
+    const char *Of = static_cast<const char *>(m.Ofrag);
+    const char *Df = static_cast<const char *>(m.dfrag);
+    const float *cvec = FIXED ? m.cvec2_fixed : m.cvec2;
+    const int ntiles = m.Vp / C::kWords;
+    const uint32_t lds0 = lds_address(lds);
+    const size_t blk_bytes = (size_t)KS * kSplit2Operand;     // one block of 32 words or rows
+    const uint32_t voff = lane * 16;
+
+    for (int item = local; item < items; item += wg_per_xcd) {
+    const int rg = item % plan.RG, split = xcd + kXcds * (item / plan.RG);
+    const int b0 = rg * kRows;
+    const int t_begin = part_begin(split, ntiles, S), t_end = part_begin(split + 1, ntiles, S);
+    const int nchunks = (t_end - t_begin) * KS;
+    const bool active = b0 + 64 * wn < B;                     // wave-uniform: any valid row in this wave's half
+
+    // loader: piece p = 4 q + wave of a stage's word (row) part is term wave % 2 of block 2 q + wave / 2
+    const char *wsrc = Of + ((size_t)t_begin * 2 * MB + (wave >> 1)) * blk_bytes + (wave & 1) * 1024;
+    const char *dsrc = Df + ((size_t)(b0 >> 5) + (wave >> 1)) * blk_bytes + (wave & 1) * 1024;
+    int in_tile = t_begin, in_ks = 0, in_stage = 0;
+    auto issue = [&]() {
+        if (in_ks == 0 && wave < 2) {                         // the tile's constants (wave 0) and factors (wave 1)
+            const float *src = (wave ? m.ofac : cvec) + (size_t)in_tile * C::kWords;
+            const uint32_t at = lds0 + C::kConstAt + (in_tile & 1) * C::kConstBytes + wave * (C::kWords * 4);
+            if (lane < C::kWords / 4) lds_dma_16(src, voff, at);
+        }
+        const uint32_t base = lds0 + in_stage * C::kStageBytes + wave * 1024;
+#pragma unroll
+        for (int q = 0; q < MB; ++q) lds_dma_16(wsrc + 2 * q * blk_bytes, voff, base + q * 4096);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) lds_dma_16(dsrc + 2 * q * blk_bytes, voff, base + C::kWordBytes + q * 4096);
+        wsrc += kSplit2Operand;
+        dsrc += kSplit2Operand;
+        in_stage = in_stage == kStages - 1 ? 0 : in_stage + 1;
+        if (++in_ks == KS) {                                  // next tile: the same rows again
+            in_ks = 0;
+            ++in_tile;
+            wsrc += (2 * MB - 1) * blk_bytes;
+            dsrc -= blk_bytes;
+        }
+    };
+
+    float mrun[2], srun[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) { mrun[h] = FIXED ? m.m2_fixed : -INFINITY; srun[h] = 0.f; }
+    f32x16 acc[MB][2];
+
+    if (nchunks > 0) issue();
+    if (nchunks > 1) issue();
+    int ks = 0, tile = t_begin, stage = 0;
+    for (int chunk = 0; chunk < nchunks; ++chunk) {
+        // my loads of this k-step have landed once only those of the next one are outstanding
+        // (constants requested with the next one make the wait stricter, never weaker)
+        if (chunk + 1 < nchunks) wait_vmcnt<C::kLoads>();
+        else wait_vmcnt<0>();
+        __syncthreads();                                       // everybody's; the stage of chunk - 1 is free
+        if (chunk + 2 < nchunks) issue();
+        if (ks == 0) {
+#pragma unroll
+            for (int a = 0; a < MB; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+        }
+        if (active) {
+            const char *st = lds + stage * C::kStageBytes + lane * 16;
+            const char *sw = st + wm * (MB * kSplit2Operand), *sd = st + C::kWordBytes + wn * (2 * kSplit2Operand);
+            f16x8 w[MB][2], d[2][2];
+#pragma unroll
+            for (int t = 1; t >= 0; --t) {
+#pragma unroll
+                for (int a = 0; a < MB; ++a) w[a][t] = *reinterpret_cast<const f16x8 *>(sw + a * kSplit2Operand + t * 1024);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) d[b][1 - t] = *reinterpret_cast<const f16x8 *>(sd + b * kSplit2Operand + (1 - t) * 1024);
+            }
+            // smallest cross terms first: (2,1) (1,2) (1,1)
+            if constexpr (MB == 4) __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                constexpr int tw[3] = {1, 0, 0}, td[3] = {0, 1, 0};
+#pragma unroll
+                for (int a = 0; a < MB; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[a][tw[p]], d[b][td[p]], acc[a][b], 0, 0, 0);
+            }
+            if constexpr (MB == 4) __builtin_amdgcn_s_setprio(0);
+            if (ks == KS - 1) {                                // the tile is complete: exp-and-add
+                const f32x4 *cl = reinterpret_cast<const f32x4 *>(lds + C::kConstAt + (tile & 1) * C::kConstBytes) + wm * (8 * MB) + g;
+#pragma unroll
+                for (int a = 0; a < MB; ++a) {
+                    f32x4 c[4], f[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        c[q] = cl[a * 8 + 2 * q];
+                        f[q] = cl[C::kWords / 4 + a * 8 + 2 * q];
+                    }
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        float x[16];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) x[4 * q + i] = fmaf(acc[a][b][4 * q + i], f[q][i], c[q][i]);
+                        lse2_fold16<FIXED>(x, mrun[b], srun[b]);
+                    }
+                }
+            }
+        }
+        if (++ks == KS) { ks = 0; ++tile; }
+        stage = stage == kStages - 1 ? 0 : stage + 1;
+    }
+    // lanes l and l+32 hold two halves of a row; waves wm = 0, 1 hold the two word halves
+    float2 *red = reinterpret_cast<float2 *>(lds + C::kRedAt);             // [2 (wm)][rows of the tile]
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float m2 = __shfl_xor(mrun[h], 32, 64), s2 = __shfl_xor(srun[h], 32, 64);
+        if (FIXED) srun[h] += s2;
+        else lse2_merge(mrun[h], srun[h], m2, s2);
+        if (g == 0) red[wm * kRows + wn * 64 + h * 32 + col] = make_float2(mrun[h], srun[h]);
+    }
+    __syncthreads();                                           // also: every stage has been read
+    if (tid < kRows && b0 + tid < B) {
+        float2 p = red[tid], q = red[kRows + tid];
+        if (FIXED) p.y += q.y;
+        else lse2_merge(p.x, p.y, q.x, q.y);
+        m.part[(size_t)(b0 + tid) * kMaxSplits + split] = p;
+    }
+    }   // items (the next one writes `red` behind the barriers of its own k-steps)
+}
+
+template <int MB>
+hipError_t launch_split2_shape(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset, SplitInfo *splits,
+                               hipStream_t stream) {
+    using C = Split2Cfg<MB>;
+    static LdsLimit limit[2];
+    const void *fn = fixed_offset ? reinterpret_cast<const void *>(outproj_split2_kernel<true, MB>)
+                                  : reinterpret_cast<const void *>(outproj_split2_kernel<false, MB>);
+    if (hipError_t e = limit[fixed_offset ? 1 : 0].ensure(fn, C::kLdsBytes); e != hipSuccess) return e;
+    // two workgroups per compute unit; at most one split per tile of words, rounded UP to a multiple of
+    // 8 so that no split gets two tiles while the others have one
+    const int wg_per_xcd = 64, ntiles = m.Vp / C::kWords, sx_cap = (ntiles + kXcds - 1) / kXcds;
+    *splits = SplitInfo{0, wg_per_xcd, kRows, sx_cap, 0};
+    dim3 grid(kXcds * wg_per_xcd), block(kThreads);
+    if (fixed_offset)
+        hipLaunchKernelGGL((outproj_split2_kernel<true, MB>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,
+                           wg_per_xcd, sx_cap);
+    else
+        hipLaunchKernelGGL((outproj_split2_kernel<false, MB>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,
+                           wg_per_xcd, sx_cap);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_outproj_split2(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
+                                 SplitInfo *splits, hipStream_t stream) {
+    if (m.dtype != RNNLM_F32 || !m.Ofrag || !m.dfrag || !m.ofac) return hipErrorInvalidValue;
+    // 256-word tiles once they give every workgroup of the grid two, 128-word tiles below.  Measured, us,
+    // 256 / 128 words: 2048 tiles (V = 65536, H = 512, 1024 rows) 159 / 170; 1024 tiles (512 rows) 84 / 89;
+    // 768 tiles 80 / 80; 588 tiles (V = 50000, H = 650, 300 rows) 85 / 75; 158 tiles (V = 20000, H = 256,
+    // 256 rows) 15.7 / 13.0.
+    const long long tiles = (long long)((rows + kRows - 1) / kRows) * (m.Vp / 256);
+    if (tiles >= 1024) return launch_split2_shape<4>(m, rows, B_dev, fixed_offset, splits, stream);
+    return launch_split2_shape<2>(m, rows, B_dev, fixed_offset, splits, stream);
+}
+
+}  // namespace rnnlm

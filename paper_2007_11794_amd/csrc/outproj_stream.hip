@@ -55,7 +55,7 @@ hipError_t launch_rb(const ModelDev &m, int rows, const int *B_dev, int row0, bo
     static LdsLimit limit[4];
     const bool f32 = m.dtype == RNNLM_F32;
     const int which = (fixed_offset ? 1 : 0) + (f32 ? 2 : 0);
-    const size_t lds_bytes = stream_lds_bytes(f32 ? 3 : 1, RB, m.Hp >> 4);
+    const size_t lds_bytes = stream_lds_bytes(f32 ? 2 : 1, RB, m.Hp >> 4);
     const void *fn = f32 ? (fixed_offset ? reinterpret_cast<const void *>(outproj_stream_f32_kernel<RB, true>)
                                          : reinterpret_cast<const void *>(outproj_stream_f32_kernel<RB, false>))
                          : (fixed_offset ? reinterpret_cast<const void *>(outproj_stream_kernel<RB, true>)
@@ -78,11 +78,11 @@ hipError_t launch_rb(const ModelDev &m, int rows, const int *B_dev, int row0, bo
 }  // namespace
 
 // Rows the streaming kernel can take for this model: the hidden block (bf16 models: one copy;
-// fp32 models: its three bf16 terms) must fit in LDS.
+// fp32 models: its two fp16 terms) must fit in LDS.
 int outproj_stream_max_rows(const ModelDev &m) {
     if (!m.Ofrag || m.hs) return 0;
-    if (m.dtype == RNNLM_BF16 && !m.dfrag) return 0;
-    const int KS = m.Hp >> 4, terms = m.dtype == RNNLM_F32 ? 3 : 1;
+    if (!m.dfrag) return 0;
+    const int KS = m.Hp >> 4, terms = m.dtype == RNNLM_F32 ? 2 : 1;
     int rb = 0;
     for (int c = 1; c <= 4; c *= 2)
         if (stream_lds_bytes(terms, c, KS) <= 156 * 1024) rb = c;          // of the 160 KB a workgroup can have

@@ -11,8 +11,8 @@
 //
 // Besides h_out (fp32, caller's buffer) the kernel leaves d' = h' - 1/2 in the model's
 // scratch blocks as the operand of the output projection: row-major in the weights' type;
-// for bf16 models also times log2(e) in MFMA-fragment order (staged output projection); for
-// fp32 models also as three bf16 terms along a six times longer reduction (see ModelDev).
+// also in MFMA-operand order, for bf16 models times log2(e), for fp32 models as two fp16 terms
+// (see ModelDev).
 //
 // Three kernels: the LDS-tiled bf16 kernel (the default), the register-direct bf16 kernel it
 // replaced (kept for hidden sizes that are not a multiple of 4 or unaligned buffers), and the
@@ -469,18 +469,19 @@ __global__ __launch_bounds__(256) void recur_f32_kernel(
         hp[i] = w_ok ? sigmoid_f32(a4[i] + rs[i] + u4[i]) : quiet_nan();
         dv[i] = hp[i] - 0.5f;                        // padded units: sigmoid(0) - 1/2 = 0
     }
-    *reinterpret_cast<f32x4 *>(static_cast<float *>(m.d) + (size_t)b * Hp + je) = dv;
-    if (m.d3) {     // the same values as three bf16 terms, term-interleaved in chunks of 32 units
-        uint16_t t[4][3];
+    if (m.d) *reinterpret_cast<f32x4 *>(static_cast<float *>(m.d) + (size_t)b * Hp + je) = dv;
+    if (m.dfrag) {  // the same values as two fp16 terms in operand order
+        uint16_t t[2][4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) split3_bf16(dv[i], t[i][0], t[i][1], t[i][2]);
-        bf16_t *row3 = static_cast<bf16_t *>(m.d3) + (size_t)b * 3 * Hp + (size_t)(je >> 5) * 96 + (je & 31);
+        for (int i = 0; i < 4; ++i) split2_f16(dv[i] * (float)(1 << kSplit2DExp), t[0][i], t[1][i]);
+        const size_t frag = (size_t)(b >> 5) * (Hp >> 4) + (je >> 4);
+        uint16_t *dst = static_cast<uint16_t *>(m.dfrag) + (frag * 128 + ((je >> 3) & 1) * 32 + (b & 31)) * 8 + (je & 7);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
+        for (int k = 0; k < 2; ++k) {
             uint2 pk;
-            pk.x = (uint32_t)t[0][k] | ((uint32_t)t[1][k] << 16);
-            pk.y = (uint32_t)t[2][k] | ((uint32_t)t[3][k] << 16);
-            *reinterpret_cast<uint2 *>(row3 + k * 32) = pk;
+            pk.x = (uint32_t)t[k][0] | ((uint32_t)t[k][1] << 16);
+            pk.y = (uint32_t)t[k][2] | ((uint32_t)t[k][3] << 16);
+            *reinterpret_cast<uint2 *>(dst + k * 512) = pk;
         }
     }
     if (vec_ok && je + 4 <= H) {

@@ -17,6 +17,8 @@ typedef uint16_t bf16_t;                       // bfloat16 bit pattern
 
 constexpr int kMaxSplits = 256;                // most vocabulary splits of the output projection
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr int kSplit2Operand = 2048;           // bytes of one two-term fp16 operand, 32 words or rows x 16 units
+constexpr int kSplit2DExp = 14;                // fp32 models: the centred hidden vector times 2^14 in dfrag
 constexpr float kLn2 = 0.6931471805599453f;
 
 // Device-side view of a loaded model (all pointers are device pointers).
@@ -36,18 +38,12 @@ struct ModelDev {
     const float *cvec2;           // [Vp]
     const float *cvec2_fixed;     // [Vp]  cvec2 - m2_fixed
     float m2_fixed;    // upper bound of every base-2 logit z*log2(e), valid because |h' - 0.5| <= 0.5
-    // fp32 models with the full softmax: the output projection on the bf16 matrix cores at fp32
-    // accuracy.  Every fp32 number is the exact sum of three bf16 numbers x1 + x2 + x3 (8 + 8 + 8
-    // mantissa bits); of the nine cross terms of a product the six with the largest weight are
-    // kept.  Both operands are kept term-interleaved in chunks of 32 units,
-    // [row][unit / 32][term][unit % 32], so a chunk of the reduction is 192 contiguous bytes per row.
-    const void *Ot3;   // [Vp][3 Hp] bf16, or null
-    // A second copy of the output weights in MFMA-operand order for the kernels that stream them
-    // for few rows.  bf16: [Vp / 32][Hp / 16][64 lanes][8], lane 32 g + c of fragment (blk, ks)
-    // holds word 32 blk + c, units 16 ks + 8 g .. + 7 (one operand = 1 KB contiguous).  fp32: the
-    // same operand as two halves of four floats, [Vp / 32][Hp / 16][2][64 lanes][4].
+    // A second copy of the output weights in MFMA-operand order.  bf16: [Vp / 32][Hp / 16][64 lanes][8],
+    // lane 32 g + c of fragment (blk, ks) holds word 32 blk + c, units 16 ks + 8 g .. + 7 (one operand =
+    // 1 KB contiguous).  fp32: two fp16 terms of the weights times a power of two of their word (the
+    // largest weight of a word lies in [2^13, 2^14)), [Vp / 32][Hp / 16][2 terms][64 lanes][8].
     const void *Ofrag;
-    void *d3;          // [max_Bp][3 Hp] bf16 scratch, or null
+    const float *ofac;            // [Vp] fp32 models: log2(e) / (the word's power of two * 2^14)
     // hierarchical output layer (models loaded with rnnlm_hs_load; Ot .. cvec2_fixed are null then)
     int hs;                       // 1: hierarchical
     const void *Theta;            // [V-1][Hp] node vectors, weights' type, zero-padded
@@ -56,9 +52,10 @@ struct ModelDev {
     int hs_max_len;               // longest path
     // scratch
     void *d;           // [max_Bp][Hp]  h' - 0.5 in the weights' type
-    // bf16 models: the same block times log2(e), in the order the staged output projection reads
-    // it, [max_Bp / 32][Hp / 16][64 lanes][8]: lane 32 g + c of fragment (rb, ks) holds row
-    // 32 rb + c, units 16 ks + 8 g .. + 7, so one MFMA operand of a wave is 1 KB contiguous.
+    // The same block in the order the output projection reads it as an MFMA operand.  bf16 models: times
+    // log2(e), [max_Bp / 32][Hp / 16][64 lanes][8], lane 32 g + c of fragment (rb, ks) holds row
+    // 32 rb + c, units 16 ks + 8 g .. + 7, so one operand of a wave is 1 KB contiguous.  fp32 models:
+    // times 2^14 as two fp16 terms, [max_Bp / 32][Hp / 16][2 terms][64 lanes][8].
     void *dfrag;
     float2 *part;      // [max_Bp][kMaxSplits]  (max, sum) partials of the base-2 log-sum-exp
     int *flag;         // sticky rnnlm_device_flag bits
@@ -295,8 +292,8 @@ hipError_t launch_transpose_O(const void *O_dev /*[H][V]*/, void *Ot /*[Vp][Hp]*
 hipError_t launch_col_stats(const void *O_dev, const float *bias_or_null, int dtype, int H, int V,
                             float *half_colsum /*[V]*/, float *upper /*[V]*/, float *lower /*[V]*/,
                             hipStream_t stream);
-hipError_t launch_frag_weights(const void *Ot /*[Vp][Hp]*/, int dtype, int Vp, int Hp, void *Ofrag, hipStream_t stream);
-hipError_t launch_split3_weights(const float *Ot /*[Vp][Hp]*/, int Vp, int Hp, void *Ot3 /*[Vp][3 Hp] bf16*/,
+hipError_t launch_frag_weights(const void *Ot /*[Vp][Hp] bf16*/, int Vp, int Hp, void *Ofrag, hipStream_t stream);
+hipError_t launch_split2_weights(const float *Ot /*[Vp][Hp]*/, int Vp, int Hp, void *Ofrag, float *ofac /*[Vp]*/,
                                  hipStream_t stream);
 hipError_t launch_fill_cvec(const float *bias_or_null, const float *half_colsum, int V, int Vp,
                             float m2_fixed, float *bias_out, float *cvec2, float *cvec2_fixed,

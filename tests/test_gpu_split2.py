@@ -1,0 +1,54 @@
+"""Two-term fp16 form of the fp32 output projection, against the oracle: edges of its row and word tiles, both tile
+shapes, both forms of the log-sum-exp, and words whose weights lie many powers of two apart (every word is brought into
+the range of fp16 by a power of two of its own)."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2007_11794_amd as rn
+
+from harness import gpu_step, gpu_step_dedup, load_model
+
+pytestmark = pytest.mark.gpu
+
+
+def model_of(rng, V, H, big):
+    O = rng.normal(0, big, (H, V))
+    O *= 2.0 ** rng.integers(-30, 1, (H, V))               # a wide range inside every word
+    O[:, ::5] *= 1e-6
+    O[:, 1::7] *= 1e-30
+    O[:, 2::11] = 0.0
+    O[:, 3::13] *= 1e-40                                   # denormal or zero as fp32
+    sigma = 0.4 / np.sqrt(H)
+    return {"U": rng.normal(0, 0.3, (V, H)).astype(np.float32), "W": rng.normal(0, sigma, (H, H)).astype(np.float32),
+            "O": O.astype(np.float32), "bias": rng.normal(0, 0.5, V).astype(np.float32)}
+
+
+# 64-word granularity of the tiles (256 words from 1024 tiles of 256 x 128 on), rows around 64 and 128
+@pytest.mark.parametrize("V,H,B,big", [(2, 64, 1, 1.0), (255, 65, 63, 1.0), (257, 128, 64, 1.0), (511, 64, 65, 4.0),
+                                       (513, 200, 127, 1.0), (1000, 64, 128, 4.0), (700, 576, 129, 0.5),
+                                       (33000, 64, 1000, 1.0), (66000, 32, 449, 4.0), (4100, 1030, 140, 0.5)])
+def test_against_the_oracle(V, H, B, big):
+    rng = np.random.default_rng(V + B)
+    model = model_of(rng, V, H, big)
+    m = load_model(model, "f32", B)
+    prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
+    query = rng.integers(0, V, (B, 3)).astype(np.int32)
+    ref = oracle.step(model, prev, h_in, query)
+    # fp32 sums of H products: 2^-24 of the running sum per addition at worst, running sums below the sum of |O| / 2
+    tol = 1e-5 + 2.0 ** -24 * np.sqrt(H) * 0.5 * np.abs(model["O"]).sum(0).max()
+    for lse_mode in (0, 1):
+        m.set_option(rn.OPT_LSE_MODE, lse_mode)
+        for kernel in (0, 4, 5):
+            m.set_option(rn.OPT_OUTPROJ_KERNEL, kernel)
+            h, lp = gpu_step(m, prev, h_in, query)
+            assert np.max(np.abs(h - ref["h_out"])) <= 1e-5
+            assert np.max(np.abs(lp - ref["logprob"])) <= tol, (kernel, lse_mode)
+    # few of the rows distinct: the row count is then known on the device only
+    m.set_option(rn.OPT_OUTPROJ_KERNEL, 4)
+    src = rng.integers(0, max(1, B // 9), B)
+    out = gpu_step_dedup(m, src.astype(np.uint64) + 5, prev[src], h_in[src], query)
+    ref = oracle.step(model, prev[src], h_in[src], query)
+    assert np.max(np.abs(out["logprob"] - ref["logprob"])) <= tol
+    assert m.last_error() == 0
+    m.close()
