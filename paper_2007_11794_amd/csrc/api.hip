@@ -146,15 +146,16 @@ int upload_recurrent(rnnlm_model *m, int V, int H, int Hp, int dtype, const void
                      bool with_partials) {
     int status = RNNLM_OK;
     const size_t es = elem_size(dtype);
+    const int Wr = round_up(Hp, 128);           // the hidden update reads W in tiles of up to 128 rows
     ModelDev &d = m->dev;
     std::vector<float> hrs;
     void *p;
     HIP_TRY(hipMalloc(&p, (size_t)V * Hp * es)); d.U = p;
-    HIP_TRY(hipMalloc(&p, (size_t)Hp * Hp * es)); d.W = p;
+    HIP_TRY(hipMalloc(&p, (size_t)Wr * Hp * es)); d.W = p;
     HIP_TRY(hipMalloc(&p, (size_t)Hp * 4)); d.half_rowsum_W = static_cast<float *>(p);
     status = alloc_scratch(m, max_Bp, with_partials);
     if (status != RNNLM_OK) return status;
-    HIP_TRY(hipMemset(const_cast<void *>(d.W), 0, (size_t)Hp * Hp * es));       // rows H .. Hp - 1
+    HIP_TRY(hipMemset(const_cast<void *>(d.W), 0, (size_t)Wr * Hp * es));       // rows H .. Wr - 1
     status = upload_rows(const_cast<void *>(d.U), U, V, H, Hp, dtype);
     if (status != RNNLM_OK) return status;
     status = upload_rows(const_cast<void *>(d.W), W, H, H, Hp, dtype);

@@ -132,6 +132,14 @@ __device__ __forceinline__ void lds_dma_16_ptr(const void *lane_ptr, uint32_t ld
                  : "memory");
 }
 
+// One float per lane (lane i writes LDS bytes [lds_base + 4 i, + 4)): rows that are not 16-byte aligned.
+__device__ __forceinline__ void lds_dma_4_ptr(const void *lane_ptr, uint32_t lds_base) {
+    asm volatile("s_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :
+                 : "{m0}"(lds_base), "v"(lane_ptr)
+                 : "memory");
+}
+
 // The same as lds_dma_16 by lane 0 alone (16 bytes to lds_base), without a branch around it: the
 // execution mask is narrowed to lane 0 for the one instruction and put back.  Counts as one
 // vector-memory operation of the wave like any other load.

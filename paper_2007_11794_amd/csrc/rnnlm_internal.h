@@ -28,7 +28,7 @@ struct ModelDev {
     int Vp;            // V rounded up to a multiple of 256; padded rows of Ot are zero
     int dtype;
     const void *U;     // [V][Hp]
-    const void *W;     // [Hp][Hp], W[j][i]
+    const void *W;     // [Hp rounded up to 128][Hp], W[j][i]
     const void *Ot;    // [Vp][Hp], Ot[v][j] = O[j][v]
     const float *half_rowsum_W;   // [Hp]  0.5 * sum_i W[j][i]
     const float *bias;            // [V]
