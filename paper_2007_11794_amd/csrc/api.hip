@@ -460,10 +460,12 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
     if (cache && (cache->dev.H != model->dev.H || N > cache->max_B)) return RNNLM_ERANGE;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     // through a cache, few enough raw queries: grouping and lookup are one launch
-    const bool one_launch = cache && N > 0 && N <= dedup_lookup_max_rows();
+    const bool one_launch = cache && N <= dedup_lookup_max_rows();
     if (one_launch) {
-        if (!workspace || workspace_bytes < dedup_workspace_bytes(N)) return RNNLM_EWORKSPACE;   // as rnnlm_dedup
-        if (reinterpret_cast<uintptr_t>(workspace) & 15) return RNNLM_EWORKSPACE;
+        if (N > 0) {                                                                              // as rnnlm_dedup
+            if (!workspace || workspace_bytes < dedup_workspace_bytes(N)) return RNNLM_EWORKSPACE;
+            if (reinterpret_cast<uintptr_t>(workspace) & 15) return RNNLM_EWORKSPACE;
+        }
         if (launch_dedup_lookup(cache->dev, history_ids, N, rep, inverse, n_unique, step_stats, s) != hipSuccess)
             return RNNLM_EDEVICE;
     } else {
@@ -492,7 +494,7 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
     }
     const CacheDev &c = cache->dev;
     if (!one_launch &&
-        launch_cache_lookup(c, N, 4096, history_ids, rep, n_unique, step_stats, s) != hipSuccess)
+        launch_cache_lookup(c, N, history_ids, rep, n_unique, step_stats, s) != hipSuccess)
         return RNNLM_EDEVICE;
     if (N == 0) return RNNLM_OK;
     // Only the histories the cache does not hold are computed: *c.n_miss rows, row r taken
@@ -535,7 +537,7 @@ int rnnlm_cache_create(const rnnlm_model *model, int capacity, rnnlm_cache **out
     c->max_B = model->max_B;
     status = alloc_cache_dev(d, capacity, model->dev.H, (size_t)model->max_B, true);
     if (status != RNNLM_OK) goto fail;
-    HIP_TRY(launch_cache_reset(d, nullptr));
+    HIP_TRY(launch_cache_reset(d, nullptr, nullptr));
     HIP_TRY(hipDeviceSynchronize());
     *out = c;
     return RNNLM_OK;
@@ -555,7 +557,7 @@ int rnnlm_cache_free(rnnlm_cache *cache) {
 
 int rnnlm_cache_reset(rnnlm_cache *cache, void *hip_stream) {
     if (!cache) return RNNLM_EINVAL;
-    return launch_cache_reset(cache->dev, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? RNNLM_OK
+    return launch_cache_reset(cache->dev, nullptr, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? RNNLM_OK
                                                                                                : RNNLM_EDEVICE;
 }
 
@@ -687,7 +689,7 @@ int rnnlm_index_create(int H, int capacity, int max_N, rnnlm_index_table **out) 
     HIP_TRY(hipMalloc(&p, 4)); d.n_unique = static_cast<int32_t *>(p);
     HIP_TRY(hipMalloc(&p, dedup_workspace_bytes(max_N))); d.dedup_ws = p;
     HIP_TRY(hipMalloc(&p, 2 * sizeof(long long))); d.errors = static_cast<long long *>(p);
-    HIP_TRY(launch_index_reset(d, nullptr));
+    HIP_TRY(launch_cache_reset(d.c, d.errors, nullptr));
     HIP_TRY(hipDeviceSynchronize());
     *out = t;
     return RNNLM_OK;
@@ -710,7 +712,7 @@ int rnnlm_index_free(rnnlm_index_table *table) {
 
 int rnnlm_index_reset(rnnlm_index_table *table, void *hip_stream) {
     if (!table) return RNNLM_EINVAL;
-    return launch_index_reset(table->dev, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? RNNLM_OK
+    return launch_cache_reset(table->dev.c, table->dev.errors, static_cast<hipStream_t>(hip_stream)) == hipSuccess ? RNNLM_OK
                                                                                                : RNNLM_EDEVICE;
 }
 
@@ -722,8 +724,15 @@ int rnnlm_index_intern(rnnlm_index_table *table, int N, const int32_t *word, con
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const IndexDev &d = table->dev;
     if (launch_context_hash(word, h, N, d.c.H, d.keys, s) != hipSuccess) return RNNLM_EDEVICE;
-    if (launch_dedup(d.keys, N, d.rep, d.inverse, d.n_unique, d.dedup_ws, s) != hipSuccess) return RNNLM_EDEVICE;
-    if (launch_cache_lookup(d.c, N, 1024, d.keys, d.rep, d.n_unique, nullptr, s) != hipSuccess) return RNNLM_EDEVICE;
+    // Grouping and lookup in one launch of one workgroup while that is no slower even when every context is new:
+    // reset, intern and fetch of 4096 contexts of H = 512, 1229 distinct 46.6 -> 31.6 us, all distinct 48.1 / 48.1;
+    // 7000 contexts, 2000 distinct 53 -> 43 but all distinct 61 -> 77.
+    if (N <= 4096) {
+        if (launch_dedup_lookup(d.c, d.keys, N, d.rep, d.inverse, d.n_unique, nullptr, s) != hipSuccess) return RNNLM_EDEVICE;
+    } else {
+        if (launch_dedup(d.keys, N, d.rep, d.inverse, d.n_unique, d.dedup_ws, s) != hipSuccess) return RNNLM_EDEVICE;
+        if (launch_cache_lookup(d.c, N, d.keys, d.rep, d.n_unique, nullptr, s) != hipSuccess) return RNNLM_EDEVICE;
+    }
     if (launch_index_commit(d, N, word, h, index, s) != hipSuccess) return RNNLM_EDEVICE;
     return RNNLM_OK;
 }

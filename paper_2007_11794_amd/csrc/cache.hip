@@ -12,8 +12,8 @@
 //   lookup   probe every distinct history; the ones not found are numbered in order of
 //            appearance by a prefix sum (row of the block that is computed now), get the next
 //            entries while there is room, and their keys are inserted.  One workgroup in one
-//            launch for few histories, three launches of a full grid (probe + counts, scan of
-//            the counts, numbering + insertion) for many;
+//            launch together with the grouping up to kMediumN raw queries, three launches of a full grid
+//            (probe + counts, scan of the counts, numbering + insertion) for more;
 //   (hidden update and output projection run on the numbered rows only)
 //   commit   per distinct history: normaliser into lse_rows; new entries are written to the
 //            stores, found ones copy their stored h' to the caller's h_out.
@@ -27,7 +27,7 @@ namespace {
 
 constexpr int kLookupThreads = 1024;
 
-__global__ __launch_bounds__(256) void cache_reset_kernel(CacheDev c) {
+__global__ __launch_bounds__(256) void cache_reset_kernel(CacheDev c, long long *errors) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < c.table_size) {
         CacheCell cell;
@@ -38,6 +38,7 @@ __global__ __launch_bounds__(256) void cache_reset_kernel(CacheDev c) {
     }
     if (i == 0) *c.n_entries = 0;
     if (i < 4) c.totals[i] = 0;
+    if (errors && i < 2) errors[i] = 0;
 }
 
 // One workgroup.  A round covers kLookupPer * 1024 distinct histories: every thread first
@@ -109,18 +110,21 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, int U, int3
                 c.entry_of[u] = found[i];
             }
         }
-        // every probe of this round is done (the scans above contain barriers)
+        // Every probe of this round is done (the scans above contain barriers).  A probe that missed ended at
+        // the first free cell of its chain, and cells are never given back: the insertion starts there.  All
+        // first attempts of a thread are in flight together.
+        int seen[kLookupPer];
+#pragma unroll
+        for (int i = 0; i < kLookupPer; ++i)
+            seen[i] = entry[i] >= 0 ? atomicCAS(&c.table[h[i]].entry, -1, entry[i]) : -1;
 #pragma unroll
         for (int i = 0; i < kLookupPer; ++i) {
             if (entry[i] < 0) continue;
-            uint32_t hh = mix64(key[i]) & mask;
-            for (int probe = 0; probe < c.table_size; ++probe) {
-                if (atomicCAS(&c.table[hh].entry, -1, entry[i]) == -1) {
-                    c.table[hh].key = key[i];
-                    break;
-                }
-                hh = (hh + 1) & mask;
+            for (int probe = 0; seen[i] != -1 && probe < c.table_size; ++probe) {
+                h[i] = (h[i] + 1) & mask;
+                seen[i] = atomicCAS(&c.table[h[i]].entry, -1, entry[i]);
             }
+            c.table[h[i]].key = key[i];
         }
         __threadfence_block();
         __syncthreads();                    // this round's insertions precede the next round's probes
@@ -140,22 +144,6 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, int U, int3
             step_stats[3] = base + stored;
         }
     }
-}
-
-__global__ __launch_bounds__(kLookupThreads) void cache_lookup_kernel(
-    CacheDev c, int rows, const uint64_t *__restrict__ ids, const int32_t *__restrict__ rep,
-    const int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats) {
-    // The first slice's representatives and ids are requested before the number of distinct
-    // histories is known (rep has `rows` slots; what lies beyond the true count is clamped into
-    // range and dropped later): one memory latency less at the head of the chain.
-    const int u_first = (int)threadIdx.x;
-    int raw_first = (u_first < rows) ? rep[u_first] : 0;
-    raw_first = max(min(raw_first, rows - 1), 0);
-    const uint64_t key_first = (rows > 0) ? ids[raw_first] : 0;
-    const int U = *n_unique;
-    cache_lookup_body(
-        c, U, step_stats, [&](int u0, int i, int u) { return (u0 == 0 && i == 0) ? raw_first : rep[u]; },
-        [&](int u0, int i, int u, int raw) { return (u0 == 0 && i == 0) ? key_first : ids[raw]; });
 }
 
 // Grouping of the step's ids and the lookup of the distinct ones in one launch of one workgroup
@@ -322,20 +310,16 @@ __global__ __launch_bounds__(256) void pack_ids_kernel(const uint32_t *__restric
 
 }  // namespace
 
-hipError_t launch_cache_reset(const CacheDev &c, hipStream_t stream) {
+hipError_t launch_cache_reset(const CacheDev &c, long long *errors, hipStream_t stream) {
     const int n = c.table_size > 4 ? c.table_size : 4;
-    hipLaunchKernelGGL(cache_reset_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, c);
+    hipLaunchKernelGGL(cache_reset_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, c, errors);
     return hipGetLastError();
 }
 
-hipError_t launch_cache_lookup(const CacheDev &c, int rows, int one_group_rows, const uint64_t *ids,
+hipError_t launch_cache_lookup(const CacheDev &c, int rows, const uint64_t *ids,
                                const int32_t *rep, const int32_t *n_unique, int32_t *step_stats,
                                hipStream_t stream) {
-    if (rows <= one_group_rows) {                       // few histories: one workgroup, one launch
-        hipLaunchKernelGGL(cache_lookup_kernel, dim3(1), dim3(kLookupThreads), 0, stream, c, rows, ids, rep, n_unique,
-                           step_stats);
-        return hipGetLastError();
-    }
+    if (rows <= 0) return hipSuccess;
     const int blocks = (rows + kLookupThreads - 1) / kLookupThreads;
     hipLaunchKernelGGL(lookup_probe_kernel, dim3(blocks), dim3(kLookupThreads), 0, stream, c, ids, rep, n_unique);
     hipLaunchKernelGGL(lookup_scan_kernel, dim3(1), dim3(kLookupThreads), 0, stream, c, blocks, n_unique,
@@ -349,7 +333,7 @@ int dedup_lookup_max_rows() { return kMediumN; }
 
 hipError_t launch_dedup_lookup(const CacheDev &c, const uint64_t *ids, int N, int32_t *rep, int32_t *inverse,
                                int32_t *n_unique, int32_t *step_stats, hipStream_t stream) {
-    if (N <= 0 || N > kMediumN) return hipErrorInvalidValue;
+    if (N < 0 || N > kMediumN) return hipErrorInvalidValue;
     if (N <= kSmallN)
         hipLaunchKernelGGL(dedup_lookup_kernel, dim3(1), dim3(kLookupThreads), 0, stream, c, ids, N, rep, inverse,
                            n_unique, step_stats);

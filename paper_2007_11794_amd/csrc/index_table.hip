@@ -23,15 +23,6 @@ namespace {
 
 constexpr uint32_t kNotStored = 0xFFFFFFFFu, kCollision = 0xFFFFFFFEu;
 
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)v, off, 64), hi = __shfl_xor((uint32_t)(v >> 32), off, 64);
-        v += ((uint64_t)hi << 32) | lo;
-    }
-    return v;
-}
-
 // Rows of H floats can be walked in 16-byte pieces when H is a multiple of 4 and the buffer is
 // 16-byte aligned (the stores of the table are).
 __device__ __forceinline__ bool vec_rows(const void *p, int H) {
@@ -50,15 +41,47 @@ __device__ __forceinline__ void copy_row(uint32_t *dst, const uint32_t *src, int
 // The hash of a vector is multilinear: sum over the positions j of a_j * x_j (mod 2^64), x_j the bit
 // pattern of element j and a_j an odd 64-bit multiplier derived from j -- order-free, so lanes and
 // their partial sums combine freely, and two vectors that differ in one element never collide
-// (a_j odd).  A wave hashes kHashRows consecutive contexts at once: the multipliers of its positions
+// (a_j odd).  A wave hashes four or eight consecutive contexts at once: the multipliers of its positions
 // are computed once and the loads of all rows are in flight together.  The word is mixed in at
 // the end.
-constexpr int kHashRows = 8;
+// Bound by the integer multiplies (two per element, and the multipliers) while the waves fit the SIMDs, by
+// the one pass over the vectors beyond.  Four contexts per wave up to kFewContexts, so that N = 4096 puts a
+// wave on every SIMD; eight beyond, where the multipliers' share counts.  The sums of a wave's contexts are
+// reduced together: half of the values change sides at every level, 7 or 10 exchanges instead of 24 or 48.
+constexpr int kFewContexts = 8192;
 
 __device__ __forceinline__ uint64_t position_multiplier(int j) {
     return mix64_full((uint64_t)j + 0x632BE59BD9B4E019ull) | 1ull;
 }
 
+// Sums over the wave of ROWS (4 or 8) per-lane values; lane l ends up with the sum of value hash_slot(l).
+template <int ROWS>
+__device__ __forceinline__ int hash_slot(int lane) {
+    const int s = (lane >> 4) & 3;                       // bits 5 and 4
+    return ROWS == 4 ? s : 2 * s + ((lane >> 3) & 1);
+}
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int off) {
+    const uint32_t lo = __shfl_xor((uint32_t)v, off, 64), hi = __shfl_xor((uint32_t)(v >> 32), off, 64);
+    return ((uint64_t)hi << 32) | lo;
+}
+template <int ROWS>
+__device__ __forceinline__ uint64_t wave_sums_u64(const uint64_t (&acc)[ROWS], int lane) {
+    uint64_t v[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) v[i] = acc[i];
+    int off = 32;
+#pragma unroll
+    for (int n = ROWS; n > 1; n /= 2, off /= 2) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int i = 0; i < n / 2; ++i) v[i] = (up ? v[n / 2 + i] : v[i]) + shfl_xor_u64(up ? v[i] : v[n / 2 + i], off);
+    }
+#pragma unroll
+    for (; off > 0; off /= 2) v[0] += shfl_xor_u64(v[0], off);
+    return v[0];
+}
+
+template <int kHashRows>
 __global__ __launch_bounds__(256) void context_hash_kernel(const int32_t *__restrict__ word,
                                                             const float *__restrict__ h, int N, int H,
                                                             uint64_t *__restrict__ keys) {
@@ -89,12 +112,10 @@ __global__ __launch_bounds__(256) void context_hash_kernel(const int32_t *__rest
             for (int r = 0; r < kHashRows; ++r) acc[r] += a * (uint64_t)base[(size_t)min(n0 + r, N - 1) * H + j];
         }
     }
-#pragma unroll
-    for (int r = 0; r < kHashRows; ++r) {
-        const uint64_t sum = wave_sum_u64(acc[r]);
-        if (lane == 0 && n0 + r < N)
-            keys[n0 + r] = mix64_full(sum ^ ((uint64_t)(uint32_t)word[n0 + r] * 0x9E3779B97F4A7C15ull));
-    }
+    const uint64_t sum = wave_sums_u64<kHashRows>(acc, lane);
+    const int n = n0 + hash_slot<kHashRows>(lane);
+    if ((lane & (kHashRows == 4 ? 15 : 7)) == 0 && n < N)
+        keys[n] = mix64_full(sum ^ ((uint64_t)(uint32_t)word[n] * 0x9E3779B97F4A7C15ull));
 }
 
 __global__ __launch_bounds__(256) void index_commit_kernel(IndexDev t, int N, const int32_t *__restrict__ word,
@@ -162,24 +183,15 @@ __global__ __launch_bounds__(256) void index_fetch_kernel(IndexDev t, int N, con
     }
 }
 
-__global__ void index_clear_errors_kernel(IndexDev t) {
-    if (threadIdx.x < 2) t.errors[threadIdx.x] = 0;
-}
-
 }  // namespace
-
-hipError_t launch_index_reset(const IndexDev &t, hipStream_t stream) {
-    hipError_t e = launch_cache_reset(t.c, stream);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(index_clear_errors_kernel, dim3(1), dim3(64), 0, stream, t);
-    return hipGetLastError();
-}
 
 hipError_t launch_context_hash(const int32_t *word, const float *h, int N, int H, uint64_t *keys,
                                hipStream_t stream) {
     if (N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(context_hash_kernel, dim3((N + 4 * kHashRows - 1) / (4 * kHashRows)), dim3(256), 0, stream, word, h,
-                       N, H, keys);
+    if (N <= kFewContexts)
+        hipLaunchKernelGGL(context_hash_kernel<4>, dim3((N + 15) / 16), dim3(256), 0, stream, word, h, N, H, keys);
+    else
+        hipLaunchKernelGGL(context_hash_kernel<8>, dim3((N + 31) / 32), dim3(256), 0, stream, word, h, N, H, keys);
     return hipGetLastError();
 }
 

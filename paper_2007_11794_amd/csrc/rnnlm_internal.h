@@ -248,17 +248,16 @@ hipError_t launch_query_cached(const ModelDev &m, const CacheDev &c, int rows, c
                                hipStream_t stream);
 
 // ---- cache kept between steps (cache.hip)
-hipError_t launch_cache_reset(const CacheDev &c, hipStream_t stream);
+// errors: an index table's two error counters, cleared along with it, or null
+hipError_t launch_cache_reset(const CacheDev &c, long long *errors, hipStream_t stream);
 // Looks the distinct histories ids[rep[u]], u < *n_unique, up; numbers the ones not found
 // (in order of u), gives them entries while there is room and inserts their keys.
-// rows = upper bound of *n_unique (sizes the grid).  Up to one_group_rows the lookup is one launch
-// of one workgroup (best while the table sits in L2: the step's cache, up to 4096), beyond it
-// three launches of a full grid (best when the probes go to HBM: the index table, from 1024).
-hipError_t launch_cache_lookup(const CacheDev &c, int rows, int one_group_rows, const uint64_t *ids,
+// rows = upper bound of *n_unique (sizes the grid).  Three launches of a full grid.
+hipError_t launch_cache_lookup(const CacheDev &c, int rows, const uint64_t *ids,
                                const int32_t *rep, const int32_t *n_unique, int32_t *step_stats,
                                hipStream_t stream);
 // Grouping of the ids (launch_dedup) and this lookup in ONE launch of one workgroup, for
-// 0 < N <= dedup_lookup_max_rows() raw queries.
+// 0 <= N <= dedup_lookup_max_rows() raw queries (or contexts of an index table).
 int dedup_lookup_max_rows();
 hipError_t launch_dedup_lookup(const CacheDev &c, const uint64_t *ids, int N, int32_t *rep, int32_t *inverse,
                                int32_t *n_unique, int32_t *step_stats, hipStream_t stream);
@@ -269,7 +268,6 @@ hipError_t launch_cache_commit(const CacheDev &c, const ModelDev &m, int rows, c
 // Index table: content hashes of N contexts; after grouping and lookup, storage of the new
 // contexts, full comparison of every context with the one it was identified with, and the
 // indices; gather of stored contexts.
-hipError_t launch_index_reset(const IndexDev &t, hipStream_t stream);
 hipError_t launch_context_hash(const int32_t *word, const float *h, int N, int H, uint64_t *keys,
                                hipStream_t stream);
 hipError_t launch_index_commit(const IndexDev &t, int N, const int32_t *word, const float *h, uint32_t *index,
