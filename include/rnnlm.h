@@ -82,7 +82,7 @@ enum rnnlm_option {
      * up to 128 rows in at most four launches, and larger batches go the automatic way,
      * 6 = (bf16 models) the kernel that sends only the weights through
      * LDS and takes the hidden rows straight into registers chunk by chunk: the automatic choice for
-     * H > 512 from 256 rows on when batch and vocabulary give every compute unit a 256 x 256 tile (with
+     * H > 704 from 256 rows on when batch and vocabulary give every compute unit a 256 x 256 tile (with
      * the running maximum it falls back to 3).
      * EINVAL if the model does not allow the choice. */
     RNNLM_OPT_OUTPROJ_KERNEL = 2

@@ -40,6 +40,7 @@ ModelDev recur_view(const rnnlm_model *m, int rows) {
     ModelDev v = m->dev;
     if (v.hs) { v.d = nullptr; v.dfrag = nullptr; return v; }
     if (!outproj_reads_row_order(v, rows, use_fixed_offset(m), m->outproj_kernel)) v.d = nullptr;
+    v.d_scale = outproj_d_scale(v, rows, use_fixed_offset(m), m->outproj_kernel);
     return v;
 }
 
@@ -67,6 +68,7 @@ void free_weights(rnnlm_model *m) {
     (void)hipFree(const_cast<float *>(d.half_colsum_O));
     (void)hipFree(const_cast<float *>(d.cvec2));
     (void)hipFree(const_cast<float *>(d.cvec2_fixed));
+    (void)hipFree(const_cast<float *>(d.cvec_fixed));
     (void)hipFree(const_cast<void *>(d.Ofrag));
     (void)hipFree(const_cast<float *>(d.ofac));
     (void)hipFree(const_cast<void *>(d.Theta));
@@ -267,6 +269,7 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
     HIP_TRY(hipMalloc(&p, (size_t)V * 4)); d.half_colsum_O = static_cast<float *>(p);
     HIP_TRY(hipMalloc(&p, (size_t)Vp * 4)); d.cvec2 = static_cast<float *>(p);
     HIP_TRY(hipMalloc(&p, (size_t)Vp * 4)); d.cvec2_fixed = static_cast<float *>(p);
+    HIP_TRY(hipMalloc(&p, (size_t)Vp * 4)); d.cvec_fixed = static_cast<float *>(p);
 
     // O: upload as given, transpose + pad on the device, column statistics
     HIP_TRY(hipMalloc(&O_stage, (size_t)H * V * es));
@@ -297,7 +300,8 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
         if (!isfinite(d.m2_fixed)) d.m2_fixed = 0.f;
     }
     HIP_TRY(launch_fill_cvec(bias_stage, d.half_colsum_O, V, Vp, d.m2_fixed, const_cast<float *>(d.bias),
-                             const_cast<float *>(d.cvec2), const_cast<float *>(d.cvec2_fixed), nullptr));
+                             const_cast<float *>(d.cvec2), const_cast<float *>(d.cvec2_fixed),
+                             const_cast<float *>(d.cvec_fixed), nullptr));
     HIP_TRY(hipMalloc(&p, (size_t)Vp * Hp * es)); d.Ofrag = p;                  // operand-ordered copy
     if (dtype == RNNLM_F32) {
         HIP_TRY(hipMalloc(&p, (size_t)Vp * 4)); d.ofac = static_cast<float *>(p);
@@ -382,7 +386,10 @@ int rnnlm_set_option(rnnlm_model *model, int option, int value) {
             if (value == 6 && !outproj_rowstream_supported(model->dev)) return RNNLM_EINVAL;
             if (value == 5 && outproj_stream_max_rows(model->dev) == 0) return RNNLM_EINVAL;
             if (value == 4 && !model->dev.ofac) return RNNLM_EINVAL;
-            if (value == 2 && !outproj_staged_supported(model->dev)) return RNNLM_EINVAL;
+            // (by itself the library takes the staged kernel for every padded size up to 512)
+            if (value == 2 && (!outproj_staged_supported(model->dev) ||
+                               (model->dev.Hp != 128 && model->dev.Hp != 256 && model->dev.Hp != 512)))
+                return RNNLM_EINVAL;
             model->outproj_kernel = value;
             return RNNLM_OK;
         default:

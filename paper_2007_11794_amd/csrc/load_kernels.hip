@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void fill_cvec_kernel(const float *__restrict_
                                                         const float *__restrict__ half_colsum, int V,
                                                         int Vp, float m2_fixed, float *__restrict__ bias_out,
                                                         float *__restrict__ cvec,
-                                                        float *__restrict__ cvec_fixed) {
+                                                        float *__restrict__ cvec2_fixed, float *__restrict__ cvec_fixed) {
     int v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= Vp) return;
     if (v < V) {
@@ -71,9 +71,11 @@ __global__ __launch_bounds__(256) void fill_cvec_kernel(const float *__restrict_
         bias_out[v] = b;
         float c = (b + half_colsum[v]) * kLog2e;
         cvec[v] = c;
-        cvec_fixed[v] = c - m2_fixed;
+        cvec2_fixed[v] = c - m2_fixed;
+        cvec_fixed[v] = (float)((double)(c - m2_fixed) * 0.6931471805599453);
     } else {
         cvec[v] = -INFINITY;
+        cvec2_fixed[v] = -INFINITY;
         cvec_fixed[v] = -INFINITY;
     }
 }
@@ -186,9 +188,10 @@ hipError_t launch_col_stats(const void *O_dev, const float *bias, int dtype, int
 }
 
 hipError_t launch_fill_cvec(const float *bias, const float *half_colsum, int V, int Vp, float m2_fixed,
-                            float *bias_out, float *cvec, float *cvec_fixed, hipStream_t stream) {
+                            float *bias_out, float *cvec2, float *cvec2_fixed, float *cvec_fixed,
+                            hipStream_t stream) {
     hipLaunchKernelGGL(fill_cvec_kernel, dim3((Vp + 255) / 256), dim3(256), 0, stream, bias, half_colsum,
-                       V, Vp, m2_fixed, bias_out, cvec, cvec_fixed);
+                       V, Vp, m2_fixed, bias_out, cvec2, cvec2_fixed, cvec_fixed);
     return hipGetLastError();
 }
 

@@ -222,6 +222,7 @@ static bool stream_choice(const ModelDev &m, int rows, int kernel_choice) {
 enum Bf16Kernel { kBf16Stream, kBf16Staged, kBf16RowStream, kBf16Tiled, kBf16Plain };
 static Bf16Kernel choose_bf16(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {
     if (stream_choice(m, rows, kernel_choice)) return kBf16Stream;
+    // the hidden block in registers wherever it fits them (Hp <= 704), from 128 rows on; figures in its file
     if (kernel_choice == 2 || (kernel_choice == 0 && outproj_staged_supported(m) && rows >= 128)) return kBf16Staged;
     // hidden sizes beyond the staged kernel's, batches and vocabularies that give every compute unit a
     // 256 x 256 tile, fixed offset: the hidden rows by-pass LDS (on request: any batch the model allows)
@@ -251,6 +252,12 @@ bool outproj_reads_row_order(const ModelDev &m, int rows, bool fixed_offset, int
     }
     const Bf16Kernel k = choose_bf16(m, rows, fixed_offset, kernel_choice);
     return k == kBf16Tiled || k == kBf16Plain;
+}
+
+float outproj_d_scale(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {
+    if (m.dtype == RNNLM_BF16 && choose_bf16(m, rows, fixed_offset, kernel_choice) == kBf16Staged && !staged_scaled_d(m.Hp))
+        return 1.f;
+    return kLog2e;
 }
 
 // The kernel launch_outproj takes for these arguments, by the name a kernel trace shows.

@@ -1,5 +1,5 @@
 // Output projection + log-sum-exp, bf16 MFMA kernel for hidden sizes beyond what the staged kernel
-// keeps in registers (Hp > 512; the H = 1024 stress workload), batches of 256 rows and more, fixed
+// keeps in registers (Hp > 704; the H = 1024 stress workload), batches of 256 rows and more, fixed
 // log-sum-exp offset.
 //
 // Same result as the other output-projection kernels (normalising over all words of the vocabulary,
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(kThreads) void outproj_rowstream_kernel(ModelDev m,
     // very few rows after all: every workgroup streams its share of the weights (as the tiled kernel)
     static_assert(kThreads == kStreamThreads, "");
     if (B <= stream_rows) {
-        if (B <= 32) outproj_stream_body<1, true>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-        else outproj_stream_body<2, true>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        if (B <= 32) outproj_stream_body<1, true, true>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        else outproj_stream_body<2, true, true>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
         return;
     }
     const RowPlan plan = plan_rows(B, kRows, wg_per_xcd, sx_cap);

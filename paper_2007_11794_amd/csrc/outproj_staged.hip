@@ -1,17 +1,16 @@
-// Output projection + log-sum-exp, LDS-staged bf16 MFMA kernel for Hp in {128, 256, 512}.
+// Output projection + log-sum-exp, LDS-staged bf16 MFMA kernel for Hp <= 704 (multiples of 64 from 128 on).
 //
 // What is computed is the same as in the plain kernel (normalising over all words of the
 // vocabulary, Section 2.1 of the paper); this is the fast form for batches of >= 128 rows.
 //
 // Shape of the work.  The hidden block d = h' - 1/2 is tiny (rows x Hp bf16, 1 MB at
-// 1024 x 512) and the output weights Ot[Vp][Hp] are large (64 MB at V = 65536), so the
+// 1024 x 512) and the output weights are large (64 MB at V = 65536), so the
 // weights are streamed exactly once per row group and the hidden block never moves:
 //   - a workgroup (8 waves) owns 256 rows; each wave keeps ITS 32 rows of d for the whole
 //     reduction length in registers (Hp/16 MFMA B-operands, 128 VGPRs at Hp = 512), loaded from
-//     the fragment-ordered copy of the block (one operand = 1 KB contiguous), which holds
-//     d * log2(e): the accumulators are base-2 logits;
+//     the fragment-ordered copy of the block (one operand = 1 KB contiguous);
 //   - the weights of 32 words (32 x Hp bf16, 32 KB at Hp = 512) form one LDS stage; four
-//     stages are filled round-robin by direct global->LDS loads (no VGPR round trip), two to
+//     stages (three beyond Hp = 512) are filled round-robin by direct global->LDS loads (no VGPR round trip), two to
 //     three blocks ahead of use;
 //   - per block a wave issues Hp/16 chained MFMA 32x32x16: A = 32 words x 16 k from LDS
 //     (read four steps ahead), B = 16 k x 32 rows from registers, so lane l holds 16 logits
@@ -29,10 +28,21 @@
 // burst behind the barrier, two accumulator sets alternate (no copy between blocks, the next chain
 // does not wait for the last MFMA of this one), and the constants a chain starts from are read
 // from LDS into the resting accumulator set half a block before they are needed.
-// LDS rows are XOR-swizzled in 16-byte chunks (chunk c of word r sits at c ^ (r & 15)) so
-// that the 16 lanes served together by one ds_read_b128 hit 16 different bank groups.  The
-// direct loads write LDS linearly (lane i -> base + 16 i), so the swizzle is applied on the
-// global side: lane i fetches the chunk that belongs at position i.
+// Where the weights come from.  Hp a multiple of 128 up to 512: from Ot, row by row; LDS rows are XOR-swizzled in 16-byte
+// chunks (chunk c of word r sits at c ^ (r & 15)) so that the 16 lanes served together by one ds_read_b128 hit 16
+// different bank groups.  The direct loads write LDS linearly (lane i -> base + 16 i), so the swizzle is applied on
+// the global side: lane i fetches the chunk that belongs at position i.  Other multiples of 64 (and 640: the
+// offsets of the swizzle would not fit the registers): from the copy in
+// MFMA-operand order (Ofrag), where a block is Hp / 16 operands of one contiguous kilobyte each and a stage a straight
+// copy of it; the upper four waves' share of the last 8 KB is a dummy load, and stages are whole 8 KB.  (Ot where it
+// can be: the words the queries ask for are then in the L2s when the query kernel reads them from the same copy;
+// the headline step 68.0 us, against 68.9 with Ofrag.)
+// Padded sizes other than 128, 256 and 512 took the row-streaming and tiled kernels before.  Us per launch:
+//   V = 65536: H = 192, 1024 rows 30.9 -> 26.6; 320, 1024 rows 44.3 -> 38.3; 384, 700 rows 45.5 -> 34.3; 448, 300
+//   rows 31.3 -> 26.6; V = 100000: H = 576, 1000 rows 113 -> 89 (running maximum 126 -> 104); 704, 2048 rows
+//   263 -> 210; 700, 200 rows 48 -> 35; V = 30011, H = 650, 317 rows, running maximum 25.2 -> 23.9.  H = 512 and
+//   below at multiples of 128: as before (54 us at V = 65536, H = 512, 1024 rows).
+// Beyond 704 the hidden block and the accumulators do not fit the 256 registers of a wave.
 //
 // When the batch turns out to hold at most 64 rows (the count may be known on the device only),
 // the kernel runs the weight-streaming body instead (outproj_stream_body.h): see the top of
@@ -52,7 +62,6 @@ namespace rnnlm {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kStages = 4;
 constexpr int kCSlots = 8;                       // ring of per-block constants (32 floats each)
 constexpr int kCSlotBytes = kStagedWords * 4;
 constexpr int kPrefetch = 4;                     // A operands read this many k-steps ahead
@@ -60,86 +69,117 @@ constexpr int kPrefetch = 4;                     // A operands read this many k-
 template <int HP>
 struct StagedCfg {
     static constexpr int KS = HP / 16;                       // MFMA k-steps per block
-    static constexpr int CPR = HP / 8;                       // 16-byte chunks per word row
-    static constexpr int kStageChunks = kStagedWords * CPR;
-    static constexpr int kStageBytes = kStageChunks * 16;
-    static constexpr int kLoadsPerThread = kStageChunks / kThreads;     // weight loads per block
+    static constexpr bool kRowOrder = HP % 128 == 0 && HP <= 512;       // weights from Ot, else from Ofrag
+    static constexpr bool kScaledD = staged_scaled_d(HP);
+    static constexpr int CPR = HP / 8;                                  // 16-byte chunks per word row
+    static constexpr int kStages = HP <= 512 ? 4 : 3;                  // as LDS allows
+    static constexpr int kLoadsPerThread = (KS + 7) / 8;                // weight loads per block: 8 KB each
+    static constexpr int kStageBytes = kLoadsPerThread * 8192;
     static constexpr int kLoadsPerBlock = kLoadsPerThread + 1;          // + one for the constants
     static constexpr int kLdsBytes = kStages * kStageBytes + kCSlots * kCSlotBytes;
-    static_assert(kStageChunks % kThreads == 0, "stage must be a whole number of loads per thread");
-    static_assert(CPR >= 16, "swizzle needs at least 16 chunks per row");
-    static_assert(kLoadsPerBlock <= 6, "s_waitcnt immediates below assume few loads per block");
+    static_assert(HP % 64 == 0 && KS >= 8, "");
+    static_assert(kLdsBytes <= 160 * 1024, "");
 };
 
-// Per-thread constants of the block loader.
+// The block loader.
 template <int HP>
 struct Loader {
-    uint32_t voff[StagedCfg<HP>::kLoadsPerThread];           // byte offset in the block of words
+    using C = StagedCfg<HP>;
     uint32_t wave;                                           // wave index, in an SGPR
+    uint32_t voff[C::kRowOrder ? C::kLoadsPerThread : 1];    // this lane's bytes of a piece (row order: of a block)
     int lane;
     __device__ __forceinline__ void init() {
-        using C = StagedCfg<HP>;
         const int tid = threadIdx.x;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         lane = tid & 63;
+        if constexpr (C::kRowOrder) {
 #pragma unroll
-        for (int q = 0; q < C::kLoadsPerThread; ++q) {
-            const int f = q * kThreads + tid;                // physical chunk this lane fills
-            const int r = f / C::CPR, p = f % C::CPR;
-            const int c = p ^ (r & 15);                      // logical chunk that belongs there
-            voff[q] = (uint32_t)(r * HP * 2 + c * 16);
+            for (int q = 0; q < C::kLoadsPerThread; ++q) {
+                const int f = q * kThreads + tid;            // physical chunk this lane fills
+                const int r = f / C::CPR, p = f % C::CPR;
+                const int c = p ^ (r & 15);                  // logical chunk that belongs there
+                voff[q] = (uint32_t)(r * HP * 2 + c * 16);
+            }
+        } else {
+            voff[0] = (uint32_t)lane * 16;
         }
     }
-    // Start the loads of the 32-word block whose first word is v0 into stage / constant slot.
-    __device__ __forceinline__ void issue(const bf16_t *Ot, const float *cvec, int v0, uint32_t stage_lds,
+    // Start the loads of 32-word block `block` into stage / constant slot.
+    __device__ __forceinline__ void issue(const char *weights, const float *cvec, int block, uint32_t stage_lds,
                                           uint32_t cslot_lds) const {
-        using C = StagedCfg<HP>;
-        const bf16_t *blk = Ot + (size_t)v0 * HP;
+        const char *src = block_of(weights, block);
 #pragma unroll
-        for (int q = 0; q < C::kLoadsPerThread; ++q)
-            lds_dma_16(blk, voff[q], stage_lds + (q * kThreads + wave * 64) * 16);
+        for (int q = 0; q < C::kLoadsPerThread; ++q) issue_weights(src, q, true, stage_lds);
         // the 32 constants of the block: 16 bytes per wave, by its lane 0
-        if (lane == 0) lds_dma_16(cvec + v0, wave * 16, cslot_lds + wave * 16);
+        if (lane == 0) lds_dma_16(cvec + (size_t)block * kStagedWords, wave * 16, cslot_lds + wave * 16);
+    }
+    // (a block is 64 HP bytes in either order)
+    __device__ __forceinline__ const char *block_of(const char *weights, int block) const {
+        return weights + (size_t)block * (64 * HP);
     }
     // The same in pieces and without branches (the fixed-offset block body is one basic block):
     // weight load q of the block, and its constants.  real = false turns the load into a dummy
     // that counts like a real one for vmcnt but fetches the first bytes of the weights (always
     // there, one cache line for the whole wave) into the same, free, LDS stage.
-    __device__ __forceinline__ void issue_weights(const bf16_t *blk, int q, bool real, uint32_t stage_lds) const {
-        lds_dma_16(blk, real ? voff[q] : 0u, stage_lds + (q * kThreads + wave * 64) * 16);
+    __device__ __forceinline__ void issue_weights(const char *src, int q, bool real, uint32_t stage_lds) const {
+        const uint32_t to = stage_lds + (q * 8 + wave) * 1024;
+        if constexpr (C::kRowOrder) {
+            lds_dma_16(src, real ? voff[q] : 0u, to);
+        } else {
+            const bool mine = real && (HP % 128 == 0 || q + 1 < C::kLoadsPerThread || wave < 4);
+            lds_dma_16(mine ? src + (q * 8 + wave) * 1024 : src, mine ? voff[0] : 0u, to);
+        }
     }
     __device__ __forceinline__ void issue_consts(const float *cblk, uint32_t cslot_lds) const {
         lds_dma_16_lane0(cblk, wave * 16, cslot_lds + wave * 16);
     }
-    __device__ __forceinline__ void issue_all(const bf16_t *Ot, const float *cvec, int v0, bool real,
-                                              uint32_t stage_lds, uint32_t cslot_lds) const {
-        using C = StagedCfg<HP>;
-        const int v = real ? v0 : 0;
-        const bf16_t *blk = Ot + (size_t)v * HP;
+    __device__ __forceinline__ void issue_all(const char *weights, const float *cvec, int block, uint32_t stage_lds,
+                                              uint32_t cslot_lds) const {
+        const char *src = block_of(weights, block);
 #pragma unroll
-        for (int q = 0; q < C::kLoadsPerThread; ++q) issue_weights(blk, q, real, stage_lds);
-        issue_consts(cvec + v, cslot_lds);
+        for (int q = 0; q < StagedCfg<HP>::kLoadsPerThread; ++q) issue_weights(src, q, true, stage_lds);
+        issue_consts(cvec + (size_t)block * kStagedWords, cslot_lds);
     }
 };
 
-// The hidden block arrives multiplied by log2(e) (fragment-ordered copy), so the accumulators
-// are base-2 already.  Fixed offset: the accumulators START at the block's constants, and a
-// finished accumulator IS the logit (one VALU instruction less per logit; |constant| < 100 there,
-// so accumulating on top of it costs nothing the tolerance would notice).  Running maximum
-// (constants of any size): the constants are added at the end, x = acc + c2.
-template <bool FIXED>
+// A hidden block that carries log2(e) (SCALED, see outproj_d_scale) makes the accumulators base-2; otherwise one
+// multiplication per logit does.  Fixed offset: the accumulators START at the block's constants, and a finished
+// accumulator IS the logit (|constant| < 100 there, so accumulating on top of it costs nothing the tolerance
+// would notice).  Running maximum (constants of any size): the constants are added at the end.
+template <bool SCALED>
+__device__ __forceinline__ float base2(float acc) { return SCALED ? acc : acc * kLog2e; }
+template <bool FIXED, bool SCALED>
 __device__ __forceinline__ void finish_logits(const f32x16 &acc, const f32x4 *cn, int g, float (&x)[16]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         f32x4 c = {0.f, 0.f, 0.f, 0.f};
         if (!FIXED) c = cn[2 * q + g];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[4 * q + i] = FIXED ? acc[4 * q + i] : acc[4 * q + i] + c[i];
+        for (int i = 0; i < 4; ++i) x[4 * q + i] = FIXED ? base2<SCALED>(acc[4 * q + i]) : SCALED ? acc[4 * q + i] + c[i] : fmaf(acc[4 * q + i], kLog2e, c[i]);
     }
 }
 
-#define RNNLM_A_FRAG(stage, ks) \
-    (*reinterpret_cast<const bf16x8 *>((stage) + aoff[(ks) & 7] + ((ks) >> 3) * 256))
+// This lane's part of an A operand.  Row order: chunk (2 ks + g) of word `col`, swizzled; only the low 4 bits
+// of the chunk index take part in the swizzle, so eight per-lane offsets plus compile-time constants cover
+// all k-steps.  Operand order: one offset.
+template <int HP>
+struct FragOffsets {
+    int at[StagedCfg<HP>::kRowOrder ? 8 : 1];
+    __device__ __forceinline__ void init(int lane) {
+        if constexpr (StagedCfg<HP>::kRowOrder) {
+            const int col = lane & 31, g = lane >> 5;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) at[j] = col * (HP * 2) + ((((2 * j) | g) ^ (col & 15)) * 16);
+        } else {
+            at[0] = lane * 16;
+        }
+    }
+    __device__ __forceinline__ int operator()(int ks) const {
+        if constexpr (StagedCfg<HP>::kRowOrder) return at[ks & 7] + (ks >> 3) * 256;
+        else return at[0] + ks * 1024;
+    }
+};
+#define RNNLM_A_FRAG(stage, ks) (*reinterpret_cast<const bf16x8 *>((stage) + aoff(ks)))
 
 // One 32-word block for this wave's 32 rows.
 //   stage      LDS stage of this block; a[] already holds its first kPrefetch A operands
@@ -152,7 +192,7 @@ __device__ __forceinline__ void finish_logits(const f32x16 &acc, const f32x4 *cn
 //   pacc, pcn  the previous block's raw accumulators and its constants: its exp-and-add is
 //              spread over this block's k-steps (fixed offset) or done up front (running max)
 template <int HP, bool FIXED>
-__device__ __forceinline__ void staged_block(const char *stage, const char *next_stage, const int (&aoff)[8],
+__device__ __forceinline__ void staged_block(const char *stage, const char *next_stage, const FragOffsets<HP> &aoff,
                                              bf16x8 (&a)[kPrefetch], const bf16x8 (&dreg)[HP / 16], int g,
                                              const f32x4 *ccur, f32x16 &pacc, const f32x4 *pcn, float &mrun,
                                              float &srun) {
@@ -168,7 +208,7 @@ __device__ __forceinline__ void staged_block(const char *stage, const char *next
         }
     } else {
         float x[16];
-        finish_logits<false>(pacc, pcn, g, x);
+        finish_logits<false, StagedCfg<HP>::kScaledD>(pacc, pcn, g, x);
         lse2_fold16<false>(x, mrun, srun);
     }
 #pragma unroll
@@ -181,7 +221,7 @@ __device__ __forceinline__ void staged_block(const char *stage, const char *next
             // sixteen logits of the previous block spread evenly over the KS steps
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                if ((e * KS) / 16 == ks) srun += fast_exp2(pacc[e]);
+                if ((e * KS) / 16 == ks) srun += fast_exp2(base2<StagedCfg<HP>::kScaledD>(pacc[e]));
         }
         // keep this order: the compiler's scheduler would otherwise sink every LDS read to
         // just before its MFMA and expose the LDS latency on each step
@@ -233,11 +273,12 @@ struct FirstBlockSchedule {
     static constexpr int KS = C::KS, HALF = KS / 2, L = C::kLoadsPerBlock, NW = C::kLoadsPerThread;
     static constexpr int kLoadStep = (HALF - 2) / NW;
     static constexpr int D0 = KS < 8 ? KS : 8;                 // operands of d requested by the prologue
-    static_assert(2 * L <= HALF, "blocks 1 and 2 are requested in the first half of block 0");
+    static constexpr int kAhead = C::kStages - 2;              // blocks requested in the first half of block 0: 1 and, with four stages, 2
+    static_assert(kAhead * L <= HALF, "");
     // loads issued in k-step k: before its MFMA an operand of d (e1) and a load of block 1 or 2 (e2),
-    // after its MFMA the regular loads of block 3 (e3)
+    // after its MFMA the regular loads of the block behind them (e3)
     static constexpr int e1(int k) { return k + D0 < KS ? 1 : 0; }
-    static constexpr int e2(int k) { return k < 2 * L ? 1 : 0; }
+    static constexpr int e2(int k) { return k < kAhead * L ? 1 : 0; }
     static constexpr int e3(int k) {
         int n = (k == KS - 2) ? 1 : 0;
         for (int q = 0; q < NW; ++q)
@@ -276,15 +317,15 @@ struct FirstBlockSchedule {
 };
 struct FirstBlockLoads {
     const bf16_t *dfr;          // this lane's 16 bytes of operand 0 of its wave's rows
-    const bf16_t *blk[2];       // weights of blocks 1 and 2 (or the dummy source)
+    const char *blk[2];         // weights of blocks 1 and 2 (or the dummy source)
     const float *cst[2];        // their constants
     bool real[2];
     uint32_t stage[2], cslot[2];
 };
 
 // Fixed offset: one 32-word block for this wave's 32 rows, as ONE basic block.
-//   acc     on entry the block's constants (the base-2 logits start from them), on return the
-//           finished logits of the block
+//   acc     on entry the block's constants (the logits start from them), on return the finished
+//           logits of the block
 //   other   on entry the finished logits of the previous block (-inf before the first): their
 //           exp-and-add is spread over the first half of the k-steps; on return the constants of
 //           block bi+1 (read from the ring in the second half; after the last block: a landed
@@ -302,9 +343,9 @@ struct FirstBlockLoads {
 // counts): the chain runs at the pace at which d arrives instead of starting after all of it.
 template <int HP, bool FIRST>
 __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *cring, uint32_t lds0,
-                                                   uint32_t cring0, const Loader<HP> &loader, const bf16_t *Ot,
+                                                   uint32_t cring0, const Loader<HP> &loader, const char *weights,
                                                    const float *cvec, int blk0, int nblk, int bi,
-                                                   const int (&aoff)[8], bf16x8 (&a)[kPrefetch],
+                                                   const FragOffsets<HP> &aoff, bf16x8 (&a)[kPrefetch],
                                                    bf16x8 (&dreg)[HP / 16], int g, f32x16 &acc,
                                                    f32x16 &other, float &srun, const FirstBlockLoads &first) {
     using C = StagedCfg<HP>;
@@ -312,20 +353,21 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
     constexpr int KS = C::KS, HALF = KS / 2, NW = C::kLoadsPerThread;
     constexpr int kLoadStep = (HALF - 2) / NW;                 // k-steps between two weight loads
     static_assert(KS >= 2 * kPrefetch && kLoadStep >= 1 && HALF + 1 + (NW - 1) * kLoadStep < KS - 2, "");
-    const char *stage = lds + (bi & 3) * C::kStageBytes;
-    const char *next_stage = lds + (((bi + 1 < nblk) ? bi + 1 : bi) & 3) * C::kStageBytes;
+    constexpr int NS = C::kStages;
+    const char *stage = lds + bi % NS * C::kStageBytes;
+    const char *next_stage = lds + ((bi + 1 < nblk) ? bi + 1 : bi) % NS * C::kStageBytes;
     const f32x4 *cnext = reinterpret_cast<const f32x4 *>(cring + ((bi + 1) & 7) * kCSlotBytes);
-    const bool real = bi + 3 < nblk;
-    const int v3 = real ? (blk0 + bi + 3) * kStagedWords : 0;
-    const bf16_t *blk3 = Ot + (size_t)v3 * HP;
-    const uint32_t stage3 = lds0 + ((bi + 3) & 3) * C::kStageBytes, cslot3 = cring0 + ((bi + 3) & 7) * kCSlotBytes;
+    const bool real = bi + NS - 1 < nblk;
+    const int block3 = real ? blk0 + bi + NS - 1 : 0;
+    const char *src3 = loader.block_of(weights, block3);
+    const uint32_t stage3 = lds0 + (bi + NS - 1) % NS * C::kStageBytes, cslot3 = cring0 + ((bi + NS - 1) & 7) * kCSlotBytes;
     // the k-steps as a compile-time loop: every condition below is a constant, and so are the vmcnt
     // immediates
     static_for<0, KS>([&](auto step) __attribute__((always_inline)) {
         constexpr int ks = decltype(step)::value;
         if constexpr (ks == HALF) {
             if constexpr (FIRST) wait_vmcnt<F::younger_than_block1()>();
-            else wait_vmcnt<C::kLoadsPerBlock>();
+            else wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
@@ -338,7 +380,7 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
             if constexpr (ks < F::L) {
                 if constexpr (ks < NW) loader.issue_weights(first.blk[0], ks, first.real[0], first.stage[0]);
                 else loader.issue_consts(first.cst[0], first.cslot[0]);
-            } else if constexpr (ks < 2 * F::L) {
+            } else if constexpr (ks < F::kAhead * F::L) {
                 if constexpr (ks - F::L < NW) loader.issue_weights(first.blk[1], ks - F::L, first.real[1], first.stage[1]);
                 else loader.issue_consts(first.cst[1], first.cslot[1]);
             }
@@ -348,12 +390,12 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
         // the previous block's sixteen logits, over k-steps 1 .. HALF
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            if (1 + (e * HALF) / 16 == ks) srun += fast_exp2(other[e]);
+            if (1 + (e * HALF) / 16 == ks) srun += fast_exp2(base2<C::kScaledD>(other[e]));
         // second half: loads of block bi+3, constants of block bi+1 into the resting accumulators
 #pragma unroll
         for (int q = 0; q < NW; ++q)
-            if (ks == HALF + 1 + q * kLoadStep) loader.issue_weights(blk3, q, real, stage3);
-        if constexpr (ks == KS - 2) loader.issue_consts(cvec + v3, cslot3);
+            if (ks == HALF + 1 + q * kLoadStep) loader.issue_weights(src3, q, real, stage3);
+        if constexpr (ks == KS - 2) loader.issue_consts(cvec + (size_t)block3 * kStagedWords, cslot3);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             if (ks == HALF + 1 + (q * (HALF - 1)) / 4) {
@@ -371,18 +413,18 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
 // of 2^(logit - offset) over the item's words for this lane's half of its row.
 template <int HP>
 __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds, char *cring, const Loader<HP> &loader,
-                                                   const int (&aoff)[8], int rg, int blk0, int nblk, int wave,
+                                                   const FragOffsets<HP> &aoff, int rg, int blk0, int nblk, int wave,
                                                    int lane, int g) {
     using C = StagedCfg<HP>;
     constexpr int KS = C::KS;
-    const bf16_t *Ot = static_cast<const bf16_t *>(m.Ot);
-    const float *cvec = m.cvec2_fixed;
+    const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
+    const float *cvec = C::kScaledD ? m.cvec2_fixed : m.cvec_fixed;
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
     // Block 0 and the first operands of this wave's rows of d (all k of 32 rows are MFMA B operands
     // held in registers; rows beyond B hold stale scratch: rows are independent and those lanes'
     // results are dropped).  The rest of d and blocks 1 and 2 are requested by block 0 itself.
     using F = FirstBlockSchedule<HP>;
-    loader.issue_all(Ot, cvec, blk0 * kStagedWords, true, lds0, cring0);
+    loader.issue_all(weights, cvec, blk0, lds0, cring0);
     bf16x8 dreg[KS];
     FirstBlockLoads first;
     // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row
@@ -393,10 +435,10 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         first.real[i] = i + 1 < nblk;
-        const int v = first.real[i] ? (blk0 + i + 1) * kStagedWords : 0;
-        first.blk[i] = Ot + (size_t)v * HP;
-        first.cst[i] = cvec + v;
-        first.stage[i] = lds0 + (i + 1) * C::kStageBytes;
+        const int block = first.real[i] ? blk0 + i + 1 : 0;
+        first.blk[i] = loader.block_of(weights, block);
+        first.cst[i] = cvec + (size_t)block * kStagedWords;
+        first.stage[i] = lds0 + (i + 1) % C::kStages * C::kStageBytes;
         first.cslot[i] = cring0 + (i + 1) * kCSlotBytes;
     }
     // Block 0 has landed once only the younger loads are outstanding: the first operands of d.
@@ -423,7 +465,7 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
     for (int i = 0; i < 16; ++i) acc1[i] = -INFINITY;        // "previous block" of block 0: adds 2^-inf = 0
     float srun = 0.f;
 #define RNNLM_BLOCK(FIRST, BI, ACC, OTHER) \
-    staged_block_fixed<HP, FIRST>(lds, cring, lds0, cring0, loader, Ot, cvec, blk0, nblk, BI, aoff, a, dreg, g, ACC, OTHER, srun, first)
+    staged_block_fixed<HP, FIRST>(lds, cring, lds0, cring0, loader, weights, cvec, blk0, nblk, BI, aoff, a, dreg, g, ACC, OTHER, srun, first)
     RNNLM_BLOCK(true, 0, acc0, acc1);
     int bi = 1;
     for (; bi + 1 < nblk; bi += 2) {
@@ -433,10 +475,10 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
     if (bi < nblk) {
         RNNLM_BLOCK(false, bi, acc1, acc0);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) srun += fast_exp2(acc1[e]);
+        for (int e = 0; e < 16; ++e) srun += fast_exp2(base2<C::kScaledD>(acc1[e]));
     } else {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) srun += fast_exp2(acc0[e]);
+        for (int e = 0; e < 16; ++e) srun += fast_exp2(base2<C::kScaledD>(acc0[e]));
     }
 #undef RNNLM_BLOCK
     // dummy loads may still be in flight into stages the next item fills first
@@ -451,7 +493,7 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
     using C = StagedCfg<HP>;
     constexpr int KS = C::KS;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    char *const cring = lds + kStages * C::kStageBytes;
+    char *const cring = lds + C::kStages * C::kStageBytes;
     const int B = B_dev ? *B_dev : rows;
     if (B <= 0) return;                                       // uniform: nothing to do, no barrier met
     // Few rows after all (after the grouping or the cache lookup only the device knows how many
@@ -461,26 +503,22 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
     static_assert(kThreads == kStreamThreads, "");
     static_assert(C::kLdsBytes >= 2 * KS * 1024 + kStreamWaves * 64 * 8, "LDS for two row blocks of the streaming form");
     if (B <= 64 && m.Ofrag && (int)gridDim.x == staged_plan(B, wg_per_xcd).S) {
-        if (B <= 32) outproj_stream_body<1, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-        else outproj_stream_body<2, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        if (B <= 32) outproj_stream_body<1, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
         return;
     }
     const StagedPlan plan = staged_plan(B, wg_per_xcd);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    const bf16_t *Ot = static_cast<const bf16_t *>(m.Ot);
-    const float *cvec = FIXED ? m.cvec2_fixed : m.cvec2;
+    const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
+    const float *cvec = FIXED ? (C::kScaledD ? m.cvec2_fixed : m.cvec_fixed) : m.cvec2;
     const int T = m.Vp / kStagedWords;                       // 32-word blocks in the vocabulary
     const int items = plan.RG * plan.Sx;
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
     Loader<HP> loader;
     loader.init();
-    // Swizzled LDS offsets of this lane's A operand: chunk (2 ks + g) of word `col`.  Only the
-    // low 4 bits of the chunk index take part in the swizzle, so eight per-lane offsets
-    // (aoff[ks % 8]) plus compile-time constants cover all k-steps.
-    int aoff[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) aoff[j] = col * (C::CPR * 16) + ((((2 * j) | g) ^ (col & 15)) * 16);
+    FragOffsets<HP> aoff;
+    aoff.init(lane);
 
     for (int item = local; item < items; item += wg_per_xcd) {
         const int rg = item % plan.RG, split = xcd + kXcds * (item / plan.RG);
@@ -501,7 +539,7 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
 #pragma unroll
         for (int i = 0; i < 2; ++i)
             if (i < nblk)
-                loader.issue(Ot, cvec, (blk0 + i) * kStagedWords, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
+                loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
         bf16x8 dreg[KS];
         {
             // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row
@@ -521,9 +559,9 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         wait_vmcnt<(KS < 64 ? KS : 63)>();
         __syncthreads();                                      // blocks 0 and 1 are published
 #pragma unroll
-        for (int i = 2; i < 4; ++i)
+        for (int i = 2; i < C::kStages; ++i)
             if (i < nblk)
-                loader.issue(Ot, cvec, (blk0 + i) * kStagedWords, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
+                loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
 
         bf16x8 a[kPrefetch];
         if (nblk > 0) {
@@ -535,17 +573,18 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
                 // Publish block bi+1: my loads of it have landed (the only younger ones are
                 // those of block bi+2), then everybody's.  Everybody is also done with block
                 // bi-1, so its stage takes block bi+3.
-                if (bi + 2 < nblk) wait_vmcnt<C::kLoadsPerBlock>();
+                constexpr int NS = C::kStages;
+                if (bi + 2 < nblk) wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();
                 else wait_vmcnt<0>();
                 asm volatile("" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                if (bi + 3 < nblk)
-                    loader.issue(Ot, cvec, (blk0 + bi + 3) * kStagedWords, lds0 + ((bi + 3) & 3) * C::kStageBytes,
-                                 cring0 + ((bi + 3) & 7) * kCSlotBytes);
+                if (bi + NS - 1 < nblk)
+                    loader.issue(weights, cvec, blk0 + bi + NS - 1, lds0 + (bi + NS - 1) % NS * C::kStageBytes,
+                                 cring0 + ((bi + NS - 1) & 7) * kCSlotBytes);
             }
-            const char *stage = lds + (bi & 3) * C::kStageBytes;
-            const char *next_stage = lds + (((bi + 1 < nblk) ? bi + 1 : bi) & 3) * C::kStageBytes;
+            const char *stage = lds + bi % C::kStages * C::kStageBytes;
+            const char *next_stage = lds + ((bi + 1 < nblk) ? bi + 1 : bi) % C::kStages * C::kStageBytes;
             // constants of the previous block (for block 0 any landed slot: its pacc is -inf)
             const f32x4 *pcn = reinterpret_cast<const f32x4 *>(cring + ((bi ? bi - 1 : 0) & 7) * kCSlotBytes);
             const f32x4 *ccur = reinterpret_cast<const f32x4 *>(cring + (bi & 7) * kCSlotBytes);
@@ -553,7 +592,7 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         }
         if (nblk > 0) {                                       // the last block's exp-and-add
             float x[16];
-            finish_logits<FIXED>(pacc, reinterpret_cast<const f32x4 *>(cring + ((nblk - 1) & 7) * kCSlotBytes), g, x);
+            finish_logits<FIXED, C::kScaledD>(pacc, reinterpret_cast<const f32x4 *>(cring + ((nblk - 1) & 7) * kCSlotBytes), g, x);
             lse2_fold16<FIXED>(x, mrun, srun);
         }
         // lanes l and l+32 hold the two halves of a row
@@ -587,7 +626,7 @@ hipError_t launch_hp(const ModelDev &m, int rows, const int *B_dev, bool fixed_o
 }  // namespace
 
 bool outproj_staged_supported(const ModelDev &m) {
-    return m.dtype == RNNLM_BF16 && (m.Hp == 128 || m.Hp == 256 || m.Hp == 512);
+    return m.dtype == RNNLM_BF16 && m.Ofrag && m.Hp >= 128 && m.Hp <= 704 && m.Hp % 64 == 0;
 }
 
 hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
@@ -597,8 +636,15 @@ hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, 
     *splits = SplitInfo{0, wg_per_xcd, kStagedRows, kMaxSplits / kXcds, 0};
     switch (m.Hp) {
         case 128: return launch_hp<128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 192: return launch_hp<192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
         case 256: return launch_hp<256>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 320: return launch_hp<320>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 384: return launch_hp<384>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 448: return launch_hp<448>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
         case 512: return launch_hp<512>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 576: return launch_hp<576>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 640: return launch_hp<640>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 704: return launch_hp<704>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
         default: return hipErrorInvalidValue;
     }
 }

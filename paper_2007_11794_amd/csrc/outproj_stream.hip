@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kThreads) void outproj_stream_kernel(ModelDev m, in
     // this launch serves rows row0 .. row0 + 32 RB - 1 (row0 a multiple of 32)
     const int B = (B_dev ? *B_dev : rows) - row0;
     if (B <= 0) return;                                       // uniform: no barrier is met
-    outproj_stream_body<RB, FIXED>(m, B, row0, blockIdx.x, gridDim.x, lds);
+    outproj_stream_body<RB, FIXED, true>(m, B, row0, blockIdx.x, gridDim.x, lds);
 }
 
 // ------------------------------------------------------------------------------ fp32 models

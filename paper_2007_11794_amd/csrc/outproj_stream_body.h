@@ -21,10 +21,11 @@ struct StreamCursor {                    // walks the groups of the blocks blk, 
 };
 
 // One launch's worth of streaming for the workgroup `split` of `S`: rows row0 .. row0 + 32 RB - 1 of
-// the hidden block (B = number of valid ones among them, > 0), partials into m.part.  Needs
+// the hidden block (B = number of valid ones among them, > 0), partials into m.part.  SCALED: the block
+// carries log2(e) (outproj_d_scale).  Needs
 // stream_lds_bytes(1, RB, Hp / 16) bytes of LDS at `lds` and kStreamThreads threads; contains two
 // workgroup barriers, so all threads of the workgroup must call it.
-template <int RB, bool FIXED>
+template <int RB, bool FIXED, bool SCALED>
 __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, int row0, int split, int S, char *lds) {
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -99,7 +100,7 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) x[4 * q + i] = acc[rb][4 * q + i] + cc[q][i];
+                            for (int i = 0; i < 4; ++i) x[4 * q + i] = SCALED ? acc[rb][4 * q + i] + cc[q][i] : fmaf(acc[rb][4 * q + i], kLog2e, cc[q][i]);
                         lse2_fold16<FIXED>(x, mrun[rb], srun[rb]);
 #pragma unroll
                         for (int i = 0; i < 16; ++i) acc[rb][i] = 0.f;

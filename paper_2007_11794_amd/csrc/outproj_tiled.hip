@@ -2,7 +2,7 @@
 //
 // Same result as the other output-projection kernels (normalising over all words of the
 // vocabulary, Section 2.1 of the paper).  This is the form for models whose hidden block
-// does not fit in registers (Hp > 512, e.g. the H = 1024 stress workload): both operands
+// does not fit in registers (Hp > 704, e.g. the H = 1024 stress workload): both operands
 // travel through LDS.
 //   - a workgroup of 2 x WN waves owns TR = 64 WN rows and walks the TW = 64 MB-word tiles of
 //     its vocabulary split; a wave owns 32 MB words x 64 rows = MB x 2 accumulators of 32x32.
@@ -98,8 +98,8 @@ __global__ __launch_bounds__(2 * WN * 64) void outproj_tiled_kernel(ModelDev m, 
     // of the weights instead, split = workgroup index.
     if constexpr (sizeof(T) == 2 && C::kThreads == kStreamThreads) {
         if (B <= stream_rows) {
-            if (B <= 32) outproj_stream_body<1, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-            else outproj_stream_body<2, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            if (B <= 32) outproj_stream_body<1, FIXED, true>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            else outproj_stream_body<2, FIXED, true>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
             return;
         }
     }

@@ -14,8 +14,8 @@
 //
 // Besides h_out (fp32, caller's buffer) the kernel leaves d' = h' - 1/2 in the model's
 // scratch blocks as the operand of the output projection: row-major in the weights' type;
-// also in MFMA-operand order, for bf16 models times log2(e), for fp32 models as two fp16 terms
-// (see ModelDev).
+// also in MFMA-operand order, for bf16 models times log2(e) where the following kernel wants that, for fp32
+// models as two fp16 terms (see ModelDev).
 //
 // What bounds it is the way of the operands into LDS: a chain of dependent reads (row count and rows to
 // take, side by side; then the rows; then the embedding rows), and after it the bytes a compute unit
@@ -149,8 +149,8 @@ __device__ __forceinline__ void finish4(const ModelDev &m, const Finish &f, int 
             const uint2 pk = {pack_bf16x2(dv[0], dv[1]), pack_bf16x2(dv[2], dv[3])};
             *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(m.d) + at) = pk;
         }
-        if (m.dfrag) {                                // times log2(e): base-2 logits come out of the MFMAs
-            const uint2 pk = {pack_bf16x2(dv[0] * kLog2e, dv[1] * kLog2e), pack_bf16x2(dv[2] * kLog2e, dv[3] * kLog2e)};
+        if (m.dfrag) {                                // (d_scale: log2(e) or 1)
+            const uint2 pk = {pack_bf16x2(dv[0] * m.d_scale, dv[1] * m.d_scale), pack_bf16x2(dv[2] * m.d_scale, dv[3] * m.d_scale)};
             *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(m.dfrag) + frag * 512 + slot) = pk;
         }
     } else {

@@ -37,6 +37,7 @@ struct ModelDev {
     // for the padded words v >= V so they add nothing to the sum.
     const float *cvec2;           // [Vp]
     const float *cvec2_fixed;     // [Vp]  cvec2 - m2_fixed
+    const float *cvec_fixed;      // [Vp]  cvec2_fixed / log2(e): kernels whose accumulators start from it
     float m2_fixed;    // upper bound of every base-2 logit z*log2(e), valid because |h' - 0.5| <= 0.5
     // A second copy of the output weights in MFMA-operand order.  bf16: [Vp / 32][Hp / 16][64 lanes][8],
     // lane 32 g + c of fragment (blk, ks) holds word 32 blk + c, units 16 ks + 8 g .. + 7 (one operand =
@@ -53,10 +54,11 @@ struct ModelDev {
     // scratch
     void *d;           // [max_Bp][Hp]  h' - 0.5 in the weights' type
     // The same block in the order the output projection reads it as an MFMA operand.  bf16 models: times
-    // log2(e), [max_Bp / 32][Hp / 16][64 lanes][8], lane 32 g + c of fragment (rb, ks) holds row
+    // d_scale, [max_Bp / 32][Hp / 16][64 lanes][8], lane 32 g + c of fragment (rb, ks) holds row
     // 32 rb + c, units 16 ks + 8 g .. + 7, so one operand of a wave is 1 KB contiguous.  fp32 models:
     // times 2^14 as two fp16 terms, [max_Bp / 32][Hp / 16][2 terms][64 lanes][8].
     void *dfrag;
+    float d_scale;     // set for the hidden update only: outproj_d_scale of the output projection that follows
     float2 *part;      // [max_Bp][kMaxSplits]  (max, sum) partials of the base-2 log-sum-exp
     int *flag;         // sticky rnnlm_device_flag bits
 };
@@ -225,6 +227,12 @@ hipError_t launch_outproj(const ModelDev &m, int rows, const int *B_dev, bool fi
 // false: the kernel launch_outproj takes for these arguments reads only the fragment-ordered copy of
 // the hidden block, and the hidden update may leave the row-ordered one (m.d) unwritten
 bool outproj_reads_row_order(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice);
+// bf16 models: the factor the fragment-ordered copy carries.  log2(e): the accumulators are base-2 logits.  1, for the
+// padded hidden sizes the staged kernel took over from the tiled one: units at their limits, h' - 1/2 = +-1/2, are
+// exact in bf16 only unscaled, and models with large weights have many (V = 30011, H = 650, weights of 0.2: error of
+// the log-probabilities 2.82e-5 unscaled, as in the tiled kernel, 3.70e-5 scaled).
+constexpr bool staged_scaled_d(int Hp) { return Hp == 128 || Hp == 256 || Hp == 512; }
+float outproj_d_scale(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice);
 const char *outproj_kernel_name(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice);
 bool outproj_staged_supported(const ModelDev &m);
 bool outproj_rowstream_supported(const ModelDev &m);   // bf16 models
@@ -294,7 +302,7 @@ hipError_t launch_frag_weights(const void *Ot /*[Vp][Hp] bf16*/, int Vp, int Hp,
 hipError_t launch_split2_weights(const float *Ot /*[Vp][Hp]*/, int Vp, int Hp, void *Ofrag, float *ofac /*[Vp]*/,
                                  hipStream_t stream);
 hipError_t launch_fill_cvec(const float *bias_or_null, const float *half_colsum, int V, int Vp,
-                            float m2_fixed, float *bias_out, float *cvec2, float *cvec2_fixed,
+                            float m2_fixed, float *bias_out, float *cvec2, float *cvec2_fixed, float *cvec_fixed,
                             hipStream_t stream);
 
 }  // namespace rnnlm
