@@ -116,6 +116,11 @@ bool ranges_overlap(const float *a, const float *b, size_t n) {
     return x < y + bytes && y < x + bytes;
 }
 
+bool bytes_overlap(const void *a, size_t an, const void *b, size_t bn) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + bn && y < x + an;
+}
+
 double widen_host(const void *p, size_t i, int dtype) {
     if (dtype == RNNLM_BF16) {
         uint32_t u = (uint32_t)static_cast<const uint16_t *>(p)[i] << 16;
@@ -436,7 +441,8 @@ int rnnlm_step(const rnnlm_model *model, int B, int K, const int32_t *prev_word,
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const ModelDev &d = model->dev;
     SplitInfo splits = fixed_split_info(1);
-    if (launch_recur(recur_view(model, B), B, nullptr, nullptr, nullptr, prev_word, h_in, h_out, s) != hipSuccess) return RNNLM_EDEVICE;
+    if (launch_recur(recur_view(model, B), B, nullptr, nullptr, nullptr, prev_word, h_in, h_out, IdGroups{}, s) != hipSuccess)
+        return RNNLM_EDEVICE;
     if (launch_outproj(d, B, nullptr, use_fixed_offset(model), model->outproj_kernel, &splits, s) != hipSuccess)
         return RNNLM_EDEVICE;
     if (launch_query(d, B, nullptr, N, K, splits, query_word, row_of_query_or_null, h_out, nullptr, nullptr, logprob, s) !=
@@ -468,12 +474,18 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     // through a cache, few enough raw queries: grouping and lookup are one launch
     const bool one_launch = cache && N <= dedup_lookup_max_rows();
-    if (one_launch) {
+    // without one: grouping and hidden update (whose workgroups all read the ids, so the results must not go there)
+    const bool grouped_update = !cache && recur_groups_ids(model->dev, N) &&
+                                !bytes_overlap(history_ids, (size_t)N * 8, rep, (size_t)N * 4) &&
+                                !bytes_overlap(history_ids, (size_t)N * 8, inverse, (size_t)N * 4) &&
+                                !bytes_overlap(history_ids, (size_t)N * 8, n_unique, 4) &&
+                                !bytes_overlap(history_ids, (size_t)N * 8, h_out, (size_t)N * model->dev.H * 4);
+    if (one_launch || grouped_update) {
         if (N > 0) {                                                                              // as rnnlm_dedup
             if (!workspace || workspace_bytes < dedup_workspace_bytes(N)) return RNNLM_EWORKSPACE;
             if (reinterpret_cast<uintptr_t>(workspace) & 15) return RNNLM_EWORKSPACE;
         }
-        if (launch_dedup_lookup(cache->dev, history_ids, N, rep, inverse, n_unique, step_stats, s) != hipSuccess)
+        if (one_launch && launch_dedup_lookup(cache->dev, history_ids, N, rep, inverse, n_unique, step_stats, s) != hipSuccess)
             return RNNLM_EDEVICE;
     } else {
         rc = rnnlm_dedup(history_ids, N, rep, inverse, n_unique, workspace, workspace_bytes, hip_stream);
@@ -484,7 +496,9 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
     if (!cache) {
         if (N == 0) return RNNLM_OK;
         // Grids cover N rows; the kernels read the true number of rows from *n_unique.
-        if (launch_recur(recur_view(model, N), N, n_unique, rep, nullptr, prev_word, h_in, h_out, s) != hipSuccess)
+        const IdGroups ids = {history_ids, rep, inverse, n_unique};
+        if (launch_recur(recur_view(model, N), N, grouped_update ? nullptr : n_unique, grouped_update ? nullptr : rep, nullptr,
+                         prev_word, h_in, h_out, grouped_update ? ids : IdGroups{}, s) != hipSuccess)
             return RNNLM_EDEVICE;
         if (d.hs) {                                         // hierarchical output layer: paths instead of the normaliser
             if (launch_hs_query(d, N, n_unique, N, K, query_word, inverse, h_out, base_score, score, s) != hipSuccess)
@@ -506,7 +520,7 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
     if (N == 0) return RNNLM_OK;
     // Only the histories the cache does not hold are computed: *c.n_miss rows, row r taken
     // from raw query c.miss_src[r], its hidden vector written to row c.miss_dst[r] of h_out.
-    if (launch_recur(recur_view(model, N), N, c.n_miss, c.miss_src, c.miss_dst, prev_word, h_in, h_out, s) != hipSuccess)
+    if (launch_recur(recur_view(model, N), N, c.n_miss, c.miss_src, c.miss_dst, prev_word, h_in, h_out, IdGroups{}, s) != hipSuccess)
         return RNNLM_EDEVICE;
     if (d.hs) {
         // Hierarchical output layer: what the cache keeps of a history is its hidden vector.  The
@@ -646,7 +660,8 @@ int rnnlm_hs_step(const rnnlm_model *model, int B, int K, const int32_t *prev_wo
     if (B > 0 && ranges_overlap(h_in, h_out, (size_t)B * model->dev.H)) return RNNLM_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const ModelDev &d = model->dev;
-    if (launch_recur(recur_view(model, B), B, nullptr, nullptr, nullptr, prev_word, h_in, h_out, s) != hipSuccess) return RNNLM_EDEVICE;
+    if (launch_recur(recur_view(model, B), B, nullptr, nullptr, nullptr, prev_word, h_in, h_out, IdGroups{}, s) != hipSuccess)
+        return RNNLM_EDEVICE;
     if (launch_hs_query(d, B, nullptr, N, K, query_word, row_of_query_or_null, h_out, base_score_or_null, logprob,
                         s) != hipSuccess)
         return RNNLM_EDEVICE;
@@ -731,9 +746,8 @@ int rnnlm_index_intern(rnnlm_index_table *table, int N, const int32_t *word, con
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const IndexDev &d = table->dev;
     if (launch_context_hash(word, h, N, d.c.H, d.keys, s) != hipSuccess) return RNNLM_EDEVICE;
-    // Grouping and lookup in one launch of one workgroup while that is no slower even when every context is new:
-    // reset, intern and fetch of 4096 contexts of H = 512, 1229 distinct 46.6 -> 31.6 us, all distinct 48.1 / 48.1;
-    // 7000 contexts, 2000 distinct 53 -> 43 but all distinct 61 -> 77.
+    // Grouping and lookup in one launch of one workgroup while that is faster even when every context is new: reset,
+    // intern and fetch of 4096 contexts of H = 512, 1229 distinct 46.6 -> 31.0 us, all distinct 48.1 -> 45.0.
     if (N <= 4096) {
         if (launch_dedup_lookup(d.c, d.keys, N, d.rep, d.inverse, d.n_unique, nullptr, s) != hipSuccess) return RNNLM_EDEVICE;
     } else {

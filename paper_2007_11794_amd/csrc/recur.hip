@@ -36,6 +36,7 @@
 // 4.7e-8 to 4.3e-8 (H = 512), bf16 models' stayed.
 #include <algorithm>
 
+#include "dedup_small_body.h"
 #include "device_utils.h"
 #include "rnnlm_internal.h"
 
@@ -344,12 +345,79 @@ __host__ __device__ inline int small_rows(int Hp, bool half) { return 32 * ((hal
 
 constexpr int ring_bytes(int elem, bool half) { return (half ? 64 : elem == 2 ? 128 : 144) * 1024; }
 
+// Grouping of the step's ids in front of the hidden update, by every workgroup for itself (N <= kGroupedMax): the same
+// numbers as dedup_small_body.  Some two microseconds of LDS work in the place of a launch that does them on one compute
+// unit and of the round trip of the count and the rows: step at V = 20000, H = 256, fp32, 256 ids 27.0 -> 25.2 us,
+// V = 65536, H = 512, bf16, 1024 ids 67.4 -> 66.9.  Workgroup 0 leaves the result for the kernels behind.
+// Returns the number of groups; representatives in LDS (valid until the ring is filled).
+constexpr int kGroupedMax = 1024;
+
+__device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, int *wsum, const int *&rep_out) {
+    constexpr int kPer = kGroupedMax / kThreads, kCap = 2 * kGroupedMax;
+    uint64_t *tkeys = reinterpret_cast<uint64_t *>(lds);                  // [kCap + 1]
+    int *tfirst = reinterpret_cast<int *>(tkeys + kCap + 2);              // [kCap + 1] min raw index, later the group number
+    int *rep = tfirst + kCap + 2;                                         // [kGroupedMax]
+    static_assert((kCap + 2) * 12 + kGroupedMax * 4 <= 64 * 1024, "fits the smallest ring");
+    const int tid = threadIdx.x, per = (N + kThreads - 1) / kThreads;
+    uint64_t key[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int n = tid * per + i;
+        key[i] = (i < per && n < N) ? ids.key[n] : 0;
+    }
+    int cap = 64;                                                         // a power of two, at most half full
+    while (cap < 2 * N) cap <<= 1;
+    for (int i = tid; i <= cap; i += kThreads) {                          // while the keys are on their way
+        tkeys[i] = kEmpty;
+        tfirst[i] = 0x7FFFFFFF;
+    }
+    __syncthreads();
+    int slot[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int n = tid * per + i;
+        slot[i] = -1;
+        if (i < per && n < N) {
+            slot[i] = find_or_insert(tkeys, cap, key[i]);
+            atomicMin(&tfirst[slot[i]], n);
+        }
+    }
+    __syncthreads();
+    int is_first[kPer], mine = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == tid * per + i) ? 1 : 0;
+        mine += is_first[i];
+    }
+    int total;
+    int u = block_exclusive_scan(mine, wsum, total);                      // barriers inside: all first indices are read
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        if (is_first[i]) {
+            rep[u] = tid * per + i;
+            tfirst[slot[i]] = u;
+            ++u;
+        }
+    }
+    __syncthreads();
+    if (blockIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            if (slot[i] >= 0) ids.inverse[tid * per + i] = tfirst[slot[i]];
+        for (int i = tid; i < total; i += kThreads) ids.rep[i] = rep[i];
+        if (tid == 0) *ids.n_unique = total;
+    }
+    rep_out = rep;
+    return total;
+}
+
 template <typename WT, bool VEC, bool HALF>
 __global__ __launch_bounds__(kThreads) void recur_kernel(
     ModelDev m, int rows, const int *__restrict__ B_dev, const int32_t *__restrict__ row_src,
     const int32_t *__restrict__ row_dst, const int32_t *__restrict__ prev_word, const float *__restrict__ h_in,
-    float *__restrict__ h_out) {
+    float *__restrict__ h_out, IdGroups ids) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
+    __shared__ int wsum[kWaves + 1];
     __shared__ int srcs[64], prevs[64];                // rows to take, their previous words
     // Workgroup id modulo 8 is the XCD (L2 domain).  Row block rb runs on XCD rb % 8 with all
     // its unit blocks, so h_in (the larger operand) is fetched into one L2 only.
@@ -358,12 +426,21 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
     const int bs = (xcd + kXcds * (local / JS)) * 32, bl = (xcd + kXcds * (local / JL)) * 64;
     // The rows to take are requested for both shapes beside the row count, not behind it (entries
     // between the true count and `rows` are read and not used).
-    int source_s = bs + tid, source_l = bl + tid;
-    if (row_src && tid < 64) {
-        source_s = row_src[min(bs + tid, rows - 1)];
-        source_l = row_src[min(bl + tid, rows - 1)];
+    int source_s = bs + tid, source_l = bl + tid, B;
+    if (ids.key) {                                     // uniform
+        const int *rep;
+        B = __builtin_amdgcn_readfirstlane(group_ids(ids, rows, lds, wsum, rep));
+        if (tid < 64) {                                // (read before the barrier in front of the first load into the ring)
+            source_s = rep[min(bs + tid, B - 1)];
+            source_l = rep[min(bl + tid, B - 1)];
+        }
+    } else {
+        if (row_src && tid < 64) {
+            source_s = row_src[min(bs + tid, rows - 1)];
+            source_l = row_src[min(bl + tid, rows - 1)];
+        }
+        B = B_dev ? *B_dev : rows;
     }
-    const int B = B_dev ? *B_dev : rows;
     constexpr int kRing = ring_bytes(sizeof(WT), HALF);
     if (B <= small_rows(m.Hp, HALF)) {                 // uniform
         if (bs >= B) return;
@@ -381,7 +458,7 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
 
 template <typename WT, bool VEC, bool HALF>
 hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
-                  const int32_t *prev_word, const float *h_in, float *h_out, hipStream_t stream) {
+                  const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
     const int lds_bytes = ring_bytes(sizeof(WT), HALF);
     static LdsLimit limit;
     if (hipError_t e = limit.ensure(reinterpret_cast<const void *>(recur_kernel<WT, VEC, HALF>), lds_bytes); e != hipSuccess)
@@ -390,35 +467,41 @@ hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *
     // With the count on the device only, the grid covers both shapes: the small one up to its limit, the
     // large one up to `rows`.
     const int few = std::min(rows, small_rows(m.Hp, HALF));
-    int grid = rows <= few || B_dev ? slots((few + 31) / 32) * (m.Hp / 64) : 0;
+    const bool on_device = B_dev || ids.key;
+    int grid = rows <= few || on_device ? slots((few + 31) / 32) * (m.Hp / 64) : 0;
     if (rows > few) grid = std::max(grid, slots((rows + 63) / 64) * ((m.Hp + 127) / 128));
     hipLaunchKernelGGL((recur_kernel<WT, VEC, HALF>), dim3(grid), dim3(kThreads), lds_bytes, stream, m, rows, B_dev, row_src,
-                       row_dst, prev_word, h_in, h_out);
+                       row_dst, prev_word, h_in, h_out, ids);
     return hipGetLastError();
 }
 
 template <bool VEC>
 hipError_t launch_type(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
-                       const int32_t *prev_word, const float *h_in, float *h_out, hipStream_t stream) {
+                       const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids,
+                       hipStream_t stream) {
     if (m.dtype != RNNLM_BF16)
-        return launch<float, VEC, false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, stream);
+        return launch<float, VEC, false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
     // half a ring beyond one round of small workgroups: H = 512, 1229 rows 12.5 -> 10.4 us, H = 1024, 3000 rows
     // 37 -> 30, H = 1024, 2048 rows 22.2 -> 22.6
     if (rows <= small_rows(m.Hp, false))
-        return launch<bf16_t, VEC, false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, stream);
-    return launch<bf16_t, VEC, true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, stream);
+        return launch<bf16_t, VEC, false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
+    return launch<bf16_t, VEC, true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
 }
 
 }  // namespace
 
+// Every workgroup repeats the grouping, so the launch must be one round of them: up to Hp = 2048 the grid for
+// kGroupedMax rows is 512 workgroups, two per compute unit (fp32 models: 256, one per unit).
+bool recur_groups_ids(const ModelDev &m, int N) { return N > 0 && N <= kGroupedMax && m.Hp <= 2048; }
+
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,
                         const int32_t *row_dst, const int32_t *prev_word, const float *h_in,
-                        float *h_out, hipStream_t stream) {
+                        float *h_out, const IdGroups &ids, hipStream_t stream) {
     if (rows <= 0) return hipSuccess;
     const bool vec = m.H % 4 == 0 && (reinterpret_cast<uintptr_t>(h_in) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(h_out) & 15) == 0;
-    return vec ? launch_type<true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, stream)
-               : launch_type<false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, stream);
+    return vec ? launch_type<true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream)
+               : launch_type<false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
 }
 
 }  // namespace rnnlm

@@ -164,9 +164,16 @@ int dedup_static_prepare();
 // *B_dev when B_dev != nullptr, else rows.  row_src (nullable) maps row b to the raw row
 // that holds its prev word and h_in; row_dst (nullable) maps it to its row of h_out (the
 // operand block m.d always takes row b).
+// ids.key set (recur_groups_ids(m, rows)): the launch groups the `rows` raw queries' ids first, as launch_dedup does,
+// and takes rows and count from that (B_dev and row_src null).
+struct IdGroups {
+    const uint64_t *key;                       // [rows] or null
+    int32_t *rep, *inverse, *n_unique;         // as launch_dedup leaves them
+};
+bool recur_groups_ids(const ModelDev &m, int N);
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,
                         const int32_t *row_dst, const int32_t *prev_word, const float *h_in,
-                        float *h_out, hipStream_t stream);
+                        float *h_out, const IdGroups &ids, hipStream_t stream);
 
 constexpr int kStagedRows = 256;   // rows per workgroup of the staged kernel
 constexpr int kStagedWords = 32;   // words per LDS stage
