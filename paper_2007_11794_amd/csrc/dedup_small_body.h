@@ -34,6 +34,7 @@ struct SmallGroups {
     int total;
     const int *rep;          // [total]
     const uint64_t *id;      // [total]
+    int *spare;              // [kSmallCap] ints of LDS that are free from then on
 };
 
 // All kSmallThreads threads of the one workgroup call it; N <= kSmallN.
@@ -104,7 +105,7 @@ __device__ __forceinline__ SmallGroups dedup_small_body(const uint64_t *__restri
         if (slot[i] >= 0) inverse[n] = tfirst[slot[i]];
     }
     if (threadIdx.x == 0) *n_unique = total;
-    return SmallGroups{total, rep_lds, id_lds};
+    return SmallGroups{total, rep_lds, id_lds, tfirst};
 }
 
 // ------------------------------------------------------------------------------ up to kMediumN ids
@@ -123,6 +124,7 @@ struct MediumGroups {
     int total;
     const int *rep;          // [total]
     const uint64_t *key;     // [N] in raw order: id of group u = key[rep[u]]
+    int *spare;              // [kMediumCap - kMediumN] ints of LDS that are free from then on
 };
 
 __device__ __forceinline__ MediumGroups dedup_medium_body(const uint64_t *__restrict__ keys, int N,
@@ -203,7 +205,7 @@ __device__ __forceinline__ MediumGroups dedup_medium_body(const uint64_t *__rest
     for (int i = 0; i < kPer; ++i) {
         if (is_first[i]) table[u++] = threadIdx.x * per + i;   // representatives, for a consumer in this workgroup
     }
-    return MediumGroups{total, table, lkey};
+    return MediumGroups{total, table, lkey, table + kMediumN};
 }
 
 }  // namespace rnnlm
