@@ -109,6 +109,14 @@ struct HsShape {
 };
 typedef HsShape<256, 11, 1024, 256> HsLarge;
 typedef HsShape<128, 9, 256, 64> HsSmall;
+// The same with twice the threads, while the queries leave compute units idle or half empty: a query's chain of
+// dependent loads gets shorter (fewer rounds of node rows), the number of chains does not matter then.  Steps at V =
+// 65536, H = 512, bf16, us, half as many threads / these: 40 queries of 25 words 17.6 / 13.9, 512 queries 20.8 / 17.3,
+// 1024 of 32 words 26.1 / 28.9; 512 queries of 6 words 16.6 / 14.2.  Short rows have several in a wave's round
+// already: up to 256 queries (V = 300000, H = 128, 40 queries 12.1 / 11.3; H = 250, fp32, 512 queries 19.8 / 23.5).
+typedef HsShape<512, 11, 1024, 256> HsLargeWide;
+typedef HsShape<256, 9, 256, 64> HsSmallWide;
+inline bool hs_wide(int N, int Hp) { return N <= (Hp == 128 || Hp == 256 ? 256 : 512); }
 
 // Dot products of the distinct nodes for a short hidden vector (Hp = 8 * LPR elements, LPR = 16 or
 // 32): a node row takes only LPR lanes of a wave, so the wave works on 64 / LPR rows side by side,
@@ -325,17 +333,19 @@ hipError_t launch_hs_query(const ModelDev &m, int rows, const int *B_dev, int N,
             hipLaunchKernelGGL(kernel, dim3(N), dim3(threads), 0, stream, m, rows, B_dev, N, K, query_word,
                                row_of_query, h_out, base_score, logprob);
         };
-        auto pick = [&](auto tag) {
+        auto pick_rows = [&](auto tag, auto shape) {
             using T = decltype(tag);
-            if (small) {
-                if (m.Hp == 128) launch(hs_query_shared_kernel<T, 16, HsSmall>, HsSmall::kThreads);
-                else if (m.Hp == 256) launch(hs_query_shared_kernel<T, 32, HsSmall>, HsSmall::kThreads);
-                else launch(hs_query_shared_kernel<T, 0, HsSmall>, HsSmall::kThreads);
-            } else {
-                if (m.Hp == 128) launch(hs_query_shared_kernel<T, 16, HsLarge>, HsLarge::kThreads);
-                else if (m.Hp == 256) launch(hs_query_shared_kernel<T, 32, HsLarge>, HsLarge::kThreads);
-                else launch(hs_query_shared_kernel<T, 0, HsLarge>, HsLarge::kThreads);
-            }
+            using S = decltype(shape);
+            if (m.Hp == 128) launch(hs_query_shared_kernel<T, 16, S>, S::kThreads);
+            else if (m.Hp == 256) launch(hs_query_shared_kernel<T, 32, S>, S::kThreads);
+            else launch(hs_query_shared_kernel<T, 0, S>, S::kThreads);
+        };
+        const bool wide = hs_wide(N, m.Hp);
+        auto pick = [&](auto tag) {
+            if (small && wide) pick_rows(tag, HsSmallWide{});
+            else if (small) pick_rows(tag, HsSmall{});
+            else if (wide) pick_rows(tag, HsLargeWide{});
+            else pick_rows(tag, HsLarge{});
         };
         if (m.dtype == RNNLM_BF16) pick(bf16_t{});
         else pick(float{});
