@@ -20,6 +20,30 @@ struct StreamCursor {                    // walks the groups of the blocks blk, 
     }
 };
 
+// The hidden block (`pieces` kilobytes at `src`) into LDS, in front of the loop over the weights.  More than two
+// kilobytes per wave go straight to LDS, all of it on its way at once, requested before the weights (stream_block_begin)
+// and awaited after the first of them have been requested (stream_block_end): 64 rows at H = 512 16.4 -> 14.5 us per
+// launch, V = 200000, H = 1024, 32 rows 73 -> 70, fp32 V = 100000, H = 512, 64 rows 40.6 -> 36.9.  Smaller blocks are
+// copied through registers behind the weights (V = 20000, H = 256, 32 rows 4.4 us, straight to LDS 4.6).
+// At the wait at least 16 younger loads of the wave are outstanding (four groups of the ring, which the memory
+// clobbers keep between request and wait); operations complete in order, so the block has landed once no more than 12 are.
+constexpr int kStreamCopyPieces = 2 * kStreamWaves;
+
+__device__ __forceinline__ void stream_block_begin(const char *src, int pieces, char *lds, int wave, int lane) {
+    if (pieces <= kStreamCopyPieces) return;                  // uniform
+    for (int p = wave; p < pieces; p += kStreamWaves) lds_dma_16(src + (size_t)p * 1024, lane * 16, lds_address(lds) + p * 1024);
+}
+__device__ __forceinline__ void stream_block_end(const char *src, int pieces, char *lds) {
+    if (pieces > kStreamCopyPieces) {
+        asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    } else {
+        const u32x4 *from = reinterpret_cast<const u32x4 *>(src);
+        u32x4 *to = reinterpret_cast<u32x4 *>(lds);
+        for (int i = threadIdx.x; i < pieces * 64; i += kStreamThreads) to[i] = from[i];
+    }
+    __syncthreads();                                          // hidden block visible to all waves
+}
+
 // One launch's worth of streaming for the workgroup `split` of `S`: rows row0 .. row0 + 32 RB - 1 of
 // the hidden block (B = number of valid ones among them, > 0), partials into m.part.  SCALED: the block
 // carries log2(e) (outproj_d_scale).  Needs
@@ -38,12 +62,8 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
     bf16x8 *dl = reinterpret_cast<bf16x8 *>(lds);
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)RB * KS * 1024);    // [kStreamWaves][RB * 32]
 
-    // the hidden block first (its arrival is then not queued behind the weights)
-    {
-        const bf16x8 *src = static_cast<const bf16x8 *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 64;
-        const int n = RB * KS * 64;
-        for (int i = tid; i < n; i += kStreamThreads) dl[i] = src[i];
-    }
+    const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 1024;
+    stream_block_begin(block, RB * KS, lds, wave, lane);
     bf16x8 ring[kStreamRing][kStreamGroup];
     StreamCursor in = {blk0 + wave, 0};
     // Always kStreamGroup loads, so that the number of younger loads behind any operand is the same on
@@ -57,9 +77,16 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
     };
 #pragma unroll
     for (int st = 0; st < kStreamRing - 1; ++st) issue(ring[st]);
-    __syncthreads();                                          // hidden block visible to all waves
-
     StreamCursor out = {blk0 + wave, 0};
+    f32x4 cc[4];
+    auto load_constants = [&]() {
+        const int blk = out.blk < blk1 ? out.blk : blk0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cc[q] = *reinterpret_cast<const f32x4 *>(cvec + blk * 32 + 8 * q + 4 * g);
+    };
+    load_constants();
+    stream_block_end(block, RB * KS, lds);
+
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
 #pragma unroll
@@ -69,13 +96,6 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[rb][i] = 0.f;
     }
-    f32x4 cc[4];
-    auto load_constants = [&]() {
-        const int blk = out.blk < blk1 ? out.blk : blk0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cc[q] = *reinterpret_cast<const f32x4 *>(cvec + blk * 32 + 8 * q + 4 * g);
-    };
-    load_constants();
     // The wave leaves the unrolled ring loop from wherever its last group falls (a return out of
     // the lambda, never a skip that rejoins the loop: the compiler sizes each wait by the path
     // with the fewest younger loads).
@@ -153,6 +173,8 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     f16x8 *dl = reinterpret_cast<f16x8 *>(lds);                             // [RB][KS][term][64]
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)2 * RB * KS * 1024);
 
+    const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 2048;
+    stream_block_begin(block, 2 * RB * KS, lds, wave, lane);
     f16x8 ring[kStreamRing][2 * kStreamGroup32];
     StreamCursor in = {blk0 + wave, 0};
     auto issue = [&](f16x8(&dst)[2 * kStreamGroup32]) {                          // always four loads (see above)
@@ -174,12 +196,7 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
         }
     };
     load_constants();
-    {
-        const f16x8 *src = static_cast<const f16x8 *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 128;
-        const int n = RB * KS * 128;
-        for (int i = tid; i < n; i += kStreamThreads) dl[i] = src[i];
-    }
-    __syncthreads();
+    stream_block_end(block, 2 * RB * KS, lds);
 
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
