@@ -24,23 +24,29 @@ struct StreamCursor {                    // walks the groups of the blocks blk, 
 // kilobytes per wave go straight to LDS, all of it on its way at once, requested before the weights (stream_block_begin)
 // and awaited after the first of them have been requested (stream_block_end): 64 rows at H = 512 16.4 -> 14.5 us per
 // launch, V = 200000, H = 1024, 32 rows 73 -> 70, fp32 V = 100000, H = 512, 64 rows 40.6 -> 36.9.  Smaller blocks are
-// copied through registers behind the weights (V = 20000, H = 256, 32 rows 4.4 us, straight to LDS 4.6).
+// copied through registers: bf16 in front of the weights (V = 20000, H = 64, 4 rows 3.8 us, behind them 4.2), fp32
+// behind them.
 // At the wait at least 16 younger loads of the wave are outstanding (four groups of the ring, which the memory
 // clobbers keep between request and wait); operations complete in order, so the block has landed once no more than 12 are.
 constexpr int kStreamCopyPieces = 2 * kStreamWaves;
 
+__device__ __forceinline__ void stream_block_copy(const char *src, int pieces, char *lds) {
+    const u32x4 *from = reinterpret_cast<const u32x4 *>(src);
+    u32x4 *to = reinterpret_cast<u32x4 *>(lds);
+    for (int i = threadIdx.x; i < pieces * 64; i += kStreamThreads) to[i] = from[i];
+}
+template <bool COPY_FIRST>
 __device__ __forceinline__ void stream_block_begin(const char *src, int pieces, char *lds, int wave, int lane) {
-    if (pieces <= kStreamCopyPieces) return;                  // uniform
+    if (pieces <= kStreamCopyPieces) {                        // uniform
+        if (COPY_FIRST) stream_block_copy(src, pieces, lds);
+        return;
+    }
     for (int p = wave; p < pieces; p += kStreamWaves) lds_dma_16(src + (size_t)p * 1024, lane * 16, lds_address(lds) + p * 1024);
 }
+template <bool COPY_FIRST>
 __device__ __forceinline__ void stream_block_end(const char *src, int pieces, char *lds) {
-    if (pieces > kStreamCopyPieces) {
-        asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-    } else {
-        const u32x4 *from = reinterpret_cast<const u32x4 *>(src);
-        u32x4 *to = reinterpret_cast<u32x4 *>(lds);
-        for (int i = threadIdx.x; i < pieces * 64; i += kStreamThreads) to[i] = from[i];
-    }
+    if (pieces > kStreamCopyPieces) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    else if (!COPY_FIRST) stream_block_copy(src, pieces, lds);
     __syncthreads();                                          // hidden block visible to all waves
 }
 
@@ -59,11 +65,13 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
     const int blk0 = part_begin(split, T, S);
     const bf16x8 *Of = static_cast<const bf16x8 *>(m.Ofrag) + lane;
     const float *cvec = FIXED ? m.cvec2_fixed : m.cvec2;
+    const float m2_fixed = m.m2_fixed;
+    asm volatile("" ::"s"(m2_fixed), "s"(m.Ofrag), "s"(cvec));   // fetched together, here, not one by one where they are used
     bf16x8 *dl = reinterpret_cast<bf16x8 *>(lds);
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)RB * KS * 1024);    // [kStreamWaves][RB * 32]
 
     const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 1024;
-    stream_block_begin(block, RB * KS, lds, wave, lane);
+    stream_block_begin<true>(block, RB * KS, lds, wave, lane);
     bf16x8 ring[kStreamRing][kStreamGroup];
     StreamCursor in = {blk0 + wave, 0};
     // Always kStreamGroup loads, so that the number of younger loads behind any operand is the same on
@@ -85,13 +93,13 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
         for (int q = 0; q < 4; ++q) cc[q] = *reinterpret_cast<const f32x4 *>(cvec + blk * 32 + 8 * q + 4 * g);
     };
     load_constants();
-    stream_block_end(block, RB * KS, lds);
+    stream_block_end<true>(block, RB * KS, lds);
 
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        mrun[rb] = FIXED ? m.m2_fixed : -INFINITY;
+        mrun[rb] = FIXED ? m2_fixed : -INFINITY;
         srun[rb] = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[rb][i] = 0.f;
@@ -170,11 +178,13 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     const int blk0 = part_begin(split, T, S);
     const f16x8 *Of = static_cast<const f16x8 *>(m.Ofrag) + lane;           // [blk][ks][term][64]
     const float *cvec = FIXED ? m.cvec2_fixed : m.cvec2;
+    const float m2_fixed = m.m2_fixed;
+    asm volatile("" ::"s"(m2_fixed), "s"(m.Ofrag), "s"(cvec), "s"(m.ofac));  // as above
     f16x8 *dl = reinterpret_cast<f16x8 *>(lds);                             // [RB][KS][term][64]
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)2 * RB * KS * 1024);
 
     const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 2048;
-    stream_block_begin(block, 2 * RB * KS, lds, wave, lane);
+    stream_block_begin<false>(block, 2 * RB * KS, lds, wave, lane);
     f16x8 ring[kStreamRing][2 * kStreamGroup32];
     StreamCursor in = {blk0 + wave, 0};
     auto issue = [&](f16x8(&dst)[2 * kStreamGroup32]) {                          // always four loads (see above)
@@ -196,13 +206,13 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
         }
     };
     load_constants();
-    stream_block_end(block, 2 * RB * KS, lds);
+    stream_block_end<false>(block, 2 * RB * KS, lds);
 
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        mrun[rb] = FIXED ? m.m2_fixed : -INFINITY;
+        mrun[rb] = FIXED ? m2_fixed : -INFINITY;
         srun[rb] = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[rb][i] = 0.f;
