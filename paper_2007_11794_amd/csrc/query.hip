@@ -46,6 +46,8 @@ __global__ __launch_bounds__(256) void query_kernel(
     const float *__restrict__ base_score, float *__restrict__ logprob, CacheDev c,
     const int32_t *__restrict__ rep) {
     constexpr int kWavesPerQuery = 4 / QPW;
+    // The arguments the first loads hang on, fetched together, not one by one where they are used.
+    asm volatile("" ::"s"(m.Ot), "s"(m.bias), "s"(m.part), "s"(m.Hp), "s"(m.H), "s"(m.V), "s"(h_out), "s"(query_word), "s"(row_of_query), "s"(lse_rows));
     constexpr int kPartsPerLane = kMaxSplits / 64;
     const int B = B_dev ? *B_dev : rows;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;

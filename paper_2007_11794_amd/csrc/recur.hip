@@ -421,6 +421,8 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
     __shared__ int srcs[64], prevs[64];                // rows to take, their previous words
     // Workgroup id modulo 8 is the XCD (L2 domain).  Row block rb runs on XCD rb % 8 with all
     // its unit blocks, so h_in (the larger operand) is fetched into one L2 only.
+    // the arguments fetched together, not one by one where they are used
+    asm volatile("" ::"s"(m.W), "s"(m.U), "s"(m.half_rowsum_W), "s"(m.d), "s"(m.dfrag), "s"(m.Hp), "s"(m.H), "s"(m.V), "s"(prev_word), "s"(h_in), "s"(h_out), "s"(row_dst));
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, tid = threadIdx.x;
     const int JS = m.Hp / 64, JL = (m.Hp + 127) / 128;
     const int bs = (xcd + kXcds * (local / JS)) * 32, bl = (xcd + kXcds * (local / JL)) * 64;
