@@ -9,8 +9,9 @@
 // in bf16 terms, two MFMA passes, so that the hidden vector is accurate to fp32 level.  fp32 models: every
 // fp32 number is the exact sum of three bf16 numbers, of the nine cross terms of a product the six with
 // the largest weight are kept (w1 d1, w1 d2, w2 d1, w1 d3, w3 d1, w2 d2; the dropped ones are below 2^-24
-// of the product): six MFMA passes, still a fraction of the time the operands take to arrive, at the range
-// of fp32 (h_in is the caller's and need not lie in [0, 1]).
+// of the product): six MFMA passes, still a fraction of the time the operands take to arrive.  h_in is
+// the caller's and need not lie in [0, 1]: sums that meet an infinity or a number beyond the largest bf16 one are done
+// again in plain fp32 (plain_sum4).
 //
 // Besides h_out (fp32, caller's buffer) the kernel leaves d' = h' - 1/2 in the model's
 // scratch blocks as the operand of the output projection: row-major in the weights' type;
@@ -104,7 +105,7 @@ struct Shape {
     static constexpr int kSums = 4 * MB;                           // four-unit results of a lane's accumulators
     static_assert(TU / (32 * MB) * (TB / 32) * WK == kWaves && kWLoads * 16 * kThreads == kWBytes && kStages >= 2, "");
     static_assert((kStages - 2) * kLoads < 64, "vmcnt");
-    static_assert(WK == 1 || kWaves * kSums * 1024 <= kStages * SUB * kChunkBytes, "partial sums fit the stages");
+    static_assert(kWaves * kSums * 1024 <= kStages * SUB * kChunkBytes, "partial sums fit the stages");
     static_assert(kSums % WK == 0 && SUB * 4 % WK == 0, "");
 };
 
@@ -175,6 +176,24 @@ __device__ __forceinline__ void finish4(const ModelDev &m, const Finish &f, int 
         for (int i = 0; i < 4; ++i)
             if (je + i < f.H) f.h_row[je + i] = hp[i];
     }
+}
+
+// W (h - 1/2) of four units (rows w of Hp weights, `units` of them real) for one row of h_in, in plain fp32.  Only taken
+// where the split of an fp32 operand into bf16 terms has no meaning: an infinity, or a number that rounds to one in bf16
+// (beyond 3.389e38), leaves inf - inf in its lower terms, and the sum is NaN then.  Ends once nothing but NaN is left.
+__device__ __forceinline__ f32x4 plain_sum4(const float *w, int Hp, int units, const float *h, int H) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < H; ++k) {
+        const float d = h[k] - 0.5f;
+        bool all_nan = true;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i < units) s[i] = fmaf(w[(size_t)i * Hp + k], d, s[i]);
+            all_nan = all_nan && (i >= units || s[i] != s[i]);
+        }
+        if (all_nan) break;
+    }
+    return s;
 }
 
 // rows b0 .. b0 + TB - 1, units j0 .. j0 + TU - 1; source: the row of h_in / prev_word that lane tid of the
@@ -312,30 +331,28 @@ __device__ __forceinline__ void recur_body(const ModelDev &m, int B, int b0, int
     const Finish f = {h_out + (size_t)dst * H, b, H, Hp, w_ok};
     auto result = [&](int r) { return f32x4{acc[r / 4][4 * (r % 4)], acc[r / 4][4 * (r % 4) + 1], acc[r / 4][4 * (r % 4) + 2],
                                             acc[r / 4][4 * (r % 4) + 3]}; };
-    if constexpr (WK == 1) {
-        if (!row_ok || !units_ok) return;
+    // the partial sums of a block meet in LDS (the stages are free)
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);   // [wave][result][lane]
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kMine; ++q) finish4<WT, VEC>(m, f, je + 8 * q, result(q), rs[q], u[q]);
-    } else {
-        // the partial sums of a block meet in LDS (the stages are free)
-        f32x4 *red = reinterpret_cast<f32x4 *>(lds);   // [wave][result][lane]
-        __syncthreads();
+    for (int r = 0; r < C::kSums; ++r) red[(wave * C::kSums + r) * 64 + lane] = result(r);
+    __syncthreads();
+    if (!row_ok || !units_ok) return;
 #pragma unroll
-        for (int r = 0; r < C::kSums; ++r) red[(wave * C::kSums + r) * 64 + lane] = result(r);
-        __syncthreads();
-        if (!row_ok || !units_ok) return;
+    for (int q = 0; q < kMine; ++q) {
+        const f32x4 *mine = red + ((wave % (WJ * WB)) * C::kSums + wk * kMine + q) * 64 + lane;
+        f32x4 sum = mine[0];
 #pragma unroll
-        for (int q = 0; q < kMine; ++q) {
-            const f32x4 *mine = red + ((wave % (WJ * WB)) * C::kSums + wk * kMine + q) * 64 + lane;
-            f32x4 sum = mine[0];
+        for (int other = 1; other < WK; ++other) { // fixed order: deterministic
+            const f32x4 t = mine[other * (WJ * WB) * C::kSums * 64];
 #pragma unroll
-            for (int other = 1; other < WK; ++other) { // fixed order: deterministic
-                const f32x4 t = mine[other * (WJ * WB) * C::kSums * 64];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) sum[i] += t[i];
-            }
-            finish4<WT, VEC>(m, f, je + 8 * q, sum, rs[q], u[q]);
+            for (int i = 0; i < 4; ++i) sum[i] += t[i];
         }
+        if constexpr (C::kF32) {
+            if (sum[0] != sum[0] || sum[1] != sum[1] || sum[2] != sum[2] || sum[3] != sum[3])
+                sum = plain_sum4(W + (size_t)(je + 8 * q) * Hp, Hp, H - (je + 8 * q), h_in + (size_t)srcs[rb] * H, H);
+        }
+        finish4<WT, VEC>(m, f, je + 8 * q, sum, rs[q], u[q]);
     }
 }
 

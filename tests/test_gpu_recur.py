@@ -9,7 +9,7 @@ import oracle
 import paper_2007_11794_amd as rn
 from workloads import round_to_bf16
 
-from harness import DEV, gpu_step_dedup, load_model
+from harness import DEV, gpu_step, gpu_step_dedup, load_model
 
 pytestmark = pytest.mark.gpu
 V = 40
@@ -57,5 +57,45 @@ def test_against_the_oracle(H, B, dtype):
     some = np.unique(np.linspace(0, u - 1, 50).astype(int))
     ref = oracle.step(model, prev[src][rep][some], h_in[src][rep][some], query[:len(some)])
     assert np.max(np.abs(res["h_out"][some] - ref["h_out"])) <= tol_h
+    assert m.last_error() == 0
+    m.close()
+
+
+@pytest.mark.parametrize("H,B", [(64, 7), (77, 40), (256, 300), (1022, 513)])
+def test_fp32_inputs_beyond_a_16_bit_term(H, B):
+    """fp32 models: infinities, and finite numbers that round to one in bf16, in h_in and W saturate the units they reach
+    (one such term per sum, so the sign is certain), in any position of the row."""
+    rng = np.random.default_rng(H + B)
+    model = model_of(rng, H, "f32")
+    prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
+    query = rng.integers(0, V, (B, 2)).astype(np.int32)
+    big = np.finfo(np.float32).max
+    rows = np.unique(np.linspace(0, B - 1, 7).astype(int))
+    for i, r in enumerate(rows):
+        h_in[r, (0, H - 1, H // 2, 3, 1, 5, 0)[i]] = (np.inf, -np.inf, -np.inf, big, -big, np.float32(3.395e38), -big)[i]
+    model["W"][2, 7] = np.inf                                  # 7: no row above has its large element there
+    h_in[:, 7] = 0.75
+    a = model["U"][prev].astype(np.float64)
+    with np.errstate(over="ignore"):
+        # no sum holds two infinities of different sign but unit 2's, where W is infinite too: left out of the check
+        a += np.einsum("bi,ji->bj", h_in.astype(np.float64), model["W"].astype(np.float64))
+        ref = 1.0 / (1.0 + np.exp(-a))
+    keep = np.ones((B, H), bool)
+    keep[rows, 2] = False
+    assert np.isfinite(ref[keep]).all()
+    m = load_model(model, "f32", B)
+    for grouped in (False, True):
+        if grouped:
+            res = gpu_step_dedup(m, np.arange(B, dtype=np.uint64) * 3 + 5, prev, h_in, query)
+            h_out, lp = res["h_out"], res["logprob"]
+        else:
+            h_out, lp = gpu_step(m, prev, h_in, query)
+        assert np.max(np.abs(h_out[keep] - ref[keep])) <= 2e-6              # as above
+        # the normaliser of a row whose units are all known: the vectors handed out, in 64 bits
+        known = np.isfinite(h_out).all(1)
+        assert known.sum() >= B - len(rows)
+        z = h_out.astype(np.float64) @ model["O"].astype(np.float64)
+        want = np.take_along_axis(z, query.astype(np.int64), 1) - np.log(np.exp(z).sum(1))[:, None]
+        assert np.max(np.abs(lp[known] - want[known])) <= 1e-5
     assert m.last_error() == 0
     m.close()
