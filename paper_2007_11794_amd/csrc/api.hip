@@ -312,6 +312,9 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
         HIP_TRY(hipMalloc(&p, (size_t)Vp * 4)); d.ofac = static_cast<float *>(p);
         HIP_TRY(launch_split2_weights(static_cast<const float *>(d.Ot), Vp, Hp, const_cast<void *>(d.Ofrag),
                                       const_cast<float *>(d.ofac), nullptr));
+        HIP_TRY(hipMemcpy(hu.data(), d.half_colsum_O, (size_t)V * 4, hipMemcpyDeviceToHost));
+        for (int v = 0; v < V; ++v)
+            if (!isfinite(hu[v])) d.infinite_O = 1;
     } else {
         HIP_TRY(launch_frag_weights(d.Ot, Vp, Hp, const_cast<void *>(d.Ofrag), nullptr));
     }

@@ -211,6 +211,7 @@ hipError_t launch_outproj_stream(const ModelDev &m, int rows, const int *B_dev, 
 // 32 to 128 rows in LDS, depending on the model).  By itself up to 64 rows in at most two launches;
 // on request up to 128 rows in at most four.
 static bool stream_choice(const ModelDev &m, int rows, int kernel_choice) {
+    if (m.infinite_O && kernel_choice == 0) return false;
     const int per = outproj_stream_max_rows(m);
     if (per == 0) return false;
     const int launches = (rows + per - 1) / per;
@@ -233,12 +234,12 @@ static Bf16Kernel choose_bf16(const ModelDev &m, int rows, bool fixed_offset, in
     return kBf16Plain;
 }
 
-// The same for fp32 models.
+// The same for fp32 models.  Infinite weights are for the plain kernel.
 enum F32Kernel { kF32Stream, kF32Split2, kF32Tiled, kF32Plain };
 static F32Kernel choose_f32(const ModelDev &m, int rows, int kernel_choice) {
     if (stream_choice(m, rows, kernel_choice)) return kF32Stream;
     if (kernel_choice == 3) return kF32Tiled;
-    if (m.ofac && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64))) return kF32Split2;
+    if (m.ofac && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64 && !m.infinite_O))) return kF32Split2;
     return kF32Plain;
 }
 

@@ -45,6 +45,7 @@ struct ModelDev {
     // largest weight of a word lies in [2^13, 2^14)), [Vp / 32][Hp / 16][2 terms][64 lanes][8].
     const void *Ofrag;
     const float *ofac;            // [Vp] fp32 models: log2(e) / (the word's power of two * 2^14)
+    int infinite_O;               // fp32 models: some output weight is infinite or NaN (the two terms of an infinity add up to NaN)
     // hierarchical output layer (models loaded with rnnlm_hs_load; Ot .. cvec2_fixed are null then)
     int hs;                       // 1: hierarchical
     const void *Theta;            // [V-1][Hp] node vectors, weights' type, zero-padded

@@ -52,3 +52,25 @@ def test_against_the_oracle(V, H, B, big):
     assert np.max(np.abs(out["logprob"] - ref["logprob"])) <= tol
     assert m.last_error() == 0
     m.close()
+
+
+@pytest.mark.parametrize("V,H,B", [(300, 1000, 8), (300, 1000, 33), (700, 128, 20), (700, 128, 130)])
+def test_a_word_masked_by_an_infinite_weight(V, H, B):
+    """A word with a weight of -inf on a unit that is above one half in every row has probability 0; the others keep theirs."""
+    rng = np.random.default_rng(V + H + B)
+    model = model_of(rng, V, H, 1.0)
+    model["U"][:, 3] = 9.0                                   # h' of unit 3 is close to 1
+    model["O"][3, 17] = -np.inf
+    m = load_model(model, "f32", B)
+    prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
+    query = rng.integers(18, V, (B, 3)).astype(np.int32)
+    query[:, 2] = 17
+    h, lp = gpu_step(m, prev, h_in, query)
+    others = np.delete(np.arange(V), 17)
+    z = h.astype(np.float64) @ model["O"][:, others].astype(np.float64) + model["bias"][others]
+    full = np.zeros((B, V))
+    full[:, others] = z - np.log(np.exp(z).sum(1))[:, None]
+    tol = 1e-5 + 2.0 ** -24 * np.sqrt(H) * 0.5 * np.abs(model["O"][:, others]).sum(0).max()      # as above
+    assert np.max(np.abs(lp[:, :2] - np.take_along_axis(full, query[:, :2].astype(np.int64), 1))) <= tol
+    assert np.all(lp[:, 2] == -np.inf)
+    m.close()
