@@ -74,8 +74,8 @@ enum rnnlm_option {
      * power of two), fp32 accuracy at fp16 matrix-core speed: the automatic choice for fp32 from 64 rows
      * on, 5 = the weight-streaming kernel for few rows, which reads the operand-ordered copy of the
      * output weights once per launch at memory speed (fp32 models: the same two fp16 terms):
-     * the automatic choice up to 64 rows when two launches suffice (the staged and the
-     * eight-wave tiled kernel also take it on the device, when a grouped or
+     * the automatic choice up to 64 rows when two launches suffice (the staged, row-streaming,
+     * eight-wave tiled and two-term kernels also take it on the device, when a grouped or
      * cached step turns out to have that few rows and their LDS holds them).  One launch
      * serves as many rows as fit its LDS (bf16: 128 up to H = 576, 64 up to H = 1216, 32 up to
      * H = 2432; fp32: 128 up to H = 256, 64 up to H = 576, 32 up to H = 1216); on request it takes

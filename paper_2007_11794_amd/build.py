@@ -31,6 +31,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 FILE_FLAGS = {"outproj_split2.hip": ["-falign-loops=64"]}
 
 
+def flags_of(src: str) -> list:
+    return FLAGS + FILE_FLAGS.get(src, [])
+
+
 def _hipcc() -> str:
     for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
         if c and (os.path.isabs(c) and os.path.exists(c) or not os.path.isabs(c)):
@@ -49,7 +53,7 @@ def _compile(src: str, force: bool, extra) -> str:
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
     path = os.path.join(CSRC, src)
     if force or _stale(obj, [path] + HEADERS):
-        cmd = [_hipcc()] + FLAGS + FILE_FLAGS.get(src, []) + list(extra) + ["-c", path, "-o", obj]
+        cmd = [_hipcc()] + flags_of(src) + list(extra) + ["-c", path, "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         err = "\n".join(l for l in r.stderr.splitlines()
                         if "packed-fp32-ops" not in l)      # the host pass does not know the feature

@@ -29,6 +29,7 @@
 //   - MFMA roles as in the other kernels (A = words, B = rows): a lane holds sixteen logits of ONE
 //     row per accumulator, the sum over words stays in the lane.
 #include "device_utils.h"
+#include "outproj_stream_body.h"
 #include "rnnlm_internal.h"
 
 namespace rnnlm {
@@ -36,6 +37,12 @@ namespace rnnlm {
 namespace {
 
 constexpr int kThreads = 256, kRows = 128, kStages = 3;
+constexpr int kMaxLds = 80 * 1024;                             // two workgroups per compute unit
+
+// Do both terms of a hidden block of 32 rb rows fit that much LDS (else the streaming form keeps the first one only)?
+__host__ __device__ inline bool block_fits(int rb, int Hp) {
+    return stream_lds_bytes(2, rb, Hp >> 4, kThreads / 64) <= (size_t)kMaxLds;
+}
 
 template <int MB>
 struct Split2Cfg {
@@ -46,13 +53,13 @@ struct Split2Cfg {
     static constexpr int kConstBytes = 2 * kWords * 4;          // constants and factors of one tile
     static constexpr int kConstAt = kStages * kStageBytes, kRedAt = kConstAt + 2 * kConstBytes;
     static constexpr int kLdsBytes = kRedAt + 2 * kRows * 8;    // + final cross-wave reduction
-    static_assert(2 * kLdsBytes <= 160 * 1024, "two workgroups per compute unit");
+    static_assert(kLdsBytes <= kMaxLds, "");
 };
 
 template <bool FIXED, int MB>
 __global__ __launch_bounds__(kThreads, 2) void outproj_split2_kernel(ModelDev m, int rows,
                                                                      const int *__restrict__ B_dev, int wg_per_xcd,
-                                                                     int sx_cap) {
+                                                                     int sx_cap, int stream_rows, int stream_splits) {
     using C = Split2Cfg<MB>;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     // The arguments fetched together with the row count, not one by one where they are used (V = 20000, H = 256, 256 rows
@@ -63,6 +70,20 @@ __global__ __launch_bounds__(kThreads, 2) void outproj_split2_kernel(ModelDev m,
     // the device knows it): few rows get many vocabulary splits, and the whole grid works.
     const int B = B_dev ? *B_dev : rows;
     if (B <= 0) return;                                       // uniform: no barrier is met
+    // Few rows after all (the count known on the device only): the time is then the time to read the weights once, and
+    // one workgroup per compute unit streams its share of them; the tiles would keep two k-steps of weights per workgroup
+    // on their way, at most one workgroup per unit having any.  Us per launch, tiles / streaming (three-term kernel before
+    // both, which streamed too): V = 20000, H = 256, 32 rows 13.7 / 5.0 (9.0), 64 rows 13.9 / 6.5 (11.8); V = 65536, H = 512,
+    // 32 rows 31.6 / 24.2 (29.9); V = 100000, H = 128, 32 rows 16.5 / 10.3 (13.6); V = 20000, H = 768, 32 rows 34.2 / 12.4
+    // (21.0).  A step at V = 20000, H = 256 with 32 of 4096 distinct 32.3 / 23.7 (27.8).
+    if (__builtin_expect(B <= stream_rows, 0)) {              // (out of the way of the code below)
+        constexpr int kWaves = kThreads / 64;
+        if ((int)blockIdx.x >= stream_splits) return;
+        if (!block_fits(1, m.Hp)) outproj_stream_f32_body<1, FIXED, kWaves, true>(m, B, 0, (int)blockIdx.x, stream_splits, lds);
+        else if (B <= 32) outproj_stream_f32_body<1, FIXED, kWaves>(m, B, 0, (int)blockIdx.x, stream_splits, lds);
+        else outproj_stream_f32_body<2, FIXED, kWaves>(m, B, 0, (int)blockIdx.x, stream_splits, lds);
+        return;
+    }
     const RowPlan plan = plan_rows(B, kRows, wg_per_xcd, sx_cap);
     const int S = plan.S, items = plan.RG * plan.Sx;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
@@ -208,18 +229,30 @@ hipError_t launch_split2_shape(const ModelDev &m, int rows, const int *B_dev, bo
     static LdsLimit limit[2];
     const void *fn = fixed_offset ? reinterpret_cast<const void *>(outproj_split2_kernel<true, MB>)
                                   : reinterpret_cast<const void *>(outproj_split2_kernel<false, MB>);
-    if (hipError_t e = limit[fixed_offset ? 1 : 0].ensure(fn, C::kLdsBytes); e != hipSuccess) return e;
     // two workgroups per compute unit; at most one split per tile of words, rounded UP to a multiple of
     // 8 so that no split gets two tiles while the others have one
     const int wg_per_xcd = 64, ntiles = m.Vp / C::kWords, sx_cap = (ntiles + kXcds - 1) / kXcds;
-    *splits = SplitInfo{0, wg_per_xcd, kRows, sx_cap, 0};
+    // Rows the streaming form takes, when the count is on the device: 64 (Hp <= 256) or 32 (Hp <= 576) with both terms
+    // of the block in half a compute unit's LDS; 32 with one term where that needs no more LDS than the tiles do.
+    int stream_rows = 0, lds_bytes = C::kLdsBytes;
+    if (B_dev) {
+        const int rb = block_fits(2, m.Hp) ? 2 : 1, terms = block_fits(1, m.Hp) ? 2 : 1;
+        const int need = (int)stream_lds_bytes(terms, rb, m.Hp >> 4, kThreads / 64);
+        if (terms == 2 || need <= lds_bytes) {
+            stream_rows = 32 * rb;
+            if (need > lds_bytes) lds_bytes = need;
+        }
+    }
+    const int stream_splits = m.Vp / 32 < kMaxSplits ? m.Vp / 32 : kMaxSplits;
+    if (hipError_t e = limit[fixed_offset ? 1 : 0].ensure(fn, kMaxLds); e != hipSuccess) return e;
+    *splits = SplitInfo{0, wg_per_xcd, kRows, sx_cap, stream_rows, stream_splits};
     dim3 grid(kXcds * wg_per_xcd), block(kThreads);
     if (fixed_offset)
-        hipLaunchKernelGGL((outproj_split2_kernel<true, MB>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,
-                           wg_per_xcd, sx_cap);
+        hipLaunchKernelGGL((outproj_split2_kernel<true, MB>), grid, block, lds_bytes, stream, m, rows, B_dev,
+                           wg_per_xcd, sx_cap, stream_rows, stream_splits);
     else
-        hipLaunchKernelGGL((outproj_split2_kernel<false, MB>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,
-                           wg_per_xcd, sx_cap);
+        hipLaunchKernelGGL((outproj_split2_kernel<false, MB>), grid, block, lds_bytes, stream, m, rows, B_dev,
+                           wg_per_xcd, sx_cap, stream_rows, stream_splits);
     return hipGetLastError();
 }
 

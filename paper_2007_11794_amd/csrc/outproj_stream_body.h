@@ -1,6 +1,6 @@
 // The weight-streaming output projection as device functions (bf16 models, then fp32 models): the
-// kernels of its own (few rows known on the host) and the staged kernel (few rows
-// known only on the device) run them.  See outproj_stream.hip for the design.
+// kernels of its own (few rows known on the host) and the staged, tiled, row-streaming and two-term kernels (few
+// rows known only on the device) run them.  See outproj_stream.hip for the design.
 #pragma once
 
 #include "device_utils.h"
@@ -13,12 +13,14 @@ constexpr int kStreamWaves = kStreamThreads / 64;
 constexpr int kStreamGroup = 4;          // MFMA operands (k-steps) per group of loads; Hp is a multiple of 64
 constexpr int kStreamRing = 5;           // groups per wave: one being consumed, four in flight
 
-struct StreamCursor {                    // walks the groups of the blocks blk, blk + kStreamWaves, ... of one wave
+template <int WAVES>
+struct StreamCursorOf {                  // walks the groups of the blocks blk, blk + WAVES, ... of one wave
     int blk, part;
     __device__ __forceinline__ void advance(int groups_per_block) {
-        if (++part == groups_per_block) { part = 0; blk += kStreamWaves; }
+        if (++part == groups_per_block) { part = 0; blk += WAVES; }
     }
 };
+typedef StreamCursorOf<kStreamWaves> StreamCursor;
 
 // The hidden block (`pieces` kilobytes at `src`) into LDS, in front of the loop over the weights.  More than two
 // kilobytes per wave go straight to LDS, all of it on its way at once, requested before the weights (stream_block_begin)
@@ -28,25 +30,27 @@ struct StreamCursor {                    // walks the groups of the blocks blk, 
 // behind them.
 // At the wait at least 16 younger loads of the wave are outstanding (four groups of the ring, which the memory
 // clobbers keep between request and wait); operations complete in order, so the block has landed once no more than 12 are.
-constexpr int kStreamCopyPieces = 2 * kStreamWaves;
+constexpr int kStreamCopyPieces = 2;                // per wave
 
+template <int WAVES>
 __device__ __forceinline__ void stream_block_copy(const char *src, int pieces, char *lds) {
     const u32x4 *from = reinterpret_cast<const u32x4 *>(src);
     u32x4 *to = reinterpret_cast<u32x4 *>(lds);
-    for (int i = threadIdx.x; i < pieces * 64; i += kStreamThreads) to[i] = from[i];
+    for (int i = threadIdx.x; i < pieces * 64; i += 64 * WAVES) to[i] = from[i];
 }
-template <bool COPY_FIRST>
-__device__ __forceinline__ void stream_block_begin(const char *src, int pieces, char *lds, int wave, int lane) {
-    if (pieces <= kStreamCopyPieces) {                        // uniform
-        if (COPY_FIRST) stream_block_copy(src, pieces, lds);
+// (pieces `stride` bytes apart, if there are more than kStreamCopyPieces per wave)
+template <bool COPY_FIRST, int WAVES = kStreamWaves>
+__device__ __forceinline__ void stream_block_begin(const char *src, int pieces, char *lds, int wave, int lane, int stride = 1024) {
+    if (pieces <= kStreamCopyPieces * WAVES) {                        // uniform
+        if (COPY_FIRST) stream_block_copy<WAVES>(src, pieces, lds);
         return;
     }
-    for (int p = wave; p < pieces; p += kStreamWaves) lds_dma_16(src + (size_t)p * 1024, lane * 16, lds_address(lds) + p * 1024);
+    for (int p = wave; p < pieces; p += WAVES) lds_dma_16(src + (size_t)p * stride, lane * 16, lds_address(lds) + p * 1024);
 }
-template <bool COPY_FIRST>
+template <bool COPY_FIRST, int WAVES = kStreamWaves>
 __device__ __forceinline__ void stream_block_end(const char *src, int pieces, char *lds) {
-    if (pieces > kStreamCopyPieces) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-    else if (!COPY_FIRST) stream_block_copy(src, pieces, lds);
+    if (pieces > kStreamCopyPieces * WAVES) asm volatile("s_waitcnt vmcnt(12) ; hidden block" ::: "memory");
+    else if (!COPY_FIRST) stream_block_copy<WAVES>(src, pieces, lds);
     __syncthreads();                                          // hidden block visible to all waves
 }
 
@@ -167,8 +171,10 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
 // weight as in fp32, and three MFMAs per operand add the cross terms (2.1, 1.2, 1.1).
 constexpr int kStreamGroup32 = 2;        // operands per group (two terms each: four loads, as above)
 
-// The fp32 form of outproj_stream_body: needs stream_lds_bytes(2, RB, Hp / 16) bytes of LDS.
-template <int RB, bool FIXED>
+// The fp32 form of outproj_stream_body, for a workgroup of WAVES waves: needs stream_lds_bytes(2, RB, Hp / 16, WAVES) bytes
+// of LDS.  ONE_TERM: stream_lds_bytes(1, ...) bytes (and more than kStreamCopyPieces kilobytes of block per wave): only the
+// first term of the hidden block is kept there, the second comes from the caches beside the weights.
+template <int RB, bool FIXED, int WAVES = kStreamWaves, bool ONE_TERM = false>
 __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B, int row0, int split, int S, char *lds) {
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -180,22 +186,28 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     const float *cvec = FIXED ? m.cvec2_fixed : m.cvec2;
     const float m2_fixed = m.m2_fixed;
     asm volatile("" ::"s"(m2_fixed), "s"(m.Ofrag), "s"(cvec), "s"(m.ofac));  // as above
+    constexpr int kTerms = ONE_TERM ? 1 : 2;
     f16x8 *dl = reinterpret_cast<f16x8 *>(lds);                             // [RB][KS][term][64]
-    float2 *red = reinterpret_cast<float2 *>(lds + (size_t)2 * RB * KS * 1024);
+    float2 *red = reinterpret_cast<float2 *>(lds + (size_t)kTerms * RB * KS * 1024);
 
     const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 2048;
-    stream_block_begin<false>(block, 2 * RB * KS, lds, wave, lane);
-    f16x8 ring[kStreamRing][2 * kStreamGroup32];
-    StreamCursor in = {blk0 + wave, 0};
-    auto issue = [&](f16x8(&dst)[2 * kStreamGroup32]) {                          // always four loads (see above)
+    stream_block_begin<false, WAVES>(block, kTerms * RB * KS, lds, wave, lane, 2048 / kTerms);
+    f16x8 ring[kStreamRing][2 * kStreamGroup32], second[kStreamRing][ONE_TERM ? RB * kStreamGroup32 : 1];
+    StreamCursorOf<WAVES> in = {blk0 + wave, 0};
+    auto issue = [&](int slot) __attribute__((always_inline)) {                  // always as many loads (see above)
         const f16x8 *p = Of + (in.blk < blk1 ? ((size_t)in.blk * KS + in.part * kStreamGroup32) * 128 : (size_t)0);
 #pragma unroll
-        for (int i = 0; i < 2 * kStreamGroup32; ++i) dst[i] = p[i * 64];
+        for (int i = 0; i < 2 * kStreamGroup32; ++i) ring[slot][i] = p[i * 64];
+        if constexpr (ONE_TERM) {
+            const f16x8 *d2 = reinterpret_cast<const f16x8 *>(block) + in.part * (kStreamGroup32 * 128) + 64 + lane;
+#pragma unroll
+            for (int i = 0; i < RB * kStreamGroup32; ++i) second[slot][i] = d2[(i / kStreamGroup32 * KS + i % kStreamGroup32) * 128];
+        }
         in.advance(GPB);
     };
 #pragma unroll
-    for (int st = 0; st < kStreamRing - 1; ++st) issue(ring[st]);
-    StreamCursor out = {blk0 + wave, 0};
+    for (int st = 0; st < kStreamRing - 1; ++st) issue(st);
+    StreamCursorOf<WAVES> out = {blk0 + wave, 0};
     f32x4 cc[4], ff[4];
     auto load_constants = [&]() {
         const int blk = out.blk < blk1 ? out.blk : blk0;
@@ -206,7 +218,7 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
         }
     };
     load_constants();
-    stream_block_end<false>(block, 2 * RB * KS, lds);
+    stream_block_end<false, WAVES>(block, kTerms * RB * KS, lds);
 
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
@@ -222,15 +234,15 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
 #pragma unroll
             for (int st = 0; st < kStreamRing; ++st) {
                 if (out.blk >= blk1) return;
-                issue(ring[(st + kStreamRing - 1) % kStreamRing]);
+                issue((st + kStreamRing - 1) % kStreamRing);
 #pragma unroll
                 for (int i = 0; i < kStreamGroup32; ++i) {
                     const int ks = out.part * kStreamGroup32 + i;
                     const f16x8 w1 = ring[st][2 * i], w2 = ring[st][2 * i + 1];
 #pragma unroll
                     for (int rb = 0; rb < RB; ++rb) {
-                        const int at = (rb * KS + ks) * 128 + lane;
-                        const f16x8 d1 = dl[at], d2 = dl[at + 64];
+                        const int at = (rb * KS + ks) * (64 * kTerms) + lane;
+                        const f16x8 d1 = dl[at], d2 = ONE_TERM ? second[st][rb * kStreamGroup32 + i] : dl[at + 64];
                         // smallest terms first
                         acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2, d1, acc[rb], 0, 0, 0);
                         acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w1, d2, acc[rb], 0, 0, 0);
@@ -267,7 +279,7 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     __syncthreads();
     if (tid < RB * 32) {
         float mm = red[tid].x, ss = red[tid].y;
-        for (int w = 1; w < kStreamWaves; ++w) {
+        for (int w = 1; w < WAVES; ++w) {
             const float2 p = red[w * (RB * 32) + tid];
             if (FIXED) ss += p.y;
             else lse2_merge(mm, ss, p.x, p.y);
@@ -277,8 +289,8 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
 }
 
 // terms = copies of the hidden block kept in LDS: 1 (bf16 models) or 2 (fp32 models)
-__host__ __device__ inline size_t stream_lds_bytes(int terms, int RB, int KS) {
-    return (size_t)terms * RB * KS * 1024 + (size_t)kStreamWaves * RB * 32 * sizeof(float2);
+__host__ __device__ inline size_t stream_lds_bytes(int terms, int RB, int KS, int waves = kStreamWaves) {
+    return (size_t)terms * RB * KS * 1024 + (size_t)waves * RB * 32 * sizeof(float2);
 }
 
 }  // namespace rnnlm

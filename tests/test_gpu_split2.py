@@ -74,3 +74,26 @@ def test_a_word_masked_by_an_infinite_weight(V, H, B):
     assert np.max(np.abs(lp[:, :2] - np.take_along_axis(full, query[:, :2].astype(np.int64), 1))) <= tol
     assert np.all(lp[:, 2] == -np.inf)
     m.close()
+
+
+# both terms of 64 and of 32 rows in LDS, one term of 32 rows, neither; rows around what each takes; a vocabulary of fewer
+# blocks of 32 words than there are workgroups, one with a remainder
+@pytest.mark.parametrize("V,H,N,unique", [(300, 64, 300, 1), (9000, 256, 1024, 64), (9000, 256, 1024, 65), (20011, 320, 513, 32),
+                                          (20011, 320, 513, 33), (9000, 576, 300, 31), (9000, 640, 300, 32), (9000, 832, 300, 20),
+                                          (9000, 832, 300, 40), (3000, 1024, 300, 9), (66000, 900, 513, 32), (3000, 1300, 300, 9)])
+def test_few_rows_known_on_the_device_only(V, H, N, unique):
+    rng = np.random.default_rng(V + H + unique)
+    model = model_of(rng, V, H, 1.0)
+    m = load_model(model, "f32", N)
+    src = np.concatenate([np.arange(unique), rng.integers(0, unique, N - unique)])
+    prev, h_in = rng.integers(0, V, unique).astype(np.int32)[src], rng.uniform(0, 1, (unique, H)).astype(np.float32)[src]
+    query = rng.integers(0, V, (N, 2)).astype(np.int32)
+    ref = oracle.step(model, prev[:unique], h_in[:unique], query, row_of_query=src.astype(np.int32))
+    tol = 1e-5 + 2.0 ** -24 * np.sqrt(H) * 0.5 * np.abs(model["O"]).sum(0).max()                 # as above
+    assert m.outproj_kernel_name(N) == "outproj_split2_kernel"
+    for lse_mode in (0, 1):
+        m.set_option(rn.OPT_LSE_MODE, lse_mode)
+        out = gpu_step_dedup(m, src.astype(np.uint64) + 5, prev, h_in, query)
+        assert out["n_unique"] == unique and np.max(np.abs(out["logprob"] - ref["logprob"])) <= tol
+    assert m.last_error() == 0
+    m.close()

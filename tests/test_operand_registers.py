@@ -56,7 +56,7 @@ def test_the_scan_finds_a_read_in_front_of_the_wait():
 @pytest.mark.parametrize("source", ["outproj_rowstream.hip", "outproj_staged.hip"])
 def test_operands_stay_untouched_until_they_have_landed(source, tmp_path):
     out = str(tmp_path / "kernel.s")
-    subprocess.run([b._hipcc()] + b.FLAGS + ["-S", "--cuda-device-only", os.path.join(b.CSRC, source), "-o", out], check=True,
+    subprocess.run([b._hipcc()] + b.flags_of(source) + ["-S", "--cuda-device-only", os.path.join(b.CSRC, source), "-o", out], check=True,
                    capture_output=True)
     with open(out) as f:
         lines = f.read().splitlines()
