@@ -203,6 +203,8 @@ __global__ __launch_bounds__(kThreads, 2) void outproj_split2_kernel(ModelDev m,
         if (++ks == KS) { ks = 0; ++tile; }
         stage = stage == kStages - 1 ? 0 : stage + 1;
     }
+    // (an item without tiles meets no barrier above: the partials of the item before are read by then)
+    __syncthreads();
     // lanes l and l+32 hold two halves of a row; waves wm = 0, 1 hold the two word halves
     float2 *red = reinterpret_cast<float2 *>(lds + C::kRedAt);             // [2 (wm)][rows of the tile]
 #pragma unroll
@@ -219,7 +221,7 @@ __global__ __launch_bounds__(kThreads, 2) void outproj_split2_kernel(ModelDev m,
         else lse2_merge(p.x, p.y, q.x, q.y);
         m.part[(size_t)(b0 + tid) * kMaxSplits + split] = p;
     }
-    }   // items (the next one writes `red` behind the barriers of its own k-steps)
+    }   // items
 }
 
 template <int MB>

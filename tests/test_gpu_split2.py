@@ -97,3 +97,20 @@ def test_few_rows_known_on_the_device_only(V, H, N, unique):
         assert out["n_unique"] == unique and np.max(np.abs(out["logprob"] - ref["logprob"])) <= tol
     assert m.last_error() == 0
     m.close()
+
+
+@pytest.mark.parametrize("V", [2, 300, 1100])
+def test_more_row_groups_than_workgroups(V):
+    """Workgroups take several row groups, of vocabulary splits that hold no word at all where there are few."""
+    H, B = 64, 9000
+    rng = np.random.default_rng(V)
+    model = model_of(rng, V, H, 1.0)
+    m = load_model(model, "f32", B)
+    prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
+    query = rng.integers(0, V, (B, 1)).astype(np.int32)
+    ref = oracle.step(model, prev, h_in, query)
+    tol = 1e-5 + 2.0 ** -24 * np.sqrt(H) * 0.5 * np.abs(model["O"]).sum(0).max()                 # as above
+    for lse_mode in (0, 1):
+        m.set_option(rn.OPT_LSE_MODE, lse_mode)
+        assert np.max(np.abs(gpu_step(m, prev, h_in, query)[1] - ref["logprob"])) <= tol
+    m.close()
