@@ -22,18 +22,18 @@
 // take, side by side; then the rows; then the embedding rows), and after it the bytes a compute unit
 // takes in.  There are two shapes of a workgroup of eight waves, picked by the true row count (which only
 // the device may know), in one launch:
-//   small  64 units x 32 rows, the reduction length split over four pairs of waves: while its
-//          workgroups fit the compute units in one round (few bytes per workgroup, all units at work);
+//   small  64 units x 32 rows, the reduction length split over four pairs of waves: while there are at most two
+//          of its workgroups per compute unit (few bytes per workgroup, all units at work; see small_rows);
 //   large  128 units x 64 rows, a wave owns 64 x 32 of them over half of the reduction: h_in is converted
 //          once for two blocks of units, and reading, converting and multiplying overlap between the waves
 //          (with 32 x 32 per wave over the whole reduction H = 1024, 3000 rows took 43 us instead of 30).
-// Launches that fit one small workgroup per compute unit use a whole unit's LDS as the ring (128 KB, all
-// but one stage in flight); larger ones of bf16 models half of it, two workgroups per unit.
+// Launches of bf16 models that fit one small workgroup per compute unit use a whole unit's LDS as the ring (128 KB, all
+// but one stage in flight), larger ones half of it, two workgroups per unit; fp32 models always the whole one.
 // Measured, us per launch (rows in brackets), before and after, the kernels before being one tiled and one
 // register-direct kernel for bf16 models and the fp32 matrix instruction for fp32 ones: bf16 H = 512 (1024)
 // 9.6 -> 8.6, (41 of 4096) 8.3 -> 5.8, (1229 of 4096) 12.0 -> 11.2; H = 1024 (2048) 30.6 -> 22.6, (200 of 2048)
 // 15.3 -> 10.8; H = 650 (317) 13.9 -> 10.7; H = 333 (1000) 14.7 -> 7.8; fp32 H = 512 (1024) 19.2 -> 12.8,
-// (4000) 53.8 -> 29.7; H = 1024 (1024) 47.0 -> 40.6.  The error of fp32 models' h' against float64 went from
+// (4000) 53.8 -> 29.7; H = 1024 (1024) 44.2 -> 32.9.  The error of fp32 models' h' against float64 went from
 // 4.7e-8 to 4.3e-8 (H = 512), bf16 models' stayed.
 #include <algorithm>
 
@@ -356,9 +356,15 @@ __device__ __forceinline__ void recur_body(const ModelDev &m, int B, int b0, int
     }
 }
 
-// Row counts up to here take the small shape: its workgroups fit the compute units in one round, one (or
-// with half a ring two) per unit.
-__host__ __device__ inline int small_rows(int Hp, bool half) { return 32 * ((half ? 2 : 1) * kGroups / (Hp / 64)); }
+// Row counts up to here take the small shape: at most `per_unit` of its workgroups for every compute unit of an XCD
+// (row block rb, with all its blocks of units, belongs to XCD rb % 8).  bf16 models: one with the whole ring, two at a time with
+// half of it; fp32 models: two, one after the other.  Us per launch, small / large shape, the limit in brackets: bf16
+// Hp = 704 (512 and 1280 rows), 600 rows with half a ring 10.6 / 14.5, with the whole one, in two rounds, 14.7; Hp = 512 (2048), 2048
+// rows 13.1 / 15.4, 2300 16.9 / 16.3; Hp = 1344 (768), 1000 rows 24.4 / 22.9; fp32 Hp = 512 (2048), 1025 rows 18.8 / 22.9, 2048 21.3
+// / 23.8, 2300 28.8 / 23.9; Hp = 1344 (768), 520 rows 37.4 / 45.7, 1000 56.3 / 48.6.
+__host__ __device__ inline int small_rows(int Hp, int per_unit) {
+    return 32 * kXcds * (per_unit * (kGroups / kXcds) / (Hp / 64));
+}
 
 constexpr int ring_bytes(int elem, bool half) { return (half ? 64 : elem == 2 ? 128 : 144) * 1024; }
 
@@ -461,7 +467,8 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
         B = B_dev ? *B_dev : rows;
     }
     constexpr int kRing = ring_bytes(sizeof(WT), HALF);
-    if (B <= small_rows(m.Hp, HALF)) {                 // uniform
+    constexpr bool kSmallOnly = sizeof(WT) == 2 && !HALF;          // launches of at most small_rows(Hp, 1) rows
+    if (kSmallOnly || B <= small_rows(m.Hp, 2)) {      // uniform
         if (bs >= B) return;
         const int j0 = (local % JS) * 64;
         if (m.Hp % 128 == 0)
@@ -485,7 +492,7 @@ hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *
     auto slots = [](int blocks) { return kXcds * ((blocks + kXcds - 1) / kXcds); };   // row blocks, spread over the XCDs
     // With the count on the device only, the grid covers both shapes: the small one up to its limit, the
     // large one up to `rows`.
-    const int few = std::min(rows, small_rows(m.Hp, HALF));
+    const int few = std::min(rows, small_rows(m.Hp, sizeof(WT) == 2 && !HALF ? 1 : 2));
     const bool on_device = B_dev || ids.key;
     int grid = rows <= few || on_device ? slots((few + 31) / 32) * (m.Hp / 64) : 0;
     if (rows > few) grid = std::max(grid, slots((rows + 63) / 64) * ((m.Hp + 127) / 128));
@@ -502,15 +509,18 @@ hipError_t launch_type(const ModelDev &m, int rows, const int *B_dev, const int3
         return launch<float, VEC, false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
     // half a ring beyond one round of small workgroups: H = 512, 1229 rows 12.5 -> 10.4 us, H = 1024, 3000 rows
     // 37 -> 30, H = 1024, 2048 rows 22.2 -> 22.6
-    if (rows <= small_rows(m.Hp, false))
+    if (rows <= small_rows(m.Hp, 1))
         return launch<bf16_t, VEC, false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
     return launch<bf16_t, VEC, true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
 }
 
 }  // namespace
 
-// Every workgroup repeats the grouping, so the launch must be one round of them: up to Hp = 2048 the grid for
-// kGroupedMax rows is 512 workgroups, two per compute unit (fp32 models: 256, one per unit).
+// Every workgroup repeats the grouping, so they must be few: up to Hp = 2048 the grid for kGroupedMax rows is at most 512 of
+// them, two per compute unit (side by side, or for fp32 models in turn).  Steps of 1024 distinct ids with the grouping here / in a
+// launch of its own, V = 4000, us: bf16 H = 64 16.2 / 17.3, 512 23.0 / 24.2, 1600 59.7 / 59.2, 2048 70.7 / 71.9; fp32 H = 512 37.8 /
+// 39.0, 1600 112.1 / 111.8, 2048 143.9 / 144.9; 102 distinct of 1024: 1.5 to 2.6 less everywhere.  A table for 2048 ids made the same
+// launch 0.2 slower at up to 1024 and gained 1.1 to 2.0 at 1100, 0.3 to 1.9 at 1536, nothing at 2048 (-0.8 to +3 when all are distinct).
 bool recur_groups_ids(const ModelDev &m, int N) { return N > 0 && N <= kGroupedMax && m.Hp <= 2048; }
 
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,

@@ -21,10 +21,11 @@ def model_of(rng, H, dtype):
     return {k: round_to_bf16(v) if k != "bias" and dtype == "bf16" else v for k, v in m.items()}
 
 
-# hidden size, rows: small_rows is 32 * 256 / (padded H / 64) rows, twice that with half a ring (bf16 batches beyond it)
+# hidden size, rows: small_rows is 256 * (32 / (padded H / 64)) rows, with 64 in the place of 32 beyond them (rounded down)
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("H,B", [(64, 31), (64, 33), (150, 64), (130, 65), (333, 257), (512, 1024), (512, 1025), (1022, 513),
-                                 (1024, 1024), (1024, 1025), (1100, 500), (1100, 931), (2048, 513), (4096, 257)])
+                                 (1024, 1024), (1024, 1025), (1100, 500), (1100, 931), (2048, 513), (4096, 257),
+                                 (64, 300), (700, 513), (704, 1280), (704, 1281), (512, 2049), (1088, 769), (320, 3073)])
 def test_against_the_oracle(H, B, dtype):
     rng = np.random.default_rng(H * 10000 + B)
     model = model_of(rng, H, dtype)
