@@ -3,6 +3,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -131,17 +132,23 @@ double widen_host(const void *p, size_t i, int dtype) {
     return (double)static_cast<const float *>(p)[i];
 }
 
-// `rows` host rows of H elements into device rows of Hp elements, the rest zero.  One contiguous copy and a
-// kernel: hipMemcpy2D from pageable memory goes row by row, 9 us each (a million words: 9.2 s of 9.3).
+// `rows` host rows of H elements into device rows of Hp elements, the rest zero.  Contiguous copies and a
+// kernel: hipMemcpy2D from pageable memory goes row by row, 9 us each (a million words: 9.2 s of 9.3).  In pieces, so that a
+// model that fits the device can be loaded: the copy in between never takes more than kUploadPiece bytes.
+constexpr size_t kUploadPiece = (size_t)64 << 20;
 int upload_rows(void *dst, const void *src, size_t rows, int H, int Hp, int dtype) {
     int status = RNNLM_OK;
-    const size_t bytes = rows * H * elem_size(dtype);
-    if (Hp == H) return hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) == hipSuccess ? RNNLM_OK : RNNLM_EDEVICE;
+    const size_t es = elem_size(dtype), row = H * es;
+    if (Hp == H) return hipMemcpy(dst, src, rows * row, hipMemcpyHostToDevice) == hipSuccess ? RNNLM_OK : RNNLM_EDEVICE;
+    const size_t at_once = std::min(rows, kUploadPiece / row);           // (a row is at most 256 KB)
     void *stage = nullptr;
-    HIP_TRY(hipMalloc(&stage, bytes));
-    HIP_TRY(hipMemcpy(stage, src, bytes, hipMemcpyHostToDevice));
-    HIP_TRY(launch_pad_rows(stage, dst, dtype, rows, H, Hp, nullptr));
-    HIP_TRY(hipStreamSynchronize(nullptr));
+    HIP_TRY(hipMalloc(&stage, at_once * row));
+    for (size_t r = 0; r < rows; r += at_once) {
+        const size_t n = std::min(at_once, rows - r);
+        HIP_TRY(hipMemcpy(stage, static_cast<const char *>(src) + r * row, n * row, hipMemcpyHostToDevice));
+        HIP_TRY(launch_pad_rows(stage, static_cast<char *>(dst) + r * Hp * es, dtype, n, H, Hp, nullptr));
+        HIP_TRY(hipStreamSynchronize(nullptr));                          // the next piece goes to the same place
+    }
 fail:
     (void)hipFree(stage);
     return status;
