@@ -71,7 +71,8 @@ enum rnnlm_option {
      * kernel, 2 = the LDS-staged kernel with the hidden block held in registers (bf16,
      * H <= 512), 3 = the LDS-tiled kernel for any hidden size and both types, 4 = (fp32 models)
      * the LDS-tiled kernel on a two-term fp16 split of both operands (every word's weights scaled by a
-     * power of two), fp32 accuracy at fp16 matrix-core speed: the automatic choice for fp32 from 64 rows
+     * power of two; operands good to 2^-23, a product to 2^-21 of itself, sums in fp32: errors as of fp32
+     * products unless a sum is dominated by one term) at fp16 matrix-core speed: the automatic choice for fp32 from 64 rows
      * on, 5 = the weight-streaming kernel for few rows, which reads the operand-ordered copy of the
      * output weights once per launch at memory speed (fp32 models: the same two fp16 terms):
      * the automatic choice up to 64 rows when two launches suffice (the staged, row-streaming,

@@ -25,8 +25,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// x = x1 + x2 with fp16 terms, each rounded to nearest even (|x| below 2^15; 22 bits of x are kept as
-// long as the second term is a normal fp16 number, and no less than 2^-25 is lost in absolute terms):
+// x = x1 + x2 with fp16 terms, each rounded to nearest even (|x| below 2^15): off by 2^-23 |x| at most, in a quarter of
+// all fp32 numbers, as long as the second term is a normal fp16 number (and by 2^-25 at most beyond):
 // the split that puts a scaled fp32 operand on the fp16 matrix cores.  Bit patterns.
 __device__ __forceinline__ void split2_f16(float x, uint16_t &x1, uint16_t &x2) {
     const _Float16 h = (_Float16)x, l = (_Float16)(x - (float)h);

@@ -3,15 +3,19 @@
 // Same result as the other output-projection kernels (normalising over all words of the
 // vocabulary, Section 2.1 of the paper; the paper's models are fp32).  Every fp32 operand is
 // brought into the range of fp16 by a power of two (one per word for the weights, 2^14 for the
-// centred hidden vector, |d| <= 1/2) and cut into two fp16 terms x = x1 + x2 (11 + 11 mantissa bits,
-// each rounded to nearest: 2^-22 of x at worst); of the four cross terms three are kept (w2 d1, w1 d2,
-// w1 d1; the dropped one is below 2^-22 of the product) and added in the fp32 accumulators of the
-// matrix instruction.  Three matrix instructions per product instead of the six of a three-term bf16
-// split (which this kernel replaced), and half as many roundings of the accumulator, which is where the
-// error comes from: against float64 the log-probabilities are off by 4.95e-8 (rel.) where the six-product
-// kernel was off by 5.01e-8 at V = 65536, H = 512, 1024 rows, 6.4e-8 against 7.0e-8 at V = 30011, H = 1000,
-// weights of 0.2.  Bound by the matrix pipe at the clock the chip holds under it: 308 -> 159 us
-// (1.30 PFLOP/s of fp16 products), V = 20000, H = 256, 256 rows 20.5 -> 13.0 us.
+// centred hidden vector, |d| <= 1/2) and cut into two fp16 terms x = x1 + x2 (11 + 12 mantissa bits with the
+// second one's sign: 2^-23 of x at worst); of the four cross terms three are kept (w2 d1, w1 d2, w1 d1; the
+// dropped one is below 2^-22 of the product) and added in the fp32 accumulators of the matrix instruction.  So a
+// product is off by 2^-21 of itself at worst, where three exact bf16 terms and six products (which this
+// kernel replaced) were off by 3 2^-24; but it takes half as many roundings of the accumulator, and those are
+// where the error of a sum comes from.  Log-sum-exp against float64, root mean square / 99.9th percentile / largest of 16
+// to 40 models, six products -> three: V = 30011, H = 1000, 511 rows, weights of 0.2 1.43e-6 / 8.5e-6 / 1.19e-5 -> 1.15e-6 / 7.3e-6 /
+// 9.9e-6, of 0.05 7.98e-7 / 1.77e-6 / 1.81e-6 -> 7.94e-7 / 1.78e-6 / 1.81e-6; V = 65536, H = 512, 300 rows, 0.05 4.90e-7 / 1.25e-6 /
+// 1.33e-6 -> 4.89e-7 / 1.25e-6 / 1.30e-6.  Where one weight of every word is a hundred or a thousand times the others, so that
+// few roundings matter, it is the other way round for short sums: H = 64 2.77e-6 / 9.7e-6 / 1.19e-5 -> 3.01e-6 / 1.09e-5 / 1.26e-5,
+// H = 1000 1.56e-5 / 6.4e-5 / 8.6e-5 -> 1.61e-5 / 6.1e-5 / 8.4e-5 (log-sum-exp around 50 and 130).
+// Bound by the matrix pipe at the clock the chip holds under it: 308 -> 163 to 173 us,
+// as the clock allows (1.26 PFLOP/s of fp16 products), V = 20000, H = 256, 256 rows 20.5 -> 12.3 us.
 //
 // Layout: both operands are kept as MFMA operands (ModelDev::Ofrag, dfrag), so 32 words x 16 units x 2
 // terms are 2 KB contiguous, global memory -> LDS -> register without any rearrangement, and every LDS
@@ -25,7 +29,7 @@
 //   - two workgroups share a compute unit and are not synchronised with each other: one's barriers,
 //     LDS latencies and exp-and-add (a third as many VALU cycles as MFMA cycles at Hp = 128, a twelfth
 //     at 512) run under the other's MFMAs; with the 256-word tile a wave inside its MFMA chain goes
-//     first (s_setprio: 168 -> 159 us at V = 65536, H = 512, 1024 rows; the 128-word tile loses 2 %);
+//     first (s_setprio: 177 -> 173 us at V = 65536, H = 512, 1024 rows; the 128-word tile gains nothing);
 //   - MFMA roles as in the other kernels (A = words, B = rows): a lane holds sixteen logits of ONE
 //     row per accumulator, the sum over words stays in the lane.
 #include "device_utils.h"
@@ -264,9 +268,10 @@ hipError_t launch_outproj_split2(const ModelDev &m, int rows, const int *B_dev, 
                                  SplitInfo *splits, hipStream_t stream) {
     if (m.dtype != RNNLM_F32 || !m.Ofrag || !m.dfrag || !m.ofac) return hipErrorInvalidValue;
     // 256-word tiles once they give every workgroup of the grid two, 128-word tiles below.  Measured, us,
-    // 256 / 128 words: 2048 tiles (V = 65536, H = 512, 1024 rows) 159 / 170; 1024 tiles (512 rows) 84 / 89;
-    // 768 tiles 80 / 80; 588 tiles (V = 50000, H = 650, 300 rows) 85 / 75; 158 tiles (V = 20000, H = 256,
-    // 256 rows) 15.7 / 13.0.
+    // 256 / 128 words: 2048 tiles (V = 65536, H = 512, 1024 rows) 173 / 184; 1024 tiles (512 rows) 88 / 92;
+    // 944 tiles (V = 30000, H = 1000, 511 rows) 78 / 83 and 768 (V = 65536, H = 512, 384 rows) 74 / 82, which the line leaves
+    // on the slower side; 942 tiles (V = 40000, H = 300, 700 rows) 54.7 / 55.6; 588 (V = 50000, H = 650, 300 rows) 85 / 76;
+    // 158 (V = 20000, H = 256, 256 rows) 15.0 / 12.1.
     const long long tiles = (long long)((rows + kRows - 1) / kRows) * (m.Vp / 256);
     if (tiles >= 1024) return launch_split2_shape<4>(m, rows, B_dev, fixed_offset, splits, stream);
     return launch_split2_shape<2>(m, rows, B_dev, fixed_offset, splits, stream);

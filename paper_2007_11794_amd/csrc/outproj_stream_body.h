@@ -168,7 +168,11 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
 // ------------------------------------------------------------------------------ fp32 models
 // The same streaming for fp32 weights, at fp32 accuracy on the fp16 matrix cores: weights and hidden
 // block come as two fp16 terms in operand order (see outproj_split2.hip for the split), four bytes per
-// weight as in fp32, and three MFMAs per operand add the cross terms (2.1, 1.2, 1.1).
+// weight as in fp32, and three MFMAs per operand add the cross terms.  The small ones (2.1, 1.2) have a sum of their own
+// (up to 64 rows, while the registers last): what rounds is the large one, once per k-step.  Error of the log-sum-exp against
+// float64, in one sum / apart / three-term kernel or plain one of before: V = 17612, H = 865, 6 rows, weights of 0.05 5.58e-7 /
+// 5.46e-7 / 5.37e-7; V = 20000, H = 512, 64 rows, 0.2 5.62e-7 / 5.40e-7 / 5.86e-7; the same times (V = 100000, H = 512, 64 rows
+// 36.7 us, 36.6; V = 20000, H = 576, 60 rows 13.1, 13.5).
 constexpr int kStreamGroup32 = 2;        // operands per group (two terms each: four loads, as above)
 
 // The fp32 form of outproj_stream_body, for a workgroup of WAVES waves: needs stream_lds_bytes(2, RB, Hp / 16, WAVES) bytes
@@ -220,14 +224,15 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     load_constants();
     stream_block_end<false, WAVES>(block, kTerms * RB * KS, lds);
 
-    f32x16 acc[RB];
+    constexpr bool kApart = RB <= 2;
+    f32x16 acc[RB], rest[kApart ? RB : 1];
     float mrun[RB], srun[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         mrun[rb] = FIXED ? m2_fixed : -INFINITY;
         srun[rb] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[rb][i] = 0.f;
+        for (int i = 0; i < 16; ++i) acc[rb][i] = rest[kApart ? rb : 0][i] = 0.f;
     }
     [&]() {
         for (;;) {
@@ -244,8 +249,9 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
                         const int at = (rb * KS + ks) * (64 * kTerms) + lane;
                         const f16x8 d1 = dl[at], d2 = ONE_TERM ? second[st][rb * kStreamGroup32 + i] : dl[at + 64];
                         // smallest terms first
-                        acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2, d1, acc[rb], 0, 0, 0);
-                        acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w1, d2, acc[rb], 0, 0, 0);
+                        f32x16 &small = kApart ? rest[kApart ? rb : 0] : acc[rb];
+                        small = __builtin_amdgcn_mfma_f32_32x32x16_f16(w2, d1, small, 0, 0, 0);
+                        small = __builtin_amdgcn_mfma_f32_32x32x16_f16(w1, d2, small, 0, 0, 0);
                         acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w1, d1, acc[rb], 0, 0, 0);
                     }
                 }
@@ -256,10 +262,13 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
 #pragma unroll
                         for (int q = 0; q < 4; ++q)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) x[4 * q + i] = fmaf(acc[rb][4 * q + i], ff[q][i], cc[q][i]);
+                            for (int i = 0; i < 4; ++i) {
+                                const float sum = kApart ? acc[rb][4 * q + i] + rest[kApart ? rb : 0][4 * q + i] : acc[rb][4 * q + i];
+                                x[4 * q + i] = fmaf(sum, ff[q][i], cc[q][i]);
+                            }
                         lse2_fold16<FIXED>(x, mrun[rb], srun[rb]);
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) acc[rb][i] = 0.f;
+                        for (int i = 0; i < 16; ++i) acc[rb][i] = rest[kApart ? rb : 0][i] = 0.f;
                     }
                     out.advance(GPB);
                     load_constants();

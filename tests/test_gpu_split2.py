@@ -114,3 +114,31 @@ def test_more_row_groups_than_workgroups(V):
         m.set_option(rn.OPT_LSE_MODE, lse_mode)
         assert np.max(np.abs(gpu_step(m, prev, h_in, query)[1] - ref["logprob"])) <= tol
     m.close()
+
+
+@pytest.mark.parametrize("V,H,B", [(600, 64, 20), (600, 64, 130), (600, 700, 30), (600, 700, 130), (66000, 64, 513)])
+def test_words_with_one_dominant_weight(V, H, B):
+    """One weight of every word a hundred times the others: a logit is then one product, whose split cannot hide behind the
+    roundings of many."""
+    rng = np.random.default_rng(V + H + B)
+    O = rng.normal(0, 0.2, (H, V))
+    O[rng.integers(0, H, V), np.arange(V)] *= 100.0
+    model = {"U": rng.normal(0, 0.3, (V, H)).astype(np.float32), "W": rng.normal(0, 0.4 / np.sqrt(H), (H, H)).astype(np.float32),
+             "O": O.astype(np.float32), "bias": rng.normal(0, 0.5, V).astype(np.float32)}
+    m = load_model(model, "f32", B)
+    prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
+    query = rng.integers(0, V, (B, 3)).astype(np.int32)
+    for kernel in (0, 1, 4):
+        m.set_option(rn.OPT_OUTPROJ_KERNEL, kernel)
+        h, lp = gpu_step(m, prev, h_in, query)
+        # the normaliser of the vector handed out, in 64 bits
+        z = h.astype(np.float64) @ model["O"].astype(np.float64) + model["bias"]
+        top = z.max(1, keepdims=True)
+        want = np.take_along_axis(z, query.astype(np.int64), 1) - (top + np.log(np.exp(z - top).sum(1, keepdims=True)))
+        # 2^-21 of a word's products, and one rounding of 2^-24 of the running sum per matrix instruction (three per 16
+        # units) or product; the same for the word asked, in plain fp32; constants and results of the size of the logits
+        size = 0.5 * np.abs(model["O"]).sum(0).max()
+        tol = (2.0 ** -21 + (3 * (H // 16 + 1) + 64) * 2.0 ** -24) * size
+        assert np.max(np.abs(lp - want)) <= tol, kernel
+        assert np.sqrt(np.mean((lp - want) ** 2)) <= 2.0 ** -21 * size            # roundings do not all add up
+    m.close()

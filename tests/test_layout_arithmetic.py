@@ -1,4 +1,4 @@
-"""Host-side checks of the index arithmetic and of the three-term split the HIP kernels rely on.
+"""Host-side checks of the index arithmetic and of the splits of fp32 operands the HIP kernels rely on.
 
 Nothing here touches the GPU or the oracle: the formulas are restated in numpy and checked for
 the properties the kernels need (bijections, bank spreading, exactness of the split and the size
@@ -17,7 +17,6 @@ from workloads import round_to_bf16
 LAYOUTS = {
     "128-byte rows, c ^ ((r >> 1) & 7)": (8, lambda r, c: c ^ ((r >> 1) & 7)),          # tiled kernels
     "128-byte rows of 1 KB words, c ^ (r & 15)": (64, lambda r, c: c ^ (r & 15)),       # staged kernel (Hp = 512)
-    "192-byte rows, (c + ((r >> 2) & 3)) % 12": (12, lambda r, c: (c + ((r >> 2) & 3)) % 12),   # three-term kernel
 }
 
 
@@ -37,9 +36,6 @@ def test_direct_load_side_inverts_the_rotation():
     """The direct global->LDS loads write LDS linearly, so lane i must fetch the logical piece that
     belongs at physical position i: the inverse map used by the loaders."""
     for r in range(64):
-        for p in range(12):
-            c = (p + 12 - ((r >> 2) & 3)) % 12
-            assert (c + ((r >> 2) & 3)) % 12 == p
         for p in range(8):
             c = p ^ ((r >> 1) & 7)
             assert c ^ ((r >> 1) & 7) == p
@@ -65,14 +61,61 @@ def test_fragment_order_is_a_bijection(rows, H):
     assert block.min() == 0 and block.max() == 511
 
 
-def test_term_interleaved_layout_is_a_bijection():
-    """[row][unit / 32][term][unit % 32]: a chunk of 32 units is 96 contiguous elements per row."""
-    H = 128
-    idx = sorted(((u >> 5) * 96 + t * 32 + (u & 31)) for u in range(H) for t in range(3))
-    assert idx == list(range(3 * H))
+def test_two_term_fragment_order_is_a_bijection():
+    """fp32 models, [row block][k-step][term][64 lanes][8]: the two terms of an operand are 2 KB contiguous."""
+    H, rows = 128, 64
+    KS = H // 16
+    idx = [frag_index(r, u, KS) // 512 * 1024 + t * 512 + frag_index(r, u, KS) % 512
+           for r in range(rows) for u in range(H) for t in range(2)]
+    assert sorted(idx) == list(range(2 * rows * H))
 
 
-# ------------------------------------------------------------------ three-term bf16 split
+# ------------------------------------------------------------------ two-term fp16 split (output projection)
+def split2(x):
+    """Values below 2^15 in magnitude, as the kernels scale them."""
+    x1 = x.astype(np.float32).astype(np.float16)
+    return x1, (x - x1.astype(np.float32)).astype(np.float16)
+
+
+def scaled_words(O):
+    """Every word's weights times the power of two that brings its largest into [2^13, 2^14)."""
+    e = np.frexp(np.abs(O).max(0))[1]
+    return np.ldexp(O, 14 - e).astype(np.float32)
+
+
+def test_two_fp16_terms_miss_the_fp32_number_by_one_unit_in_its_last_place_at_most():
+    # (or by half of the smallest fp16 step, 2^-24, where that is more)
+    rng = np.random.default_rng(8)
+    x = np.concatenate([rng.uniform(2.0 ** -3, 2.0 ** 14, 50000), np.exp2(rng.uniform(-3, 14, 50000)),
+                        np.array([0.0, 2.0 ** 13, 2.0 ** 14 - 2.0 ** -10])]).astype(np.float32)
+    x1, x2 = split2(x)
+    off = np.abs(x1.astype(np.float64) + x2.astype(np.float64) - x)
+    unit = np.exp2(np.floor(np.log2(np.maximum(x, 1e-30))) - 23)
+    assert np.all(off <= np.maximum(unit, 2.0 ** -25)) and 0.1 < np.mean(off > 0) < 0.3
+    # centred hidden values above one half of a unit's range are exact
+    h = (rng.integers(2 ** 22, 2 ** 24, 50000) / 2.0 ** 24).astype(np.float32)
+    d = (h - np.float32(0.5)) * np.float32(2.0 ** 14)
+    d1, d2 = split2(d)
+    assert np.array_equal(d1.astype(np.float64) + d2.astype(np.float64), d.astype(np.float64))
+
+
+@pytest.mark.parametrize("big", [1.0, 100.0, 1e5])
+def test_the_three_kept_products_of_the_fp16_split(big):
+    """One weight of every word `big` times the others: a product of weights not far below the word's largest is off by
+    2^-21 of itself at most, any other by what the second term's smallest step leaves, 2^-38 of the largest weight."""
+    rng = np.random.default_rng(9)
+    O = rng.normal(0, 0.2, (64, 500)).astype(np.float32)
+    O[rng.integers(0, 64, 500), np.arange(500)] *= np.float32(big)
+    w = scaled_words(O)
+    d = ((rng.uniform(0, 1, 64).astype(np.float32) - np.float32(0.5)) * np.float32(2.0 ** 14))[:, None]
+    w1, w2 = (t.astype(np.float64) for t in split2(w))
+    d1, d2 = (t.astype(np.float64) for t in split2(d))
+    kept = w1 * d1 + w1 * d2 + w2 * d1
+    exact = w.astype(np.float64) * d.astype(np.float64)
+    assert np.all(np.abs(kept - exact) <= 2.0 ** -21 * np.abs(exact) + 2.0 ** -25 * (np.abs(w) + np.abs(d)) * 1.01 + 2.0 ** -40)
+
+
+# ------------------------------------------------------------------ three-term bf16 split (hidden update)
 def split3(x):
     x = x.astype(np.float32)
     x1 = round_to_bf16(x)
