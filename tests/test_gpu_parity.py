@@ -115,7 +115,7 @@ def test_f32_reduced_elementwise_both_lse_modes(V, H, B, K):
     x = make_step_inputs(cfg, np.random.default_rng(cfg.seed + V))
     m = load_model(model, "f32", B)
     ref = oracle.step(model, x["prev"], x["h_in"], x["query"])
-    # plain FMA, LDS-tiled fp32-MFMA, bf16 three-term split, weight streaming (where it applies), automatic
+    # plain FMA, LDS-tiled fp32-MFMA, fp16 two-term split, weight streaming (where it applies), automatic
     for kernel in (1, 3, 4, 5, 0):
         m.set_option(rn.OPT_OUTPROJ_KERNEL, kernel)
         for lse_mode in (1, 2):
@@ -211,10 +211,10 @@ def test_many_raw_queries_few_distinct_histories(V, H, N, distinct):
 @pytest.mark.parametrize("V,H,N,distinct", [(20000, 256, 300, 20),     # fewer splits than workgroups
                                             (40000, 256, 400, 50),     # two row blocks
                                             (5000, 512, 260, 30),      # one row block is all that fits
-                                            (5000, 512, 260, 40),      # does not fit: three-term kernel, one row group
+                                            (5000, 512, 260, 40),      # does not fit: two-term kernel, one row group
                                             (3000, 256, 500, 150)])
 def test_many_raw_queries_few_distinct_histories_fp32(V, H, N, distinct):
-    """The same for fp32 models (the paper's precision): the three-term kernel derives its work split
+    """The same for fp32 models (the paper's precision): the two-term kernel derives its work split
     from the true count and streams the fp32 weights when at most 64 rows are left."""
     cfg = CONFIGS[2].scaled(V=V, H=H, B=N, K=5)
     model = make_model(cfg)
@@ -238,7 +238,7 @@ def test_many_raw_queries_few_distinct_histories_fp32(V, H, N, distinct):
 
 @pytest.mark.parametrize("dtype,V,H,B,K", [("bf16", 1500, 640, 5000, 2),     # tiled kernel: more row groups than workgroups per XCD
                                            ("bf16", 3000, 256, 9000, 2),     # staged kernel, 36 row groups
-                                           ("f32", 1200, 128, 6000, 2)])     # three-term kernel, 24 row groups
+                                           ("f32", 1200, 128, 6000, 2)])     # two-term kernel, 24 row groups
 def test_more_row_groups_than_workgroups(dtype, V, H, B, K):
     """Large batches on a small vocabulary: a workgroup takes several (row group, split) items in turn."""
     cfg = CONFIGS[3 if dtype == "bf16" else 2].scaled(V=V, H=H, B=B, K=K)
@@ -491,7 +491,7 @@ def test_running_maximum_fallback_when_logits_are_huge():
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_million_word_vocabulary(dtype):
     """V = 1,000,003 (Section 5.1's in-house vocabulary is about a million words; odd on purpose:
-    ragged last tile), H = 128, full softmax: 130 rows (bf16: staged kernel; fp32: three-term
+    ragged last tile), H = 128, full softmax: 130 rows (bf16: staged kernel; fp32: two-term
     kernel) and the first 20 of them alone (weight-streaming kernels)."""
     rng = np.random.default_rng(99)
     V, H, B, K = 1000003, 128, 130, 6

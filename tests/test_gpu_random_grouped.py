@@ -1,6 +1,6 @@
 """Seeded random grouped steps against the oracle: shapes drawn so that they cross the choices the
 library makes from the true number of distinct histories, which only the device knows (weight
-streaming inside the staged, tiled and three-term kernels at <= 64 rows, the two shapes of the hidden
+streaming inside the staged, tiled and two-term kernels at <= 64 rows, the two shapes of the hidden
 update, the work split of the output projection), in both number types and all three
 log-sum-exp modes."""
 import numpy as np
