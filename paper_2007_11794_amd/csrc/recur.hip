@@ -27,6 +27,7 @@
 //   large  128 units x 64 rows, a wave owns 64 x 32 of them over half of the reduction: h_in is converted
 //          once for two blocks of units, and reading, converting and multiplying overlap between the waves
 //          (with 32 x 32 per wave over the whole reduction H = 1024, 3000 rows took 43 us instead of 30).
+// Models of few units have a third, in kernels of its own (recur_few_units_f32_kernel, recur_few_units_bf16_kernel).
 // Launches of bf16 models that fit one small workgroup per compute unit use a whole unit's LDS as the ring (128 KB, all
 // but one stage in flight), larger ones half of it, two workgroups per unit; fp32 models always the whole one.
 // Measured, us per launch (rows in brackets), before and after, the kernels before being one tiled and one
@@ -52,6 +53,7 @@ __device__ __forceinline__ float sigmoid_f32(float a) {
 
 constexpr int kThreads = 512, kWaves = kThreads / 64;
 constexpr int kGroups = 256;                          // workgroups in one round: one per compute unit
+constexpr int kFewUnits = 256, kFewUnitsBf16 = 128;   // largest (only) Hp of recur_few_units_f32 (_bf16) _kernel
 
 // MFMA 32x32x16 operand layout (lane l, g = l / 32):
 //   A: 8 consecutive k of row (l % 32), starting at 8 g;   B: same for column (l % 32);
@@ -356,6 +358,132 @@ __device__ __forceinline__ void recur_body(const ModelDev &m, int B, int b0, int
     }
 }
 
+// Few units, fp32 models first: 32 units x 32 rows per workgroup of four waves, a quarter of the reduction each, every operand
+// straight into registers in one go (no ring, no split into terms) and products on the fp32 matrix instruction.  While its
+// workgroups fit the compute units in one round the chain of loads is all there is to it, and the shorter one wins.  Us per
+// launch, the ring above / this: H = 64, 73 rows 4.1 / 3.6, 3000 4.7 / 3.9; H = 99, 172 rows 5.9 / 4.7; H = 204, 674 rows 6.9 / 5.6; H = 256,
+// 1000 rows (one round) 7.2 / 6.5, 1500 7.4 / 8.7, 3000 13.7 / 12.5; H = 128, 2048 rows (one round) 5.6 / 4.8, 3000 5.7 / 5.9.
+// MFMA 32x32x2 operand layout: lane l holds k = l / 32 of row (column) l % 32; here a lane takes four consecutive k, and
+// instruction e of a group multiplies the k pair {k0 + e, k0 + 4 + e}.
+// bf16 models the same with the products of the ring form, where rows are not 16-byte aligned and Hp = 128: steps of 172 rows at
+// H = 69 with the hierarchical layer 10.1 / 9.8, 20 rows 9.3 / 8.9, 600 rows at H = 117 10.5 / 10.4 (H = 226, 60 rows 10.8 / 11.4).
+template <typename WT, bool VEC>
+struct FewUnits {
+    f32x4 (*red)[4][64];                               // LDS: [source wave][result][lane]
+    int wave, lane, col, g, j0, b, src, je;
+    bool row_ok, w_ok;
+    f32x4 rs, u;
+
+    __device__ __forceinline__ FewUnits(const ModelDev &m, int B, f32x4 (*lds)[4][64], const int32_t *row_src) : red(lds) {
+        wave = threadIdx.x >> 6; lane = threadIdx.x & 63; col = lane & 31; g = lane >> 5;
+        j0 = blockIdx.x * 32;
+        b = blockIdx.y * 32 + col;
+        row_ok = b < B;
+        const int last = min(b, B - 1);                // rows beyond B repeat the last one; dropped later
+        src = row_src ? row_src[last] : last;
+        je = j0 + 8 * wave + 4 * g;                    // the four units this lane finishes
+        rs = load4(m.half_rowsum_W + je);
+    }
+    // the embedding row hangs on the previous word: requested behind the operands
+    __device__ __forceinline__ void word(const ModelDev &m, int w) {
+        w_ok = w >= 0 && w < m.V;
+        u = load4(static_cast<const WT *>(m.U) + (size_t)(w_ok ? w : 0) * m.Hp + je);
+    }
+    __device__ __forceinline__ void finish(const ModelDev &m, const f32x16 &acc, const int32_t *row_dst, float *h_out) const {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave][q][lane] = f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        __syncthreads();
+        if (!row_ok) return;
+        if (!w_ok && g == 0 && wave == 0 && blockIdx.x == 0) atomicOr(m.flag, RNNLM_FLAG_BAD_PREV_WORD);
+        f32x4 sum = red[0][wave][lane];
+#pragma unroll
+        for (int other = 1; other < 4; ++other) {      // fixed order: deterministic
+            const f32x4 t = red[other][wave][lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[i] += t[i];
+        }
+        const Finish f = {h_out + (size_t)(row_dst ? row_dst[b] : b) * m.H, b, m.H, m.Hp, w_ok};
+        finish4<WT, VEC>(m, f, je, sum, rs, u);
+    }
+};
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void recur_few_units_f32_kernel(
+    ModelDev m, int rows, const int *__restrict__ B_dev, const int32_t *__restrict__ row_src,
+    const int32_t *__restrict__ row_dst, const int32_t *__restrict__ prev_word, const float *__restrict__ h_in,
+    float *__restrict__ h_out) {
+    const int B = B_dev ? *B_dev : rows;
+    if ((int)blockIdx.y * 32 >= B) return;             // uniform
+    __shared__ f32x4 red[4][4][64];
+    FewUnits<float, VEC> t(m, B, red, row_src);
+    const int H = m.H, Hp = m.Hp;
+    const float *hrow = h_in + (size_t)t.src * H, *wrow = static_cast<const float *>(m.W) + (size_t)(t.j0 + t.col) * Hp;
+    const int w = prev_word[t.src];
+    const int kq = Hp / 4, k_begin = t.wave * kq + 4 * t.g;
+    f32x4 wf[kFewUnits / 32], hf[kFewUnits / 32];
+#pragma unroll
+    for (int u = 0; u < kFewUnits / 32; ++u) {
+        const int k0 = k_begin + 8 * u;
+        if (8 * u < kq) {
+            wf[u] = load4(wrow + k0);
+            if (VEC) {                                 // past the end of the row the weights are zero
+                hf[u] = k0 + 4 <= H ? load4(hrow + k0) : f32x4{0.5f, 0.5f, 0.5f, 0.5f};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) hf[u][i] = k0 + i < H ? hrow[k0 + i] : 0.5f;
+            }
+        }
+    }
+    t.word(m, w);
+    f32x16 acc = {};
+#pragma unroll
+    for (int u = 0; u < kFewUnits / 32; ++u) {
+        if (8 * u < kq) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][e], hf[u][e] - 0.5f, acc, 0, 0, 0);
+        }
+    }
+    t.finish(m, acc, row_dst, h_out);
+}
+
+__global__ __launch_bounds__(256) void recur_few_units_bf16_kernel(
+    ModelDev m, int rows, const int *__restrict__ B_dev, const int32_t *__restrict__ row_src,
+    const int32_t *__restrict__ row_dst, const int32_t *__restrict__ prev_word, const float *__restrict__ h_in,
+    float *__restrict__ h_out) {
+    const int B = B_dev ? *B_dev : rows;
+    if ((int)blockIdx.y * 32 >= B) return;             // uniform
+    __shared__ f32x4 red[4][4][64];
+    FewUnits<bf16_t, false> t(m, B, red, row_src);
+    const int H = m.H;
+    const float *hrow = h_in + (size_t)t.src * H;
+    const bf16_t *wrow = static_cast<const bf16_t *>(m.W) + (size_t)(t.j0 + t.col) * kFewUnitsBf16;
+    const int w = prev_word[t.src];
+    constexpr int kSteps = kFewUnitsBf16 / 64;         // of 16 units each, this wave's
+    const int k_begin = t.wave * (16 * kSteps) + 8 * t.g;
+    u32x4 wf[kSteps];
+    float x[kSteps][8];
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        const int k0 = k_begin + 16 * u;
+        wf[u] = *reinterpret_cast<const u32x4 *>(wrow + k0);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {                  // past the end of the row the weights are zero
+            const float h = hrow[min(k0 + i, H - 1)];
+            x[u][i] = k0 + i < H ? h - 0.5f : 0.f;
+        }
+    }
+    t.word(m, w);
+    f32x16 acc = {};
+#pragma unroll
+    for (int u = 0; u < kSteps; ++u) {
+        u32x4 d[2];
+        bf16_terms(x[u], d);
+        acc = mma(wf[u], d[0], acc);
+        acc = mma(wf[u], d[1], acc);
+    }
+    t.finish(m, acc, row_dst, h_out);
+}
+
 // Row counts up to here take the small shape: at most `per_unit` of its workgroups for every compute unit of an XCD
 // (row block rb, with all its blocks of units, belongs to XCD rb % 8).  bf16 models: one with the whole ring, two at a time with
 // half of it; fp32 models: two, one after the other.  Us per launch, small / large shape, the limit in brackets: bf16
@@ -529,6 +657,17 @@ hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int
     if (rows <= 0) return hipSuccess;
     const bool vec = m.H % 4 == 0 && (reinterpret_cast<uintptr_t>(h_in) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(h_out) & 15) == 0;
+    const dim3 grid(m.Hp / 32, (rows + 31) / 32), block(256);
+    const bool few_units = m.dtype == RNNLM_F32 ? m.Hp <= kFewUnits : m.Hp == kFewUnitsBf16 && !vec;
+    if (!ids.key && few_units && grid.x * grid.y <= (unsigned)kGroups) {
+        auto few = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, stream, m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out);
+        };
+        if (m.dtype == RNNLM_BF16) few(recur_few_units_bf16_kernel);
+        else if (vec) few(recur_few_units_f32_kernel<true>);
+        else few(recur_few_units_f32_kernel<false>);
+        return hipGetLastError();
+    }
     return vec ? launch_type<true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream)
                : launch_type<false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
 }
