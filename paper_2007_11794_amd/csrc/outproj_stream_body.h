@@ -26,31 +26,37 @@ typedef StreamCursorOf<kStreamWaves> StreamCursor;
 // kilobytes per wave go straight to LDS, all of it on its way at once, requested before the weights (stream_block_begin)
 // and awaited after the first of them have been requested (stream_block_end): 64 rows at H = 512 16.4 -> 14.5 us per
 // launch, V = 200000, H = 1024, 32 rows 73 -> 70, fp32 V = 100000, H = 512, 64 rows 40.6 -> 36.9.  Smaller blocks are
-// copied through registers: bf16 in front of the weights (V = 20000, H = 64, 4 rows 3.8 us, behind them 4.2), fp32
-// behind them.
+// requested into registers in the same place and written to LDS behind the first weights' requests (V = 20000, H = 128, 20
+// rows: bf16 4.0 us, copied in front of the weights 4.1, fp32, copied behind them, 5.2 -> 4.9; a step at V = 1000000, H = 128, 64
+// rows 51.6 -> 50.8).
 // At the wait at least 16 younger loads of the wave are outstanding (four groups of the ring, which the memory
 // clobbers keep between request and wait); operations complete in order, so the block has landed once no more than 12 are.
 constexpr int kStreamCopyPieces = 2;                // per wave
 
-template <int WAVES>
-__device__ __forceinline__ void stream_block_copy(const char *src, int pieces, char *lds) {
-    const u32x4 *from = reinterpret_cast<const u32x4 *>(src);
-    u32x4 *to = reinterpret_cast<u32x4 *>(lds);
-    for (int i = threadIdx.x; i < pieces * 64; i += 64 * WAVES) to[i] = from[i];
-}
+// What a lane holds of a small block between its request and its way into LDS.
+struct StreamPieces {
+    u32x4 at[kStreamCopyPieces];
+};
 // (pieces `stride` bytes apart, if there are more than kStreamCopyPieces per wave)
-template <bool COPY_FIRST, int WAVES = kStreamWaves>
-__device__ __forceinline__ void stream_block_begin(const char *src, int pieces, char *lds, int wave, int lane, int stride = 1024) {
-    if (pieces <= kStreamCopyPieces * WAVES) {                        // uniform
-        if (COPY_FIRST) stream_block_copy<WAVES>(src, pieces, lds);
+template <int WAVES = kStreamWaves>
+__device__ __forceinline__ void stream_block_begin(const char *src, int pieces, char *lds, int wave, int lane, StreamPieces &held, int stride = 1024) {
+    if (pieces <= kStreamCopyPieces * WAVES) {                // uniform
+#pragma unroll
+        for (int k = 0; k < kStreamCopyPieces; ++k)
+            if (wave + k * WAVES < pieces) held.at[k] = *reinterpret_cast<const u32x4 *>(src + (size_t)(wave + k * WAVES) * 1024 + lane * 16);
         return;
     }
     for (int p = wave; p < pieces; p += WAVES) lds_dma_16(src + (size_t)p * stride, lane * 16, lds_address(lds) + p * 1024);
 }
-template <bool COPY_FIRST, int WAVES = kStreamWaves>
-__device__ __forceinline__ void stream_block_end(const char *src, int pieces, char *lds) {
-    if (pieces > kStreamCopyPieces * WAVES) asm volatile("s_waitcnt vmcnt(12) ; hidden block" ::: "memory");
-    else if (!COPY_FIRST) stream_block_copy<WAVES>(src, pieces, lds);
+template <int WAVES = kStreamWaves>
+__device__ __forceinline__ void stream_block_end(int pieces, char *lds, int wave, int lane, const StreamPieces &held) {
+    if (pieces > kStreamCopyPieces * WAVES) {
+        asm volatile("s_waitcnt vmcnt(12) ; hidden block" ::: "memory");
+    } else {
+#pragma unroll
+        for (int k = 0; k < kStreamCopyPieces; ++k)
+            if (wave + k * WAVES < pieces) *reinterpret_cast<u32x4 *>(lds + (wave + k * WAVES) * 1024 + lane * 16) = held.at[k];
+    }
     __syncthreads();                                          // hidden block visible to all waves
 }
 
@@ -75,7 +81,8 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)RB * KS * 1024);    // [kStreamWaves][RB * 32]
 
     const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 1024;
-    stream_block_begin<true>(block, RB * KS, lds, wave, lane);
+    StreamPieces held;
+    stream_block_begin(block, RB * KS, lds, wave, lane, held);
     bf16x8 ring[kStreamRing][kStreamGroup];
     StreamCursor in = {blk0 + wave, 0};
     // Always kStreamGroup loads, so that the number of younger loads behind any operand is the same on
@@ -97,7 +104,7 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
         for (int q = 0; q < 4; ++q) cc[q] = *reinterpret_cast<const f32x4 *>(cvec + blk * 32 + 8 * q + 4 * g);
     };
     load_constants();
-    stream_block_end<true>(block, RB * KS, lds);
+    stream_block_end(RB * KS, lds, wave, lane, held);
 
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
@@ -195,7 +202,8 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)kTerms * RB * KS * 1024);
 
     const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 2048;
-    stream_block_begin<false, WAVES>(block, kTerms * RB * KS, lds, wave, lane, 2048 / kTerms);
+    StreamPieces held;
+    stream_block_begin<WAVES>(block, kTerms * RB * KS, lds, wave, lane, held, 2048 / kTerms);
     f16x8 ring[kStreamRing][2 * kStreamGroup32], second[kStreamRing][ONE_TERM ? RB * kStreamGroup32 : 1];
     StreamCursorOf<WAVES> in = {blk0 + wave, 0};
     auto issue = [&](int slot) __attribute__((always_inline)) {                  // always as many loads (see above)
@@ -222,7 +230,7 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
         }
     };
     load_constants();
-    stream_block_end<false, WAVES>(block, kTerms * RB * KS, lds);
+    stream_block_end<WAVES>(kTerms * RB * KS, lds, wave, lane, held);
 
     constexpr bool kApart = RB <= 2;
     f32x16 acc[RB], rest[kApart ? RB : 1];
