@@ -112,11 +112,19 @@ typedef HsShape<128, 9, 256, 64> HsSmall;
 // The same with twice the threads, while the queries leave compute units idle or half empty: a query's chain of
 // dependent loads gets shorter (fewer rounds of node rows), the number of chains does not matter then.  Steps at V =
 // 65536, H = 512, bf16, us, half as many threads / these: 40 queries of 25 words 17.6 / 13.9, 512 queries 20.8 / 17.3,
-// 1024 of 32 words 26.1 / 28.9; 512 queries of 6 words 16.6 / 14.2.  Short rows have several in a wave's round
-// already: up to 256 queries (V = 300000, H = 128, 40 queries 12.1 / 11.3; H = 250, fp32, 512 queries 19.8 / 23.5).
+// 640 of 30 words 22.4 / 24.4, 1024 of 32 words 26.1 / 28.9; 512 queries of 6 words 16.6 / 14.2, 640 15.6 / 13.9.  Short rows have
+// several in a wave's round already: up to 256 queries (V = 300000, H = 128, 40 queries 12.1 / 11.3; H = 250, fp32, 512 queries
+// 19.8 / 23.5), and with the large shape only once the words' nodes are more than one round of half as many threads: kernel at V =
+// 250000, H = 128, bf16, 100 queries of 17 words 0.3 slower, 24 words 0.3 faster, 32 words 1.3 faster; rows that are not 16-byte
+// aligned, which every wave reads for itself, H = 75, 17, 24 and 32 words 1.0, 0.3 and 0.5 slower; V = 60000, H = 256, 17 words 1.0
+// faster, H = 250 0.3 slower, 24 words 0.3 faster.
 typedef HsShape<512, 11, 1024, 256> HsLargeWide;
 typedef HsShape<256, 9, 256, 64> HsSmallWide;
-inline bool hs_wide(int N, int Hp) { return N <= (Hp == 128 || Hp == 256 ? 256 : 512); }
+inline bool hs_wide(int N, int K, int H, int Hp, bool small) {
+    if (Hp != 128 && Hp != 256) return N <= 512;
+    const bool aligned = H % 4 == 0;
+    return N <= 256 && (small || (Hp == 128 ? aligned && K >= 24 : K >= (aligned ? 16 : 24)));
+}
 
 // Dot products of the distinct nodes for a short hidden vector (Hp = 8 * LPR elements, LPR = 16 or
 // 32): a node row takes only LPR lanes of a wave, so the wave works on 64 / LPR rows side by side,
@@ -340,7 +348,7 @@ hipError_t launch_hs_query(const ModelDev &m, int rows, const int *B_dev, int N,
             else if (m.Hp == 256) launch(hs_query_shared_kernel<T, 32, S>, S::kThreads);
             else launch(hs_query_shared_kernel<T, 0, S>, S::kThreads);
         };
-        const bool wide = hs_wide(N, m.Hp);
+        const bool wide = hs_wide(N, K, m.H, m.Hp, small);
         auto pick = [&](auto tag) {
             if (small && wide) pick_rows(tag, HsSmallWide{});
             else if (small) pick_rows(tag, HsSmall{});

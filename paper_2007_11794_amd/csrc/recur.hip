@@ -53,7 +53,7 @@ __device__ __forceinline__ float sigmoid_f32(float a) {
 
 constexpr int kThreads = 512, kWaves = kThreads / 64;
 constexpr int kGroups = 256;                          // workgroups in one round: one per compute unit
-constexpr int kFewUnits = 256, kFewUnitsBf16 = 128;   // largest (only) Hp of recur_few_units_f32 (_bf16) _kernel
+constexpr int kFewUnitsBf16 = 128;                    // the only Hp of recur_few_units_bf16_kernel
 
 // MFMA 32x32x16 operand layout (lane l, g = l / 32):
 //   A: 8 consecutive k of row (l % 32), starting at 8 g;   B: same for column (l % 32);
@@ -407,7 +407,8 @@ struct FewUnits {
     }
 };
 
-template <bool VEC>
+// GROUPS of eight k are in flight together; longer reductions go in several passes.
+template <bool VEC, int GROUPS>
 __global__ __launch_bounds__(256) void recur_few_units_f32_kernel(
     ModelDev m, int rows, const int *__restrict__ B_dev, const int32_t *__restrict__ row_src,
     const int32_t *__restrict__ row_dst, const int32_t *__restrict__ prev_word, const float *__restrict__ h_in,
@@ -420,28 +421,38 @@ __global__ __launch_bounds__(256) void recur_few_units_f32_kernel(
     const float *hrow = h_in + (size_t)t.src * H, *wrow = static_cast<const float *>(m.W) + (size_t)(t.j0 + t.col) * Hp;
     const int w = prev_word[t.src];
     const int kq = Hp / 4, k_begin = t.wave * kq + 4 * t.g;
-    f32x4 wf[kFewUnits / 32], hf[kFewUnits / 32];
+    f32x4 wf[GROUPS], hf[GROUPS];
+    f32x16 acc = {};
+    auto request = [&](int k_first) {
 #pragma unroll
-    for (int u = 0; u < kFewUnits / 32; ++u) {
-        const int k0 = k_begin + 8 * u;
-        if (8 * u < kq) {
-            wf[u] = load4(wrow + k0);
-            if (VEC) {                                 // past the end of the row the weights are zero
-                hf[u] = k0 + 4 <= H ? load4(hrow + k0) : f32x4{0.5f, 0.5f, 0.5f, 0.5f};
-            } else {
+        for (int u = 0; u < GROUPS; ++u) {
+            const int k0 = k_begin + k_first + 8 * u;
+            if (k_first + 8 * u < kq) {
+                wf[u] = load4(wrow + k0);
+                if (VEC) {                             // past the end of the row the weights are zero
+                    hf[u] = k0 + 4 <= H ? load4(hrow + k0) : f32x4{0.5f, 0.5f, 0.5f, 0.5f};
+                } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) hf[u][i] = k0 + i < H ? hrow[k0 + i] : 0.5f;
+                    for (int i = 0; i < 4; ++i) hf[u][i] = k0 + i < H ? hrow[k0 + i] : 0.5f;
+                }
             }
         }
-    }
-    t.word(m, w);
-    f32x16 acc = {};
+    };
+    auto multiply = [&](int k_first) {
 #pragma unroll
-    for (int u = 0; u < kFewUnits / 32; ++u) {
-        if (8 * u < kq) {
+        for (int u = 0; u < GROUPS; ++u) {
+            if (k_first + 8 * u < kq) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][e], hf[u][e] - 0.5f, acc, 0, 0, 0);
+                for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wf[u][e], hf[u][e] - 0.5f, acc, 0, 0, 0);
+            }
         }
+    };
+    request(0);
+    t.word(m, w);
+    multiply(0);
+    for (int k = 8 * GROUPS; k < kq; k += 8 * GROUPS) {
+        request(k);
+        multiply(k);
     }
     t.finish(m, acc, row_dst, h_out);
 }
@@ -651,6 +662,17 @@ hipError_t launch_type(const ModelDev &m, int rows, const int *B_dev, const int3
 // launch 0.2 slower at up to 1024 and gained 1.1 to 2.0 at 1100, 0.3 to 1.9 at 1536, nothing at 2048 (-0.8 to +3 when all are distinct).
 bool recur_groups_ids(const ModelDev &m, int N) { return N > 0 && N <= kGroupedMax && m.Hp <= 2048; }
 
+// Steps with the hierarchical layer, V = 5000, fp32, us, ring / short form (the kernel of before the ring in brackets): H = 320, 7 rows
+// 10.7 / 9.7 (9.9), 512 rows 11.7 / 11.0; H = 512, 7 rows 12.6 / 11.5 (11.7), 512 rows 13.6 / 13.4; unaligned rows H = 333, 7 rows 12.3 /
+// 11.4, 30 rows 13.2 / 13.4; H = 1024, 7 rows 20.2 (18.0), 200 rows 22.2 (21.0); H = 832, 7 rows 17.1 (16.1), 64 rows 17.8 (17.8), 200
+// rows 18.5 (20.1).
+static bool few_units(int dtype, int Hp, bool vec, int rows) {
+    if (dtype == RNNLM_BF16) return Hp == kFewUnitsBf16 && !vec;
+    if (Hp <= 256) return true;
+    if (!vec) return rows <= 16 && Hp <= 512;
+    return Hp <= 512 || (Hp <= 1024 && rows <= 64);
+}
+
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,
                         const int32_t *row_dst, const int32_t *prev_word, const float *h_in,
                         float *h_out, const IdGroups &ids, hipStream_t stream) {
@@ -658,14 +680,15 @@ hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int
     const bool vec = m.H % 4 == 0 && (reinterpret_cast<uintptr_t>(h_in) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(h_out) & 15) == 0;
     const dim3 grid(m.Hp / 32, (rows + 31) / 32), block(256);
-    const bool few_units = m.dtype == RNNLM_F32 ? m.Hp <= kFewUnits : m.Hp == kFewUnitsBf16 && !vec;
-    if (!ids.key && few_units && grid.x * grid.y <= (unsigned)kGroups) {
+    if (!ids.key && grid.x * grid.y <= (unsigned)kGroups && few_units(m.dtype, m.Hp, vec, rows)) {
         auto few = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, 0, stream, m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out);
         };
         if (m.dtype == RNNLM_BF16) few(recur_few_units_bf16_kernel);
-        else if (vec) few(recur_few_units_f32_kernel<true>);
-        else few(recur_few_units_f32_kernel<false>);
+        else if (m.Hp <= 256 && vec) few(recur_few_units_f32_kernel<true, 8>);
+        else if (m.Hp <= 256) few(recur_few_units_f32_kernel<false, 8>);
+        else if (vec) few(recur_few_units_f32_kernel<true, 16>);
+        else few(recur_few_units_f32_kernel<false, 16>);
         return hipGetLastError();
     }
     return vec ? launch_type<true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream)
