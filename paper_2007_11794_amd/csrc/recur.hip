@@ -664,13 +664,14 @@ bool recur_groups_ids(const ModelDev &m, int N) { return N > 0 && N <= kGroupedM
 
 // Steps with the hierarchical layer, V = 5000, fp32, us, ring / short form (the kernel of before the ring in brackets): H = 320, 7 rows
 // 10.7 / 9.7 (9.9), 512 rows 11.7 / 11.0; H = 512, 7 rows 12.6 / 11.5 (11.7), 512 rows 13.6 / 13.4; unaligned rows H = 333, 7 rows 12.3 /
-// 11.4, 30 rows 13.2 / 13.4; H = 1024, 7 rows 20.2 (18.0), 200 rows 22.2 (21.0); H = 832, 7 rows 17.1 (16.1), 64 rows 17.8 (17.8), 200
-// rows 18.5 (20.1).
+// 11.4, 30 rows 13.2 / 13.4, H = 1022, 7 rows 23.6 / 22.2, 16 rows 23.9 / 23.1; H = 1024, 7 rows 20.2 / 17.9 (18.0), 256 rows (one round)
+// 22.1 / 20.6 (21.6); H = 2048, 1 row 33.2 / 27.0 (27.8), 64 rows (one round) 36.6 / 34.2 (34.6).  Where the ring's stages are single chunks
+// (Hp no multiple of 128) it catches up: H = 960, 64 rows 19.1 / 19.1 (19.1), 256 rows 21.2 / 22.1 (23.3), H = 832, 200 rows 18.5 (20.1).
 static bool few_units(int dtype, int Hp, bool vec, int rows) {
     if (dtype == RNNLM_BF16) return Hp == kFewUnitsBf16 && !vec;
     if (Hp <= 256) return true;
-    if (!vec) return rows <= 16 && Hp <= 512;
-    return Hp <= 512 || (Hp <= 1024 && rows <= 64);
+    if (!vec) return rows <= 16;
+    return Hp <= 512 || Hp % 128 == 0 || rows <= 64;
 }
 
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,

@@ -25,7 +25,8 @@ def model_of(rng, H, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("H,B", [(64, 31), (64, 33), (150, 64), (130, 65), (333, 257), (512, 1024), (512, 1025), (1022, 513),
                                  (1024, 1024), (1024, 1025), (1100, 500), (1100, 931), (2048, 513), (4096, 257),
-                                 (64, 300), (64, 4096), (64, 4097), (61, 1), (192, 1344), (190, 1345), (256, 1024), (700, 513), (704, 1280), (704, 1281), (512, 2049), (1088, 769), (320, 3073)])
+                                 (64, 300), (64, 4096), (64, 4097), (61, 1), (192, 1344), (190, 1345), (256, 1024), (512, 512), (650, 16), (1024, 256),
+                                 (1100, 64), (2048, 64), (700, 513), (704, 1280), (704, 1281), (512, 2049), (1088, 769), (320, 3073)])
 def test_against_the_oracle(H, B, dtype):
     rng = np.random.default_rng(H * 10000 + B)
     model = model_of(rng, H, dtype)
