@@ -68,8 +68,9 @@ enum rnnlm_option {
      * 1 = always the running maximum;  2 = always the fixed offset (EINVAL if unusable). */
     RNNLM_OPT_LSE_MODE = 1,
     /* Which output-projection kernel: 0 = automatic (default), 1 = the plain any-shape
-     * kernel, 2 = the LDS-staged kernel with the hidden block held in registers (bf16,
-     * H <= 512), 3 = the LDS-tiled kernel for any hidden size and both types, 4 = (fp32 models)
+     * kernel, 2 = the LDS-staged kernel with the hidden block held in registers (bf16;
+     * on request only where H rounded up to a multiple of 64 is 128, 256 or 512; by itself the library
+     * takes it for every H from 65 to 704, from 128 rows on), 3 = the LDS-tiled kernel for any hidden size and both types, 4 = (fp32 models)
      * the LDS-tiled kernel on a two-term fp16 split of both operands (every word's weights scaled by a
      * power of two; operands good to 2^-23, a product to 2^-21 of itself, sums in fp32: errors as of fp32
      * products unless a sum is dominated by one term) at fp16 matrix-core speed: the automatic choice for fp32 from 64 rows

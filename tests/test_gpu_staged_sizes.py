@@ -12,6 +12,19 @@ from harness import gpu_step, gpu_step_dedup, load_model
 pytestmark = pytest.mark.gpu
 
 
+def logprob_of_rounded_rows(model, h, query, scale):
+    """What the kernel computes, in float64: the rows h' - 1/2 enter the normaliser as bf16 numbers, times scale where that is
+    folded in.  Also the smallest share in a normaliser that a whole block of 32 words has."""
+    O, bias = model["O"].astype(np.float64), model["bias"].astype(np.float64)
+    d = round_to_bf16((h - np.float32(0.5)) * np.float32(scale)).astype(np.float64) / scale
+    z = d @ O + (bias + 0.5 * O.sum(0))
+    top = z.max(1, keepdims=True)
+    p = np.exp(z - top)
+    blocks = p[:, :p.shape[1] // 32 * 32].reshape(len(p), -1, 32).sum(2) / p.sum(1, keepdims=True)
+    exact = np.take_along_axis(h.astype(np.float64) @ O + bias, query, 1)
+    return exact - top - np.log(p.sum(1, keepdims=True)), blocks.min()
+
+
 @pytest.mark.parametrize("H,V,B", [(100, 33, 128), (129, 5000, 129), (192, 8300, 255), (300, 4097, 257), (333, 20000, 130),
                                    (384, 700, 512), (445, 9000, 300), (512, 12345, 200), (570, 6000, 131), (600, 33000, 140),
                                    (640, 1000, 513), (650, 16500, 317), (704, 4100, 128)])
@@ -34,6 +47,11 @@ def test_against_the_oracle(H, V, B):
         h, lp = gpu_step(m, prev, h_in, query)
         assert np.max(np.abs(h - ref["h_out"])) <= 1e-5 and np.max(np.abs(lp - ref["logprob"])) <= tol, lse_mode
         by_mode.append(lp)
+        # beside that rounding: fp32 sums, 2^-24 of logits below 40 some hundred times, random signs.  A block of 32 words that
+        # the normaliser misses moves it by the block's share, three times that or more at every size here
+        scale = np.log2(np.e) if -(-H // 64) * 64 in (128, 256, 512) else 1.0
+        tight, share = logprob_of_rounded_rows(model, h, query, scale)
+        assert share > 3e-4 and np.max(np.abs(lp - tight)) <= 1e-4, lse_mode
     # the same operands, fp32 sums in another order: 2^-24 of logits below 40 some hundred times, random signs
     assert np.max(np.abs(by_mode[0] - by_mode[1])) <= 1e-4
     m.set_option(rn.OPT_LSE_MODE, 0)
