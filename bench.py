@@ -30,9 +30,9 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E, published
 # launch that was timed is that kernel on that workload (otherwise "traffic" is null).
 TRAFFIC = {
     ("outproj_staged_kernel<512, true>", 3): (78.0e6, "profiles/step_kernels_cfg3_large_vocab_hbm_traffic.md"),
-    ("outproj_rowstream_kernel", 5): (1238.0e6, "profiles/outproj_rowstream_cfg5_stress_hbm_fetch.md"),
+    ("outproj_rowstream_kernel", 5): (1236.9e6, "profiles/outproj_rowstream_cfg5_stress_hbm_fetch.md"),
     ("outproj_stream_kernel", 6): (260.3e6, "profiles/step_kernels_cfg6_paper_regime_kernel_trace.md"),
-    ("outproj_stream_kernel", 2): (21.2e6, "profiles/outproj_stream_few_rows_kernel_trace_and_fetch.md"),
+    ("outproj_stream_kernel", 2): (21.3e6, "profiles/outproj_stream_few_rows_kernel_trace_and_fetch.md"),
     ("outproj_stream_kernel", 3): (67.8e6, "profiles/outproj_stream_few_rows_kernel_trace_and_fetch.md"),
     ("outproj_stream_kernel", 5): (411.5e6, "profiles/outproj_stream_few_rows_kernel_trace_and_fetch.md"),
 }
@@ -40,7 +40,7 @@ TRAFFIC = {
 # (FETCH_SIZE + WRITE_SIZE, copy-calibrated).
 HS_TRAFFIC = {
     3: (53.8e6, "profiles/hs_step_cfg3_shape_kernel_trace_and_traffic.md"),
-    6: (2.83e6, "profiles/hs_step_cfg6_paper_regime_kernel_trace_and_traffic.md"),
+    6: (2.79e6, "profiles/hs_step_cfg6_paper_regime_kernel_trace_and_traffic.md"),
 }
 MIN_TIMED_REGION_S = 0.1         # the event-timed repetitions together last at least this long
 MIN_REPETITIONS = 20
