@@ -262,7 +262,7 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
     memset(m, 0, sizeof(*m));
     int status = RNNLM_OK;
     const size_t es = elem_size(dtype);
-    // bf16 models pad to at least 128 so that every Hp <= 512 fits the staged kernel
+    // bf16 models pad to at least 128, where the staged kernel's sizes begin
     const int Hp = (dtype == RNNLM_BF16 && H < 128) ? 128 : round_up(H, 64), Vp = round_up(V, 256);
     const int max_Bp = round_up(max_B, 256);
     ModelDev &d = m->dev;

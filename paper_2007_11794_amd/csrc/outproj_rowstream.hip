@@ -301,7 +301,7 @@ hipError_t launch_outproj_rowstream(const ModelDev &m, int rows, const int *B_de
         if (stream_lds_bytes(1, 2, KS) <= (size_t)kLdsBytes) stream_rows = 64;
         else if (stream_lds_bytes(1, 1, KS) <= (size_t)kLdsBytes) stream_rows = 32;
     }
-    *splits = SplitInfo{0, wg_per_xcd, kRows, sx_cap, stream_rows, kXcds * wg_per_xcd};
+    *splits = SplitInfo{0, wg_per_xcd, kRows, sx_cap, stream_rows, 0};
     hipLaunchKernelGGL(outproj_rowstream_kernel, dim3(kXcds * wg_per_xcd), dim3(kThreads), kLdsBytes, stream, m, rows, B_dev,
                        wg_per_xcd, sx_cap, stream_rows);
     return hipGetLastError();

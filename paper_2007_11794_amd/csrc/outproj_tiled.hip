@@ -359,7 +359,7 @@ hipError_t launch_tiled_shape(const ModelDev &m, int rows, const int *B_dev, boo
         if (stream_lds_bytes(1, 2, KS) <= (size_t)C::kLdsBytes) stream_rows = 64;
         else if (stream_lds_bytes(1, 1, KS) <= (size_t)C::kLdsBytes) stream_rows = 32;
     }
-    *splits = SplitInfo{0, wg_per_xcd, C::kRows, sx_cap, stream_rows, kXcds * wg_per_xcd};
+    *splits = SplitInfo{0, wg_per_xcd, C::kRows, sx_cap, stream_rows, 0};
     dim3 grid(kXcds * wg_per_xcd), block(C::kThreads);
     if (fixed_offset)
         hipLaunchKernelGGL((outproj_tiled_kernel<T, true, MB, WN, NS, OVL>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,

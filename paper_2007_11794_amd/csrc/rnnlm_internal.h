@@ -220,12 +220,12 @@ struct SplitInfo {
     int wg_per_xcd;        // else plan_rows(B, group_rows, wg_per_xcd, sx_cap).S
     int group_rows;
     int sx_cap;
-    int stream_rows;       // 0 < B <= stream_rows: stream_splits instead
+    int stream_rows;       // 0 < B <= stream_rows: stream_splits instead (0: every workgroup of the grid has one)
     int stream_splits;
 };
 __host__ __device__ inline int splits_of(const SplitInfo &si, int B) {
     if (si.fixed_splits > 0) return si.fixed_splits;
-    if (B > 0 && B <= si.stream_rows) return si.stream_splits;
+    if (B > 0 && B <= si.stream_rows) return si.stream_splits > 0 ? si.stream_splits : kXcds * si.wg_per_xcd;
     return plan_rows(B, si.group_rows, si.wg_per_xcd, si.sx_cap).S;
 }
 __host__ inline SplitInfo fixed_split_info(int S) { return SplitInfo{S, 0, 1, 1, 0, 0}; }
