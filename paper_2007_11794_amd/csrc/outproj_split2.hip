@@ -70,8 +70,8 @@ __global__ __launch_bounds__(kThreads, 2) void outproj_split2_kernel(ModelDev m,
     // 13.1 -> 12.9 us); not in the long-running shape, where it had the compiler await LDS in front of every barrier
     // (V = 65536, H = 512, 1024 rows 160 -> 172).
     if constexpr (MB == 2) asm volatile("" ::"s"(m.Ofrag), "s"(m.dfrag), "s"(m.ofac), "s"(FIXED ? m.cvec2_fixed : m.cvec2), "s"(m.Hp), "s"(m.Vp), "s"(m.part));
-    // The split follows the TRUE number of rows (after the grouping of ids or the cache lookup only
-    // the device knows it): few rows get many vocabulary splits, and the whole grid works.
+    // The split follows the TRUE number of rows (after the grouping of ids or the cache lookup only the device knows it):
+    // few rows get many vocabulary splits, 256 at most, which up to 128 rows is one workgroup per compute unit of the grid's two.
     const int B = B_dev ? *B_dev : rows;
     if (B <= 0) return;                                       // uniform: no barrier is met
     // Few rows after all (the count known on the device only): the time is then the time to read the weights once, and
