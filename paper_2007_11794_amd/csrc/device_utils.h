@@ -65,15 +65,50 @@ __device__ __forceinline__ void load8_row(const float *row, int k0, int H, bool 
     }
 }
 
+// The value of lane (own ^ MASK), without LDS: a shuffle through LDS (ds_bpermute, what __shfl_xor makes) occupies the unit that
+// the whole compute unit shares and takes its latency once per level of a reduction.  Rows are 16 lanes; masks 16 and 32 come
+// as swaps of registers (row_pair, half_pair).  Steps with all reductions and prefix sums in registers, us, before / after: tree
+// layer, 925 queries of 15 words, H = 448 22.0 / 20.0, 1024 of 32 words, H = 512 24.7 / 23.7; cached steps, 972 ids, H = 243, eight
+// of them 244 / 235; 8 rows at V = 1000, H = 64 13.2 / 12.5; index table, 4096 contexts 27.3 / 26.2; nothing slower.
+template <int MASK>
+__device__ __forceinline__ float lane_xor(float v) {
+    static_assert(MASK == 1 || MASK == 2 || MASK == 4 || MASK == 8, "");
+    const int x = __float_as_int(v);
+    if (MASK == 1) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));      // quad_perm 1 0 3 2
+    if (MASK == 2) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));      // quad_perm 2 3 0 1
+    if (MASK == 8) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false));     // row_ror 8
+    const int up = __builtin_amdgcn_update_dpp(x, x, 0x104, 0xF, 0x5, false);                             // quads 0, 2: row_shl 4
+    return __int_as_float(__builtin_amdgcn_update_dpp(up, x, 0x114, 0xF, 0xA, false));                    // quads 1, 3: row_shr 4
+}
+// {x, y} such that, in lanes with bit 5 (bit 4) clear, they are a of this lane and of the lane 32 (16) further, and in the other
+// lanes b of the lane 32 (16) before and of this one.
+__device__ __forceinline__ void half_pair(float a, float b, float &x, float &y) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void row_pair(float a, float b, float &x, float &y) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+}
+
+// Butterflies over 32, 16, 8, 4, 2, 1: every lane gets the result.
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    float x, y;
+    half_pair(v, v, x, y); v = x + y;
+    row_pair(v, v, x, y); v = x + y;
+    v += lane_xor<8>(v);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    return v + lane_xor<1>(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
+    float x, y;
+    half_pair(v, v, x, y); v = fmaxf(x, y);
+    row_pair(v, v, x, y); v = fmaxf(x, y);
+    v = fmaxf(v, lane_xor<8>(v));
+    v = fmaxf(v, lane_xor<4>(v));
+    v = fmaxf(v, lane_xor<2>(v));
+    return fmaxf(v, lane_xor<1>(v));
 }
 
 // 2^x with the hardware instruction (x = -inf gives 0).
@@ -180,34 +215,30 @@ __device__ __forceinline__ uint64_t mix64_full(uint64_t k) {
     return k;
 }
 
-// Block-wide exclusive prefix sum of one int per thread; returns the exclusive prefix and,
+// Inclusive prefix sum over the wave, in registers as well: within rows of 16 lanes, then the last lane of a row to the next one,
+// then lane 31 to the upper half.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);      // row_shr 1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);      // row_bcast 15 to rows 1 and 3
+    return v + __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast 31 to rows 2 and 3
+}
+
+// Block-wide exclusive prefix sum of one int per thread (whole waves, at most 16); returns the exclusive prefix and,
 // through `total`, the block sum.  `wsum` is LDS scratch of blockDim.x/64 + 1 ints.
 __device__ __forceinline__ int block_exclusive_scan(int v, int *wsum, int &total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int t = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += t;
-    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+    const int incl = wave_inclusive_scan(v);
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    if (wave == 0) {
-        int w = (lane < nwaves) ? wsum[lane] : 0;
-        int wi = w;
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) {
-            int t = __shfl_up(wi, off, 64);
-            if (lane >= off) wi += t;
-        }
-        if (lane < nwaves) wsum[lane] = wi - w;       // exclusive prefix of the wave sums
-        if (lane == nwaves - 1) wsum[nwaves] = wi;    // block total
-    }
-    __syncthreads();
-    int excl = wsum[wave] + incl - v;
-    total = wsum[nwaves];
+    // every wave for itself: the sums of all waves up to each
+    const int upto = wave_inclusive_scan(lane < nwaves ? wsum[lane] : 0);
+    const int before = wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0;
+    total = __builtin_amdgcn_readlane(upto, nwaves - 1);
     __syncthreads();                                  // wsum may be reused by the caller
-    return excl;
+    return before + incl - v;
 }
 
 // Natural-log normaliser of one row from its `splits` per-split (max, sum) partials of the
@@ -232,20 +263,18 @@ constexpr int lane_of_batch_slot(int u) { return 32 * ((u >> 2) & 1) + 16 * ((u 
 
 // Sums over the wave of eight per-lane values at once: the same xor butterfly (32, 16, ...,
 // 1) as wave_sum, but in the first three levels a lane passes on the half of the values it
-// will not finish, so 10 exchanges do the work of 48.  Returns the sum of value
-// batch_slot_of_lane(lane); bit-identical to wave_sum of that value.
+// will not finish.  Returns the sum of value batch_slot_of_lane(lane); bit-identical to wave_sum of that value.
 __device__ __forceinline__ float wave_sum8(const float (&acc)[8], int lane) {
-    float v4[4], v2[2];
-    const bool up5 = (lane & 32) != 0, up4 = (lane & 16) != 0, up3 = (lane & 8) != 0;
+    float v4[4], v2[2], x, y;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v4[i] = (up5 ? acc[4 + i] : acc[i]) + __shfl_xor(up5 ? acc[i] : acc[4 + i], 32, 64);
+    for (int i = 0; i < 4; ++i) { half_pair(acc[i], acc[4 + i], x, y); v4[i] = x + y; }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) v2[i] = (up4 ? v4[2 + i] : v4[i]) + __shfl_xor(up4 ? v4[i] : v4[2 + i], 16, 64);
-    float v = (up3 ? v2[1] : v2[0]) + __shfl_xor(up3 ? v2[0] : v2[1], 8, 64);
-    v += __shfl_xor(v, 4, 64);
-    v += __shfl_xor(v, 2, 64);
-    v += __shfl_xor(v, 1, 64);
-    return v;
+    for (int i = 0; i < 2; ++i) { row_pair(v4[i], v4[2 + i], x, y); v2[i] = x + y; }
+    const bool up3 = (lane & 8) != 0;
+    float v = (up3 ? v2[1] : v2[0]) + lane_xor<8>(up3 ? v2[0] : v2[1]);
+    v += lane_xor<4>(v);
+    v += lane_xor<2>(v);
+    return v + lane_xor<1>(v);
 }
 
 __device__ __forceinline__ float quiet_nan() { return __uint_as_float(0x7FC00000u); }

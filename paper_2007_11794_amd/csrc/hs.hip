@@ -74,9 +74,10 @@ __global__ __launch_bounds__(256) void hs_query_kernel(
         }
         const float x = wave_sum8(acc, lane);
         float term = valid ? log_sigmoid_f32((entry >> 31) ? -x : x) : 0.f;
-        term += __shfl_xor(term, 32, 64);                // the eight slots differ in lane bits 5, 4, 3
-        term += __shfl_xor(term, 16, 64);
-        term += __shfl_xor(term, 8, 64);
+        float a, b;
+        half_pair(term, term, a, b); term = a + b;       // the eight slots differ in lane bits 5, 4, 3
+        row_pair(term, term, a, b); term = a + b;
+        term += lane_xor<8>(term);
         total += term;
     }
     if (lane == 0) {
@@ -160,14 +161,17 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *
             for (int i = 0; i < 8; ++i) acc[u] = fmaf(w8[u][i], h8[i], acc[u]);
         }
         // three levels that halve the number of values a lane carries, then the rest of the butterfly
-        float v4[4], v2[2];
+        float v4[4], v2[2], x, y;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v4[i] = (upa ? acc[4 + i] : acc[i]) + __shfl_xor(upa ? acc[i] : acc[4 + i], top, 64);
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (LPR == 32) { row_pair(acc[i], acc[4 + i], x, y); v4[i] = x + y; }
+            else v4[i] = (upa ? acc[4 + i] : acc[i]) + lane_xor<8>(upa ? acc[i] : acc[4 + i]);
+        }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) v2[i] = (upb ? v4[2 + i] : v4[i]) + __shfl_xor(upb ? v4[i] : v4[2 + i], top / 2, 64);
-        float v = (upc ? v2[1] : v2[0]) + __shfl_xor(upc ? v2[0] : v2[1], top / 4, 64);
-#pragma unroll
-        for (int step = top / 8; step >= 1; step >>= 1) v += __shfl_xor(v, step, 64);
+        for (int i = 0; i < 2; ++i) v2[i] = (upb ? v4[2 + i] : v4[i]) + lane_xor<top / 2>(upb ? v4[i] : v4[2 + i]);
+        float v = (upc ? v2[1] : v2[0]) + lane_xor<top / 4>(upc ? v2[0] : v2[1]);
+        if constexpr (LPR == 32) v += lane_xor<2>(v);
+        v += lane_xor<1>(v);
         const int d = first + g + G * u_mine;
         if (writer && d < D) dx[d] = v;
     };
@@ -311,9 +315,9 @@ __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
         const int b0 = wbase[k], b1 = wbase[k + 1];
         float t = 0.f;
         for (int e = b0 + (tid & 7); e < b1; e += 8) t += eterm[e];
-        t += __shfl_xor(t, 4, 64);
-        t += __shfl_xor(t, 2, 64);
-        t += __shfl_xor(t, 1, 64);
+        t += lane_xor<4>(t);
+        t += lane_xor<2>(t);
+        t += lane_xor<1>(t);
         if ((tid & 7) == 0) {
             const int qk = query_word[(size_t)n * K + k];
             const bool ok = qk >= 0 && qk < m.V;

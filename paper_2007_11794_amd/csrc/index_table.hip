@@ -60,25 +60,38 @@ __device__ __forceinline__ int hash_slot(int lane) {
     const int s = (lane >> 4) & 3;                       // bits 5 and 4
     return ROWS == 4 ? s : 2 * s + ((lane >> 3) & 1);
 }
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int off) {
-    const uint32_t lo = __shfl_xor((uint32_t)v, off, 64), hi = __shfl_xor((uint32_t)(v >> 32), off, 64);
+template <int MASK>
+__device__ __forceinline__ uint64_t lane_xor_u64(uint64_t v) {
+    const uint32_t lo = __float_as_uint(lane_xor<MASK>(__uint_as_float((uint32_t)v))), hi = __float_as_uint(lane_xor<MASK>(__uint_as_float((uint32_t)(v >> 32))));
     return ((uint64_t)hi << 32) | lo;
+}
+// a + b over pairs of lanes, as half_pair and row_pair pair them
+template <bool HALF>
+__device__ __forceinline__ uint64_t pair_sum_u64(uint64_t a, uint64_t b) {
+    float x0, y0, x1, y1;
+    const float a0 = __uint_as_float((uint32_t)a), a1 = __uint_as_float((uint32_t)(a >> 32));
+    const float b0 = __uint_as_float((uint32_t)b), b1 = __uint_as_float((uint32_t)(b >> 32));
+    if (HALF) { half_pair(a0, b0, x0, y0); half_pair(a1, b1, x1, y1); }
+    else { row_pair(a0, b0, x0, y0); row_pair(a1, b1, x1, y1); }
+    return (((uint64_t)__float_as_uint(x1) << 32) | __float_as_uint(x0)) + (((uint64_t)__float_as_uint(y1) << 32) | __float_as_uint(y0));
 }
 template <int ROWS>
 __device__ __forceinline__ uint64_t wave_sums_u64(const uint64_t (&acc)[ROWS], int lane) {
-    uint64_t v[ROWS];
+    uint64_t half[ROWS / 2], quarter[ROWS / 4];
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) v[i] = acc[i];
-    int off = 32;
+    for (int i = 0; i < ROWS / 2; ++i) half[i] = pair_sum_u64<true>(acc[i], acc[ROWS / 2 + i]);
 #pragma unroll
-    for (int n = ROWS; n > 1; n /= 2, off /= 2) {
-        const bool up = (lane & off) != 0;
-#pragma unroll
-        for (int i = 0; i < n / 2; ++i) v[i] = (up ? v[n / 2 + i] : v[i]) + shfl_xor_u64(up ? v[i] : v[n / 2 + i], off);
+    for (int i = 0; i < ROWS / 4; ++i) quarter[i] = pair_sum_u64<false>(half[i], half[ROWS / 4 + i]);
+    uint64_t v = quarter[0];
+    if constexpr (ROWS == 8) {
+        const bool up = (lane & 8) != 0;
+        v = (up ? quarter[1] : quarter[0]) + lane_xor_u64<8>(up ? quarter[0] : quarter[1]);
+    } else {
+        v += lane_xor_u64<8>(v);
     }
-#pragma unroll
-    for (; off > 0; off /= 2) v[0] += shfl_xor_u64(v[0], off);
-    return v[0];
+    v += lane_xor_u64<4>(v);
+    v += lane_xor_u64<2>(v);
+    return v + lane_xor_u64<1>(v);
 }
 
 template <int kHashRows>
