@@ -52,7 +52,7 @@ void free_scratch(rnnlm_model *m) {
     (void)hipFree(d.dfrag);
     (void)hipFree(d.part);
     (void)hipFree(d.flag);
-    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = nullptr;
+    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = d.done = nullptr;
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
     m->ev0 = m->ev1 = nullptr;
@@ -64,6 +64,7 @@ void free_weights(rnnlm_model *m) {
     (void)hipFree(const_cast<void *>(d.U));
     (void)hipFree(const_cast<void *>(d.W));
     (void)hipFree(const_cast<void *>(d.Ot));
+    (void)hipFree(const_cast<void *>(d.Wfrag));
     (void)hipFree(const_cast<float *>(d.half_rowsum_W));
     (void)hipFree(const_cast<float *>(d.bias));
     (void)hipFree(const_cast<float *>(d.half_colsum_O));
@@ -94,8 +95,8 @@ int alloc_scratch(rnnlm_model *m, int max_Bp, bool with_partials) {
     void *p;
     HIP_TRY(hipMalloc(&p, block)); d.d = p;
     HIP_TRY(hipMemset(d.d, 0, block));
-    HIP_TRY(hipMalloc(&p, 4)); d.flag = static_cast<int *>(p);
-    HIP_TRY(hipMemset(d.flag, 0, 4));
+    HIP_TRY(hipMalloc(&p, 8)); d.flag = static_cast<int *>(p); d.done = d.flag + 1;
+    HIP_TRY(hipMemset(d.flag, 0, 8));
     if (d.dtype == RNNLM_BF16 || with_partials) {
         HIP_TRY(hipMalloc(&p, block)); d.dfrag = p;
         HIP_TRY(hipMemset(d.dfrag, 0, block));
@@ -121,6 +122,32 @@ bool bytes_overlap(const void *a, size_t an, const void *b, size_t bn) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
     return x < y + bn && y < x + an;
 }
+
+// Does one of `outs` share a byte with one of `ins` or with another one of `outs`?  A step of several launches reads some inputs
+// after it has written some outputs; a step of one launch does not, so it is only taken where no order can be seen.
+struct Bytes {
+    const void *p;
+    size_t n;
+};
+template <size_t NI, size_t NO>
+bool outputs_overlap(const Bytes (&ins)[NI], const Bytes (&outs)[NO]) {
+    for (size_t o = 0; o < NO; ++o) {
+        for (const Bytes &i : ins)
+            if (i.p && bytes_overlap(i.p, i.n, outs[o].p, outs[o].n)) return true;
+        for (size_t q = 0; q < o; ++q)
+            if (bytes_overlap(outs[q].p, outs[q].n, outs[o].p, outs[o].n)) return true;
+    }
+    return false;
+}
+
+// The whole step of few rows in one launch (step_few.hip).  The words asked for are finished by one workgroup: up to kFewPairs.
+constexpr long long kFewPairs = 8192;
+bool few_step(const rnnlm_model *m, int rows, bool grouped, int N, int K) {
+    return step_few_chosen(m->dev, rows, grouped) && N > 0 && K > 0 && (long long)N * K <= kFewPairs &&
+           outproj_streams_in_one_launch(m->dev, rows, m->outproj_kernel);
+}
+uint32_t inverse_of(int K) { return K > 1 ? (uint32_t)(((1ull << 32) + K - 1) / K) : 0; }
+bool rows_in_pieces(const ModelDev &d, const float *h_in) { return d.H % 4 == 0 && (reinterpret_cast<uintptr_t>(h_in) & 15) == 0; }
 
 double widen_host(const void *p, size_t i, int dtype) {
     if (dtype == RNNLM_BF16) {
@@ -276,6 +303,10 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
     void *p;
     status = upload_recurrent(m, V, H, Hp, dtype, U, W, max_Bp, true);
     if (status != RNNLM_OK) goto fail;
+    if (step_few_supported(dtype, Hp)) {
+        HIP_TRY(hipMalloc(&p, (size_t)Hp * Hp * es)); d.Wfrag = p;
+        HIP_TRY(launch_frag_recurrent(d.W, dtype, Hp, p, nullptr));
+    }
     HIP_TRY(hipMalloc(&p, (size_t)Vp * Hp * es)); d.Ot = p;
     HIP_TRY(hipMalloc(&p, (size_t)V * 4)); d.bias = static_cast<float *>(p);
     HIP_TRY(hipMalloc(&p, (size_t)V * 4)); d.half_colsum_O = static_cast<float *>(p);
@@ -364,7 +395,7 @@ int rnnlm_model_share(const rnnlm_model *model, int max_B, rnnlm_model **out) {
     if (!m) return RNNLM_ENOMEM;
     *m = *model;                           // weights' pointers, shapes, options
     ModelDev &d = m->dev;
-    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = nullptr;
+    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = d.done = nullptr;
     m->ev0 = m->ev1 = nullptr;
     m->max_B = max_B;
     m->max_Bp = round_up(max_B, 256);
@@ -451,6 +482,15 @@ int rnnlm_step(const rnnlm_model *model, int B, int K, const int32_t *prev_word,
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const ModelDev &d = model->dev;
     SplitInfo splits = fixed_split_info(1);
+    if (few_step(model, B, false, N, K)) {
+        const size_t h_bytes = (size_t)B * d.H * 4, nk = (size_t)N * K * 4;
+        const Bytes ins[] = {{prev_word, (size_t)B * 4}, {h_in, h_bytes}, {query_word, nk}, {row_of_query_or_null, (size_t)N * 4}};
+        const Bytes outs[] = {{h_out, h_bytes}, {logprob, nk}};
+        if (!outputs_overlap(ins, outs)) {
+            const FewStep a = {B, N, K, IdGroups{}, prev_word, h_in, query_word, row_of_query_or_null, nullptr, h_out, logprob, rows_in_pieces(d, h_in), inverse_of(K)};
+            return launch_step_few(d, a, use_fixed_offset(model), s) == hipSuccess ? RNNLM_OK : RNNLM_EDEVICE;
+        }
+    }
     if (launch_recur(recur_view(model, B), B, nullptr, nullptr, nullptr, prev_word, h_in, h_out, IdGroups{}, s) != hipSuccess)
         return RNNLM_EDEVICE;
     if (launch_outproj(d, B, nullptr, use_fixed_offset(model), model->outproj_kernel, &splits, s) != hipSuccess)
@@ -507,6 +547,15 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
         if (N == 0) return RNNLM_OK;
         // Grids cover N rows; the kernels read the true number of rows from *n_unique.
         const IdGroups ids = {history_ids, rep, inverse, n_unique};
+        if (few_step(model, N, true, N, K)) {
+            const size_t n4 = (size_t)N * 4, h_bytes = n4 * d.H, nk = n4 * K;
+            const Bytes ins[] = {{history_ids, n4 * 2}, {prev_word, n4}, {h_in, h_bytes}, {query_word, nk}, {base_score, nk}};
+            const Bytes outs[] = {{h_out, h_bytes}, {score, nk}, {rep, n4}, {inverse, n4}, {n_unique, 4}};
+            if (grouped_update && !outputs_overlap(ins, outs)) {
+                const FewStep a = {N, N, K, ids, prev_word, h_in, query_word, nullptr, base_score, h_out, score, rows_in_pieces(d, h_in), inverse_of(K)};
+                return launch_step_few(d, a, use_fixed_offset(model), s) == hipSuccess ? RNNLM_OK : RNNLM_EDEVICE;
+            }
+        }
         if (launch_recur(recur_view(model, N), N, grouped_update ? nullptr : n_unique, grouped_update ? nullptr : rep, nullptr,
                          prev_word, h_in, h_out, grouped_update ? ids : IdGroups{}, s) != hipSuccess)
             return RNNLM_EDEVICE;

@@ -198,6 +198,20 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// Values that another workgroup of the same launch, on another XCD perhaps, reads: relaxed agent-scope accesses, which pass
+// by the caches that are not shared.  The writer's waves await their stores (seen_by_all) in front of the barrier behind
+// which one thread counts the workgroup as done; the reader begins behind the count.  Fences that write back and drop
+// the whole L2 (__threadfence) in their place took 30 us a launch with 256 workgroups.
+__device__ __forceinline__ void store_seen(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_seen(float2 *p, float2 v) {
+    __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float load_seen(const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float2 load_seen(const float2 *p) {
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void seen_by_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // 64-bit key -> 32 well-mixed bits (hash tables of history ids).
 __device__ __forceinline__ uint32_t mix64(uint64_t k) {
     // splitmix64 finaliser

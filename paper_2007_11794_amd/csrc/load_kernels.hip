@@ -92,6 +92,14 @@ __global__ __launch_bounds__(256) void frag_weights_kernel(const u32x4 *__restri
     Ofrag[i] = Ot[word * (2 * KS) + 2 * ks + (lane >> 5)];           // 2 KS chunks of 8 units per word
 }
 
+// fp32 [Hp][Hp] recurrent weights: [blk][ks][half][64 lanes][4]
+__global__ __launch_bounds__(256) void frag_recurrent_f32_kernel(const f32x4 *__restrict__ W, int n, int KS, f32x4 *__restrict__ Wfrag) {
+    const int i = blockIdx.x * 256 + threadIdx.x;                  // (blk, ks, half, lane)
+    if (i >= n) return;
+    const int lane = i & 63, half = (i >> 6) & 1, frag = i >> 7, blk = frag / KS, ks = frag % KS;
+    Wfrag[i] = W[(blk * 32 + (lane & 31)) * (4 * KS) + 4 * ks + 2 * (lane >> 5) + half];
+}
+
 // fp32 [Vp][Hp] weights as two fp16 terms in the same operand order, [blk][ks][term][64 lanes][8 halves].
 // One workgroup per block of 32 words: eight threads find the largest weight of a word, then lane
 // 32 g + c of fragment ks takes word 32 blk + c, units 16 ks + 8 g .. + 7.  Words scaled to [2^13, 2^14):
@@ -154,6 +162,14 @@ hipError_t launch_frag_weights(const void *Ot, int Vp, int Hp, void *Ofrag, hipS
     const size_t n = (size_t)Vp * Hp / 8;
     hipLaunchKernelGGL(frag_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
                        static_cast<const u32x4 *>(Ot), n, Hp / 16, static_cast<u32x4 *>(Ofrag));
+    return hipGetLastError();
+}
+
+hipError_t launch_frag_recurrent(const void *W, int dtype, int Hp, void *Wfrag, hipStream_t stream) {
+    if (dtype == RNNLM_BF16) return launch_frag_weights(W, Hp, Hp, Wfrag, stream);
+    const int n = Hp * Hp / 4;
+    hipLaunchKernelGGL(frag_recurrent_f32_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, static_cast<const f32x4 *>(W), n, Hp / 16,
+                       static_cast<f32x4 *>(Wfrag));
     return hipGetLastError();
 }
 

@@ -219,6 +219,10 @@ static bool stream_choice(const ModelDev &m, int rows, int kernel_choice) {
     return kernel_choice == 0 && rows <= 64 && launches <= 2;
 }
 
+bool outproj_streams_in_one_launch(const ModelDev &m, int rows, int kernel_choice) {
+    return rows > 0 && kernel_choice == 0 && stream_choice(m, rows, 0) && rows <= outproj_stream_max_rows(m);
+}
+
 // Which bf16 kernel launch_outproj takes for a launch sized for `rows` rows.
 enum Bf16Kernel { kBf16Stream, kBf16Staged, kBf16RowStream, kBf16Tiled, kBf16Plain };
 static Bf16Kernel choose_bf16(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {

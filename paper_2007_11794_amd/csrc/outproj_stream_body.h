@@ -60,13 +60,28 @@ __device__ __forceinline__ void stream_block_end(int pieces, char *lds, int wave
     __syncthreads();                                          // hidden block visible to all waves
 }
 
+// Where the hidden block in LDS comes from: the copy a launch in front of this one left in memory.  (The other source:
+// HiddenHere in step_few.hip, which computes it between the same two calls.)
+template <int WAVES = kStreamWaves>
+struct StoredBlock {
+    // its wait counts the loads of the weights behind it: a wave without weights of its own asks for some all the same
+    static constexpr bool kCountsLoads = true;
+    const char *src;
+    int pieces, stride;
+    int B;                                            // rows of it that are valid, > 0
+    StreamPieces held;
+    __device__ __forceinline__ void begin(char *lds, int wave, int lane) { stream_block_begin<WAVES>(src, pieces, lds, wave, lane, held, stride); }
+    __device__ __forceinline__ void end(char *lds, int wave, int lane) { stream_block_end<WAVES>(pieces, lds, wave, lane, held); }
+    __device__ __forceinline__ static void put(float2 *at, float2 v) { *at = v; }             // a partial
+};
+
 // One launch's worth of streaming for the workgroup `split` of `S`: rows row0 .. row0 + 32 RB - 1 of
-// the hidden block (B = number of valid ones among them, > 0), partials into m.part.  SCALED: the block
-// carries log2(e) (outproj_d_scale).  Needs
+// the hidden block (block.B valid ones among them, known once block.begin has run), partials into m.part.  SCALED: the
+// block carries log2(e) (outproj_d_scale).  Needs
 // stream_lds_bytes(1, RB, Hp / 16) bytes of LDS at `lds` and kStreamThreads threads; contains two
 // workgroup barriers, so all threads of the workgroup must call it.
-template <int RB, bool FIXED, bool SCALED>
-__device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, int row0, int split, int S, char *lds) {
+template <int RB, bool FIXED, bool SCALED, class Block>
+__device__ __forceinline__ void outproj_stream_block(const ModelDev &m, Block &block, int row0, int split, int S, char *lds) {
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = m.Hp >> 4, GPB = KS / kStreamGroup;
@@ -80,9 +95,7 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
     bf16x8 *dl = reinterpret_cast<bf16x8 *>(lds);
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)RB * KS * 1024);    // [kStreamWaves][RB * 32]
 
-    const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 1024;
-    StreamPieces held;
-    stream_block_begin(block, RB * KS, lds, wave, lane, held);
+    block.begin(lds, wave, lane);
     bf16x8 ring[kStreamRing][kStreamGroup];
     StreamCursor in = {blk0 + wave, 0};
     // Always kStreamGroup loads, so that the number of younger loads behind any operand is the same on
@@ -94,8 +107,11 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
         for (int i = 0; i < kStreamGroup; ++i) dst[i] = p[i * 64];
         in.advance(GPB);
     };
+    const bool any = Block::kCountsLoads || blk0 + wave < blk1;
+    if (any) {
 #pragma unroll
-    for (int st = 0; st < kStreamRing - 1; ++st) issue(ring[st]);
+        for (int st = 0; st < kStreamRing - 1; ++st) issue(ring[st]);
+    }
     StreamCursor out = {blk0 + wave, 0};
     f32x4 cc[4];
     auto load_constants = [&]() {
@@ -103,8 +119,8 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
 #pragma unroll
         for (int q = 0; q < 4; ++q) cc[q] = *reinterpret_cast<const f32x4 *>(cvec + blk * 32 + 8 * q + 4 * g);
     };
-    load_constants();
-    stream_block_end(RB * KS, lds, wave, lane, held);
+    if (any) load_constants();
+    block.end(lds, wave, lane);
 
     f32x16 acc[RB];
     float mrun[RB], srun[RB];
@@ -168,8 +184,15 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
             if (FIXED) ss += p.y;
             else lse2_merge(mm, ss, p.x, p.y);
         }
-        if (tid < B) m.part[(size_t)(row0 + tid) * kMaxSplits + split] = make_float2(mm, ss);
+        if (tid < block.B) block.put(&m.part[(size_t)(row0 + tid) * kMaxSplits + split], make_float2(mm, ss));
     }
+}
+
+template <int RB, bool FIXED, bool SCALED>
+__device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, int row0, int split, int S, char *lds) {
+    const int KS = m.Hp >> 4;
+    StoredBlock<> block = {static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 1024, RB * KS, 1024, B, {}};
+    outproj_stream_block<RB, FIXED, SCALED>(m, block, row0, split, S, lds);
 }
 
 // ------------------------------------------------------------------------------ fp32 models
@@ -182,11 +205,11 @@ __device__ __forceinline__ void outproj_stream_body(const ModelDev &m, int B, in
 // 36.7 us, 36.6; V = 20000, H = 576, 60 rows 13.1, 13.5).
 constexpr int kStreamGroup32 = 2;        // operands per group (two terms each: four loads, as above)
 
-// The fp32 form of outproj_stream_body, for a workgroup of WAVES waves: needs stream_lds_bytes(2, RB, Hp / 16, WAVES) bytes
-// of LDS.  ONE_TERM: stream_lds_bytes(1, ...) bytes (and more than kStreamCopyPieces kilobytes of block per wave): only the
-// first term of the hidden block is kept there, the second comes from the caches beside the weights.
-template <int RB, bool FIXED, int WAVES = kStreamWaves, bool ONE_TERM = false>
-__device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B, int row0, int split, int S, char *lds) {
+// The fp32 form of outproj_stream_block, for a workgroup of WAVES waves: needs stream_lds_bytes(2, RB, Hp / 16, WAVES) bytes
+// of LDS.  ONE_TERM (a StoredBlock only): stream_lds_bytes(1, ...) bytes (and more than kStreamCopyPieces kilobytes of block
+// per wave): only the first term of the hidden block is kept there, the second comes from the caches beside the weights.
+template <int RB, bool FIXED, int WAVES, bool ONE_TERM, class Block>
+__device__ __forceinline__ void outproj_stream_f32_block(const ModelDev &m, Block &block, int row0, int split, int S, char *lds) {
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int KS = m.Hp >> 4, GPB = KS / kStreamGroup32;
@@ -201,9 +224,7 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
     f16x8 *dl = reinterpret_cast<f16x8 *>(lds);                             // [RB][KS][term][64]
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)kTerms * RB * KS * 1024);
 
-    const char *block = static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 2048;
-    StreamPieces held;
-    stream_block_begin<WAVES>(block, kTerms * RB * KS, lds, wave, lane, held, 2048 / kTerms);
+    block.begin(lds, wave, lane);
     f16x8 ring[kStreamRing][2 * kStreamGroup32], second[kStreamRing][ONE_TERM ? RB * kStreamGroup32 : 1];
     StreamCursorOf<WAVES> in = {blk0 + wave, 0};
     auto issue = [&](int slot) __attribute__((always_inline)) {                  // always as many loads (see above)
@@ -211,14 +232,17 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
 #pragma unroll
         for (int i = 0; i < 2 * kStreamGroup32; ++i) ring[slot][i] = p[i * 64];
         if constexpr (ONE_TERM) {
-            const f16x8 *d2 = reinterpret_cast<const f16x8 *>(block) + in.part * (kStreamGroup32 * 128) + 64 + lane;
+            const f16x8 *d2 = reinterpret_cast<const f16x8 *>(block.src) + in.part * (kStreamGroup32 * 128) + 64 + lane;
 #pragma unroll
             for (int i = 0; i < RB * kStreamGroup32; ++i) second[slot][i] = d2[(i / kStreamGroup32 * KS + i % kStreamGroup32) * 128];
         }
         in.advance(GPB);
     };
+    const bool any = Block::kCountsLoads || blk0 + wave < blk1;
+    if (any) {
 #pragma unroll
-    for (int st = 0; st < kStreamRing - 1; ++st) issue(st);
+        for (int st = 0; st < kStreamRing - 1; ++st) issue(st);
+    }
     StreamCursorOf<WAVES> out = {blk0 + wave, 0};
     f32x4 cc[4], ff[4];
     auto load_constants = [&]() {
@@ -229,8 +253,8 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
             ff[q] = *reinterpret_cast<const f32x4 *>(m.ofac + blk * 32 + 8 * q + 4 * g);
         }
     };
-    load_constants();
-    stream_block_end<WAVES>(kTerms * RB * KS, lds, wave, lane, held);
+    if (any) load_constants();
+    block.end(lds, wave, lane);
 
     constexpr bool kApart = RB <= 2;
     f32x16 acc[RB], rest[kApart ? RB : 1];
@@ -301,8 +325,15 @@ __device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B
             if (FIXED) ss += p.y;
             else lse2_merge(mm, ss, p.x, p.y);
         }
-        if (tid < B) m.part[(size_t)(row0 + tid) * kMaxSplits + split] = make_float2(mm, ss);
+        if (tid < block.B) block.put(&m.part[(size_t)(row0 + tid) * kMaxSplits + split], make_float2(mm, ss));
     }
+}
+
+template <int RB, bool FIXED, int WAVES = kStreamWaves, bool ONE_TERM = false>
+__device__ __forceinline__ void outproj_stream_f32_body(const ModelDev &m, int B, int row0, int split, int S, char *lds) {
+    const int KS = m.Hp >> 4, terms = ONE_TERM ? 1 : 2;
+    StoredBlock<WAVES> block = {static_cast<const char *>(m.dfrag) + (size_t)(row0 >> 5) * KS * 2048, terms * RB * KS, 2048 / terms, B, {}};
+    outproj_stream_f32_block<RB, FIXED, WAVES, ONE_TERM>(m, block, row0, split, S, lds);
 }
 
 // terms = copies of the hidden block kept in LDS: 1 (bf16 models) or 2 (fp32 models)

@@ -30,6 +30,10 @@ struct ModelDev {
     const void *U;     // [V][Hp]
     const void *W;     // [Hp rounded up to 128][Hp], W[j][i]
     const void *Ot;    // [Vp][Hp], Ot[v][j] = O[j][v]
+    // W in MFMA-operand order for the one-launch step (step_few_supported), else null.  bf16: [Hp / 32][Hp / 16][64 lanes][8], lane
+    // 32 g + c of fragment (blk, ks) holds unit 32 blk + c, inputs 16 ks + 8 g .. + 7; fp32: [Hp / 32][Hp / 16][2][64 lanes][4], the
+    // first and the last four of those eight.
+    const void *Wfrag;
     const float *half_rowsum_W;   // [Hp]  0.5 * sum_i W[j][i]
     const float *bias;            // [V]
     const float *half_colsum_O;   // [V]   0.5 * sum_j O[j][v]
@@ -62,6 +66,7 @@ struct ModelDev {
     float d_scale;     // set for the hidden update only: outproj_d_scale of the output projection that follows
     float2 *part;      // [max_Bp][kMaxSplits]  (max, sum) partials of the base-2 log-sum-exp
     int *flag;         // sticky rnnlm_device_flag bits
+    int *done;         // workgroups of a one-launch step (step_few.hip) that have finished; 0 between launches
 };
 
 // Device-side view of a cache kept between steps (cache.hip).
@@ -255,6 +260,27 @@ hipError_t launch_query(const ModelDev &m, int rows, const int *B_dev, int N, in
                         const float *h_out, const float *lse_rows, const float *base_score,
                         float *logprob, hipStream_t stream);
 
+// Grouping of ids, hidden update, output projection and query gather of few rows in one launch.
+struct FewStep {
+    int rows;                                  // rows, or raw queries (ids.key set: the launch groups the ids)
+    int N, K;
+    IdGroups ids;
+    const int32_t *prev_word;
+    const float *h_in;
+    const int32_t *query_word, *row_of_query;  // (row_of_query is not read with ids)
+    const float *base_score;
+    float *h_out, *logprob;
+    bool vec;                                  // rows of h_in in 16-byte pieces
+    uint32_t inverse_K;                        // ceil(2^32 / K), for K > 1
+    // query that pair p (word p % K of query p / K) belongs to: exact while N * K * K < 2^32
+    __host__ __device__ int query_of(int p) const { return K == 1 ? p : (int)(((uint64_t)(uint32_t)p * inverse_K) >> 32); }
+};
+bool step_few_supported(int dtype, int Hp);               // the model gets a Wfrag
+bool step_few_chosen(const ModelDev &m, int rows, bool grouped);
+hipError_t launch_step_few(const ModelDev &m, const FewStep &a, bool fixed_offset, hipStream_t stream);
+// the output projection takes the weight-streaming kernel by itself, in one launch
+bool outproj_streams_in_one_launch(const ModelDev &m, int rows, int kernel_choice);
+
 // The same through a cache (after launch_cache_lookup and the computation of the histories not
 // found): found histories take h' and lse from the stores, and the first raw query of every distinct
 // history passes its h' on (to h_out when found, into the store with its lse when it got an entry),
@@ -308,6 +334,8 @@ hipError_t launch_col_stats(const void *O_dev, const float *bias_or_null, int dt
                             float *half_colsum /*[V]*/, float *upper /*[V]*/, float *lower /*[V]*/,
                             hipStream_t stream);
 hipError_t launch_frag_weights(const void *Ot /*[Vp][Hp] bf16*/, int Vp, int Hp, void *Ofrag, hipStream_t stream);
+// W [Hp][Hp] in the order of Wfrag
+hipError_t launch_frag_recurrent(const void *W, int dtype, int Hp, void *Wfrag, hipStream_t stream);
 hipError_t launch_split2_weights(const float *Ot /*[Vp][Hp]*/, int Vp, int Hp, void *Ofrag, float *ofac /*[Vp]*/,
                                  hipStream_t stream);
 hipError_t launch_fill_cvec(const float *bias_or_null, const float *half_colsum, int V, int Vp,
