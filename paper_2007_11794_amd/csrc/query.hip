@@ -23,8 +23,8 @@ namespace {
 constexpr int kQueryBatch = 8;
 
 // A workgroup of four waves serves QPW raw queries (4, 2 or 1): with few words per query a
-// whole wave per query keeps the eight-row batches full; with many, the four waves share
-// one query's words.  Nothing branches on loaded values before the stores, so the loads of
+// whole wave per query keeps the eight-row batches full; with many words and few queries, the four waves share
+// one query's words (launch_query_typed).  Nothing branches on loaded values before the stores, so the loads of
 // a batch (row index, word ids, their bias and base score, the partials, eight weight rows,
 // the hidden row) are in flight together.
 __device__ __forceinline__ void store8_row(float *row, int k0, int H, bool vec_ok, const float (&v)[8]) {
@@ -161,15 +161,20 @@ void launch_query_typed(const ModelDev &m, int rows, const int *B_dev, int N, in
                         const int32_t *query_word, const int32_t *row_of_query, float *h_out,
                         const float *lse_rows, const float *base_score, float *logprob, const CacheDev &c,
                         const int32_t *rep, hipStream_t stream) {
-    if (K <= kQueryBatch)
-        hipLaunchKernelGGL((query_kernel<T, 4, CACHED>), dim3((N + 3) / 4), dim3(256), 0, stream, m, rows, B_dev, N,
-                           K, splits, query_word, row_of_query, h_out, lse_rows, base_score, logprob, c, rep);
-    else if (K <= 2 * kQueryBatch)
-        hipLaunchKernelGGL((query_kernel<T, 2, CACHED>), dim3((N + 1) / 2), dim3(256), 0, stream, m, rows, B_dev, N,
-                           K, splits, query_word, row_of_query, h_out, lse_rows, base_score, logprob, c, rep);
-    else
-        hipLaunchKernelGGL((query_kernel<T, 1, CACHED>), dim3(N), dim3(256), 0, stream, m, rows, B_dev, N, K, splits,
+    // A wave per eight words of a query, four at most, as long as the waves of all queries fit the chip at once (256 compute units of
+    // sixteen): beyond, fewer waves in longer rounds, not more rounds of workgroups.  Us per launch with 4 / 2 / 1 waves per query, H = 512:
+    // 1024 queries of 32 words 5.2 / 4.9 / 7.1, 2048 of 18, 32, 64 7.9 / 6.6 / 6.8, 8.2 / 6.8 / 8.1, 12.1 / 10.5 / 13.1; 4096 of 10, 18, 32, 64
+    // - / 7.9 / 7.3, 14.1 / 11.7 / 9.1, 13.9 / 11.8 / 10.9, 22.3 / 19.6 / 18.9; H = 1024, 2048 of 64 18.4 / 17.3 / 21.9.
+    int waves = K <= kQueryBatch ? 1 : K <= 2 * kQueryBatch ? 2 : 4;
+    while (waves > 1 && (long long)N * waves > 4096) waves /= 2;
+    auto launch = [&](auto kernel) {
+        const int queries = 4 / waves;                   // of a workgroup
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(((long long)N + queries - 1) / queries)), dim3(256), 0, stream, m, rows, B_dev, N, K, splits,
                            query_word, row_of_query, h_out, lse_rows, base_score, logprob, c, rep);
+    };
+    if (waves == 1) launch(query_kernel<T, 4, CACHED>);
+    else if (waves == 2) launch(query_kernel<T, 2, CACHED>);
+    else launch(query_kernel<T, 1, CACHED>);
 }
 }  // namespace
 
