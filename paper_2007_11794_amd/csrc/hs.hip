@@ -118,18 +118,21 @@ typedef HsShape<128, 9, 256, 64> HsSmall;
 // 19.8 / 23.5), and with the large shape only once the words' nodes are more than one round of half as many threads: kernel at V =
 // 250000, H = 128, bf16, 100 queries of 17 words 0.3 slower, 24 words 0.3 faster, 32 words 1.3 faster; rows that are not 16-byte
 // aligned, which every wave reads for itself, H = 75, 17, 24 and 32 words 1.0, 0.3 and 0.5 slower; V = 60000, H = 256, 17 words 1.0
-// faster, H = 250 0.3 slower, 24 words 0.3 faster.
+// faster, H = 250 0.3 slower, 24 words 0.3 faster.  Steps at Hp = 64 and 192, which have several rows in a wave's round as well: V =
+// 250000, H = 64, fp32, 512 queries of 15 words 13.2 / 9.8 with the narrow shape, of 30 14.9 / 12.1; V = 60000, H = 192, bf16, 256 queries
+// of 30 words 10.5 with the wide one, of 15 words 10.3 wide, 10.9 narrow.
 typedef HsShape<512, 11, 1024, 256> HsLargeWide;
 typedef HsShape<256, 9, 256, 64> HsSmallWide;
 inline bool hs_wide(int N, int K, int H, int Hp, bool small) {
-    if (Hp != 128 && Hp != 256) return N <= 512;
+    if (Hp > 256) return N <= 512;
     const bool aligned = H % 4 == 0;
-    return N <= 256 && (small || (Hp == 128 ? aligned && K >= 24 : K >= (aligned ? 16 : 24)));
+    return N <= 256 && (small || (Hp <= 128 ? aligned && K >= 24 : K >= (aligned ? 16 : 24)));
 }
 
-// Dot products of the distinct nodes for a short hidden vector (Hp = 8 * LPR elements, LPR = 16 or
-// 32): a node row takes only LPR lanes of a wave, so the wave works on 64 / LPR rows side by side,
-// eight per lane group in flight: 32 (16) rows per wave and round trip to memory instead of 8.  Lane
+// Dot products of the distinct nodes for a short hidden vector (Hp = 8 * LPR elements at most, LPR = 16 or
+// 32; lanes beyond the row drop what they compute): a node row takes only LPR lanes of a wave, so the wave works on 64 / LPR rows side by side,
+// eight per lane group in flight: 32 (16) rows per wave and round trip to memory instead of 8 (steps at H = 64, fp32, V = 250000, 4096
+// queries of 30 words, a wave per eight rows / this 70.6 / 42.9 us, 32 queries 12.5 / 9.7; H = 192, bf16, V = 60000 58.9 / 40.7, 12.0 / 10.2).  Lane
 // group g of wave w takes the nodes d = first + g + G * u, u = 0..7; the eight sums of a group are
 // reduced together (a lane passes on the half it will not finish, as in wave_sum8).
 template <typename T, int LPR, int THREADS>
@@ -137,7 +140,9 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *
                                                    const int *dnode, float *dx, int D, int wave, int lane) {
     static_assert(LPR == 16 || LPR == 32, "");
     constexpr int G = 64 / LPR, kPerWave = G * kHsBatch;
-    const int g = lane / LPR, sl = lane % LPR, j0 = sl * 8;
+    const int g = lane / LPR, sl = lane % LPR;
+    const bool in_row = sl * 8 < Hp;
+    const int j0 = in_row ? sl * 8 : 0;
     float h8[8];
     load8_row(hrow, j0, H, vec_ok, 0.f, h8);
     constexpr int top = LPR / 2;                           // 8 or 16
@@ -159,6 +164,7 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *
             acc[u] = 0.f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[u] = fmaf(w8[u][i], h8[i], acc[u]);
+            acc[u] = in_row ? acc[u] : 0.f;
         }
         // three levels that halve the number of values a lane carries, then the rest of the butterfly
         float v4[4], v2[2], x, y;
@@ -186,7 +192,7 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *
     }
 }
 
-// LPR: lanes per node row of the short-row form (16: Hp = 128, 32: Hp = 256), 0: any hidden size.
+// LPR: lanes per node row of the short-row form (16: Hp <= 128, 32: Hp <= 256), 0: any hidden size.
 // Kernels of their own, so that the registers of the short-row form do not cost the general one occupancy.
 template <typename T, int LPR, class S>
 __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
@@ -348,8 +354,8 @@ hipError_t launch_hs_query(const ModelDev &m, int rows, const int *B_dev, int N,
         auto pick_rows = [&](auto tag, auto shape) {
             using T = decltype(tag);
             using S = decltype(shape);
-            if (m.Hp == 128) launch(hs_query_shared_kernel<T, 16, S>, S::kThreads);
-            else if (m.Hp == 256) launch(hs_query_shared_kernel<T, 32, S>, S::kThreads);
+            if (m.Hp <= 128) launch(hs_query_shared_kernel<T, 16, S>, S::kThreads);
+            else if (m.Hp <= 256) launch(hs_query_shared_kernel<T, 32, S>, S::kThreads);
             else launch(hs_query_shared_kernel<T, 0, S>, S::kThreads);
         };
         const bool wide = hs_wide(N, K, m.H, m.Hp, small);
