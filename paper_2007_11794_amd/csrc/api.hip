@@ -719,6 +719,14 @@ int rnnlm_hs_step(const rnnlm_model *model, int B, int K, const int32_t *prev_wo
     if (B > 0 && ranges_overlap(h_in, h_out, (size_t)B * model->dev.H)) return RNNLM_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const ModelDev &d = model->dev;
+    if (hs_step_chosen(d, B, N, K, row_of_query_or_null != nullptr)) {
+        const size_t h_bytes = (size_t)B * d.H * 4, nk = (size_t)N * K * 4;
+        const Bytes ins[] = {{prev_word, (size_t)B * 4}, {h_in, h_bytes}, {query_word, nk}, {row_of_query_or_null, (size_t)N * 4}, {base_score_or_null, nk}};
+        const Bytes outs[] = {{h_out, h_bytes}, {logprob, nk}};
+        if (!outputs_overlap(ins, outs))
+            return launch_hs_step(d, B, N, K, prev_word, h_in, query_word, row_of_query_or_null, h_out, base_score_or_null, logprob, s) == hipSuccess
+                       ? RNNLM_OK : RNNLM_EDEVICE;
+    }
     if (launch_recur(recur_view(model, B), B, nullptr, nullptr, nullptr, prev_word, h_in, h_out, IdGroups{}, s) != hipSuccess)
         return RNNLM_EDEVICE;
     if (launch_hs_query(d, B, nullptr, N, K, query_word, row_of_query_or_null, h_out, base_score_or_null, logprob,

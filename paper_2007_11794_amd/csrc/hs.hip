@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "device_utils.h"
+#include "recur_math.h"
 #include "rnnlm_internal.h"
 
 namespace rnnlm {
@@ -27,6 +28,9 @@ __device__ __forceinline__ float log_sigmoid_f32(float x) {
     const float t = fast_exp2(-fabsf(x) * kLog2e);
     return fminf(x, 0.f) - fast_log2(1.0f + t) * kLn2;
 }
+
+__device__ __forceinline__ float weight_f32(bf16_t w) { return bf16_to_f32(w); }
+__device__ __forceinline__ float weight_f32(float w) { return w; }
 
 template <typename T>
 __global__ __launch_bounds__(256) void hs_query_kernel(
@@ -135,16 +139,14 @@ inline bool hs_wide(int N, int K, int H, int Hp, bool small) {
 // queries of 30 words, a wave per eight rows / this 70.6 / 42.9 us, 32 queries 12.5 / 9.7; H = 192, bf16, V = 60000 58.9 / 40.7, 12.0 / 10.2).  Lane
 // group g of wave w takes the nodes d = first + g + G * u, u = 0..7; the eight sums of a group are
 // reduced together (a lane passes on the half it will not finish, as in wave_sum8).
-template <typename T, int LPR, int THREADS>
-__device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *hrow, int H, int Hp, bool vec_ok,
-                                                   const int *dnode, float *dx, int D, int wave, int lane) {
+// row(d): which row of the weights; asked for d < D.
+template <typename T, int LPR, int THREADS, class Row>
+__device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float (&h8)[8], int Hp, Row row, float *dx, int D, int wave, int lane) {
     static_assert(LPR == 16 || LPR == 32, "");
     constexpr int G = 64 / LPR, kPerWave = G * kHsBatch;
     const int g = lane / LPR, sl = lane % LPR;
     const bool in_row = sl * 8 < Hp;
     const int j0 = in_row ? sl * 8 : 0;
-    float h8[8];
-    load8_row(hrow, j0, H, vec_ok, 0.f, h8);
     constexpr int top = LPR / 2;                           // 8 or 16
     const bool upa = (lane & top) != 0, upb = (lane & (top / 2)) != 0, upc = (lane & (top / 4)) != 0;
     const int u_mine = (upa ? 4 : 0) + (upb ? 2 : 0) + (upc ? 1 : 0);
@@ -153,7 +155,7 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *
 #pragma unroll
         for (int u = 0; u < kHsBatch; ++u) {
             const int d = first + g + G * u;
-            const int node = d < D ? dnode[d] : 0;
+            const int node = d < D ? row(d) : 0;
             load8_weights(Theta, (size_t)node * Hp + j0, w8[u]);
         }
     };
@@ -194,11 +196,19 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float *
 
 // LPR: lanes per node row of the short-row form (16: Hp <= 128, 32: Hp <= 256), 0: any hidden size.
 // Kernels of their own, so that the registers of the short-row form do not cost the general one occupancy.
-template <typename T, int LPR, class S>
+// HERE (short rows only): the hidden update is part of the launch.  A workgroup computes the hidden vector of its query's row for
+// itself, in plain fp32, while its words' paths are on their way: W (Hp x Hp) comes through the same row dot products.  Without
+// row_of_query it also writes the row out; with it, `rows` further workgroups do.
+struct HsHidden {
+    const int32_t *prev_word;
+    const float *h_in;
+    float *h_out;
+};
+template <typename T, int LPR, class S, bool HERE>
 __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
     ModelDev m, int rows, const int *__restrict__ B_dev, int N, int K,
     const int32_t *__restrict__ query_word, const int32_t *__restrict__ row_of_query,
-    const float *__restrict__ h_out, const float *__restrict__ base_score, float *__restrict__ logprob) {
+    const float *__restrict__ h_out, const float *__restrict__ base_score, float *__restrict__ logprob, HsHidden hidden) {
     __shared__ int wbase[S::kMaxK + 1];               // start of word k's entries
     __shared__ int woff[S::kMaxK];                    // where word k's path starts in the model's entries
     __shared__ uint16_t eslot[S::kMaxEntries];        // entry -> table slot of its node | code bit << 15
@@ -208,18 +218,26 @@ __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
     __shared__ float dx[S::kMaxEntries];              // their dot products
     __shared__ int dcount;
     __shared__ int wsum[S::kThreads / 64 + 1];
+    __shared__ __attribute__((aligned(16))) float hvec[HERE ? 8 * LPR : 4];        // W (h - 1/2), then the hidden vector, zeros beyond H
     static_assert(S::kTable <= 32768, "slot index and code bit share sixteen bits");
     static_assert(S::kMaxK <= S::kThreads, "one word per thread in step 1");
     const int B = B_dev ? *B_dev : rows;
-    const int n = blockIdx.x;
+    const bool query = !HERE || (int)blockIdx.x < N;        // (HERE) or a row that only has to be written
+    const int n = query ? blockIdx.x : 0;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int H = m.H, Hp = m.Hp;
-    const int r_raw = row_of_query ? row_of_query[n] : n;
+    const int r_raw = !query ? blockIdx.x - N : row_of_query ? row_of_query[n] : n;
     const bool r_ok = r_raw >= 0 && r_raw < B;
     const int r = r_ok ? r_raw : 0;
+    int word_before = 0;
+    float h8[8];
+    if constexpr (HERE) {
+        word_before = hidden.prev_word[r];
+        load8_row(hidden.h_in + (size_t)r * H, 8 * (lane % LPR), H, (H % 4) == 0 && (reinterpret_cast<uintptr_t>(hidden.h_in) & 15) == 0, 0.5f, h8);
+    }
     // 1. lengths of the K paths -> offsets (K <= 256: one word per thread)
     int len = 0;
-    if (tid < K) {
+    if (query && tid < K) {
         const int q_raw = query_word[(size_t)n * K + tid];
         const int q = (q_raw >= 0 && q_raw < m.V) ? q_raw : 0;
         const int o = m.path_off[q];
@@ -228,10 +246,35 @@ __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
     }
     for (int i = tid; i < S::kTable; i += S::kThreads) tnode[i] = -1;
     if (tid == 0) dcount = 0;
+    float embedding = 0.f, half_rowsum = 0.f;
+    const bool word_ok = word_before >= 0 && word_before < m.V;
+    if constexpr (HERE) {
+        if (tid < Hp) {                                    // (further units below)
+            embedding = weight_f32(static_cast<const T *>(m.U)[(size_t)(word_ok ? word_before : 0) * Hp + tid]);
+            half_rowsum = m.half_rowsum_W[tid];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h8[i] -= 0.5f;
+        hs_dots_short_rows<T, LPR, S::kThreads>(static_cast<const T *>(m.W), h8, Hp, [](int d) { return d; }, hvec, Hp, wave, lane);
+    }
     int total;
     const int mybase = block_exclusive_scan(len, wsum, total);      // barriers inside
     if (tid < K) wbase[tid] = mybase;
     if (tid == 0) wbase[K] = total;
+    if constexpr (HERE) {                                  // (the sums were there with the scan's barriers)
+        const bool writes = query ? !row_of_query : true;
+        for (int j = tid; j < Hp; j += S::kThreads) {
+            if (j != tid) {
+                embedding = weight_f32(static_cast<const T *>(m.U)[(size_t)(word_ok ? word_before : 0) * Hp + j]);
+                half_rowsum = m.half_rowsum_W[j];
+            }
+            const float h = word_ok ? sigmoid_f32(hvec[j] + half_rowsum + embedding) : quiet_nan();
+            hvec[j] = j < H ? h : 0.f;
+            if (writes && j < H) hidden.h_out[(size_t)r * H + j] = h;
+        }
+        if (writes && !word_ok && tid == 0) atomicOr(m.flag, RNNLM_FLAG_BAD_PREV_WORD);
+        if (!query) return;                                // uniform
+    }
     __syncthreads();
     // 2. distinct nodes (a thread per path entry, all entries of a thread requested before the first
     //    is used: one round trip to memory for the whole query): the thread whose insertion claims
@@ -278,8 +321,16 @@ __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
     const float *hrow = h_out + (size_t)r * H;
     const bool vec_ok = (H % 4) == 0;
     const int umine = batch_slot_of_lane(lane);
-    if constexpr (LPR != 0) hs_dots_short_rows<T, LPR, S::kThreads>(Theta, hrow, H, Hp, vec_ok, dnode, dx, D, wave, lane);
-    else
+    if constexpr (LPR != 0) {
+        if constexpr (HERE) {
+            const f32x4 lo = *reinterpret_cast<const f32x4 *>(hvec + 8 * (lane % LPR)), hi = *reinterpret_cast<const f32x4 *>(hvec + 8 * (lane % LPR) + 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { h8[i] = lo[i]; h8[4 + i] = hi[i]; }      // (lanes beyond the row drop what they compute)
+        } else {
+            load8_row(hrow, 8 * (lane % LPR), H, vec_ok, 0.f, h8);
+        }
+        hs_dots_short_rows<T, LPR, S::kThreads>(Theta, h8, Hp, [&](int d) { return dnode[d]; }, dx, D, wave, lane);
+    } else
     for (int d0 = wave * kHsBatch; d0 < D; d0 += (S::kThreads / 64) * kHsBatch) {
         const int node_mine = (d0 + umine < D) ? dnode[d0 + umine] : 0;
         int node[kHsBatch];
@@ -340,35 +391,57 @@ __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
 
 }  // namespace
 
+// Several words per query, few enough path entries: one workgroup per raw query, shared path nodes computed once.
+static bool hs_shared(const ModelDev &m, int K) { return K >= 4 && K <= HsLarge::kMaxK && (long long)K * m.hs_max_len <= HsLarge::kMaxEntries; }
+
+template <bool HERE>
+static hipError_t launch_shared(const ModelDev &m, int rows, const int *B_dev, int N, int K, const int32_t *query_word, const int32_t *row_of_query,
+                                const float *h_out, const float *base_score, float *logprob, const HsHidden &hidden, hipStream_t stream) {
+    const bool small = K <= HsSmall::kMaxK && (long long)K * m.hs_max_len <= HsSmall::kMaxEntries;
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(HERE && row_of_query ? N + rows : N), dim3(threads), 0, stream, m, rows, B_dev, N, K, query_word,
+                           row_of_query, h_out, base_score, logprob, hidden);
+    };
+    auto pick_rows = [&](auto tag, auto shape) {
+        using T = decltype(tag);
+        using S = decltype(shape);
+        if (m.Hp <= 128) launch(hs_query_shared_kernel<T, 16, S, HERE>, S::kThreads);
+        else if (HERE || m.Hp <= 256) launch(hs_query_shared_kernel<T, 32, S, HERE>, S::kThreads);
+        else if constexpr (!HERE) launch(hs_query_shared_kernel<T, 0, S, HERE>, S::kThreads);
+    };
+    const bool wide = hs_wide(N, K, m.H, m.Hp, small);
+    auto pick = [&](auto tag) {
+        if (small && wide) pick_rows(tag, HsSmallWide{});
+        else if (small) pick_rows(tag, HsSmall{});
+        else if (wide) pick_rows(tag, HsLargeWide{});
+        else pick_rows(tag, HsLarge{});
+    };
+    if (m.dtype == RNNLM_BF16) pick(bf16_t{});
+    else pick(float{});
+    return hipGetLastError();
+}
+
+// Every workgroup reads W: while that is little beside its nodes' rows, and the workgroups are few.  Replayed steps, us, two launches
+// / this one (the host's part, 9.3 us for two launches, 6 to 7 for one, is not in it): bf16, V = 250000, H = 128, 64 queries of 30 words
+// 9.7 / 7.8, 1024 of 6, 30 9.8 / 8.3, 13.1 / 11.7, 2048 of 30 19.5 / 20.3; fp32, V = 60000, H = 128, 512 of 30 11.4 / 9.8, 1024 17.7 /
+// 18.3; V = 60000, H = 256, bf16, 200 of 6, 30 9.5 / 7.9, 10.4 / 8.1, 512 11.2 / 13.2, 12.9 / 12.1, fp32 200 of 30 11.8 / 9.1, 512 of
+// 6 from 153 rows 11.9 / 13.1.
+bool hs_step_chosen(const ModelDev &m, int B, int N, int K, bool mapped) {
+    if (m.Hp > 256 || B <= 0 || N <= 0 || !hs_shared(m, K)) return false;
+    const int limit = m.Hp > 128 ? 256 : m.dtype == RNNLM_BF16 ? 1024 : 512;
+    return N <= limit && (!mapped || N + B <= limit + limit / 2);
+}
+
+hipError_t launch_hs_step(const ModelDev &m, int B, int N, int K, const int32_t *prev_word, const float *h_in, const int32_t *query_word,
+                          const int32_t *row_of_query, float *h_out, const float *base_score, float *logprob, hipStream_t stream) {
+    return launch_shared<true>(m, B, nullptr, N, K, query_word, row_of_query, h_out, base_score, logprob, HsHidden{prev_word, h_in, h_out}, stream);
+}
+
 hipError_t launch_hs_query(const ModelDev &m, int rows, const int *B_dev, int N, int K,
                            const int32_t *query_word, const int32_t *row_of_query, const float *h_out,
                            const float *base_score, float *logprob, hipStream_t stream) {
     if (N <= 0 || K <= 0) return hipSuccess;
-    if (K >= 4 && K <= HsLarge::kMaxK && (long long)K * m.hs_max_len <= HsLarge::kMaxEntries) {
-        // several words per query: one workgroup per raw query, shared path nodes computed once
-        const bool small = K <= HsSmall::kMaxK && (long long)K * m.hs_max_len <= HsSmall::kMaxEntries;
-        auto launch = [&](auto kernel, int threads) {
-            hipLaunchKernelGGL(kernel, dim3(N), dim3(threads), 0, stream, m, rows, B_dev, N, K, query_word,
-                               row_of_query, h_out, base_score, logprob);
-        };
-        auto pick_rows = [&](auto tag, auto shape) {
-            using T = decltype(tag);
-            using S = decltype(shape);
-            if (m.Hp <= 128) launch(hs_query_shared_kernel<T, 16, S>, S::kThreads);
-            else if (m.Hp <= 256) launch(hs_query_shared_kernel<T, 32, S>, S::kThreads);
-            else launch(hs_query_shared_kernel<T, 0, S>, S::kThreads);
-        };
-        const bool wide = hs_wide(N, K, m.H, m.Hp, small);
-        auto pick = [&](auto tag) {
-            if (small && wide) pick_rows(tag, HsSmallWide{});
-            else if (small) pick_rows(tag, HsSmall{});
-            else if (wide) pick_rows(tag, HsLargeWide{});
-            else pick_rows(tag, HsLarge{});
-        };
-        if (m.dtype == RNNLM_BF16) pick(bf16_t{});
-        else pick(float{});
-        return hipGetLastError();
-    }
+    if (hs_shared(m, K)) return launch_shared<false>(m, rows, B_dev, N, K, query_word, row_of_query, h_out, base_score, logprob, HsHidden{}, stream);
     const long long pairs = (long long)N * K;
     const dim3 grid((unsigned)((pairs + 3) / 4));
     if (m.dtype == RNNLM_BF16)

@@ -322,6 +322,10 @@ hipError_t launch_index_fetch(const IndexDev &t, int N, const uint32_t *index, i
 hipError_t launch_hs_query(const ModelDev &m, int rows, const int *B_dev, int N, int K,
                            const int32_t *query_word, const int32_t *row_of_query, const float *h_out,
                            const float *base_score, float *logprob, hipStream_t stream);
+// The same with the hidden update in the launch (mapped: row_of_query is given).
+bool hs_step_chosen(const ModelDev &m, int B, int N, int K, bool mapped);
+hipError_t launch_hs_step(const ModelDev &m, int B, int N, int K, const int32_t *prev_word, const float *h_in, const int32_t *query_word,
+                          const int32_t *row_of_query, float *h_out, const float *base_score, float *logprob, hipStream_t stream);
 hipError_t launch_pack_ids(const uint32_t *ctx, const uint32_t *small_lm, int N, uint64_t *ids,
                            hipStream_t stream);
 
