@@ -68,11 +68,23 @@ __device__ __forceinline__ bool claim_cell(int *claims, int claim_slots, uint32_
     }
 }
 
+// What the lookup adds to, requested in front of the grouping: the counters are a trip to memory at its beginning and, in the
+// one thread that ends the launch, another one behind everything else (with the prefix sums in registers, 4096 ids, 410 distinct 9.0
+// -> 8.2 us, 3631, 1089 distinct 11.3 -> 10.2).
+struct CacheCounts {
+    int entries;
+    long long totals[4];                    // thread 0
+    __device__ __forceinline__ explicit CacheCounts(const CacheDev &c) : entries(*c.n_entries) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) totals[i] = threadIdx.x == 0 ? c.totals[i] : 0;
+    }
+};
+
 template <typename RawOf, typename KeyOf>
-__device__ __forceinline__ void cache_lookup_body(const CacheDev &c, int U, int32_t *__restrict__ step_stats,
+__device__ __forceinline__ void cache_lookup_body(const CacheDev &c, const CacheCounts &counts, int U, int32_t *__restrict__ step_stats,
                                                   int *claims, int claim_slots, RawOf raw_of, KeyOf key_of) {
     __shared__ int wsum[kLookupThreads / 64 + 1];
-    const int base = *c.n_entries;          // read by everyone before thread 0 updates it below
+    const int base = counts.entries;        // read by everyone before thread 0 updates it below
     const uint32_t mask = (uint32_t)(c.table_size - 1);
     int n_miss = 0;                         // misses numbered so far (same in every thread)
     for (int i = threadIdx.x; i < claim_slots; i += kLookupThreads) claims[i] = -1;   // barriers before the first claim
@@ -149,10 +161,10 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, int U, int3
         const int stored = min(n_miss, max(c.capacity - base, 0));
         *c.n_miss = n_miss;
         *c.n_entries = base + stored;
-        c.totals[0] += U;
-        c.totals[1] += U - n_miss;
-        c.totals[2] += n_miss;
-        c.totals[3] += n_miss - stored;
+        c.totals[0] = counts.totals[0] + U;
+        c.totals[1] = counts.totals[1] + U - n_miss;
+        c.totals[2] = counts.totals[2] + n_miss;
+        c.totals[3] = counts.totals[3] + n_miss - stored;
         if (step_stats) {
             step_stats[0] = U;
             step_stats[1] = U - n_miss;
@@ -169,10 +181,11 @@ static_assert(kLookupThreads == kSmallThreads, "");
 __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_kernel(
     CacheDev c, const uint64_t *__restrict__ ids, int N, int32_t *__restrict__ rep,
     int32_t *__restrict__ inverse, int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats) {
+    const CacheCounts counts(c);
     const SmallGroups g = dedup_small_body(ids, N, rep, inverse, n_unique);
     __syncthreads();                        // the groups in LDS are complete
     cache_lookup_body(
-        c, g.total, step_stats, g.spare, kSmallCap, [&](int, int, int u) { return g.rep[u]; },
+        c, counts, g.total, step_stats, g.spare, kSmallCap, [&](int, int, int u) { return g.rep[u]; },
         [&](int, int, int u, int) { return g.id[u]; });
 }
 
@@ -180,10 +193,11 @@ __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_kernel(
 __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_medium_kernel(
     CacheDev c, const uint64_t *__restrict__ ids, int N, int32_t *__restrict__ rep,
     int32_t *__restrict__ inverse, int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats) {
+    const CacheCounts counts(c);
     const MediumGroups g = dedup_medium_body(ids, N, rep, inverse, n_unique);
     __syncthreads();                        // the representatives in LDS are complete
     cache_lookup_body(
-        c, g.total, step_stats, g.spare, kMediumCap - kMediumN, [&](int, int, int u) { return g.rep[u]; },
+        c, counts, g.total, step_stats, g.spare, kMediumCap - kMediumN, [&](int, int, int u) { return g.rep[u]; },
         [&](int, int, int, int raw) { return g.key[raw]; });
 }
 
