@@ -44,6 +44,12 @@
 //   below at multiples of 128: as before (54 us at V = 65536, H = 512, 1024 rows).
 // Beyond 704 the hidden block and the accumulators do not fit the 256 registers of a wave.
 //
+// The last row group is rarely full.  A wave without rows takes part in the loads and barriers only, so the others have the matrix
+// pipes to themselves: alone on its SIMD a wave is nearly twice as fast.  Us per launch, all waves multiplying / this: V = 65536,
+// H = 512, 70, 128, 300, 384, 600, 1229 rows 20.5 / 15.0, 18.5 / 15.3, 26.2 / 21.7, 26.4 / 23.3, 38.2 / 33.7, 61.3 / 60.3; V = 100390, H = 448,
+// 100 rows 21.2 / 17.0, 513 51.8 / 43.2; V = 30011, H = 650, running maximum, 97, 317 rows 15.6 / 11.9, 21.8 / 20.4 (18.7 as groups of 128:
+// staged_split).  Full groups: the same.
+//
 // When the batch turns out to hold at most 64 rows (the count may be known on the device only),
 // the kernel runs the weight-streaming body instead (outproj_stream_body.h): see the top of
 // the kernel.
@@ -71,6 +77,7 @@ struct StagedCfg {
     static constexpr int KS = HP / 16;                       // MFMA k-steps per block
     static constexpr bool kRowOrder = HP % 128 == 0 && HP <= 512;       // weights from Ot, else from Ofrag
     static constexpr bool kScaledD = staged_scaled_d(HP);
+    static constexpr bool kHalves = HP > 512;                           // groups of 128 rows where they pay (staged_split)
     static constexpr int CPR = HP / 8;                                  // 16-byte chunks per word row
     static constexpr int kStages = HP <= 512 ? 4 : 3;                  // as LDS allows
     static constexpr int kLoadsPerThread = (KS + 7) / 8;                // weight loads per block: 8 KB each
@@ -413,7 +420,7 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
 // of 2^(logit - offset) over the item's words for this lane's half of its row.
 template <int HP>
 __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds, char *cring, const Loader<HP> &loader,
-                                                   const FragOffsets<HP> &aoff, int rg, int blk0, int nblk, int wave,
+                                                   const FragOffsets<HP> &aoff, int row0, int blk0, int nblk, int wave,
                                                    int lane, int g) {
     using C = StagedCfg<HP>;
     constexpr int KS = C::KS;
@@ -428,7 +435,7 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
     bf16x8 dreg[KS];
     FirstBlockLoads first;
     // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row
-    first.dfr = static_cast<const bf16_t *>(m.dfrag) + ((size_t)(rg * (kStagedRows / 32) + wave) * KS * 64 + lane) * 8;
+    first.dfr = static_cast<const bf16_t *>(m.dfrag) + ((size_t)(row0 / 32 + wave) * KS * 64 + lane) * 8;
     static_for<0, F::D0>([&](auto j) __attribute__((always_inline)) {
         load_d_operand_at<decltype(j)::value>(dreg[decltype(j)::value], first.dfr);
     });
@@ -486,6 +493,40 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
     return srun;
 }
 
+// A wave without rows in an item: its share of the loads and all barriers, as staged_item_fixed has them (block 0 is published by the
+// first barrier; the barrier of block bi publishes block bi + 1 and frees the stage of block bi - 1), and nothing else.  The matrix
+// pipes are left to the waves that have rows: with up to four of them each has one to itself.
+template <int HP>
+__device__ __forceinline__ void staged_item_fixed_loads(const ModelDev &m, uint32_t lds0, uint32_t cring0, const Loader<HP> &loader, int blk0, int nblk) {
+    using C = StagedCfg<HP>;
+    constexpr int NS = C::kStages;
+    const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
+    const float *cvec = C::kScaledD ? m.cvec2_fixed : m.cvec_fixed;
+    auto issue = [&](int bi) __attribute__((always_inline)) {            // always as many loads
+        const bool real = bi < nblk;
+        const int block = real ? blk0 + bi : 0;
+        const char *src = loader.block_of(weights, block);
+#pragma unroll
+        for (int q = 0; q < C::kLoadsPerThread; ++q) loader.issue_weights(src, q, real, lds0 + bi % NS * C::kStageBytes);
+        loader.issue_consts(cvec + (size_t)block * kStagedWords, cring0 + (bi & 7) * kCSlotBytes);
+    };
+    issue(0);
+    wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 1; i < NS - 1; ++i) issue(i);
+    for (int bi = 0; bi < nblk; ++bi) {
+        wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();                      // block bi + 1 has landed
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(bi + NS - 1);
+    }
+    wait_vmcnt<0>();                                                     // (dummies: the next item fills these stages)
+}
+
 template <int HP, bool FIXED>
 __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, int rows,
                                                                   const int *__restrict__ B_dev,
@@ -507,7 +548,8 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
         return;
     }
-    const StagedPlan plan = staged_plan(B, wg_per_xcd);
+    const StagedSplit split_of = staged_split(B, wg_per_xcd, C::kHalves);
+    const StagedPlan plan = split_of.plan;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, g = lane >> 5;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
     const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
@@ -524,10 +566,17 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         const int rg = item % plan.RG, split = xcd + kXcds * (item / plan.RG);
         const int blk0 = part_begin(split, T, plan.S);
         const int nblk = part_begin(split + 1, T, plan.S) - blk0;
-        const int b = rg * kStagedRows + wave * 32 + col;     // this lane's row
+        const int row0 = rg * split_of.rows;
+        const int b = row0 + wave * 32 + col;                 // this lane's row
+        const bool has_rows = (int)loader.wave * 32 < min(split_of.rows, B - row0);       // (wave-uniform)
+        if (FIXED && !has_rows) {
+            if (nblk > 0) staged_item_fixed_loads<HP>(m, lds0, cring0, loader, blk0, nblk);
+            __syncthreads();
+            continue;
+        }
         if (FIXED) {
             float srun = 0.f;
-            if (nblk > 0) srun = staged_item_fixed<HP>(m, lds, cring, loader, aoff, rg, blk0, nblk, wave, lane, g);
+            if (nblk > 0) srun = staged_item_fixed<HP>(m, lds, cring, loader, aoff, row0, blk0, nblk, wave, lane, g);
             srun += __shfl_xor(srun, 32, 64);                 // lanes l and l+32 hold the two halves of a row
             if (g == 0 && b < B) m.part[(size_t)b * kMaxSplits + split] = make_float2(m.m2_fixed, srun);
             __syncthreads();                                  // LDS is reused by the next item
@@ -540,11 +589,31 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         for (int i = 0; i < 2; ++i)
             if (i < nblk)
                 loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
+        if (!has_rows) {                                      // the loads and barriers of what follows
+            constexpr int NS = C::kStages;
+            wait_vmcnt<0>();
+            __syncthreads();
+#pragma unroll
+            for (int i = 2; i < NS; ++i)
+                if (i < nblk) loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
+            for (int bi = 1; bi < nblk; ++bi) {
+                if (bi + 2 < nblk) wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();
+                else wait_vmcnt<0>();
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                if (bi + NS - 1 < nblk)
+                    loader.issue(weights, cvec, blk0 + bi + NS - 1, lds0 + (bi + NS - 1) % NS * C::kStageBytes,
+                                 cring0 + ((bi + NS - 1) & 7) * kCSlotBytes);
+            }
+            __syncthreads();
+            continue;
+        }
         bf16x8 dreg[KS];
         {
             // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row
             const bf16_t *dfr = static_cast<const bf16_t *>(m.dfrag) +
-                                ((size_t)(rg * (kStagedRows / 32) + wave) * KS * 64 + lane) * 8;
+                                ((size_t)(row0 / 32 + wave) * KS * 64 + lane) * 8;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) dreg[ks] = *reinterpret_cast<const bf16x8 *>(dfr + (size_t)ks * 512);
         }
@@ -633,7 +702,7 @@ hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, 
                                  SplitInfo *splits, hipStream_t stream) {
     // One workgroup per compute unit: 256 CUs in 8 XCDs.
     const int wg_per_xcd = 32;
-    *splits = SplitInfo{0, wg_per_xcd, kStagedRows, kMaxSplits / kXcds, 0, 0};
+    *splits = SplitInfo{0, wg_per_xcd, m.Hp > 512 ? 0 : kStagedRows, kMaxSplits / kXcds, 0, 0};
     switch (m.Hp) {
         case 128: return launch_hp<128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
         case 192: return launch_hp<192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);

@@ -216,6 +216,19 @@ typedef RowPlan StagedPlan;
 __host__ __device__ inline StagedPlan staged_plan(int B, int wg_per_xcd) {
     return plan_rows(B, kStagedRows, wg_per_xcd, kMaxSplits / kXcds);
 }
+// The staged kernel's row groups: 256 rows.  Beyond Hp = 512, three groups of 128 (four of a workgroup's eight waves each, with a
+// matrix pipe to itself) where two of 256 would leave one less than half full.  Us per launch, 256 / 128, V = 30011, H = 650: 257, 300, 384
+// rows 17.4 / 16.3, 17.5 / 16.2, 18.8 / 17.1, running maximum 20.9 / 19.0, 21.1 / 18.6, 21.8 / 19.4.  Not for five groups instead of
+// three (600 rows 24.3 / 24.2) and not below (V = 65536, H = 512, 300 rows 23.1 / 22.7, 600 35.2 / 36.4; V = 20000, H = 256, 300 rows 6.6 / 6.8).
+struct StagedSplit {
+    StagedPlan plan;
+    int rows;              // of a group
+};
+__host__ __device__ inline StagedSplit staged_split(int B, int wg_per_xcd, bool halves) {
+    if (halves && B > kStagedRows && B <= 3 * kStagedRows / 2)
+        return StagedSplit{plan_rows(B, kStagedRows / 2, wg_per_xcd, kMaxSplits / kXcds), kStagedRows / 2};
+    return StagedSplit{staged_plan(B, wg_per_xcd), kStagedRows};
+}
 
 // How many (max, sum) partials per row the output projection left in m.part: a fixed number, or
 // the S of plan_rows for the true number of rows; a kernel that streams the weights when at most
@@ -223,7 +236,7 @@ __host__ __device__ inline StagedPlan staged_plan(int B, int wg_per_xcd) {
 struct SplitInfo {
     int fixed_splits;      // > 0: that many
     int wg_per_xcd;        // else plan_rows(B, group_rows, wg_per_xcd, sx_cap).S
-    int group_rows;
+    int group_rows;        // 0: staged_split(B, wg_per_xcd, true).plan.S
     int sx_cap;
     int stream_rows;       // 0 < B <= stream_rows: stream_splits instead (0: every workgroup of the grid has one)
     int stream_splits;
@@ -231,6 +244,7 @@ struct SplitInfo {
 __host__ __device__ inline int splits_of(const SplitInfo &si, int B) {
     if (si.fixed_splits > 0) return si.fixed_splits;
     if (B > 0 && B <= si.stream_rows) return si.stream_splits > 0 ? si.stream_splits : kXcds * si.wg_per_xcd;
+    if (si.group_rows == 0) return staged_split(B, si.wg_per_xcd, true).plan.S;
     return plan_rows(B, si.group_rows, si.wg_per_xcd, si.sx_cap).S;
 }
 __host__ inline SplitInfo fixed_split_info(int S) { return SplitInfo{S, 0, 1, 1, 0, 0}; }
