@@ -535,8 +535,10 @@ int rnnlm_step_cached(const rnnlm_model *model, rnnlm_cache *cache, int N, int K
             if (!workspace || workspace_bytes < dedup_workspace_bytes(N)) return RNNLM_EWORKSPACE;
             if (reinterpret_cast<uintptr_t>(workspace) & 15) return RNNLM_EWORKSPACE;
         }
-        if (one_launch && launch_dedup_lookup(cache->dev, history_ids, N, rep, inverse, n_unique, step_stats, s) != hipSuccess)
-            return RNNLM_EDEVICE;
+        if (one_launch) {
+            const WeightsAhead ahead = outproj_weights_ahead(model->dev, N, use_fixed_offset(model), model->outproj_kernel);
+            if (launch_dedup_lookup(cache->dev, history_ids, N, rep, inverse, n_unique, step_stats, ahead, s) != hipSuccess) return RNNLM_EDEVICE;
+        }
     } else {
         rc = rnnlm_dedup(history_ids, N, rep, inverse, n_unique, workspace, workspace_bytes, hip_stream);
         if (rc != RNNLM_OK) return rc;
@@ -816,7 +818,7 @@ int rnnlm_index_intern(rnnlm_index_table *table, int N, const int32_t *word, con
     // Grouping and lookup in one launch of one workgroup while that is faster even when every context is new: reset,
     // intern and fetch of 4096 contexts of H = 512, 1229 distinct 46.6 -> 31.0 us, all distinct 48.1 -> 45.0.
     if (N <= 4096) {
-        if (launch_dedup_lookup(d.c, d.keys, N, d.rep, d.inverse, d.n_unique, nullptr, s) != hipSuccess) return RNNLM_EDEVICE;
+        if (launch_dedup_lookup(d.c, d.keys, N, d.rep, d.inverse, d.n_unique, nullptr, WeightsAhead{}, s) != hipSuccess) return RNNLM_EDEVICE;
     } else {
         if (launch_dedup(d.keys, N, d.rep, d.inverse, d.n_unique, d.dedup_ws, s) != hipSuccess) return RNNLM_EDEVICE;
         if (launch_cache_lookup(d.c, N, d.keys, d.rep, d.n_unique, nullptr, s) != hipSuccess) return RNNLM_EDEVICE;

@@ -174,13 +174,47 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, const Cache
     }
 }
 
+// The lookup is one workgroup.  The others of its launch bring what the output projection's workgroups read first into the L2s they
+// read it through, for the case that few rows are left and the weights are streamed: a line read by one kernel is still there for the
+// next one, and the workgroup of split s runs on XCD s % 8.  Bound by the lookup, which they hide behind; more bytes push each other out before
+// they are used, or last longer than it.  A search's eight steps, us, none / 48 / 64 / 96 KB of every split: V = 65536, H = 512, 41 new
+// histories of 4096 ids 303.7 / 294.3 / 294.6 / 298.2; V = 100000, H = 320 245.1 / 234.4 / 233.2 / 226.7; V = 200000, H = 1024 885 / 873 / 875 /
+// 869; fp32 V = 65536, H = 512 410.6 / 404.1 / 403.5 / 400.2; 450 new ones of 3000 ids, nothing streamed, 411.7 / 411.7 / 413.4 / 414.3.
+// (In the shadow of the hidden update instead, on the compute units it leaves idle: 300 -> 324, it is the shorter launch.)
+constexpr int kAheadGroups = 128, kAheadBytes = 64 * 1024;
+__device__ __forceinline__ void read_ahead(const WeightsAhead &a) {
+    constexpr int kWaves = kLookupThreads / 64, kSplits = kMaxSplits / kXcds, kPieces = kAheadBytes / 4096 * kSplits;
+    constexpr int kWavesPerXcd = kAheadGroups / kXcds * kWaves, kEach = kPieces / kWavesPerXcd;
+    static_assert(kEach * kWavesPerXcd == kPieces, "");
+    if ((int)blockIdx.x < kXcds) return;
+    const int xcd = blockIdx.x % kXcds, w = ((int)blockIdx.x / kXcds - 1) * kWaves + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    u32x4 v[kEach][4];
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+        const int t = w + k * kWavesPerXcd;              // every split's first piece, then every split's second
+        const long long at = ahead_piece(a, xcd + kXcds * (t % kSplits), t / kSplits);
+        const u32x4 *p = static_cast<const u32x4 *>(a.Ofrag) + (at > 0 ? at * 64 : 0) + lane;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[k][i] = p[i * 64];
+    }
+#pragma unroll
+    for (int k = 0; k < kEach; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(v[k][i]));
+}
+
 // Grouping of the step's ids and the lookup of the distinct ones in one launch of one workgroup
 // (N <= kSmallN): the lookup takes representatives and ids from LDS, where the grouping left them,
 // so nothing is read back from memory between the two and one launch is saved.
 static_assert(kLookupThreads == kSmallThreads, "");
 __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_kernel(
     CacheDev c, const uint64_t *__restrict__ ids, int N, int32_t *__restrict__ rep,
-    int32_t *__restrict__ inverse, int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats) {
+    int32_t *__restrict__ inverse, int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats,
+    WeightsAhead ahead) {
+    if (blockIdx.x != 0) {                  // uniform
+        read_ahead(ahead);
+        return;
+    }
     const CacheCounts counts(c);
     const SmallGroups g = dedup_small_body(ids, N, rep, inverse, n_unique);
     __syncthreads();                        // the groups in LDS are complete
@@ -192,7 +226,12 @@ __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_kernel(
 // The same for up to kMediumN raw queries (the grouping keeps the keys in LDS in raw order).
 __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_medium_kernel(
     CacheDev c, const uint64_t *__restrict__ ids, int N, int32_t *__restrict__ rep,
-    int32_t *__restrict__ inverse, int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats) {
+    int32_t *__restrict__ inverse, int32_t *__restrict__ n_unique, int32_t *__restrict__ step_stats,
+    WeightsAhead ahead) {
+    if (blockIdx.x != 0) {                  // uniform
+        read_ahead(ahead);
+        return;
+    }
     const CacheCounts counts(c);
     const MediumGroups g = dedup_medium_body(ids, N, rep, inverse, n_unique);
     __syncthreads();                        // the representatives in LDS are complete
@@ -362,14 +401,15 @@ hipError_t launch_cache_lookup(const CacheDev &c, int rows, const uint64_t *ids,
 int dedup_lookup_max_rows() { return kMediumN; }
 
 hipError_t launch_dedup_lookup(const CacheDev &c, const uint64_t *ids, int N, int32_t *rep, int32_t *inverse,
-                               int32_t *n_unique, int32_t *step_stats, hipStream_t stream) {
+                               int32_t *n_unique, int32_t *step_stats, const WeightsAhead &ahead, hipStream_t stream) {
     if (N < 0 || N > kMediumN) return hipErrorInvalidValue;
+    const dim3 grid(ahead.splits > 0 ? kXcds + kAheadGroups : 1);
     if (N <= kSmallN)
-        hipLaunchKernelGGL(dedup_lookup_kernel, dim3(1), dim3(kLookupThreads), 0, stream, c, ids, N, rep, inverse,
-                           n_unique, step_stats);
+        hipLaunchKernelGGL(dedup_lookup_kernel, grid, dim3(kLookupThreads), 0, stream, c, ids, N, rep, inverse,
+                           n_unique, step_stats, ahead);
     else
-        hipLaunchKernelGGL(dedup_lookup_medium_kernel, dim3(1), dim3(kLookupThreads), 0, stream, c, ids, N, rep,
-                           inverse, n_unique, step_stats);
+        hipLaunchKernelGGL(dedup_lookup_medium_kernel, grid, dim3(kLookupThreads), 0, stream, c, ids, N, rep,
+                           inverse, n_unique, step_stats, ahead);
     return hipGetLastError();
 }
 

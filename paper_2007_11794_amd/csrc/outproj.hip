@@ -265,6 +265,26 @@ float outproj_d_scale(const ModelDev &m, int rows, bool fixed_offset, int kernel
     return kLog2e;
 }
 
+// For a launch sized for `rows` rows that streams its weights where few of them are left (the tiled kernel's form of it apart).  Weights that
+// fit the L2s (8 x 4 MB) are still there from the step before: V = 20000, H = 256, 8 steps through the cache 169.5 us, 170 to 174 read
+// ahead; as fp32 model 200.8, 200.0.
+constexpr size_t kAllL2s = (size_t)kXcds * 4 << 20;
+WeightsAhead outproj_weights_ahead(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {
+    WeightsAhead a = {};
+    if (rows <= 0 || m.hs || !m.Ofrag || (size_t)m.Vp * m.Hp * (m.dtype == RNNLM_BF16 ? 2 : 4) <= kAllL2s || m.Vp / 32 < kMaxSplits) return a;
+    a = {m.Ofrag, m.Vp / 32, m.Hp / 16, kMaxSplits, 8};
+    if (m.dtype == RNNLM_BF16) {
+        const Bf16Kernel k = choose_bf16(m, rows, fixed_offset, kernel_choice);
+        if (k != kBf16Stream && k != kBf16Staged && k != kBf16RowStream) a.splits = 0;
+    } else {
+        const F32Kernel k = choose_f32(m, rows, kernel_choice);
+        a.block_kb *= 2;
+        if (k == kF32Split2) a.waves = 4;
+        else if (k != kF32Stream) a.splits = 0;
+    }
+    return a;
+}
+
 // The kernel launch_outproj takes for these arguments, by the name a kernel trace shows.
 const char *outproj_kernel_name(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {
     if (m.dtype == RNNLM_BF16) {

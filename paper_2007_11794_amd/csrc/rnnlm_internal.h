@@ -316,8 +316,22 @@ hipError_t launch_cache_lookup(const CacheDev &c, int rows, const uint64_t *ids,
 // Grouping of the ids (launch_dedup) and this lookup in ONE launch of one workgroup, for
 // 0 <= N <= dedup_lookup_max_rows() raw queries (or contexts of an index table).
 int dedup_lookup_max_rows();
+// The output weights as a weight-streaming launch further on reads them; splits 0: nothing to read ahead.
+struct WeightsAhead {
+    const void *Ofrag;
+    int blocks, block_kb;  // blocks of 32 words, kilobytes of each (a multiple of 4)
+    int splits, waves;     // workgroups of that launch, waves of each
+};
+// Where piece number `piece` of four kilobytes, in the order the workgroup of `split` reads them (rounds of `waves` blocks side by
+// side, a piece of each at a time), lies, in kilobytes; -1: that workgroup has no such piece.
+__host__ __device__ inline long long ahead_piece(const WeightsAhead &a, int split, int piece) {
+    const int per_round = a.block_kb / 4 * a.waves, round = piece / per_round, rest = piece % per_round;
+    const int blk = part_begin(split, a.blocks, a.splits) + round * a.waves + rest % a.waves;
+    return blk < part_begin(split + 1, a.blocks, a.splits) ? (long long)blk * a.block_kb + rest / a.waves * 4 : -1;
+}
+WeightsAhead outproj_weights_ahead(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice);
 hipError_t launch_dedup_lookup(const CacheDev &c, const uint64_t *ids, int N, int32_t *rep, int32_t *inverse,
-                               int32_t *n_unique, int32_t *step_stats, hipStream_t stream);
+                               int32_t *n_unique, int32_t *step_stats, const WeightsAhead &ahead, hipStream_t stream);
 // After the computed block is done: normalisers of all distinct histories into c.lse_rows,
 // new entries into the stores, stored hidden vectors of found histories into h_out.
 hipError_t launch_cache_commit(const CacheDev &c, const ModelDev &m, int rows, const int32_t *n_unique,

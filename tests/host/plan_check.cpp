@@ -3,6 +3,8 @@
 // run by tests/test_host_plan.py.  Prints "ok" or the first violated property.
 #include <stdio.h>
 
+#include <vector>
+
 #include "rnnlm_internal.h"
 
 using namespace rnnlm;
@@ -56,6 +58,26 @@ int main() {
                 const long long want = ((long long)index * units) / parts;
                 REQUIRE(part_begin(index, units, parts) == (int)want, "part_begin(%d, %d, %d) = %d, want %lld", index, units,
                         parts, part_begin(index, units, parts), want);
+            }
+    // what a launch reads ahead of a streaming one: inside the workgroup's own share, every piece once, all of them in the end
+    const int blocks_of[] = {256, 257, 2047, 2048, 6250, 31250}, hp_of[] = {64, 128, 192, 512, 704, 1024};
+    for (int blocks : blocks_of)
+        for (int hp : hp_of)
+            for (int fp32 = 0; fp32 < 2; ++fp32) {
+                const WeightsAhead a = {nullptr, blocks, hp / 16 * (1 + fp32), kMaxSplits, fp32 ? 4 : 8};
+                for (int split : {0, 1, 100, 255}) {
+                    const int b0 = part_begin(split, blocks, kMaxSplits), b1 = part_begin(split + 1, blocks, kMaxSplits);
+                    const int rounds = (b1 - b0 + a.waves - 1) / a.waves, pieces = rounds * a.waves * (a.block_kb / 4);
+                    std::vector<int> seen((size_t)(b1 - b0) * (a.block_kb / 4));
+                    for (int piece = 0; piece < pieces + 40; ++piece) {
+                        const long long at = ahead_piece(a, split, piece);
+                        if (at < 0) continue;
+                        REQUIRE(at % 4 == 0 && at >= (long long)b0 * a.block_kb && at + 4 <= (long long)b1 * a.block_kb, "blocks=%d hp=%d split=%d: %lld",
+                                blocks, hp, split, at);
+                        REQUIRE(++seen[(size_t)(at / 4 - (long long)b0 * (a.block_kb / 4))] == 1, "blocks=%d hp=%d split=%d: %lld twice", blocks, hp, split, at);
+                    }
+                    for (int n : seen) REQUIRE(n == 1, "blocks=%d hp=%d split=%d: a piece is left out", blocks, hp, split);
+                }
             }
     printf("ok\n");
     return 0;
