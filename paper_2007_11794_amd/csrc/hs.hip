@@ -194,7 +194,56 @@ __device__ __forceinline__ void hs_dots_short_rows(const T *Theta, const float (
     }
 }
 
-// LPR: lanes per node row of the short-row form (16: Hp <= 128, 32: Hp <= 256), 0: any hidden size.
+// The same for bf16 rows that a wave reads in one piece (256 < Hp <= 512, lane l has elements 8 l .. + 7), its eight floats of the hidden
+// vector read once.  Bound by the rows' way from the L2s; with more than three rounds of nodes, eight rows are on their way while the eight
+// before them are multiplied and reduced.  The rounds past the end, which fetch the first node again, are there so that a wait has the same
+// loads in front of it on every way to it (left out, the compiler waited for everything: 4096 queries of 32 words 81 us), and cost more
+// than they give in two or three rounds (2000 queries of 5 words 14.8 -> 15.5 us).  Steps, us, general form / this one: V = 65536, H = 512, 4096 queries
+// of 32 words from 1229 rows 63.3 / 57.5, of 8 words 34.4 / 32.8, 1024 of 32 words 22.5 / 22.2; V = 100000, H = 300, 1500 of 10 words 21.4 / 18.7;
+// V = 20000, H = 320, 2000 of 5 words 15.8 / 15.5; V = 50000, H = 333, 100 of 12 words 13.9 / 12.1.  fp32 rows take twice the registers: not tried.
+template <typename T, int THREADS>
+__device__ __forceinline__ void hs_dots_one_piece(const T *Theta, const float (&h8)[8], int Hp, const int *dnode, float *dx, int D, int wave, int lane) {
+    const int umine = batch_slot_of_lane(lane);
+    const bool in_row = lane * 8 < Hp;                     // lanes beyond the row drop what they compute
+    const int j0 = in_row ? lane * 8 : 0;
+    auto fetch = [&](int first, float (&w8)[kHsBatch][8]) {
+        const int node_mine = dnode[first + umine < D ? first + umine : 0];
+#pragma unroll
+        for (int u = 0; u < kHsBatch; ++u)
+            load8_weights(Theta, (size_t)__builtin_amdgcn_readlane(node_mine, lane_of_batch_slot(u)) * Hp + j0, w8[u]);
+    };
+    auto finish = [&](int first, const float (&w8)[kHsBatch][8]) {
+        float acc[kHsBatch];
+#pragma unroll
+        for (int u = 0; u < kHsBatch; ++u) {
+            acc[u] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[u] = fmaf(w8[u][i], h8[i], acc[u]);
+            acc[u] = in_row ? acc[u] : 0.f;
+        }
+        const float x = wave_sum8(acc, lane);
+        if ((lane & 7) == 0 && first + umine < D) dx[first + umine] = x;
+    };
+    constexpr int stride = (THREADS / 64) * kHsBatch;
+    int first = wave * kHsBatch;
+    float wa[kHsBatch][8], wb[kHsBatch][8];
+    if (D <= 3 * stride) {
+        for (; first < D; first += stride) {
+            fetch(first, wa);
+            finish(first, wa);
+        }
+        return;
+    }
+    fetch(first, wa);
+    for (; first < D; first += 2 * stride) {
+        fetch(first + stride, wb);
+        finish(first, wa);
+        fetch(first + 2 * stride, wa);
+        finish(first + stride, wb);
+    }
+}
+
+// LPR: lanes per node row of the short-row form (16: Hp <= 128, 32: Hp <= 256), 64: bf16 rows in one piece, 0: any hidden size.
 // Kernels of their own, so that the registers of the short-row form do not cost the general one occupancy.
 // HERE (short rows only): the hidden update is part of the launch.  A workgroup computes the hidden vector of its query's row for
 // itself, in plain fp32, while its words' paths are on their way: W (Hp x Hp) comes through the same row dot products.  Without
@@ -321,7 +370,10 @@ __global__ __launch_bounds__(S::kThreads) void hs_query_shared_kernel(
     const float *hrow = h_out + (size_t)r * H;
     const bool vec_ok = (H % 4) == 0;
     const int umine = batch_slot_of_lane(lane);
-    if constexpr (LPR != 0) {
+    if constexpr (LPR == 64) {
+        load8_row(hrow, lane * 8 < Hp ? lane * 8 : 0, H, vec_ok, 0.f, h8);
+        hs_dots_one_piece<T, S::kThreads>(Theta, h8, Hp, dnode, dx, D, wave, lane);
+    } else if constexpr (LPR != 0) {
         if constexpr (HERE) {
             const f32x4 lo = *reinterpret_cast<const f32x4 *>(hvec + 8 * (lane % LPR)), hi = *reinterpret_cast<const f32x4 *>(hvec + 8 * (lane % LPR) + 4);
 #pragma unroll
@@ -407,7 +459,10 @@ static hipError_t launch_shared(const ModelDev &m, int rows, const int *B_dev, i
         using S = decltype(shape);
         if (m.Hp <= 128) launch(hs_query_shared_kernel<T, 16, S, HERE>, S::kThreads);
         else if (HERE || m.Hp <= 256) launch(hs_query_shared_kernel<T, 32, S, HERE>, S::kThreads);
-        else if constexpr (!HERE) launch(hs_query_shared_kernel<T, 0, S, HERE>, S::kThreads);
+        else if constexpr (!HERE) {
+            if (sizeof(T) == 2 && m.Hp <= 512) launch(hs_query_shared_kernel<T, sizeof(T) == 2 ? 64 : 0, S, HERE>, S::kThreads);
+            else launch(hs_query_shared_kernel<T, 0, S, HERE>, S::kThreads);
+        }
     };
     const bool wide = hs_wide(N, K, m.H, m.Hp, small);
     auto pick = [&](auto tag) {
