@@ -117,7 +117,10 @@ typedef HsShape<128, 9, 256, 64> HsSmall;
 // The same with twice the threads, while the queries leave compute units idle or half empty: a query's chain of
 // dependent loads gets shorter (fewer rounds of node rows), the number of chains does not matter then.  Steps at V =
 // 65536, H = 512, bf16, us, half as many threads / these: 40 queries of 25 words 17.6 / 13.9, 512 queries 20.8 / 17.3,
-// 640 of 30 words 22.4 / 24.4, 1024 of 32 words 26.1 / 28.9; 512 queries of 6 words 16.6 / 14.2, 640 15.6 / 13.9.  Short rows have
+// 640 of 30 words 22.4 / 24.4, 1024 of 32 words 26.1 / 28.9; 512 queries of 6 words 16.6 / 14.2, 640 15.6 / 13.9.  With few words four
+// workgroups of the doubled shape fit a compute unit (sixteen waves), so the line lies at 1024 queries there: 1024 of 6 words 15.6 / 14.6, of 12, H =
+// 400, 17.5 / 15.9, H = 1024 32.7 / 27.7, fp32, H = 320, 21.0 / 20.2; 700 of 8, H = 640, 21.1 / 17.5; 1300 of 8 20.4 / 20.6, of 4, H = 320, 13.0 /
+// 13.9; 2048 of 8 21.2 / 23.1.  Short rows have
 // several in a wave's round already: up to 256 queries (V = 300000, H = 128, 40 queries 12.1 / 11.3; H = 250, fp32, 512 queries
 // 19.8 / 23.5), and with the large shape only once the words' nodes are more than one round of half as many threads: kernel at V =
 // 250000, H = 128, bf16, 100 queries of 17 words 0.3 slower, 24 words 0.3 faster, 32 words 1.3 faster; rows that are not 16-byte
@@ -128,7 +131,7 @@ typedef HsShape<128, 9, 256, 64> HsSmall;
 typedef HsShape<512, 11, 1024, 256> HsLargeWide;
 typedef HsShape<256, 9, 256, 64> HsSmallWide;
 inline bool hs_wide(int N, int K, int H, int Hp, bool small) {
-    if (Hp > 256) return N <= 512;
+    if (Hp > 256) return N <= (small ? 1024 : 512);
     const bool aligned = H % 4 == 0;
     return N <= 256 && (small || (Hp <= 128 ? aligned && K >= 24 : K >= (aligned ? 16 : 24)));
 }

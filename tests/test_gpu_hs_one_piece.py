@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H", [257, 320, 333, 448, 512, 513])
-@pytest.mark.parametrize("N,K", [(3, 4), (20, 13), (513, 4), (600, 9), (513, 30), (16, 60)])
+@pytest.mark.parametrize("N,K", [(3, 4), (20, 13), (513, 4), (600, 9), (1024, 5), (1025, 5), (513, 30), (16, 60)])
 def test_against_the_oracle(H, N, K):
     out, ref = run(3000, H, N, K, "bf16")
     # up to 18 terms of fp32 dot products of H products: 2^-24 of sums below 2, some hundred roundings, random signs
