@@ -291,6 +291,10 @@ struct HiddenHere {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) sum[e] += t[e];
                 }
+                if (kF32 && H != Hp) {                                   // units beyond H are 0, an infinity in h_in times zero weights is not
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[e] = k + e < H ? sum[e] : 0.f;
+                }
                 const bool ok = (uint32_t)w[i] < (uint32_t)m.V;
                 if (leader && !ok && k == 0) atomicOr(m.flag, RNNLM_FLAG_BAD_PREV_WORD);
                 store4(lds, b, k, sum, u[i], ok);

@@ -101,3 +101,32 @@ def test_fp32_inputs_beyond_a_16_bit_term(H, B):
         assert np.max(np.abs(lp[known] - want[known])) <= 1e-5
     assert m.last_error() == 0
     m.close()
+
+
+@pytest.mark.parametrize("H,B", [(63, 7), (77, 20), (100, 32)])
+def test_fp32_rows_with_an_infinity_and_padded_units(H, B):
+    """An infinity in h_in, which the zero weights of units beyond H meet as well: every unit of the row saturates, and
+    its log-probabilities are those of the saturated units, grouped and not."""
+    rng = np.random.default_rng(H * B)
+    model = model_of(rng, H, "f32")
+    prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
+    query = rng.integers(0, V, (B, 3)).astype(np.int32)
+    rows = np.unique(np.linspace(0, B - 1, 5).astype(int))
+    for i, r in enumerate(rows):
+        h_in[r, (0, H - 1, H // 2, 3, 1)[i]] = (np.inf, -np.inf, -np.inf, np.inf, -np.inf)[i]
+    a = model["U"][prev].astype(np.float64) + np.einsum("bi,ji->bj", h_in.astype(np.float64), model["W"].astype(np.float64))
+    with np.errstate(over="ignore"):
+        h_ref = 1.0 / (1.0 + np.exp(-a))
+    z = h_ref @ model["O"].astype(np.float64)
+    want = np.take_along_axis(z, query.astype(np.int64), 1) - np.log(np.exp(z).sum(1))[:, None]
+    m = load_model(model, "f32", B)
+    for grouped in (False, True):
+        if grouped:
+            res = gpu_step_dedup(m, np.arange(B, dtype=np.uint64) * 3 + 5, prev, h_in, query)
+            h_out, lp = res["h_out"], res["logprob"]
+        else:
+            h_out, lp = gpu_step(m, prev, h_in, query)
+        # as in test_against_the_oracle
+        assert np.max(np.abs(h_out - h_ref)) <= 2e-6 and np.max(np.abs(lp - want)) <= 1e-5, grouped
+    assert m.last_error() == 0
+    m.close()
