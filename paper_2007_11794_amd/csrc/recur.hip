@@ -368,6 +368,10 @@ struct FewUnits {
 #pragma unroll
             for (int i = 0; i < 4; ++i) sum[i] += t[i];
         }
+        if (sizeof(WT) == 4 && m.H != m.Hp) {          // units beyond H are 0, an infinity in h_in times zero weights is not
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[i] = je + i < m.H ? sum[i] : 0.f;
+        }
         const Finish f = {h_out + (size_t)(row_dst ? row_dst[b] : b) * m.H, b, m.H, m.Hp, w_ok};
         finish4<WT, VEC>(m, f, je, sum, rs, u);
     }

@@ -103,7 +103,7 @@ def test_fp32_inputs_beyond_a_16_bit_term(H, B):
     m.close()
 
 
-@pytest.mark.parametrize("H,B", [(63, 7), (77, 20), (100, 32)])
+@pytest.mark.parametrize("H,B", [(63, 7), (77, 20), (100, 32), (77, 40), (130, 9), (250, 70), (300, 12), (1022, 5)])
 def test_fp32_rows_with_an_infinity_and_padded_units(H, B):
     """An infinity in h_in, which the zero weights of units beyond H meet as well: every unit of the row saturates, and
     its log-probabilities are those of the saturated units, grouped and not."""
