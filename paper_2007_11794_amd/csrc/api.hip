@@ -52,7 +52,7 @@ void free_scratch(rnnlm_model *m) {
     (void)hipFree(d.dfrag);
     (void)hipFree(d.part);
     (void)hipFree(d.flag);
-    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = d.done = nullptr;
+    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = nullptr; d.done = nullptr;
     if (m->ev0) (void)hipEventDestroy(m->ev0);
     if (m->ev1) (void)hipEventDestroy(m->ev1);
     m->ev0 = m->ev1 = nullptr;
@@ -95,7 +95,7 @@ int alloc_scratch(rnnlm_model *m, int max_Bp, bool with_partials) {
     void *p;
     HIP_TRY(hipMalloc(&p, block)); d.d = p;
     HIP_TRY(hipMemset(d.d, 0, block));
-    HIP_TRY(hipMalloc(&p, 8)); d.flag = static_cast<int *>(p); d.done = d.flag + 1;
+    HIP_TRY(hipMalloc(&p, 8)); d.flag = static_cast<int *>(p); d.done = reinterpret_cast<unsigned *>(d.flag + 1);
     HIP_TRY(hipMemset(d.flag, 0, 8));
     if (d.dtype == RNNLM_BF16 || with_partials) {
         HIP_TRY(hipMalloc(&p, block)); d.dfrag = p;
@@ -395,7 +395,7 @@ int rnnlm_model_share(const rnnlm_model *model, int max_B, rnnlm_model **out) {
     if (!m) return RNNLM_ENOMEM;
     *m = *model;                           // weights' pointers, shapes, options
     ModelDev &d = m->dev;
-    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = d.done = nullptr;
+    d.d = d.dfrag = nullptr; d.part = nullptr; d.flag = nullptr; d.done = nullptr;
     m->ev0 = m->ev1 = nullptr;
     m->max_B = max_B;
     m->max_Bp = round_up(max_B, 256);

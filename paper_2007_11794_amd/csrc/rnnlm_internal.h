@@ -66,7 +66,7 @@ struct ModelDev {
     float d_scale;     // set for the hidden update only: outproj_d_scale of the output projection that follows
     float2 *part;      // [max_Bp][kMaxSplits]  (max, sum) partials of the base-2 log-sum-exp
     int *flag;         // sticky rnnlm_device_flag bits
-    int *done;         // workgroups of a one-launch step (step_few.hip) that have finished; 0 between launches
+    unsigned *done;    // workgroups of a one-launch step (step_few.hip) that have finished; wraps to 0 with the last one
 };
 
 // Device-side view of a cache kept between steps (cache.hip).

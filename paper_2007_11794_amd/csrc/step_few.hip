@@ -365,10 +365,11 @@ __global__ __launch_bounds__(kThreads) void step_few_kernel(ModelDev m, FewStep 
     // The workgroup that comes last has all partials and logits before it.
     seen_by_all();
     __syncthreads();
-    if (tid == 0) s.last = atomicAdd(m.done, 1) == S - 1;
+    // The count wraps at S, the same for every launch on a handle, so it is 0 again behind any number of whole launches: two that
+    // a caller let overlap, against the rules, may spoil each other's answers but not those of later ones.
+    if (tid == 0) s.last = atomicInc(m.done, S - 1) == (unsigned)S - 1;
     __syncthreads();
     if (!s.last) return;
-    if (tid == 0) atomicExch(m.done, 0);                                 // for the next launch on this handle
     constexpr int kHeld = 4;                                             // answers of a thread, beside the partials
     float z[kHeld], base[kHeld];
     int row[kHeld];
