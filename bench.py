@@ -36,11 +36,11 @@ TRAFFIC = {
     ("outproj_stream_kernel", 3): (67.8e6, "profiles/outproj_stream_few_rows_kernel_trace_and_fetch.md"),
     ("outproj_stream_kernel", 5): (411.5e6, "profiles/outproj_stream_few_rows_kernel_trace_and_fetch.md"),
 }
-# The path kernel of the hierarchical output layer, by workload number: HBM bytes per launch
-# (FETCH_SIZE + WRITE_SIZE, copy-calibrated).
+# The path kernel of the hierarchical output layer, by workload number and whether the hidden update is part of its
+# launch: HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated).
 HS_TRAFFIC = {
-    3: (53.8e6, "profiles/hs_step_cfg3_shape_kernel_trace_and_traffic.md"),
-    6: (2.79e6, "profiles/hs_step_cfg6_paper_regime_kernel_trace_and_traffic.md"),
+    (3, False): (53.8e6, "profiles/hs_step_cfg3_shape_kernel_trace_and_traffic.md"),
+    (6, True): (3.18e6, "profiles/hs_step_cfg6_paper_regime_kernel_trace_and_traffic.md"),
 }
 MIN_TIMED_REGION_S = 0.1         # the event-timed repetitions together last at least this long
 MIN_REPETITIONS = 20
@@ -111,17 +111,21 @@ def bench_hs(args, cfg, rn, torch, np) -> int:
     rep_ms = timed_repetitions(step, args.steps, dt_first, torch)
     dt = median(rep_ms) * 1e-3
     assert m.last_error() == 0
-    k_ms = median([rn.rnnlm_hs_time_query(m, query, h_out, lp, 20) for _ in range(7)])
+    # the path kernel alone, or the step itself where it is a single launch
+    one_launch = m.one_launch(N, N, K)
+    k_ms = dt / args.steps * 1e3 if one_launch else median([rn.rnnlm_hs_time_query(m, query, h_out, lp, 20) for _ in range(7)])
     nodes = int(np.diff(off)[x["query"]].sum())              # path nodes of all queried words
     # the kernel computes one dot product per DISTINCT node of a raw query's K paths
     node_of = entry & 0x7FFFFFFF
     distinct = sum(len(set(np.concatenate([node_of[off[w]:off[w + 1]] for w in row]).tolist())) for row in x["query"])
     es = 2 if bf16 else 4
     alg_bytes = distinct * H * es + N * H * 4 + N * K * 8.0
+    if one_launch:                                           # and the hidden update: W, embedding rows, h_in, previous words
+        alg_bytes += H * H * es + N * H * (es + 4.0) + N * 4.0
     # HBM bytes per launch of the path kernel as rocprofv3 counted them (FETCH_SIZE + WRITE_SIZE, scaled by a
     # plain copy of known size): the upper tree levels repeat across queries and come out of L2, so this is
     # less than the algorithmic figure; the roofline fraction is taken on what HBM really moved
-    traffic, traffic_source = HS_TRAFFIC.get(args.config, (None, None))
+    traffic, traffic_source = HS_TRAFFIC.get((args.config, one_launch), (None, None))
     moved = traffic if traffic is not None else alg_bytes
     cpu = None
     if not args.no_cpu_baseline:
@@ -146,7 +150,8 @@ def bench_hs(args, cfg, rn, torch, np) -> int:
                                   % (cfg.name, V, H, N, K, cfg.zipf_s or 0, nodes / float(N * K), distinct / float(N), K)},
            "timing": {"method": "median of %d repetitions of %d steps, each bracketed by HIP events on the launch stream"
                                 % (len(rep_ms), args.steps)},
-           "roofline": {"kernel": "hs_query_shared_kernel" if K >= 4 else "hs_query_kernel", "bound": "hbm",
+           "roofline": {"kernel": "hs_query_shared_kernel (hidden update in the launch: the whole step)" if one_launch else
+                                  "hs_query_shared_kernel" if K >= 4 else "hs_query_kernel", "bound": "hbm",
                         "achieved": round(moved / (k_ms * 1e-3) / 1e9, 1),
                         "peak": 8000.0, "unit": "GB/s", "frac": round(moved / (k_ms * 1e-3) / 8e12, 4),
                         "traffic": traffic, "traffic_source": traffic_source,
@@ -155,8 +160,8 @@ def bench_hs(args, cfg, rn, torch, np) -> int:
                         "note": ("achieved = HBM bytes per launch from the profile / launch time" if traffic is not None else
                                  "no HBM counter figure for this workload: achieved uses the algorithmic bytes, an "
                                  "upper bound of what HBM moved") +
-                                "; algorithmic bytes = one node vector per distinct path node of every raw query + "
-                                "hidden rows + ids and outputs (the upper tree levels repeat across queries and are "
+                                "; algorithmic bytes = one node vector per distinct path node of every raw query + " +
+                                ("W, embedding rows, h_in + " if one_launch else "") + "hidden rows + ids and outputs (the upper tree levels repeat across queries and are "
                                 "served by L2)"},
            "cpu_baseline": cpu}
     print(json.dumps(out))
@@ -504,9 +509,11 @@ def main() -> int:
                       "value": round(N * replays * args.graph_steps / g_dt, 1)}
 
     # dominant kernel: output projection + log-sum-exp, timed alone with HIP events on its stream, launched
-    # as the timed step launches it (the kernel reads the number of distinct rows from the device)
+    # as the timed step launches it (the kernel reads the number of distinct rows from the device); a step that is
+    # a single launch has no such kernel: there it is the step, as timed above
     reps = 50 if cfg.V * cfg.H <= 65536 * 512 else 10
-    k3_groups = sorted(m.time_outproj(cfg.N, reps, n_rows_dev=nu) for _ in range(7))
+    one_launch = cache_info is None and m.one_launch(cfg.N, cfg.N, cfg.K, grouped=True)
+    k3_groups = [t / args.steps for t in rep_ms] if one_launch else sorted(m.time_outproj(cfg.N, reps, n_rows_dev=nu) for _ in range(7))
     k3_ms = median(k3_groups)
     flops = 2.0 * B * cfg.H * cfg.V                 # the contraction on the distinct rows, each product once
     # fp32 models run the contraction on the fp16 matrix cores (from 64 rows on the tiled kernel, below that
@@ -520,22 +527,24 @@ def main() -> int:
     # few rows (one launch of the weight-streaming kernel): the launch reads the (padded) output weights
     # once, nothing else of size
     Hp = max(128 if bf16 else 64, -(-cfg.H // 64) * 64)
-    kernel_name = m.outproj_kernel_name(cfg.N)      # the library names the kernel it launches
+    # the library names the kernel it launches
+    kernel_name = "step_few_kernel" if one_launch else m.outproj_kernel_name(cfg.N)
     if kernel_name == "outproj_staged_kernel":
         kernel_name += "<%d, %s>" % (Hp, "true" if args.lse_mode in (0, 2) else "false")
-    streamed = kernel_name == "outproj_stream_kernel" and B <= (64 if cfg.H <= (1216 if bf16 else 576) else 32)
+    streamed = one_launch or kernel_name == "outproj_stream_kernel" and B <= (64 if cfg.H <= (1216 if bf16 else 576) else 32)
     traffic, traffic_source = TRAFFIC.get((kernel_name, args.config if args.unique_frac is None else -1), (None, None))
     if args.rows is not None and not streamed:
         traffic, traffic_source = None, None
     k3_timing = {"us_per_launch": round(k3_ms * 1e3, 2), "us_per_launch_min": round(k3_groups[0] * 1e3, 2),
                  "us_per_launch_max": round(k3_groups[-1] * 1e3, 2),
-                 "timing": "median of 7 groups of %d back-to-back launches between HIP events on the launch stream, "
+                 "timing": "the step itself: one launch" if one_launch else
+                           "median of 7 groups of %d back-to-back launches between HIP events on the launch stream, "
                            "row count read on the device as in the step" % reps}
     if streamed:
         Vp = -(-cfg.V // 256) * 256
         wbytes = float(Hp) * Vp * (2 if bf16 else 4)
         gbs = wbytes / (k3_ms * 1e-3) / 1e9
-        roofline = {"kernel": "%s (weight streaming, %d rows)" % (kernel_name, B), "bound": "hbm",
+        roofline = {"kernel": "%s (%s, %d rows)" % (kernel_name, "the whole step" if one_launch else "weight streaming", B), "bound": "hbm",
                     "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                     "frac": round(gbs / PEAK_HBM_GBS, 4), "traffic": traffic, "traffic_source": traffic_source,
                     "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE, copy-calibrated)",

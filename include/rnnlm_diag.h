@@ -15,7 +15,9 @@ extern "C" {
  * Run only the output-projection + log-sum-exp kernel (the whole-vocabulary normalisation of
  * Section 2.1) on the hidden block left in the model by the latest step, `repeats` times back to
  * back on `hip_stream`, bracketed by HIP events on that stream, and return the mean time of one
- * launch in milliseconds in *ms_per_launch.  Synchronises the stream.
+ * launch in milliseconds in *ms_per_launch.  Synchronises the stream.  A step that is one launch
+ * (rnnlm_one_launch) has no such kernel and leaves no hidden block: what is timed behind it is the
+ * kernel of the separate launches, on the block of the latest step that took them (zeros if none did).
  *   B           rows the launch is sized for
  *   n_rows_dev  dev i32[1] or NULL: when given, the kernel reads the true number of rows (<= B)
  *               from it on the device, exactly as inside rnnlm_step_dedup / rnnlm_step_cached
@@ -26,11 +28,20 @@ int rnnlm_time_outproj(const rnnlm_model *model, int B, const int32_t *n_rows_de
 
 /* Name (as a kernel trace shows it, without template arguments) of the kernel that a launch of the
  * output projection sized for B rows takes on this model with its current options; a static string,
- * NULL for a bad argument or a model with the hierarchical output layer. */
+ * NULL for a bad argument or a model with the hierarchical output layer.  (Launched by the steps that
+ * are not one launch, and by rnnlm_time_outproj.) */
 const char *rnnlm_outproj_kernel_name(const rnnlm_model *model, int B);
 
-/* Only the path-evaluation kernel of rnnlm_hs_step (no hidden update) on
- * h_out as a step left it, `repeats` times back to back on `hip_stream` between HIP events on
+/* Is a step of these sizes ONE launch (grouping, hidden update, output layer and words) on this model with its
+ * current options?  1: it is, if no output shares a byte with an input or another output; 0: it takes separate
+ * launches; RNNLM_EINVAL for a null model or an unknown form.  Reads nothing on the device.
+ *   form 0      rnnlm_step, rnnlm_hs_step with row_of_query NULL (N = B)
+ *   form 1      the same with row_of_query
+ *   form 2      rnnlm_step_dedup, rnnlm_step_cached without a cache, of N raw queries (B is not looked at) */
+int rnnlm_one_launch(const rnnlm_model *model, int B, int N, int K, int form);
+
+/* Only the path-evaluation kernel of rnnlm_hs_step (no hidden update: the second launch of a step that is not one
+ * launch) on h_out as a step left it, `repeats` times back to back on `hip_stream` between HIP events on
  * that stream; mean time of one launch in milliseconds.  Synchronises the stream. */
 int rnnlm_hs_time_query(const rnnlm_model *model, int B, int K, const int32_t *query_word,
                         const int32_t *row_of_query_or_null, int N, const float *h_out, float *logprob,

@@ -27,7 +27,8 @@ EXPORTS = ["rnnlm_strerror", "rnnlm_load", "rnnlm_free", "rnnlm_model_share", "r
            "rnnlm_cache_stats", "rnnlm_step_cached", "rnnlm_pack_ids", "rnnlm_index_create",
            "rnnlm_index_free", "rnnlm_index_reset", "rnnlm_index_intern", "rnnlm_index_fetch",
            "rnnlm_index_stats", "rnnlm_huffman_build", "rnnlm_hs_load", "rnnlm_hs_step", "rnnlm_hs_time_query",
-           "rnnlm_probe_mfma_rate", "rnnlm_time_empty_launch", "rnnlm_outproj_kernel_name"]
+           "rnnlm_probe_mfma_rate", "rnnlm_time_empty_launch", "rnnlm_outproj_kernel_name",
+           "rnnlm_one_launch"]
 
 
 class RnnlmError(RuntimeError):
@@ -77,6 +78,8 @@ def lib() -> ctypes.CDLL:
         L.rnnlm_time_empty_launch.restype = I
         L.rnnlm_outproj_kernel_name.argtypes = [P, I]
         L.rnnlm_outproj_kernel_name.restype = ctypes.c_char_p
+        L.rnnlm_one_launch.argtypes = [P, I, I, I, I]
+        L.rnnlm_one_launch.restype = I
         L.rnnlm_probe_mfma_rate.argtypes = [I, I, I, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double)]
         L.rnnlm_probe_mfma_rate.restype = I
         L.rnnlm_cache_create.argtypes = [P, I, ctypes.POINTER(P)]
@@ -191,6 +194,13 @@ class RnnlmModel:
         if name is None:
             raise ValueError("rnnlm_outproj_kernel_name: bad argument")
         return name.decode()
+
+    def one_launch(self, B: int, N: int, K: int, mapped: bool = False, grouped: bool = False) -> bool:
+        """Is a step of these sizes a single launch?  mapped: with row_of_query; grouped: by history id (B is not looked at)."""
+        answer = lib().rnnlm_one_launch(self.handle, int(B), int(N), int(K), 2 if grouped else int(mapped))
+        if answer < 0:
+            _check(answer, "rnnlm_one_launch")
+        return bool(answer)
 
     def close(self):
         if self._h:

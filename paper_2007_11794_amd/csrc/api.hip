@@ -868,6 +868,12 @@ const char *rnnlm_outproj_kernel_name(const rnnlm_model *model, int B) {
     return outproj_kernel_name(model->dev, B, use_fixed_offset(model), model->outproj_kernel);
 }
 
+int rnnlm_one_launch(const rnnlm_model *model, int B, int N, int K, int form) {
+    if (!model || form < 0 || form > 2) return RNNLM_EINVAL;
+    if (model->dev.hs) return form < 2 && hs_step_chosen(model->dev, B, N, K, form == 1);
+    return few_step(model, form == 2 ? N : B, form == 2, N, K);
+}
+
 int rnnlm_time_outproj(const rnnlm_model *model, int B, const int32_t *n_rows_dev, int repeats, void *hip_stream,
                        float *ms_per_launch) {
     if (!model || !ms_per_launch || repeats <= 0 || B <= 0 || model->dev.hs) return RNNLM_EINVAL;

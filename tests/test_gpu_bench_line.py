@@ -49,3 +49,12 @@ def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=60, cwd=ROOT)
     assert r.returncode != 0 and "ONE GPU" in r.stderr
+
+
+@pytest.mark.parametrize("args,kernel", [(("--config", "1"), "step_few_kernel"), (("--hs", "--config", "6"), "hs_query_shared_kernel")])
+def test_a_step_of_one_launch_is_its_own_kernel(args, kernel):
+    """The roofline is that of the launch the timed step is, not of a kernel it does not take."""
+    j = bench_line(*args, "--no-cpu-baseline")
+    r = j["roofline"]
+    assert r["kernel"].startswith(kernel) and "the whole step" in r["kernel"] and r["bound"] == "hbm"
+    assert abs(r["us_per_launch"] - j["ms_per_step"] * 1e3) <= 0.06          # both printed to some hundredths
