@@ -140,11 +140,9 @@ bool outputs_overlap(const Bytes (&ins)[NI], const Bytes (&outs)[NO]) {
     return false;
 }
 
-// The whole step of few rows in one launch (step_few.hip).  The words asked for are finished by one workgroup: up to kFewPairs.
-constexpr long long kFewPairs = 8192;
+// The whole step of few rows in one launch (step_few.hip).
 bool few_step(const rnnlm_model *m, int rows, bool grouped, int N, int K) {
-    return step_few_chosen(m->dev, rows, grouped) && N > 0 && K > 0 && (long long)N * K <= kFewPairs &&
-           outproj_streams_in_one_launch(m->dev, rows, m->outproj_kernel);
+    return step_few_chosen(m->dev, rows, grouped, N, K) && outproj_streams_in_one_launch(m->dev, rows, m->outproj_kernel);
 }
 uint32_t inverse_of(int K) { return K > 1 ? (uint32_t)(((1ull << 32) + K - 1) / K) : 0; }
 bool rows_in_pieces(const ModelDev &d, const float *h_in) { return d.H % 4 == 0 && (reinterpret_cast<uintptr_t>(h_in) & 15) == 0; }

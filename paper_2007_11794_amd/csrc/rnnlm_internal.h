@@ -290,7 +290,7 @@ struct FewStep {
     __host__ __device__ int query_of(int p) const { return K == 1 ? p : (int)(((uint64_t)(uint32_t)p * inverse_K) >> 32); }
 };
 bool step_few_supported(int dtype, int Hp);               // the model gets a Wfrag
-bool step_few_chosen(const ModelDev &m, int rows, bool grouped);
+bool step_few_chosen(const ModelDev &m, int rows, bool grouped, int N, int K);
 hipError_t launch_step_few(const ModelDev &m, const FewStep &a, bool fixed_offset, hipStream_t stream);
 // the output projection takes the weight-streaming kernel by itself, in one launch
 bool outproj_streams_in_one_launch(const ModelDev &m, int rows, int kernel_choice);

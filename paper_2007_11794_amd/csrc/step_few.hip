@@ -23,6 +23,7 @@ namespace {
 
 constexpr int kThreads = kStreamThreads, kWaves = kStreamWaves;
 constexpr int kHereRows = 32;                         // most rows (or raw queries, grouped here)
+constexpr int kMostPairs = 8192;                      // most words asked for (FewStep::query_of)
 
 // LDS behind what the streaming needs: fp32 rows (h_in, then the hidden vectors) and the sums of the matrix products,
 // [wave][result][half][row], both with 16 bytes between them that spread them over the banks.
@@ -400,6 +401,30 @@ __global__ __launch_bounds__(kThreads) void step_few_kernel(ModelDev m, FewStep 
 
 bool step_few_supported(int dtype, int Hp) { return dtype == RNNLM_BF16 ? Hp <= 256 : Hp <= 128; }
 
+// Workgroups: one per block of 32 words up to 40 of them, then one per six blocks, between 40 and 160.  More of them share the stream,
+// but each repeats the hidden update and leaves partials to the last one (bf16, Hp = 128, 16 rows, 256 / 160 / 105 / 79 workgroups:
+// V = 20000 11.5 / 10.5 / 10.2 / 10.5 us, V = 80000 12.8 / 12.3 / - / 12.5; V = 5000, 160 / 80 / 40: 10.1 / 9.3 / 9.3).
+static int few_splits(int T) { return std::min(T, std::min(160, std::max(40, T / 6))); }
+
+static size_t few_bytes(const ModelDev &m) { return (size_t)m.Vp * m.Hp * (m.dtype == RNNLM_BF16 ? 2 : 4); }
+
+// Do the words asked for, P = N * K, suit the launch?  Up to 2048 its last workgroup finishes them beside the partials.  Beyond, every further 2048
+// are a round of that workgroup, about 1 us, and more than a batch for every wave another batch, 1.5; the query kernel pays 1.4 us for every 32
+// words of a query beyond the first 32.  Small weights leave it 1.5 us ahead.  (In units of half a microsecond.)  Replayed steps of N queries of K
+// words from 8 rows, us, three launches / this one:
+//   V = 1000, Hp = 64, fp32    128 of 32 11.1 / 9.8, 256 of 24 11.2 / 12.5, 100 of 64 12.6 / 13.1, 64 of 128 15.6 / 13.6, 1000 of 8 11.2 / 13.5, 1 of 8192 302 / 13.3
+//   V = 4000, Hp = 128, fp32   128 of 32 12.2 / 12.1, 256 of 24 12.2 / 14.7, 100 of 64 13.5 / 15.2, 64 of 128 16.1 / 15.7, 1000 of 8 12.2 / 15.8
+//   V = 8000, Hp = 256, bf16 (6 rows)    256 of 8 12.0 / 11.9, 100 of 30 11.9 / 14.2, 64 of 64 13.2 / 14.5, 32 of 128 15.5 / 14.5, 64 of 128 15.6 / 19.1
+//   V = 90000, Hp = 128, bf16 (4 rows)   256 of 8 12.1 / 11.7, 100 of 30 12.2 / 12.7, 64 of 64 13.4 / 12.8, 64 of 128 16.5 / 14.4, 1000 of 8 12.1 / 14.2
+static bool words_chosen(const ModelDev &m, int N, int K) {
+    const long long P = (long long)N * K;
+    if (P <= 2048) return P > 0;
+    if (P > kMostPairs) return false;
+    const int per_batch = few_splits(m.Vp / 32) * kWaves * (m.Hp <= 128 ? 16 : 8);       // (Pairs::per_batch of every wave)
+    const int rounds = ((int)P - 1) / 2048, batches = ((int)P - 1) / per_batch, old_rounds = (K - 1) / 32;
+    return 2 * rounds + 3 * batches < 3 * old_rounds + (m.Hp <= 128 && few_bytes(m) <= 8u << 20 ? 3 : 0);
+}
+
 // Replayed steps of 8 words per query, us, three launches / this one (the host's part, 14 to 16.5 us for three launches, 9 to 10.5 for
 // one, is not in it):
 //   V = 1200    Hp = 128 rows 1, 16, 32   10.4 / 7.7, 11.0 / 8.7, 11.0 / 10.4;  Hp = 192, 32   11.7 / 13.1;  Hp = 256, 16   11.7 / 11.4
@@ -409,18 +434,13 @@ bool step_few_supported(int dtype, int Hp) { return dtype == RNNLM_BF16 ? Hp <= 
 // and with the ids to group in front: V = 20000, Hp = 128, 16, 32 rows 12.7 / 10.8, 13.0 / 12.7, V = 80000 1, 16 rows 12.8 / 12.1, 13.6 / 13.0,
 // Hp = 192 1 row 14.1 / 13.4.  fp32 models: V = 5000, Hp = 64, 32 rows 11.5 / 10.6, V = 80000, Hp = 128, 16 rows 17.9 / 17.4.  What this launch
 // pays more for is rows x units, computed in every workgroup, and the weights it cannot request meanwhile; what it saves is launches.
-bool step_few_chosen(const ModelDev &m, int rows, bool grouped) {
-    if (rows <= 0 || rows > kHereRows || !m.Wfrag) return false;
-    const size_t bytes = (size_t)m.Vp * m.Hp * (m.dtype == RNNLM_BF16 ? 2 : 4);
+bool step_few_chosen(const ModelDev &m, int rows, bool grouped, int N, int K) {
+    if (rows <= 0 || rows > kHereRows || !m.Wfrag || !words_chosen(m, N, K)) return false;
+    const size_t bytes = few_bytes(m);
     if (bytes <= (grouped ? 8u : 2u) << 20) return rows * m.Hp <= 4096;
     if (bytes <= 8u << 20) return rows * m.Hp <= 2048;
     return bytes <= 48u << 20 && m.Hp <= (grouped ? 192 : 128) && rows * m.Hp <= (grouped ? 2048 : 1024);
 }
-
-// Workgroups: one per block of 32 words up to 40 of them, then one per six blocks, between 40 and 160.  More of them share the stream,
-// but each repeats the hidden update and leaves partials to the last one (bf16, Hp = 128, 16 rows, 256 / 160 / 105 / 79 workgroups:
-// V = 20000 11.5 / 10.5 / 10.2 / 10.5 us, V = 80000 12.8 / 12.3 / - / 12.5; V = 5000, 160 / 80 / 40: 10.1 / 9.3 / 9.3).
-static int few_splits(int T) { return std::min(T, std::min(160, std::max(40, T / 6))); }
 
 template <auto Kernel>
 static hipError_t launch_kernel(const ModelDev &m, const FewStep &a, int S, size_t lds_bytes, hipStream_t stream) {

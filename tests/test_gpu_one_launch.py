@@ -65,6 +65,19 @@ def test_rows_and_grouped(dtype, V, H, B, K, one):
     m.close()
 
 
+@pytest.mark.parametrize("dtype,V,H,B,N,K,one", [("f32", 1000, 64, 8, 1, 8192, True), ("f32", 1000, 64, 8, 1, 8193, False), ("f32", 1000, 64, 8, 128, 32, True),
+                                                 ("f32", 1000, 64, 8, 64, 128, True), ("f32", 1000, 64, 8, 256, 24, False), ("f32", 4000, 128, 8, 200, 40, False),
+                                                 ("bf16", 8000, 256, 6, 256, 8, True), ("bf16", 8000, 256, 6, 100, 30, False), ("bf16", 8000, 256, 6, 32, 128, True),
+                                                 ("bf16", 8000, 256, 6, 64, 128, False), ("bf16", 90000, 128, 4, 64, 64, True), ("bf16", 90000, 128, 4, 400, 20, False)])
+def test_many_words(dtype, V, H, B, N, K, one):
+    """Where the last workgroup would take longer over the words than the separate launches."""
+    m = load_model(make(V, H, dtype), dtype, 512)
+    s = Step(m, V, H, B, N, K)
+    assert m.one_launch(B, N, K, mapped=True) == one
+    assert (launches(lambda: s.rows(mapped=True)) == 1) == one
+    m.close()
+
+
 @pytest.mark.parametrize("dtype,H,B,N,K,mapped,one", [("f32", 128, 512, 512, 4, False, True), ("f32", 128, 513, 513, 4, False, False), ("bf16", 128, 9, 9, 3, False, False),
                                                       ("bf16", 256, 256, 256, 6, False, True), ("bf16", 257, 9, 9, 8, False, False), ("f32", 180, 128, 256, 6, True, True),
                                                       ("f32", 180, 129, 256, 6, True, False)])

@@ -69,6 +69,19 @@ def test_more_queries_than_rows(dtype, N, K):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K", [(128, 32), (64, 128), (40, 150), (20, 409), (8, 1024)])
+def test_more_words_than_one_round(dtype, N, K):
+    """More answers than the last workgroup holds beside the partials, and more than one batch of dot products a wave."""
+    V, H, B = 3000, 96, 12
+    model = make(V, H, dtype)
+    m = load_model(model, dtype, 256)
+    assert m.one_launch(B, N, K, mapped=True)
+    prev, h_in, query, row = inputs(V, H, B, N, K)
+    check(gpu_step(m, prev, h_in, query, row), oracle.step(model, prev, h_in, query, row_of_query=row), dtype)
+    m.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,H", [(1, 70), (2, 128), (31, 64), (32, 120), (20, 190), (16, 256)])
 def test_grouped(dtype, N, H):
     V, K = 1500, 6
