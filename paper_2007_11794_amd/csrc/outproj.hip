@@ -268,7 +268,6 @@ float outproj_d_scale(const ModelDev &m, int rows, bool fixed_offset, int kernel
 // For a launch sized for `rows` rows that streams its weights where few of them are left (the tiled kernel's form of it apart).  Weights that
 // fit the L2s (8 x 4 MB) are still there from the step before: V = 20000, H = 256, 8 steps through the cache 169.5 us, 170 to 174 read
 // ahead; as fp32 model 200.8, 200.0.
-constexpr size_t kAllL2s = (size_t)kXcds * 4 << 20;
 WeightsAhead outproj_weights_ahead(const ModelDev &m, int rows, bool fixed_offset, int kernel_choice) {
     WeightsAhead a = {};
     if (rows <= 0 || m.hs || !m.Ofrag || (size_t)m.Vp * m.Hp * (m.dtype == RNNLM_BF16 ? 2 : 4) <= kAllL2s || m.Vp / 32 < kMaxSplits) return a;

@@ -184,6 +184,7 @@ hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int
 constexpr int kStagedRows = 256;   // rows per workgroup of the staged kernel
 constexpr int kStagedWords = 32;   // words per LDS stage
 constexpr int kXcds = 8;           // workgroup id modulo 8 = the XCD (L2 domain) it runs on
+constexpr size_t kAllL2s = (size_t)kXcds * 4 << 20;
 
 // Work split of an output-projection kernel for B rows on a grid of kXcds * wg_per_xcd workgroups.
 // The true B may be known on the device only (after the grouping of ids or the cache lookup), so the

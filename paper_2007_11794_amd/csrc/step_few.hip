@@ -432,14 +432,25 @@ static bool words_chosen(const ModelDev &m, int N, int K) {
 //   V = 20000   Hp = 128 rows 1, 16   10.5 / 9.2, 11.3 / 10.2;  Hp = 192, 1, 16   11.2 / 10.4, 11.8 / 12.0
 //   V = 80000   Hp = 128 rows 1, 16   11.2 / 11.2, 11.9 / 12.3;  Hp = 256, 1   16.2 / 17.1
 // and with the ids to group in front: V = 20000, Hp = 128, 16, 32 rows 12.7 / 10.8, 13.0 / 12.7, V = 80000 1, 16 rows 12.8 / 12.1, 13.6 / 13.0,
-// Hp = 192 1 row 14.1 / 13.4.  fp32 models: V = 5000, Hp = 64, 32 rows 11.5 / 10.6, V = 80000, Hp = 128, 16 rows 17.9 / 17.4.  What this launch
-// pays more for is rows x units, computed in every workgroup, and the weights it cannot request meanwhile; what it saves is launches.
+// Hp = 192 1 row 14.1 / 13.4.  What this launch pays more for is rows x units, computed in every workgroup (Hp = 192 beyond 16 rows in a third
+// piece a thread: 21 rows, V = 5000 11.4 / 11.8, grouped V = 20000 13.1 / 13.4), and the weights it cannot request meanwhile; what it saves is launches.
+// fp32 models pay twice the latter.  Rows the caller has told apart, weights that the L2s still hold from the step before:
+//   V = 4000    Hp = 128 rows 24, 32   12.1 / 11.8, 12.2 / 12.6;  V = 22000   Hp = 64, 24, 32   11.4 / 10.9, 11.4 / 11.4
+//   V = 30000   Hp = 64 rows 16, 24, 32   11.1 / 10.9, 11.4 / 11.5, 11.5 / 12.1;  V = 70000   Hp = 64, 8, 16   11.8 / 11.5, 11.9 / 12.2
+//   Hp = 128 rows 1, 8   V = 40000 12.3 / 12.5, 12.6 / 12.8;  V = 46000 12.2 / 13.1, 12.7 / 13.4;  V = 58000 12.7 / 13.5, 13.4 / 13.7
+// and beyond them   V = 70000   Hp = 128 rows 1, 8   15.7 / 14.6, 16.2 / 14.9;  V = 130000   Hp = 64, 16   14.8 / 14.0;  grouped   V = 5000   Hp = 64, 32
+// 11.5 / 10.6, V = 50000   Hp = 128, 16   15.6 / 14.9.
 bool step_few_chosen(const ModelDev &m, int rows, bool grouped, int N, int K) {
     if (rows <= 0 || rows > kHereRows || !m.Wfrag || !words_chosen(m, N, K)) return false;
     const size_t bytes = few_bytes(m);
-    if (bytes <= (grouped ? 8u : 2u) << 20) return rows * m.Hp <= 4096;
-    if (bytes <= 8u << 20) return rows * m.Hp <= 2048;
-    return bytes <= 48u << 20 && m.Hp <= (grouped ? 192 : 128) && rows * m.Hp <= (grouped ? 2048 : 1024);
+    const int units = rows * m.Hp;
+    if (bytes <= (grouped ? 8u : 2u) << 20) return m.Hp == 192 ? rows <= 16 : units <= (m.dtype != RNNLM_BF16 && !grouped ? 3072 : 4096);
+    if (m.dtype != RNNLM_BF16 && !grouped && bytes <= kAllL2s) {
+        if (bytes <= 8u << 20) return units <= 2048 && (rows <= 16 || bytes <= 6u << 20);
+        return rows <= 8 && (m.Hp <= 64 || bytes <= 22u << 20);
+    }
+    if (bytes <= 8u << 20) return units <= 2048;
+    return bytes <= 48u << 20 && m.Hp <= (grouped ? 192 : 128) && units <= (grouped ? 2048 : 1024);
 }
 
 template <auto Kernel>

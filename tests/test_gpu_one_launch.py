@@ -78,6 +78,19 @@ def test_many_words(dtype, V, H, B, N, K, one):
     m.close()
 
 
+@pytest.mark.parametrize("dtype,V,H,B,rows,grouped", [("f32", 4000, 128, 24, True, True), ("f32", 4000, 128, 25, False, True), ("bf16", 4000, 128, 32, True, True),
+                                                      ("bf16", 5000, 192, 16, True, True), ("bf16", 5000, 192, 17, False, False), ("f32", 30000, 64, 16, True, True),
+                                                      ("f32", 30000, 64, 17, False, True), ("f32", 34000, 64, 8, True, True), ("f32", 34000, 64, 9, False, True),
+                                                      ("f32", 42000, 128, 8, True, True), ("f32", 46000, 128, 1, False, True), ("f32", 67000, 128, 8, True, True)])
+def test_rows_times_units_and_bytes(dtype, V, H, B, rows, grouped):
+    """The lines of step_few_chosen, where the caller has told the rows apart and where the ids are grouped."""
+    m = load_model(make(V, H, dtype), dtype, 64)
+    s = Step(m, V, H, B, B, 4)
+    assert m.one_launch(B, B, 4) == rows and m.one_launch(0, B, 4, grouped=True) == grouped
+    assert (launches(s.rows) == 1) == rows and (launches(s.grouped) == 1) == grouped
+    m.close()
+
+
 @pytest.mark.parametrize("dtype,H,B,N,K,mapped,one", [("f32", 128, 512, 512, 4, False, True), ("f32", 128, 513, 513, 4, False, False), ("bf16", 128, 9, 9, 3, False, False),
                                                       ("bf16", 256, 256, 256, 6, False, True), ("bf16", 257, 9, 9, 8, False, False), ("f32", 180, 128, 256, 6, True, True),
                                                       ("f32", 180, 129, 256, 6, True, False)])
