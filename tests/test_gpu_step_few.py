@@ -8,7 +8,7 @@ import oracle
 import paper_2007_11794_amd as rn
 from workloads import round_to_bf16
 
-from harness import DEV, gpu_step, gpu_step_dedup, load_model
+from harness import DEV, CachedStepper, gpu_step, gpu_step_dedup, load_model
 
 pytestmark = pytest.mark.gpu
 BARS = {"f32": (1e-5, 1e-5), "bf16": (1e-3, 2e-3)}
@@ -60,7 +60,7 @@ def test_rows(dtype, V, H, B, K):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,K", [(1, 8192), (200, 40), (201, 41), (3, 3)])
 def test_more_queries_than_rows(dtype, N, K):
-    V, H, B = 3000, 96, min(N, 12)                                # (201 x 41 words: beyond what one workgroup finishes)
+    V, H, B = 3000, 96, min(N, 12)                                # (200 x 40 words and more: the separate launches)
     model = make(V, H, dtype)
     m = load_model(model, dtype, 256)
     prev, h_in, query, row = inputs(V, H, B, N, K)
@@ -154,4 +154,50 @@ def test_rows_in_single_floats():
     h_out, lp = torch.zeros((B, H), device=DEV), torch.zeros((B, K), device=DEV)
     rn.rnnlm_step(m, torch.from_numpy(prev).to(DEV), flat[1:].view(B, H), torch.from_numpy(query).to(DEV), h_out, lp)
     check((h_out.cpu().numpy(), lp.cpu().numpy()), oracle.step(model, prev, h_in, query), "bf16")
+    m.close()
+
+
+@pytest.mark.parametrize("dtype,V,H,B,K", [("f32", 1300, 65, 17, 3), ("f32", 4000, 128, 24, 8), ("f32", 15000, 100, 16, 7), ("f32", 20011, 100, 8, 11), ("f32", 30011, 50, 16, 5),
+                                           ("bf16", 900, 192, 16, 8), ("bf16", 8000, 117, 32, 6), ("bf16", 4100, 200, 5, 2), ("bf16", 16000, 251, 8, 4), ("bf16", 30011, 128, 16, 9)])
+def test_rows_up_to_the_lines(dtype, V, H, B, K):
+    """The largest steps that are one launch, and that they are."""
+    model = make(V, H, dtype)
+    m = load_model(model, dtype, 64)
+    assert m.one_launch(B, B, K)
+    prev, h_in, query, _ = inputs(V, H, B, B, K)
+    out = gpu_step(m, prev, h_in, query)
+    check(out, oracle.step(model, prev, h_in, query), dtype)
+    m.set_option(rn.OPT_OUTPROJ_KERNEL, 5)
+    assert not m.one_launch(B, B, K)
+    old = gpu_step(m, prev, h_in, query)
+    assert np.max(np.abs(out[0] - old[0])) <= 1e-6 and np.max(np.abs(out[1] - old[1])) <= ROUTES[dtype]
+    m.close()
+
+
+# (32, 100): more answers than the last workgroup holds beside the partials
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,K", [(1, 5), (16, 7), (32, 3), (32, 100)])
+def test_grouped_with_base_scores(dtype, N, K):
+    V, H = 1500, 90
+    model = make(V, H, dtype)
+    m = load_model(model, dtype, 64)
+    assert m.one_launch(0, N, K, grouped=True)
+    prev, h_in, query, _ = inputs(V, H, N, N, K)
+    rng = np.random.default_rng(N + K)
+    ids = rng.integers(0, 2 ** 63, max(1, N // 2), dtype=np.uint64)[rng.integers(0, max(1, N // 2), N)]
+    u, rep, inv = oracle.dedup(ids)
+    prev, h_in = prev[rep][inv], h_in[rep][inv]
+    base = rng.normal(0, 2, (N, K)).astype(np.float32)
+    st = CachedStepper(m, None, N, K)
+    plain, less = st.step(ids, prev, h_in, query), st.step(ids, prev, h_in, query, base)
+    assert plain["n_unique"] == less["n_unique"] == u and np.array_equal(plain["rep"], rep) and np.array_equal(less["inverse"], inv)
+    assert np.array_equal(less["score"], plain["score"] - base)             # one fp32 subtraction
+    assert np.array_equal(less["h_out"], plain["h_out"])
+    check((plain["h_out"], plain["score"]), oracle.step(model, prev[rep], h_in[rep], query, row_of_query=inv), dtype)
+    # the answers in the place of the base scores: the launches that read them first
+    t = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(DEV)
+    both, h_out = t(base), torch.zeros((N, H), device=DEV)
+    r, i, nu = (torch.zeros(n, dtype=torch.int32, device=DEV) for n in (N, N, 1))
+    rn.rnnlm_step_cached(m, None, t(ids.view(np.int64)), t(prev), t(h_in), t(query), r, i, nu, h_out, both, st.ws, base_score=both)
+    assert np.max(np.abs(both.cpu().numpy() - less["score"])) <= ROUTES[dtype] + 1e-6         # (one more rounding of sums below 16)
     m.close()
