@@ -179,7 +179,18 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, const Cache
 // next one, and the workgroup of split s runs on XCD s % 8.  Bound by the lookup, which they hide behind; more bytes push each other out before
 // they are used, or last longer than it.  A search's eight steps, us, none / 48 / 64 / 96 KB of every split: V = 65536, H = 512, 41 new
 // histories of 4096 ids 303.7 / 294.3 / 294.6 / 298.2; V = 100000, H = 320 245.1 / 234.4 / 233.2 / 226.7; V = 200000, H = 1024 885 / 873 / 875 /
-// 869; fp32 V = 65536, H = 512 410.6 / 404.1 / 403.5 / 400.2; 450 new ones of 3000 ids, nothing streamed, 411.7 / 411.7 / 413.4 / 414.3.
+// 869; fp32 V = 65536, H = 512 410.6 / 404.1 / 403.5 / 400.2.  How many rows are left only the lookup finds out, too late to read ahead by it.
+// One step, us, none / 64 KB:          few new (streamed)               all found                many new (not streamed)
+//   V = 65536, H = 512    64 ids       4 new 28.9 / 28.7                12.4 / 13.5              64 new 29.9 / 28.8 (streamed)
+//                         1024         10 new 30.4 / 29.1               13.5 / 14.2              100 new 32.0 / 32.2
+//                         4096         41 new 35.7 / 35.2               18.0 / 18.8              410 new 46.7 / 47.0
+//                         7000         60 new 45.2 / 44.5               27.4 / 28.4              2000 new 135.2 / 136.8
+//   V = 100000, H = 320   1024         10 new 28.4 / 26.8               13.2 / 13.9              100 new 29.9 / 28.8 (69.7 / 70.0 for 1024)
+//                         4096         41 new 33.6 / 32.0               17.8 / 18.3              410 new 45.7 / 45.9
+//   V = 200000, H = 1024  1024         10 new 95.6 / 93.7               15.1 / 15.6              100 new 151.2 / 151.3
+//   fp32 65536, 512       1024         10 new 43.9 / 42.0               14.3 / 14.4              100 new 51.4 / 50.8
+//                         4096         41 new 56.1 / 55.9               21.3 / 21.8              410 new 114.0 / 114.4
+// So at every number of ids it gives 0.2 to 1.9 us where few histories are new, the usual step, and takes 0.1 to 1.1 where none is.
 // (In the shadow of the hidden update instead, on the compute units it leaves idle: 300 -> 324, it is the shorter launch.)
 constexpr int kAheadGroups = 128, kAheadBytes = 64 * 1024;
 __device__ __forceinline__ void read_ahead(const WeightsAhead &a) {
