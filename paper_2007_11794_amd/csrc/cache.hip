@@ -42,22 +42,22 @@ __global__ __launch_bounds__(256) void cache_reset_kernel(CacheDev c, long long 
 }
 
 // One workgroup.  A round covers kLookupPer * 1024 distinct histories: every thread first
-// requests the first table cell of all its kLookupPer histories (the usual probe ends there),
-// then finishes the probes, then the round's misses are numbered chunk by chunk in order of
+// requests the first table cell of all its up to kLookupPer histories (the usual probe ends there),
+// then finishes the probes, then one prefix sum numbers the round's misses in order of
 // u, and last the new keys are inserted.  Insertions happen only after every probe of the
-// round is over (barriers of the scans in between), so no probe reads a half-written cell;
+// round is over (barriers of the scan in between), so no probe reads a half-written cell;
 // the keys of one step are distinct, so a later round can never look for a key that an
 // earlier round of the same step inserted.
 constexpr int kLookupPer = 4;
 
-// raw_of(u0, i, u) / key_of(u0, i, u, raw): representative and id of distinct history u (slice i of
-// the round that starts at u0), u < U.
+// raw_of(u) / key_of(u, raw): representative and id of distinct history u < U.
 //
 // This workgroup is the only one that inserts, so who gets a free cell is settled in LDS: `claims` (claim_slots ints,
 // more than there can be insertions) is a set of the cells given away in this launch, and a new cell is one
 // 16-byte store.  (Compare-and-swaps on the table itself, one cache line each, were part of what the
 // launch takes when every history is new: 4096 new contexts 33.5 us, now 30.0; 2048: 17.6, now 13.2.)  The set also makes a cell that an
-// earlier round took, and that this compute unit may still read as free, unavailable.
+// earlier round took, and that this compute unit may still read as free, unavailable.  (All the slots there are room for, not twice the
+// histories: half full, their chains made 1229 new contexts 2.6 us slower.)
 __device__ __forceinline__ bool claim_cell(int *claims, int claim_slots, uint32_t cell) {
     uint32_t s = (uint32_t)(((uint64_t)(cell * 0x9E3779B1u) * (uint32_t)claim_slots) >> 32);
     for (;;) {                                       // fewer claims than slots: a free one is always met
@@ -88,25 +88,28 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, const Cache
     const uint32_t mask = (uint32_t)(c.table_size - 1);
     int n_miss = 0;                         // misses numbered so far (same in every thread)
     for (int i = threadIdx.x; i < claim_slots; i += kLookupThreads) claims[i] = -1;   // barriers before the first claim
+    // Thread t takes the `per` distinct histories from u0 + t * per on: one prefix sum numbers a round's misses in order of u.
+    const int per = per_thread(U, kLookupThreads);
     for (int u0 = 0; u0 < U; u0 += kLookupPer * kLookupThreads) {
+        const int first = u0 + (int)threadIdx.x * per;
         uint64_t key[kLookupPer];
         int raw[kLookupPer], found[kLookupPer];
         uint32_t h[kLookupPer];
         CacheCell cell[kLookupPer];
 #pragma unroll
         for (int i = 0; i < kLookupPer; ++i) {
-            const int u = u0 + i * kLookupThreads + (int)threadIdx.x;
-            raw[i] = (u < U) ? raw_of(u0, i, u) : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < kLookupPer; ++i) {
-            const int u = u0 + i * kLookupThreads + (int)threadIdx.x;
-            key[i] = (u < U) ? key_of(u0, i, u, raw[i]) : 0;
-            h[i] = mix64(key[i]) & mask;
+            found[i] = 0;                               // (not a miss)
+            if (i >= per || first >= U) continue;
+            const int u = min(first + i, U - 1);
+            raw[i] = raw_of(u);
+            key[i] = key_of(u, raw[i]);
+            h[i] = id_hash(key[i]) & mask;
             cell[i] = c.table[h[i]];
         }
+        int mine = 0;
 #pragma unroll
         for (int i = 0; i < kLookupPer; ++i) {
+            if (i >= per || first >= U) continue;
             found[i] = -1;
             // At most capacity <= table_size / 2 cells are taken: a free cell is always met.
             for (int probe = 0; probe < c.table_size; ++probe) {
@@ -115,35 +118,32 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, const Cache
                 h[i] = (h[i] + 1) & mask;
                 cell[i] = c.table[h[i]];
             }
+            mine += first + i < U && found[i] < 0 ? 1 : 0;
         }
-        int entry[kLookupPer];
+        int total;
+        int rank = n_miss + block_exclusive_scan(mine, wsum, total);
+        n_miss += total;
+        int entry[kLookupPer], row[kLookupPer];
 #pragma unroll
         for (int i = 0; i < kLookupPer; ++i) {
-            const int u = u0 + i * kLookupThreads + (int)threadIdx.x;
-            entry[i] = -1;
-            if (u0 + i * kLookupThreads >= U) continue;       // uniform: nobody has a history in this slice
-            const bool active = u < U;
-            const int miss = (active && found[i] < 0) ? 1 : 0;
-            int total;
-            const int rank = n_miss + block_exclusive_scan(miss, wsum, total);
-            n_miss += total;
-            entry[i] = -1;
-            if (miss) {
-                entry[i] = (base + rank < c.capacity) ? base + rank : -1;
-                c.miss_of[u] = rank;
+            entry[i] = found[i];
+            row[i] = -1;
+            if (first + i < U && found[i] < 0) {        // (false beyond `per`)
+                entry[i] = base + rank < c.capacity ? base + rank : -1;
+                row[i] = rank;
                 c.miss_src[rank] = raw[i];
-                c.miss_dst[rank] = u;
-                c.entry_of[u] = entry[i];
-            } else if (active) {
-                c.miss_of[u] = -1;
-                c.entry_of[u] = found[i];
+                c.miss_dst[rank] = first + i;
+                ++rank;
             }
         }
-        // Every probe of this round is done (the scans above contain barriers).  A probe that missed ended at
+        store_some(c.miss_of, first, per, U, row);
+        store_some(c.entry_of, first, per, U, entry);
+        if (total == 0) continue;                       // uniform
+        // Every probe of this round is done (the scan above contains barriers).  A probe that missed ended at
         // the first free cell of its chain, and cells are never given back: the insertion starts there.
 #pragma unroll
         for (int i = 0; i < kLookupPer; ++i) {
-            if (entry[i] < 0) continue;
+            if (row[i] < 0 || entry[i] < 0) continue;
             while (!claim_cell(claims, claim_slots, h[i])) {
                 do h[i] = (h[i] + 1) & mask;
                 while (c.table[h[i]].entry >= 0);
@@ -154,8 +154,10 @@ __device__ __forceinline__ void cache_lookup_body(const CacheDev &c, const Cache
             mine.pad = 0;
             c.table[h[i]] = mine;
         }
-        __threadfence_block();
-        __syncthreads();                    // this round's insertions precede the next round's probes
+        if (u0 + kLookupPer * kLookupThreads < U) {     // uniform: this round's insertions precede the next round's probes
+            __threadfence_block();
+            __syncthreads();
+        }
     }
     if (threadIdx.x == 0) {
         const int stored = min(n_miss, max(c.capacity - base, 0));
@@ -230,8 +232,7 @@ __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_kernel(
     const SmallGroups g = dedup_small_body(ids, N, rep, inverse, n_unique);
     __syncthreads();                        // the groups in LDS are complete
     cache_lookup_body(
-        c, counts, g.total, step_stats, g.spare, kSmallCap, [&](int, int, int u) { return g.rep[u]; },
-        [&](int, int, int u, int) { return g.id[u]; });
+        c, counts, g.total, step_stats, g.spare, kSmallCap, [&](int u) { return g.rep[u]; }, [&](int u, int) { return g.id[u]; });
 }
 
 // The same for up to kMediumN raw queries (the grouping keeps the keys in LDS in raw order).
@@ -247,8 +248,8 @@ __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_medium_kernel(
     const MediumGroups g = dedup_medium_body(ids, N, rep, inverse, n_unique);
     __syncthreads();                        // the representatives in LDS are complete
     cache_lookup_body(
-        c, counts, g.total, step_stats, g.spare, kMediumCap - kMediumN, [&](int, int, int u) { return g.rep[u]; },
-        [&](int, int, int, int raw) { return g.key[raw]; });
+        c, counts, g.total, step_stats, g.spare, kMediumCap - kMediumN, [&](int u) { return g.rep[u]; },
+        [&](int, int raw) { return g.key[raw]; });
 }
 
 // ---- the same lookup for many histories (more than one workgroup can number in one round):
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(kLookupThreads) void dedup_lookup_medium_kernel(
 // launch boundaries put every probe before every insertion.
 __device__ __forceinline__ int probe_table(const CacheDev &c, uint64_t key) {
     const uint32_t mask = (uint32_t)(c.table_size - 1);
-    uint32_t h = mix64(key) & mask;
+    uint32_t h = id_hash(key) & mask;
     for (int probe = 0; probe < c.table_size; ++probe) {
         const CacheCell cell = c.table[h];
         if (cell.entry < 0) return -1;
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(kLookupThreads) void lookup_assign_kernel(
         c.entry_of[u] = entry;
         if (entry >= 0) {
             const uint32_t mask = (uint32_t)(c.table_size - 1);
-            uint32_t h = mix64(key) & mask;
+            uint32_t h = id_hash(key) & mask;
             for (int probe = 0; probe < c.table_size; ++probe) {
                 if (atomicCAS(&c.table[h].entry, -1, entry) == -1) {
                     c.table[h].key = key;

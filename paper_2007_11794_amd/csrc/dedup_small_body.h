@@ -17,7 +17,7 @@ constexpr int kSmallThreads = 1024;
 template <typename KeyPtr>
 __device__ __forceinline__ int find_or_insert(KeyPtr tkeys, int cap, uint64_t key) {
     if (key == kEmpty) return cap;
-    uint32_t h = mix64(key) & (uint32_t)(cap - 1);
+    uint32_t h = id_hash(key) & (uint32_t)(cap - 1);
     // The table holds at most N <= cap/2 keys, so a free slot is always met.
     for (int probe = 0; probe < cap; ++probe) {
         unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long *>(&tkeys[h]),
@@ -26,6 +26,70 @@ __device__ __forceinline__ int find_or_insert(KeyPtr tkeys, int cap, uint64_t ke
         h = (h + 1) & (uint32_t)(cap - 1);
     }
     return -1;   // unreachable for N <= cap/2
+}
+
+// The same for a table in LDS and PER keys of a thread.  The first probes, with which most end, are on their way together (all the
+// further ones too was slower: a loop over PER keys is long).  What the insertion lasts is its longest chain, some 60 ns a probe, so the further
+// slots of a key are an odd number apart that is its own: with a step of one 1024 different ids in 2048 slots made chains of 9 to 19, and a hidden
+// update with them in front of it took 1 to 2 us more for the longer ones.  slot[i] = -1 where valid(i) is false.
+template <int PER, typename KeyPtr, class Valid>
+__device__ __forceinline__ void find_or_insert_lds(KeyPtr tkeys, int cap, const uint64_t (&key)[PER], int (&slot)[PER], Valid valid) {
+    unsigned long long old[PER];
+    int step[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        slot[i] = -1;
+        old[i] = kEmpty;
+        step[i] = 1;
+        if (!valid(i)) continue;
+        slot[i] = cap;
+        if (key[i] == kEmpty) continue;
+        const uint32_t h = id_hash(key[i]);
+        slot[i] = (int)(h & (uint32_t)(cap - 1));
+        step[i] = (int)(h >> 16) | 1;
+        old[i] = atomicCAS(reinterpret_cast<unsigned long long *>(&tkeys[slot[i]]), (unsigned long long)kEmpty, (unsigned long long)key[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        // The table holds at most half as many keys as it has slots, so a free slot is always met.
+        for (int probe = 1; probe < cap && old[i] != kEmpty && old[i] != key[i]; ++probe) {
+            slot[i] = (slot[i] + step[i]) & (cap - 1);
+            old[i] = atomicCAS(reinterpret_cast<unsigned long long *>(&tkeys[slot[i]]), (unsigned long long)kEmpty, (unsigned long long)key[i]);
+        }
+    }
+}
+
+// How many of n things, side by side, a thread of `threads` takes: 1, 2 or 4 (more threads do nothing instead), so that what they
+// read and write goes in whole vectors.  For n <= 4 * threads.
+__device__ __forceinline__ int per_thread(int n, int threads) { return n > 2 * threads ? 4 : n > threads ? 2 : 1; }
+
+// Elements at .. at + per - 1 (per <= CAP <= 4, a power of two, the same in all threads) of p[n], together where they all exist; 0
+// in the others.
+template <typename T, int CAP>
+__device__ __forceinline__ void load_some(const T *p, int at, int per, int n, T (&v)[CAP]) {
+#pragma unroll
+    for (int i = 0; i < CAP; ++i) v[i] = 0;
+    if (CAP == 4 && per == 4 && at + 4 <= n) {
+        __builtin_memcpy(v, p + at, sizeof v);
+    } else if (per == 2 && at + 2 <= n) {
+        __builtin_memcpy(v, p + at, 2 * sizeof(T));
+    } else {
+#pragma unroll
+        for (int i = 0; i < CAP; ++i)
+            if (i < per && at + i < n) v[i] = p[at + i];
+    }
+}
+template <int CAP>
+__device__ __forceinline__ void store_some(int32_t *p, int at, int per, int n, const int (&v)[CAP]) {
+    if (CAP == 4 && per == 4 && at + 4 <= n) {
+        __builtin_memcpy(p + at, v, sizeof v);
+    } else if (per == 2 && at + 2 <= n) {
+        __builtin_memcpy(p + at, v, 2 * sizeof(int));
+    } else {
+#pragma unroll
+        for (int i = 0; i < CAP; ++i)
+            if (i < per && at + i < n) p[at + i] = v[i];
+    }
 }
 
 // What the grouping leaves in LDS for a consumer in the same workgroup (valid after a barrier):
@@ -38,51 +102,43 @@ struct SmallGroups {
 };
 
 // All kSmallThreads threads of the one workgroup call it; N <= kSmallN.
+// What bounds it is what one compute unit can issue, sixteen waves on four SIMDs, and the LDS trips behind each other.  Us per launch of 4096 ids,
+// 1229 distinct, before / with the short hash, whole vectors and first probes side by side 6.5 / 5.5; with the lookup behind it (cache.hip), 410
+// distinct, some 41 of them new 8.3 / 7.0, 1229 distinct, all new 12.2 / 10.3.
 __device__ __forceinline__ SmallGroups dedup_small_body(const uint64_t *__restrict__ keys, int N,
                                                         int32_t *__restrict__ rep, int32_t *__restrict__ inverse,
                                                         int32_t *__restrict__ n_unique) {
-    __shared__ uint64_t tkeys[kSmallCap + 1];
-    __shared__ int tfirst[kSmallCap + 1];    // min raw index per slot, later the group number
+    constexpr int kPer = kSmallN / kSmallThreads;      // queries per thread at most
+    static_assert(kPer == 4, "load_some, store_some");
+    __shared__ __attribute__((aligned(16))) uint64_t tkeys[kSmallCap + 2];
+    __shared__ __attribute__((aligned(16))) int tfirst[kSmallCap + 4];   // min raw index per slot, later the group number
     __shared__ int wsum[kSmallThreads / 64 + 1];
-    constexpr int kPer = kSmallN / kSmallThreads;      // queries per thread
     static_assert(kSmallN * 4 + kSmallN * 8 <= kSmallCap * 8, "rep and id of every group fit the key table");
     int *const rep_lds = reinterpret_cast<int *>(tkeys);                 // [kSmallN] ints = kSmallN / 2 slots
     uint64_t *const id_lds = tkeys + kSmallN / 2;                        // [kSmallN]
 
-    // Thread t owns the `per` contiguous queries from t * per on (per = ceil(N / threads), so all
-    // threads take part whatever N is); contiguous ownership makes the scan below run over
+    // Thread t owns the `per` contiguous queries from t * per on; contiguous ownership makes the scan below run over
     // raw-index order.  The keys are fetched first, all at once: an insertion is a loop around an
     // LDS atomic, and a load behind it would wait for it.
-    const int per = (N + kSmallThreads - 1) / kSmallThreads;
+    const int per = per_thread(N, kSmallThreads), n0 = threadIdx.x * per;
     uint64_t key[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int n = threadIdx.x * per + i;
-        key[i] = (i < per && n < N) ? keys[n] : 0;
-    }
-    for (int i = threadIdx.x; i <= kSmallCap; i += kSmallThreads) {     // while the keys are on their way
-        tkeys[i] = kEmpty;
-        tfirst[i] = 0x7FFFFFFF;
-    }
+    load_some(keys, n0, per, N, key);
+    constexpr u32x4 kFree = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, kNone = {0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu};
+    for (int i = threadIdx.x; i < (kSmallCap + 2) / 2; i += kSmallThreads) reinterpret_cast<u32x4 *>(tkeys)[i] = kFree;      // while the keys are on their way
+    for (int i = threadIdx.x; i < (kSmallCap + 4) / 4; i += kSmallThreads) reinterpret_cast<u32x4 *>(tfirst)[i] = kNone;
     __syncthreads();
     int slot[kPer];
+    find_or_insert_lds(tkeys, kSmallCap, key, slot, [&](int i) { return i < per && n0 + i < N; });
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int n = threadIdx.x * per + i;
-        slot[i] = -1;
-        if (i < per && n < N) {
-            slot[i] = find_or_insert(tkeys, kSmallCap, key[i]);
-            atomicMin(&tfirst[slot[i]], n);
-        }
-    }
+    for (int i = 0; i < kPer; ++i)
+        if (slot[i] >= 0) atomicMin(&tfirst[slot[i]], n0 + i);
     __syncthreads();
 
     int is_first[kPer];
     int mine = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        int n = threadIdx.x * per + i;
-        is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == n) ? 1 : 0;
+        is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == n0 + i) ? 1 : 0;
         mine += is_first[i];
     }
     int total;
@@ -90,20 +146,18 @@ __device__ __forceinline__ SmallGroups dedup_small_body(const uint64_t *__restri
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         if (is_first[i]) {
-            int n = threadIdx.x * per + i;
-            rep[u] = n;
-            rep_lds[u] = n;                            // (the key table is not read any more)
+            rep[u] = n0 + i;
+            rep_lds[u] = n0 + i;                       // (the key table is not read any more)
             id_lds[u] = key[i];
             tfirst[slot[i]] = u;                       // the slot now carries its group number
             ++u;
         }
     }
     __syncthreads();
+    int group[kPer];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        int n = threadIdx.x * per + i;
-        if (slot[i] >= 0) inverse[n] = tfirst[slot[i]];
-    }
+    for (int i = 0; i < kPer; ++i) group[i] = slot[i] >= 0 ? tfirst[slot[i]] : 0;
+    store_some(inverse, n0, per, N, group);
     if (threadIdx.x == 0) *n_unique = total;
     return SmallGroups{total, rep_lds, id_lds, tfirst};
 }
@@ -154,7 +208,8 @@ __device__ __forceinline__ MediumGroups dedup_medium_body(const uint64_t *__rest
         const int n = threadIdx.x * per + i;
         slot[i] = -1;
         if (i < per && n < N) {
-            uint32_t h = mix64(key[i]) & (uint32_t)(kMediumCap - 1);
+            const uint32_t hash = id_hash(key[i]), step = hash >> 16 | 1;      // as find_or_insert_lds
+            uint32_t h = hash & (uint32_t)(kMediumCap - 1);
             // at most N <= kMediumCap / 2 slots are ever taken: a free one is always met
             for (int probe = 0; probe < kMediumCap; ++probe) {
                 int cur = table[h];
@@ -167,7 +222,7 @@ __device__ __forceinline__ MediumGroups dedup_medium_body(const uint64_t *__rest
                     slot[i] = (int)h;
                     break;
                 }
-                h = (h + 1) & (uint32_t)(kMediumCap - 1);
+                h = (h + step) & (uint32_t)(kMediumCap - 1);
             }
         }
     }

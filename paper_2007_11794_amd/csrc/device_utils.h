@@ -212,16 +212,18 @@ __device__ __forceinline__ float2 load_seen(const float2 *p) {
 }
 __device__ __forceinline__ void seen_by_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// 64-bit key -> 32 well-mixed bits (hash tables of history ids).
-__device__ __forceinline__ uint32_t mix64(uint64_t k) {
-    // splitmix64 finaliser
-    k ^= k >> 30; k *= 0xBF58476D1CE4E5B9ull;
-    k ^= k >> 27; k *= 0x94D049BB133111EBull;
-    k ^= k >> 31;
-    return (uint32_t)k;
+// 64-bit key -> 32 mixed bits for the hash tables of history ids: the high word, multiplied and folded, added to the low one, then
+// a round of folding and multiplying.  Two 32-bit products, which take four slots of a SIMD each: one workgroup that hashes
+// 4096 ids issues little else (a 64-bit finaliser has eight of them, and shifts of 64 bits).
+__device__ __forceinline__ uint32_t id_hash(uint64_t k) {
+    uint32_t x = (uint32_t)(k >> 32) * 0x9E3779B1u;
+    x = (uint32_t)k + (x ^ (x >> 16));
+    x ^= x >> 16;
+    x *= 0x7FEB352Du;
+    return x ^ (x >> 15);
 }
 
-// The same finaliser with all 64 bits kept.
+// splitmix64 finaliser: 64 well-mixed bits
 __device__ __forceinline__ uint64_t mix64_full(uint64_t k) {
     k ^= k >> 30; k *= 0xBF58476D1CE4E5B9ull;
     k ^= k >> 27; k *= 0x94D049BB133111EBull;

@@ -485,40 +485,30 @@ constexpr int ring_bytes(int elem, bool half) { return (half ? 64 : elem == 2 ? 
 constexpr int kGroupedMax = 1024;
 
 __device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, int *wsum, const int *&rep_out) {
-    constexpr int kPer = kGroupedMax / kThreads, kCap = 2 * kGroupedMax;
+    constexpr int kPer = kGroupedMax / kThreads, kCap = 4 * kGroupedMax;
     uint64_t *tkeys = reinterpret_cast<uint64_t *>(lds);                  // [kCap + 1]
-    int *tfirst = reinterpret_cast<int *>(tkeys + kCap + 2);              // [kCap + 1] min raw index, later the group number
-    int *rep = tfirst + kCap + 2;                                         // [kGroupedMax]
-    static_assert((kCap + 2) * 12 + kGroupedMax * 4 <= 64 * 1024, "fits the smallest ring");
-    const int tid = threadIdx.x, per = (N + kThreads - 1) / kThreads;
+    int *tfirst = reinterpret_cast<int *>(tkeys + kCap + 4);              // [kCap + 1] min raw index, later the group number
+    int *rep = tfirst + kCap + 4;                                         // [kGroupedMax]
+    static_assert((kCap + 4) * 12 + kGroupedMax * 4 <= 64 * 1024, "fits the smallest ring");
+    const int tid = threadIdx.x, per = per_thread(N, kThreads), n0 = tid * per;
     uint64_t key[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int n = tid * per + i;
-        key[i] = (i < per && n < N) ? ids.key[n] : 0;
-    }
-    int cap = 64;                                                         // a power of two, at most half full
-    while (cap < 2 * N) cap <<= 1;
-    for (int i = tid; i <= cap; i += kThreads) {                          // while the keys are on their way
-        tkeys[i] = kEmpty;
-        tfirst[i] = 0x7FFFFFFF;
-    }
+    load_some(ids.key, n0, per, N, key);
+    int cap = 64;                                                         // a power of two, at most half full, many ids a quarter
+    while (cap < (N <= kThreads ? 2 : 4) * N) cap <<= 1;
+    constexpr u32x4 kFree = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, kNone = {0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu};
+    for (int i = tid; i < (cap + 4) / 2; i += kThreads) reinterpret_cast<u32x4 *>(tkeys)[i] = kFree;      // while the keys are on their way
+    for (int i = tid; i < (cap + 4) / 4; i += kThreads) reinterpret_cast<u32x4 *>(tfirst)[i] = kNone;
     __syncthreads();
     int slot[kPer];
+    find_or_insert_lds(tkeys, cap, key, slot, [&](int i) { return i < per && n0 + i < N; });
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int n = tid * per + i;
-        slot[i] = -1;
-        if (i < per && n < N) {
-            slot[i] = find_or_insert(tkeys, cap, key[i]);
-            atomicMin(&tfirst[slot[i]], n);
-        }
-    }
+    for (int i = 0; i < kPer; ++i)
+        if (slot[i] >= 0) atomicMin(&tfirst[slot[i]], n0 + i);
     __syncthreads();
     int is_first[kPer], mine = 0;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == tid * per + i) ? 1 : 0;
+        is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == n0 + i) ? 1 : 0;
         mine += is_first[i];
     }
     int total;
@@ -526,16 +516,17 @@ __device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, 
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
         if (is_first[i]) {
-            rep[u] = tid * per + i;
+            rep[u] = n0 + i;
             tfirst[slot[i]] = u;
             ++u;
         }
     }
     __syncthreads();
     if (blockIdx.x == 0) {
+        int group[kPer];
 #pragma unroll
-        for (int i = 0; i < kPer; ++i)
-            if (slot[i] >= 0) ids.inverse[tid * per + i] = tfirst[slot[i]];
+        for (int i = 0; i < kPer; ++i) group[i] = slot[i] >= 0 ? tfirst[slot[i]] : 0;
+        store_some(ids.inverse, n0, per, N, group);
         for (int i = tid; i < total; i += kThreads) ids.rep[i] = rep[i];
         if (tid == 0) *ids.n_unique = total;
     }
