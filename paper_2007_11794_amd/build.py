@@ -15,10 +15,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "librnnlm.so")
-SOURCES = ["api.hip", "dedup.hip", "recur.hip", "outproj.hip", "outproj_staged.hip", "outproj_tiled.hip", "outproj_stream.hip", "outproj_rowstream.hip", "outproj_split2.hip", "query.hip", "step_few.hip",
+SOURCES = ["api.hip", "dedup.hip", "recur.hip", "recur_whole.hip", "outproj.hip", "outproj_staged.hip", "outproj_tiled.hip", "outproj_stream.hip", "outproj_rowstream.hip", "outproj_split2.hip", "query.hip", "step_few.hip",
            "load_kernels.hip", "cache.hip", "index_table.hip", "hs.hip", "diag.hip"]
 HEADERS = [os.path.join(CSRC, "rnnlm_internal.h"), os.path.join(CSRC, "device_utils.h"),
            os.path.join(CSRC, "outproj_stream_body.h"), os.path.join(CSRC, "dedup_small_body.h"), os.path.join(CSRC, "recur_math.h"),
+           os.path.join(CSRC, "recur_parts.h"), os.path.join(CSRC, "recur_whole.h"),
            os.path.join(ROOT, "include", "rnnlm.h"), os.path.join(ROOT, "include", "rnnlm_diag.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          # packed-fp32 instructions stay off: the compiler must not form them on its own

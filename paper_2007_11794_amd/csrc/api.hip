@@ -64,7 +64,8 @@ void free_weights(rnnlm_model *m) {
     (void)hipFree(const_cast<void *>(d.U));
     (void)hipFree(const_cast<void *>(d.W));
     (void)hipFree(const_cast<void *>(d.Ot));
-    (void)hipFree(const_cast<void *>(d.Wfrag));
+    if (d.Wfrag != d.Wops) (void)hipFree(const_cast<void *>(d.Wfrag));
+    (void)hipFree(const_cast<void *>(d.Wops));
     (void)hipFree(const_cast<float *>(d.half_rowsum_W));
     (void)hipFree(const_cast<float *>(d.bias));
     (void)hipFree(const_cast<float *>(d.half_colsum_O));
@@ -207,6 +208,11 @@ int upload_recurrent(rnnlm_model *m, int V, int H, int Hp, int dtype, const void
         hrs[j] = (float)(0.5 * sum);
     }
     HIP_TRY(hipMemcpy(const_cast<float *>(d.half_rowsum_W), hrs.data(), (size_t)Hp * 4, hipMemcpyHostToDevice));
+    if (recur_whole_supported(dtype, Hp)) {
+        HIP_TRY(hipMalloc(&p, (size_t)Hp * Hp * (dtype == RNNLM_BF16 ? 2 : 6))); d.Wops = p;
+        if (dtype == RNNLM_BF16) HIP_TRY(launch_frag_recurrent(d.W, dtype, Hp, p, nullptr));
+        else HIP_TRY(launch_recurrent_terms(static_cast<const float *>(d.W), Hp, p, nullptr));
+    }
     return RNNLM_OK;
 fail:
     return status;
@@ -301,7 +307,9 @@ int rnnlm_load(int V, int H, int dtype, const void *U, const void *W, const void
     void *p;
     status = upload_recurrent(m, V, H, Hp, dtype, U, W, max_Bp, true);
     if (status != RNNLM_OK) goto fail;
-    if (step_few_supported(dtype, Hp)) {
+    if (step_few_supported(dtype, Hp) && dtype == RNNLM_BF16) {
+        d.Wfrag = d.Wops;                                                  // (set for every hidden size of that step)
+    } else if (step_few_supported(dtype, Hp)) {
         HIP_TRY(hipMalloc(&p, (size_t)Hp * Hp * es)); d.Wfrag = p;
         HIP_TRY(launch_frag_recurrent(d.W, dtype, Hp, p, nullptr));
     }

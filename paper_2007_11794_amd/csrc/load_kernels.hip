@@ -2,6 +2,7 @@
 // the K-major operand of the matrix cores and a single contiguous read per queried word),
 // and the per-word constants of the centred logit  z = (bias + colsum(O)/2) + O^T (h' - 1/2).
 #include "device_utils.h"
+#include "recur_math.h"
 #include "rnnlm_internal.h"
 
 namespace rnnlm {
@@ -100,6 +101,19 @@ __global__ __launch_bounds__(256) void frag_recurrent_f32_kernel(const f32x4 *__
     Wfrag[i] = W[(blk * 32 + (lane & 31)) * (4 * KS) + 4 * ks + 2 * (lane >> 5) + half];
 }
 
+// fp32 W [Hp][Hp] as three bf16 terms in operand order, a thread per eight weights (Wops).
+__global__ __launch_bounds__(256) void recurrent_terms_kernel(const float *__restrict__ W, int n, int KS, u32x4 *__restrict__ Wops) {
+    const int i = blockIdx.x * 256 + threadIdx.x;                  // (blk, ks, lane)
+    if (i >= n) return;
+    const int lane = i & 63, ks = (i >> 6) % KS, blk = (i >> 6) / KS;
+    float x[8];
+    load8_weights(W, (size_t)(blk * 32 + (lane & 31)) * (16 * KS) + 16 * ks + 8 * (lane >> 5), x);
+    u32x4 t[3];
+    bf16_terms(x, t);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) Wops[((i >> 6) * 3 + k) * 64 + lane] = t[k];
+}
+
 // fp32 [Vp][Hp] weights as two fp16 terms in the same operand order, [blk][ks][term][64 lanes][8 halves].
 // One workgroup per block of 32 words: eight threads find the largest weight of a word, then lane
 // 32 g + c of fragment ks takes word 32 blk + c, units 16 ks + 8 g .. + 7.  Words scaled to [2^13, 2^14):
@@ -170,6 +184,12 @@ hipError_t launch_frag_recurrent(const void *W, int dtype, int Hp, void *Wfrag, 
     const int n = Hp * Hp / 4;
     hipLaunchKernelGGL(frag_recurrent_f32_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, static_cast<const f32x4 *>(W), n, Hp / 16,
                        static_cast<f32x4 *>(Wfrag));
+    return hipGetLastError();
+}
+
+hipError_t launch_recurrent_terms(const float *W, int Hp, void *Wops, hipStream_t stream) {
+    const int n = Hp * Hp / 8;
+    hipLaunchKernelGGL(recurrent_terms_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, W, n, Hp / 16, static_cast<u32x4 *>(Wops));
     return hipGetLastError();
 }
 

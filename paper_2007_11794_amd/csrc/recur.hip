@@ -27,7 +27,9 @@
 //   large  128 units x 64 rows, a wave owns 64 x 32 of them over half of the reduction: h_in is converted
 //          once for two blocks of units, and reading, converting and multiplying overlap between the waves
 //          (with 32 x 32 per wave over the whole reduction H = 1024, 3000 rows took 43 us instead of 30).
-// Models of few units have a third, in kernels of its own (recur_few_units_f32_kernel, recur_few_units_bf16_kernel).
+// Models of few units have a third, in kernels of its own (recur_few_units_f32_kernel, recur_few_units_bf16_kernel), and where the
+// whole of a workgroup's operands fits registers and LDS and its workgroups the compute units there is a fourth (recur_whole.h): the
+// figures below are of sizes some of which it has taken over.
 // Launches of bf16 models that fit one small workgroup per compute unit use a whole unit's LDS as the ring (128 KB, all
 // but one stage in flight), larger ones half of it, two workgroups per unit; fp32 models always the whole one.
 // Measured, us per launch (rows in brackets), before and after, the kernels before being one tiled and one
@@ -40,15 +42,15 @@
 
 #include "dedup_small_body.h"
 #include "device_utils.h"
-#include "recur_math.h"
+#include "recur_whole.h"
 #include "rnnlm_internal.h"
 
 namespace rnnlm {
 
 namespace {
 
-constexpr int kThreads = 512, kWaves = kThreads / 64;
-constexpr int kGroups = 256;                          // workgroups in one round: one per compute unit
+constexpr int kThreads = kRecurThreads, kWaves = kThreads / 64;
+constexpr int kGroups = kChipGroups;
 constexpr int kFewUnitsBf16 = 128;                    // the only Hp of recur_few_units_bf16_kernel
 
 // Tiles in LDS.  A half row is 128 bytes, eight pieces of 16; piece c of row r sits at c ^ ((r >> 1) & 7), so
@@ -91,77 +93,6 @@ __device__ __forceinline__ void wait_stages(int later) {
     if constexpr (MAX == 0) wait_vmcnt<0>();
     else if (later >= MAX) wait_vmcnt<MAX * L>();
     else wait_stages<MAX - 1, L>(later);
-}
-
-struct Finish {                                       // where the results of one row go
-    float *h_row;
-    int b, H, Hp;
-    bool word_ok;
-};
-
-// Four finished units je .. je + 3 of a row.  Padded units (zero weights, zero embedding) come out as
-// sigmoid(0) - 1/2 = 0; either copy of the block is left out (null pointer) when the kernel that follows
-// does not read it.
-template <typename WT, bool VEC>
-__device__ __forceinline__ void finish4(const ModelDev &m, const Finish &f, int je, const f32x4 &sum, const f32x4 &rs,
-                                        const f32x4 &u) {
-    f32x4 hp, dv;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        hp[i] = f.word_ok ? sigmoid_f32(sum[i] + rs[i] + u[i]) : quiet_nan();
-        dv[i] = hp[i] - 0.5f;
-    }
-    const size_t at = (size_t)f.b * f.Hp + je;
-    const size_t frag = (size_t)(f.b >> 5) * (f.Hp >> 4) + (je >> 4);
-    const int slot = (((je >> 3) & 1) * 32 + (f.b & 31)) * 8 + (je & 7);
-    if constexpr (sizeof(WT) == 2) {
-        if (m.d) {
-            const uint2 pk = {pack_bf16x2(dv[0], dv[1]), pack_bf16x2(dv[2], dv[3])};
-            *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(m.d) + at) = pk;
-        }
-        if (m.dfrag) {                                // (d_scale: log2(e) or 1)
-            const uint2 pk = {pack_bf16x2(dv[0] * m.d_scale, dv[1] * m.d_scale), pack_bf16x2(dv[2] * m.d_scale, dv[3] * m.d_scale)};
-            *reinterpret_cast<uint2 *>(static_cast<bf16_t *>(m.dfrag) + frag * 512 + slot) = pk;
-        }
-    } else {
-        if (m.d) *reinterpret_cast<f32x4 *>(static_cast<float *>(m.d) + at) = dv;
-        if (m.dfrag) {                                // two fp16 terms
-            uint16_t t[2][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) split2_f16(dv[i] * (float)(1 << kSplit2DExp), t[0][i], t[1][i]);
-            uint16_t *dst = static_cast<uint16_t *>(m.dfrag) + frag * 1024 + slot;
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const uint2 pk = {(uint32_t)t[k][0] | ((uint32_t)t[k][1] << 16), (uint32_t)t[k][2] | ((uint32_t)t[k][3] << 16)};
-                *reinterpret_cast<uint2 *>(dst + k * 512) = pk;
-            }
-        }
-    }
-    if (VEC) {
-        if (je + 4 <= f.H) *reinterpret_cast<f32x4 *>(f.h_row + je) = hp;
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (je + i < f.H) f.h_row[je + i] = hp[i];
-    }
-}
-
-// W (h - 1/2) of four units (rows w of Hp weights, `units` of them real) for one row of h_in, in plain fp32.  Only taken
-// where the split of an fp32 operand into bf16 terms has no meaning: an infinity, or a number that rounds to one in bf16
-// (beyond 3.389e38), leaves inf - inf in its lower terms, and the sum is NaN then.  Ends once nothing but NaN is left.
-__device__ __forceinline__ f32x4 plain_sum4(const float *w, int Hp, int units, const float *h, int H) {
-    f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < H; ++k) {
-        const float d = h[k] - 0.5f;
-        bool all_nan = true;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i < units) s[i] = fmaf(w[(size_t)i * Hp + k], d, s[i]);
-            all_nan = all_nan && (i >= units || s[i] != s[i]);
-        }
-        if (all_nan) break;
-    }
-    return s;
 }
 
 // rows b0 .. b0 + TB - 1, units j0 .. j0 + TU - 1; source: the row of h_in / prev_word that lane tid of the
@@ -477,64 +408,23 @@ __host__ __device__ inline int small_rows(int Hp, int per_unit) {
 
 constexpr int ring_bytes(int elem, bool half) { return (half ? 64 : elem == 2 ? 128 : 144) * 1024; }
 
-// Grouping of the step's ids in front of the hidden update, by every workgroup for itself (N <= kGroupedMax): the same
-// numbers as dedup_small_body.  Some two microseconds of LDS work in the place of a launch that does them on one compute
-// unit and of the round trip of the count and the rows: step at V = 20000, H = 256, fp32, 256 ids 27.0 -> 25.2 us,
-// V = 65536, H = 512, bf16, 1024 ids 67.4 -> 66.9.  Workgroup 0 leaves the result for the kernels behind.
-// Returns the number of groups; representatives in LDS (valid until the ring is filled).
-constexpr int kGroupedMax = 1024;
-
-__device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, int *wsum, const int *&rep_out) {
-    constexpr int kPer = kGroupedMax / kThreads, kCap = 4 * kGroupedMax;
-    uint64_t *tkeys = reinterpret_cast<uint64_t *>(lds);                  // [kCap + 1]
-    int *tfirst = reinterpret_cast<int *>(tkeys + kCap + 4);              // [kCap + 1] min raw index, later the group number
-    int *rep = tfirst + kCap + 4;                                         // [kGroupedMax]
-    static_assert((kCap + 4) * 12 + kGroupedMax * 4 <= 64 * 1024, "fits the smallest ring");
-    const int tid = threadIdx.x, per = per_thread(N, kThreads), n0 = tid * per;
-    uint64_t key[kPer];
-    load_some(ids.key, n0, per, N, key);
-    int cap = 64;                                                         // a power of two, at most half full, many ids a quarter
-    while (cap < (N <= kThreads ? 2 : 4) * N) cap <<= 1;
-    constexpr u32x4 kFree = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, kNone = {0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu};
-    for (int i = tid; i < (cap + 4) / 2; i += kThreads) reinterpret_cast<u32x4 *>(tkeys)[i] = kFree;      // while the keys are on their way
-    for (int i = tid; i < (cap + 4) / 4; i += kThreads) reinterpret_cast<u32x4 *>(tfirst)[i] = kNone;
-    __syncthreads();
-    int slot[kPer];
-    find_or_insert_lds(tkeys, cap, key, slot, [&](int i) { return i < per && n0 + i < N; });
-#pragma unroll
-    for (int i = 0; i < kPer; ++i)
-        if (slot[i] >= 0) atomicMin(&tfirst[slot[i]], n0 + i);
-    __syncthreads();
-    int is_first[kPer], mine = 0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == n0 + i) ? 1 : 0;
-        mine += is_first[i];
-    }
-    int total;
-    int u = block_exclusive_scan(mine, wsum, total);                      // barriers inside: all first indices are read
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        if (is_first[i]) {
-            rep[u] = n0 + i;
-            tfirst[slot[i]] = u;
-            ++u;
-        }
-    }
-    __syncthreads();
-    if (blockIdx.x == 0) {
-        int group[kPer];
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) group[i] = slot[i] >= 0 ? tfirst[slot[i]] : 0;
-        store_some(ids.inverse, n0, per, N, group);
-        for (int i = tid; i < total; i += kThreads) ids.rep[i] = rep[i];
-        if (tid == 0) *ids.n_unique = total;
-    }
-    rep_out = rep;
-    return total;
+// UNITS > 0 (the count is known on the device only, Hp <= UNITS): the whole form where it would be taken for a count known on the host, 32
+// units a workgroup while those fit the compute units in one round, then 64, bf16 models two workgroups of them side by side.
+__host__ __device__ inline int whole_rows(int Hp, int units, int rounds) { return 32 * kXcds * (rounds * kChipGroups / kXcds / (Hp / units)); }
+template <typename WT, int UNITS, int UB, bool VEC>
+__device__ __forceinline__ void whole_body(const ModelDev &m, int B, int b0, int j0, const int32_t *row_src, const int32_t *row_dst,
+                                           const int32_t *prev_word, const float *h_in, float *h_out, char *lds) {
+    if (b0 >= B) return;                               // uniform
+    RecurWhole<WT, UNITS, UB, VEC> t(b0, j0);
+    int source = min(b0 + t.col, B - 1);
+    if (row_src) source = row_src[source];
+    __builtin_amdgcn_sched_barrier(0);                 // (loads are awaited in order)
+    t.request_weights(m);
+    t.request_rows(m, prev_word, h_in, source);
+    t.run(m, B, row_dst, h_in, h_out, lds);
 }
 
-template <typename WT, bool VEC, bool HALF>
+template <typename WT, bool VEC, bool HALF, int UNITS>
 __global__ __launch_bounds__(kThreads) void recur_kernel(
     ModelDev m, int rows, const int *__restrict__ B_dev, const int32_t *__restrict__ row_src,
     const int32_t *__restrict__ row_dst, const int32_t *__restrict__ prev_word, const float *__restrict__ h_in,
@@ -566,6 +456,17 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
         }
         B = B_dev ? *B_dev : rows;
     }
+    if constexpr (UNITS > 0) {
+        if (B <= whole_rows(m.Hp, 32, 1)) {            // uniform
+            const int JW = m.Hp / 32;
+            whole_body<WT, UNITS, 1, VEC>(m, B, (xcd + kXcds * (local / JW)) * 32, local % JW * 32, row_src, row_dst, prev_word, h_in, h_out, lds);
+            return;
+        }
+        if (VEC && B <= whole_rows(m.Hp, 64, sizeof(WT) == 2 ? 2 : 1)) {
+            whole_body<WT, UNITS, 2, VEC>(m, B, bs, local % JS * 64, row_src, row_dst, prev_word, h_in, h_out, lds);
+            return;
+        }
+    }
     constexpr int kRing = ring_bytes(sizeof(WT), HALF);
     constexpr bool kSmallOnly = sizeof(WT) == 2 && !HALF;          // launches of at most small_rows(Hp, 1) rows
     if (kSmallOnly || B <= small_rows(m.Hp, 2)) {      // uniform
@@ -582,12 +483,13 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
     }
 }
 
-template <typename WT, bool VEC, bool HALF>
-hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
-                  const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
-    const int lds_bytes = ring_bytes(sizeof(WT), HALF);
+template <typename WT, bool VEC, bool HALF, int UNITS>
+hipError_t launch_ring(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
+                       const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
+    int lds_bytes = ring_bytes(sizeof(WT), HALF);
+    if constexpr (UNITS > 0) lds_bytes = std::max(lds_bytes, RecurWhole<WT, UNITS, 1, VEC>::lds_bytes(m.Hp));
     static LdsLimit limit;
-    if (hipError_t e = limit.ensure(reinterpret_cast<const void *>(recur_kernel<WT, VEC, HALF>), lds_bytes); e != hipSuccess)
+    if (hipError_t e = limit.ensure(reinterpret_cast<const void *>(recur_kernel<WT, VEC, HALF, UNITS>), lds_bytes); e != hipSuccess)
         return e;
     auto slots = [](int blocks) { return kXcds * ((blocks + kXcds - 1) / kXcds); };   // row blocks, spread over the XCDs
     // With the count on the device only, the grid covers both shapes: the small one up to its limit, the
@@ -596,9 +498,26 @@ hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *
     const bool on_device = B_dev || ids.key;
     int grid = rows <= few || on_device ? slots((few + 31) / 32) * (m.Hp / 64) : 0;
     if (rows > few) grid = std::max(grid, slots((rows + 63) / 64) * ((m.Hp + 127) / 128));
-    hipLaunchKernelGGL((recur_kernel<WT, VEC, HALF>), dim3(grid), dim3(kThreads), lds_bytes, stream, m, rows, B_dev, row_src,
+    if (UNITS > 0) {
+        grid = std::max(grid, slots((std::min(rows, whole_rows(m.Hp, 32, 1)) + 31) / 32) * (m.Hp / 32));
+        grid = std::max(grid, slots((std::min(rows, whole_rows(m.Hp, 64, sizeof(WT) == 2 ? 2 : 1)) + 31) / 32) * (m.Hp / 64));
+    }
+    hipLaunchKernelGGL((recur_kernel<WT, VEC, HALF, UNITS>), dim3(grid), dim3(kThreads), lds_bytes, stream, m, rows, B_dev, row_src,
                        row_dst, prev_word, h_in, h_out, ids);
     return hipGetLastError();
+}
+
+// The whole form beside the ring: where its LDS leaves room for two workgroups of half a ring.
+template <typename WT, bool VEC, bool HALF>
+hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
+                  const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
+    auto go = [&](auto fn) { return fn(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream); };
+    if (B_dev && m.Wops && m.Hp <= 512 && (VEC || m.H >= 4)) {
+        if (m.Hp <= 128) return go(launch_ring<WT, VEC, HALF, 128>);
+        if (m.Hp <= 256) return go(launch_ring<WT, VEC, HALF, 256>);
+        return go(launch_ring<WT, VEC, HALF, 512>);
+    }
+    return go(launch_ring<WT, VEC, HALF, 0>);
 }
 
 template <bool VEC>
@@ -653,6 +572,8 @@ hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int
         else few(recur_few_units_f32_kernel<false, 16>);
         return hipGetLastError();
     }
+    if (const int units = recur_whole_units(m, rows, vec, ids.key != nullptr); units > 0)
+        return launch_recur_whole(m, units, vec, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
     return vec ? launch_type<true>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream)
                : launch_type<false>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
 }

@@ -34,6 +34,9 @@ struct ModelDev {
     // 32 g + c of fragment (blk, ks) holds unit 32 blk + c, inputs 16 ks + 8 g .. + 7; fp32: [Hp / 32][Hp / 16][2][64 lanes][4], the
     // first and the last four of those eight.
     const void *Wfrag;
+    // W in MFMA-operand order as bf16 terms (one of bf16 models, the same as Wfrag there; three of fp32 models) for the whole form of the
+    // hidden update (recur_whole_supported), else null: [Hp / 32][Hp / 16][terms][64 lanes][8].
+    const void *Wops;
     const float *half_rowsum_W;   // [Hp]  0.5 * sum_i W[j][i]
     const float *bias;            // [V]
     const float *half_colsum_O;   // [V]   0.5 * sum_j O[j][v]
@@ -180,6 +183,11 @@ bool recur_groups_ids(const ModelDev &m, int N);
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,
                         const int32_t *row_dst, const int32_t *prev_word, const float *h_in,
                         float *h_out, const IdGroups &ids, hipStream_t stream);
+// Its whole form (recur_whole.hip): units per workgroup for these rows, 0 where the ring is taken.
+bool recur_whole_supported(int dtype, int Hp);            // the model gets Wops
+int recur_whole_units(const ModelDev &m, int rows, bool vec, bool grouped);
+hipError_t launch_recur_whole(const ModelDev &m, int units, bool vec, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
+                              const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream);
 
 constexpr int kStagedRows = 256;   // rows per workgroup of the staged kernel
 constexpr int kStagedWords = 32;   // words per LDS stage
@@ -369,6 +377,8 @@ hipError_t launch_col_stats(const void *O_dev, const float *bias_or_null, int dt
 hipError_t launch_frag_weights(const void *Ot /*[Vp][Hp] bf16*/, int Vp, int Hp, void *Ofrag, hipStream_t stream);
 // W [Hp][Hp] in the order of Wfrag
 hipError_t launch_frag_recurrent(const void *W, int dtype, int Hp, void *Wfrag, hipStream_t stream);
+// fp32 W [Hp][Hp] in the order of Wops
+hipError_t launch_recurrent_terms(const float *W, int Hp, void *Wops, hipStream_t stream);
 hipError_t launch_split2_weights(const float *Ot /*[Vp][Hp]*/, int Vp, int Hp, void *Ofrag, float *ofac /*[Vp]*/,
                                  hipStream_t stream);
 hipError_t launch_fill_cvec(const float *bias_or_null, const float *half_colsum, int V, int Vp,
