@@ -17,17 +17,18 @@
 //     of ONE row and the sum over words stays inside the lane;
 //   - the exp-and-add of block i is interleaved, instruction by instruction, with the MFMAs
 //     of block i+1, so the vector ALU works in the shadow of the matrix core (the unrolled
-//     block body is kept free of branches for that: see staged_block_fixed / staged_block);
+//     block body is kept free of branches for that: see staged_block);
 //   - one workgroup barrier per block.  It publishes the landing of block i+1 while block i
 //     is being computed, so no wave ever waits at a barrier for data it is about to use, and
 //     the first operands of block i+1 are already in registers when block i ends.
-// With the fixed log-sum-exp offset (the usual case) nothing at all happens at the boundary
+// Nothing at all happens at the boundary
 // between two blocks: the barrier sits in the MIDDLE of a block's MFMA chain (a wave that waits
 // there has its last MFMA in the pipe, and the chain goes on without any hand-over), the loads of
 // block i+3 are issued one by one between the MFMAs of the block's second half instead of in a
 // burst behind the barrier, two accumulator sets alternate (no copy between blocks, the next chain
-// does not wait for the last MFMA of this one), and the constants a chain starts from are read
-// from LDS into the resting accumulator set half a block before they are needed.
+// does not wait for the last MFMA of this one), and the constants a chain starts from (fixed log-sum-exp offset, the usual
+// case) are read from LDS into the resting accumulator set half a block before they are needed.  With the running maximum a
+// chain starts from zero and the constants are added in front of the exponentials.
 // Where the weights come from.  Hp a multiple of 128 up to 512: from Ot, row by row; LDS rows are XOR-swizzled in 16-byte
 // chunks (chunk c of word r sits at c ^ (r & 15)) so that the 16 lanes served together by one ds_read_b128 hit 16
 // different bank groups.  The direct loads write LDS linearly (lane i -> base + 16 i), so the swizzle is applied on
@@ -39,8 +40,8 @@
 // the headline step 68.0 us, against 68.9 with Ofrag.)
 // Padded sizes other than 128, 256 and 512 took the row-streaming and tiled kernels before.  Us per launch:
 //   V = 65536: H = 192, 1024 rows 30.9 -> 26.6; 320, 1024 rows 44.3 -> 38.3; 384, 700 rows 45.5 -> 34.3; 448, 300
-//   rows 31.3 -> 26.6; V = 100000: H = 576, 1000 rows 113 -> 89 (running maximum 126 -> 104); 704, 2048 rows
-//   263 -> 210; 700, 200 rows 48 -> 35; V = 30011, H = 650, 317 rows, running maximum 25.2 -> 23.9.  H = 512 and
+//   rows 31.3 -> 26.6; V = 100000: H = 576, 1000 rows 113 -> 89 (running maximum 126 -> 91); 704, 2048 rows
+//   263 -> 210; 700, 200 rows 48 -> 35; V = 30011, H = 650, 317 rows, running maximum 25.2 -> 19.3.  H = 512 and
 //   below at multiples of 128: as before (54 us at V = 65536, H = 512, 1024 rows).
 // Beyond 704 the hidden block and the accumulators do not fit the 256 registers of a wave.
 //
@@ -111,21 +112,12 @@ struct Loader {
             voff[0] = (uint32_t)lane * 16;
         }
     }
-    // Start the loads of 32-word block `block` into stage / constant slot.
-    __device__ __forceinline__ void issue(const char *weights, const float *cvec, int block, uint32_t stage_lds,
-                                          uint32_t cslot_lds) const {
-        const char *src = block_of(weights, block);
-#pragma unroll
-        for (int q = 0; q < C::kLoadsPerThread; ++q) issue_weights(src, q, true, stage_lds);
-        // the 32 constants of the block: 16 bytes per wave, by its lane 0
-        if (lane == 0) lds_dma_16(cvec + (size_t)block * kStagedWords, wave * 16, cslot_lds + wave * 16);
-    }
     // (a block is 64 HP bytes in either order)
     __device__ __forceinline__ const char *block_of(const char *weights, int block) const {
         return weights + (size_t)block * (64 * HP);
     }
-    // The same in pieces and without branches (the fixed-offset block body is one basic block):
-    // weight load q of the block, and its constants.  real = false turns the load into a dummy
+    // The loads of a 32-word block into a stage and a slot of constants, in pieces and without branches (the block body is one
+    // basic block): weight load q of the block, and its constants.  real = false turns the load into a dummy
     // that counts like a real one for vmcnt but fetches the first bytes of the weights (always
     // there, one cache line for the whole wave) into the same, free, LDS stage.
     __device__ __forceinline__ void issue_weights(const char *src, int q, bool real, uint32_t stage_lds) const {
@@ -155,16 +147,8 @@ struct Loader {
 // would notice).  Running maximum (constants of any size): the constants are added at the end.
 template <bool SCALED>
 __device__ __forceinline__ float base2(float acc) { return SCALED ? acc : acc * kLog2e; }
-template <bool FIXED, bool SCALED>
-__device__ __forceinline__ void finish_logits(const f32x16 &acc, const f32x4 *cn, int g, float (&x)[16]) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        f32x4 c = {0.f, 0.f, 0.f, 0.f};
-        if (!FIXED) c = cn[2 * q + g];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[4 * q + i] = FIXED ? base2<SCALED>(acc[4 * q + i]) : SCALED ? acc[4 * q + i] + c[i] : fmaf(acc[4 * q + i], kLog2e, c[i]);
-    }
-}
+template <bool SCALED>
+__device__ __forceinline__ float base2_plus(float acc, float c) { return SCALED ? acc + c : fmaf(acc, kLog2e, c); }
 
 // This lane's part of an A operand.  Row order: chunk (2 ks + g) of word `col`, swizzled; only the low 4 bits
 // of the chunk index take part in the swizzle, so eight per-lane offsets plus compile-time constants cover
@@ -187,55 +171,6 @@ struct FragOffsets {
     }
 };
 #define RNNLM_A_FRAG(stage, ks) (*reinterpret_cast<const bf16x8 *>((stage) + aoff(ks)))
-
-// One 32-word block for this wave's 32 rows.
-//   stage      LDS stage of this block; a[] already holds its first kPrefetch A operands
-//   next_stage LDS stage of the following block (after the last block: any stage, the operands
-//              read from it are not used); on return a[] holds ITS first kPrefetch A operands
-//              -- that block was published one barrier earlier.  Never a branch here: the
-//              unrolled body must stay ONE basic block, or the compiler sinks the exp-and-add
-//              of the previous block out of the MFMA sequence into the last block
-//   ccur       this block's constants (fixed offset: the accumulators start from them)
-//   pacc, pcn  the previous block's raw accumulators and its constants: its exp-and-add is
-//              spread over this block's k-steps (fixed offset) or done up front (running max)
-template <int HP, bool FIXED>
-__device__ __forceinline__ void staged_block(const char *stage, const char *next_stage, const FragOffsets<HP> &aoff,
-                                             bf16x8 (&a)[kPrefetch], const bf16x8 (&dreg)[HP / 16], int g,
-                                             const f32x4 *ccur, f32x16 &pacc, const f32x4 *pcn, float &mrun,
-                                             float &srun) {
-    constexpr int KS = HP / 16;
-    static_assert(KS >= 2 * kPrefetch, "");
-    f32x16 acc = {0};
-    if (FIXED) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f32x4 c = ccur[2 * q + g];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[4 * q + i] = c[i];
-        }
-    } else {
-        float x[16];
-        finish_logits<false, StagedCfg<HP>::kScaledD>(pacc, pcn, g, x);
-        lse2_fold16<false>(x, mrun, srun);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 cur = a[ks % kPrefetch];
-        if (ks + kPrefetch < KS) a[ks % kPrefetch] = RNNLM_A_FRAG(stage, ks + kPrefetch);
-        else a[ks % kPrefetch] = RNNLM_A_FRAG(next_stage, ks + kPrefetch - KS);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, dreg[ks], acc, 0, 0, 0);
-        if (FIXED) {
-            // sixteen logits of the previous block spread evenly over the KS steps
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if ((e * KS) / 16 == ks) srun += fast_exp2(base2<StagedCfg<HP>::kScaledD>(pacc[e]));
-        }
-        // keep this order: the compiler's scheduler would otherwise sink every LDS read to
-        // just before its MFMA and expose the LDS latency on each step
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    pacc = acc;
-}
 
 // One MFMA B operand (this lane's 16 bytes of a 1 KB fragment) requested WITHOUT the compiler
 // knowing that a load is in flight: the register is defined for it at once, and the caller keeps
@@ -270,7 +205,7 @@ __device__ __forceinline__ void load_d_operand_at(bf16x8 &dst, const bf16_t *dfr
     load_d_operand<(J % 4) * 1024>(dst, dfr + (size_t)(J / 4) * 2048);
 }
 
-// What block 0 of an item issues besides its own work (staged_block_fixed<HP, true>): the part of
+// What block 0 of an item issues besides its own work (staged_block<HP, FIXED, true>): the part of
 // d that the prologue has not requested, and blocks 1 and 2.  All loads of a wave are issued in
 // one fixed program order, so the number of loads younger than any given one is a compile-time
 // figure: that is what the vmcnt immediates of block 0 are computed from.
@@ -330,12 +265,32 @@ struct FirstBlockLoads {
     uint32_t stage[2], cslot[2];
 };
 
-// Fixed offset: one 32-word block for this wave's 32 rows, as ONE basic block.
-//   acc     on entry the block's constants (the logits start from them), on return the finished
-//           logits of the block
-//   other   on entry the finished logits of the previous block (-inf before the first): their
-//           exp-and-add is spread over the first half of the k-steps; on return the constants of
-//           block bi+1 (read from the ring in the second half; after the last block: a landed
+// Where in a block's KS k-steps the running maximum takes in the previous block: its constants are read and added, four logits at
+// a time, in the first quarter; then the new maximum; then one term after the other.  Up front, in one piece, in front of the chain
+// the same instructions were in nobody's shadow.  Us per launch, up front / spread: V = 30011, H = 650, 317 rows 21.0 / 19.3, 511 25.6 /
+// 24.3; V = 100000, H = 576, 1000 rows 98.8 / 90.9; V = 65536, H = 512, 1024 rows 63.5 / 57.4 (fixed offset 54), 300 31.7 / 27.9; H = 320, 1229
+// rows 55.7 / 50.1; V = 200000, H = 128, 1000 rows 73.8 / 68.6; with two or three blocks in all V = 20000, H = 192, 200 rows 6.0 / 6.2.
+template <int KS>
+struct RunningMaxSchedule {
+    static constexpr int constants(int q) { return q * KS / 16; }
+    static constexpr int kRead = KS < 12 ? 1 : KS < 16 ? 2 : 3;    // k-steps for an LDS read
+    static constexpr int logits(int q) { return constants(q) + kRead; }
+    static constexpr int kMaximum = logits(3) + 1;
+    static constexpr int term(int e) { return kMaximum + 1 + e * (KS / 2) / 16; }
+    static_assert(term(15) < KS, "");
+};
+// (max, sum) of a lane's logits so far; of the block being taken in its largest logit, then what its terms are taken from, and their
+// sum.  The fixed offset needs the first sum alone.
+struct RunningLse {
+    float m, s, offset, terms;
+};
+
+// One 32-word block for this wave's 32 rows, as ONE basic block.
+//   acc     on entry the block's constants (fixed offset: the logits start from them) or zero, on return the finished
+//           logits of the block (running maximum: without their constants)
+//   other   on entry the same of the previous block (-inf before the first): their
+//           exp-and-add is spread over the k-steps (fixed offset: of the first half); on return the start of
+//           block bi+1 (constants read from the ring in the second half; after the last block: a landed
 //           slot, unused)
 // Half way through, the barrier publishes block bi+1 (everybody's loads of it have landed: the
 // only younger loads of a wave are those of block bi+2) and frees the stage of block bi-1, which
@@ -348,13 +303,13 @@ struct FirstBlockLoads {
 // k-steps ahead of its use, and blocks 1 and 2 load by load in the first half.  Every MFMA waits
 // for ITS operand of d alone, and the barrier for block 1 alone (FirstBlockSchedule has the
 // counts): the chain runs at the pace at which d arrives instead of starting after all of it.
-template <int HP, bool FIRST>
-__device__ __forceinline__ void staged_block_fixed(const char *lds, const char *cring, uint32_t lds0,
+template <int HP, bool FIXED, bool FIRST>
+__device__ __forceinline__ void staged_block(const char *lds, const char *cring, uint32_t lds0,
                                                    uint32_t cring0, const Loader<HP> &loader, const char *weights,
                                                    const float *cvec, int blk0, int nblk, int bi,
                                                    const FragOffsets<HP> &aoff, bf16x8 (&a)[kPrefetch],
                                                    bf16x8 (&dreg)[HP / 16], int g, f32x16 &acc,
-                                                   f32x16 &other, float &srun, const FirstBlockLoads &first) {
+                                                   f32x16 &other, RunningLse &lse, const FirstBlockLoads &first) {
     using C = StagedCfg<HP>;
     using F = FirstBlockSchedule<HP>;
     constexpr int KS = C::KS, HALF = KS / 2, NW = C::kLoadsPerThread;
@@ -363,7 +318,10 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
     constexpr int NS = C::kStages;
     const char *stage = lds + bi % NS * C::kStageBytes;
     const char *next_stage = lds + ((bi + 1 < nblk) ? bi + 1 : bi) % NS * C::kStageBytes;
-    const f32x4 *cnext = reinterpret_cast<const f32x4 *>(cring + ((bi + 1) & 7) * kCSlotBytes);
+    // fixed offset: the constants the next block starts from; else those of the previous one (in front of the first any landed slot)
+    const f32x4 *cn = reinterpret_cast<const f32x4 *>(cring + (FIXED ? (bi + 1) & 7 : FIRST ? 0 : (bi - 1) & 7) * kCSlotBytes);
+    using R = RunningMaxSchedule<KS>;
+    f32x4 c4[4];                                               // (running maximum: one of them in use at a time)
     const bool real = bi + NS - 1 < nblk;
     const int block3 = real ? blk0 + bi + NS - 1 : 0;
     const char *src3 = loader.block_of(weights, block3);
@@ -394,19 +352,48 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
             await_d_operand<F::younger_than_d(ks)>(dreg[ks]);
         }
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, dreg[ks], acc, 0, 0, 0);
-        // the previous block's sixteen logits, over k-steps 1 .. HALF
+        if constexpr (FIXED) {
+            // the previous block's sixteen logits, over k-steps 1 .. HALF
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if (1 + (e * HALF) / 16 == ks) srun += fast_exp2(base2<C::kScaledD>(other[e]));
-        // second half: loads of block bi+3, constants of block bi+1 into the resting accumulators
+            for (int e = 0; e < 16; ++e)
+                if (1 + (e * HALF) / 16 == ks) lse.s += fast_exp2(base2<C::kScaledD>(other[e]));
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (ks == R::logits(q)) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        other[4 * q + i] = base2_plus<C::kScaledD>(other[4 * q + i], c4[q][i]);
+                        lse.offset = q + i == 0 ? other[0] : fmaxf(lse.offset, other[4 * q + i]);
+                    }
+                }
+                if (ks == R::constants(q)) c4[q] = cn[2 * q + g];
+            }
+            if constexpr (ks == R::kMaximum) {
+                const float mn = fmaxf(lse.m, lse.offset);
+                lse.offset = mn == -INFINITY ? 0.f : mn;       // (nothing but -inf so far: the terms below are 2^-inf)
+                lse.s *= fast_exp2(lse.m - lse.offset);
+                lse.m = mn;
+                lse.terms = 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (R::term(e) == ks) lse.terms += fast_exp2(other[e] - lse.offset);
+            if constexpr (ks == KS - 1) {
+                lse.s += lse.terms;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) other[i] = 0.f;
+            }
+        }
+        // second half: loads of block bi+3, with the fixed offset the constants of block bi+1 into the resting accumulators
 #pragma unroll
         for (int q = 0; q < NW; ++q)
             if (ks == HALF + 1 + q * kLoadStep) loader.issue_weights(src3, q, real, stage3);
         if constexpr (ks == KS - 2) loader.issue_consts(cvec + (size_t)block3 * kStagedWords, cslot3);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (ks == HALF + 1 + (q * (HALF - 1)) / 4) {
-                const f32x4 c = cnext[2 * q + g];
+            if (FIXED && ks == HALF + 1 + (q * (HALF - 1)) / 4) {
+                const f32x4 c = cn[2 * q + g];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) other[4 * q + i] = c[i];
             }
@@ -416,16 +403,40 @@ __device__ __forceinline__ void staged_block_fixed(const char *lds, const char *
     });
 }
 
-// Fixed offset: all blocks of one (row group, split) item for this wave's rows; returns the sum
-// of 2^(logit - offset) over the item's words for this lane's half of its row.
-template <int HP>
-__device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds, char *cring, const Loader<HP> &loader,
+template <bool FIXED, bool SCALED>
+__device__ __forceinline__ const float *block_constants(const ModelDev &m) {
+    return !FIXED ? m.cvec2 : SCALED ? m.cvec2_fixed : m.cvec_fixed;
+}
+
+// The exp-and-add of an item's last block.
+template <bool FIXED, bool SCALED>
+__device__ __forceinline__ void fold_last_block(const f32x16 &acc, const char *cring, int bi, int g, RunningLse &lse) {
+    if constexpr (FIXED) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) lse.s += fast_exp2(base2<SCALED>(acc[e]));
+    } else {
+        const f32x4 *cn = reinterpret_cast<const f32x4 *>(cring + (bi & 7) * kCSlotBytes);
+        float x[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4 c = cn[2 * q + g];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[4 * q + i] = base2_plus<SCALED>(acc[4 * q + i], c[i]);
+        }
+        lse2_fold16<false>(x, lse.m, lse.s);
+    }
+}
+
+// All blocks of one (row group, split) item for this wave's rows: the item's words' part of the log-sum-exp for this lane's half of
+// its row, as (lse.m, lse.s); with the fixed offset the sum of 2^(logit - offset) alone.
+template <int HP, bool FIXED>
+__device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *cring, const Loader<HP> &loader,
                                                    const FragOffsets<HP> &aoff, int row0, int blk0, int nblk, int wave,
-                                                   int lane, int g) {
+                                            int lane, int g, RunningLse &lse) {
     using C = StagedCfg<HP>;
     constexpr int KS = C::KS;
     const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
-    const float *cvec = C::kScaledD ? m.cvec2_fixed : m.cvec_fixed;
+    const float *cvec = block_constants<FIXED, C::kScaledD>(m);
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
     // Block 0 and the first operands of this wave's rows of d (all k of 32 rows are MFMA B operands
     // held in registers; rows beyond B hold stale scratch: rows are independent and those lanes'
@@ -465,14 +476,15 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
         for (int q = 0; q < 4; ++q) {
             const f32x4 c = c0[2 * q + g];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc0[4 * q + i] = c[i];
+            for (int i = 0; i < 4; ++i) acc0[4 * q + i] = FIXED ? c[i] : 0.f;
         }
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc1[i] = -INFINITY;        // "previous block" of block 0: adds 2^-inf = 0
-    float srun = 0.f;
+    lse.m = -INFINITY;
+    lse.s = 0.f;
 #define RNNLM_BLOCK(FIRST, BI, ACC, OTHER) \
-    staged_block_fixed<HP, FIRST>(lds, cring, lds0, cring0, loader, weights, cvec, blk0, nblk, BI, aoff, a, dreg, g, ACC, OTHER, srun, first)
+    staged_block<HP, FIXED, FIRST>(lds, cring, lds0, cring0, loader, weights, cvec, blk0, nblk, BI, aoff, a, dreg, g, ACC, OTHER, lse, first)
     RNNLM_BLOCK(true, 0, acc0, acc1);
     int bi = 1;
     for (; bi + 1 < nblk; bi += 2) {
@@ -481,27 +493,24 @@ __device__ __forceinline__ float staged_item_fixed(const ModelDev &m, char *lds,
     }
     if (bi < nblk) {
         RNNLM_BLOCK(false, bi, acc1, acc0);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) srun += fast_exp2(base2<C::kScaledD>(acc1[e]));
+        fold_last_block<FIXED, C::kScaledD>(acc1, cring, nblk - 1, g, lse);
     } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) srun += fast_exp2(base2<C::kScaledD>(acc0[e]));
+        fold_last_block<FIXED, C::kScaledD>(acc0, cring, nblk - 1, g, lse);
     }
 #undef RNNLM_BLOCK
     // dummy loads may still be in flight into stages the next item fills first
     wait_vmcnt<0>();
-    return srun;
 }
 
-// A wave without rows in an item: its share of the loads and all barriers, as staged_item_fixed has them (block 0 is published by the
+// A wave without rows in an item: its share of the loads and all barriers, as staged_item has them (block 0 is published by the
 // first barrier; the barrier of block bi publishes block bi + 1 and frees the stage of block bi - 1), and nothing else.  The matrix
 // pipes are left to the waves that have rows: with up to four of them each has one to itself.
-template <int HP>
-__device__ __forceinline__ void staged_item_fixed_loads(const ModelDev &m, uint32_t lds0, uint32_t cring0, const Loader<HP> &loader, int blk0, int nblk) {
+template <int HP, bool FIXED>
+__device__ __forceinline__ void staged_item_loads(const ModelDev &m, uint32_t lds0, uint32_t cring0, const Loader<HP> &loader, int blk0, int nblk) {
     using C = StagedCfg<HP>;
     constexpr int NS = C::kStages;
     const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
-    const float *cvec = C::kScaledD ? m.cvec2_fixed : m.cvec_fixed;
+    const float *cvec = block_constants<FIXED, C::kScaledD>(m);
     auto issue = [&](int bi) __attribute__((always_inline)) {            // always as many loads
         const bool real = bi < nblk;
         const int block = real ? blk0 + bi : 0;
@@ -550,10 +559,8 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
     }
     const StagedSplit split_of = staged_split(B, wg_per_xcd, C::kHalves);
     const StagedPlan plan = split_of.plan;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, g = lane >> 5;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
-    const float *cvec = FIXED ? (C::kScaledD ? m.cvec2_fixed : m.cvec_fixed) : m.cvec2;
     const int T = m.Vp / kStagedWords;                       // 32-word blocks in the vocabulary
     const int items = plan.RG * plan.Sx;
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
@@ -567,108 +574,27 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         const int blk0 = part_begin(split, T, plan.S);
         const int nblk = part_begin(split + 1, T, plan.S) - blk0;
         const int row0 = rg * split_of.rows;
-        const int b = row0 + wave * 32 + col;                 // this lane's row
         const bool has_rows = (int)loader.wave * 32 < min(split_of.rows, B - row0);       // (wave-uniform)
-        if (FIXED && !has_rows) {
-            if (nblk > 0) staged_item_fixed_loads<HP>(m, lds0, cring0, loader, blk0, nblk);
+        if (!has_rows) {
+            if (nblk > 0) staged_item_loads<HP, FIXED>(m, lds0, cring0, loader, blk0, nblk);
             __syncthreads();
             continue;
         }
+        RunningLse lse;
+        lse.m = -INFINITY;
+        lse.s = 0.f;
+        if (nblk > 0) staged_item<HP, FIXED>(m, lds, cring, loader, aoff, row0, blk0, nblk, wave, lane, g, lse);
+        // lanes l and l+32 hold the two halves of a row (the lane asked for anew: with Hp = 704 there is no register to keep it in)
+        const int lane_now = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int b = row0 + (int)loader.wave * 32 + (lane_now & 31);                        // this lane's row
+        const float s2 = __shfl_xor(lse.s, 32, 64);
         if (FIXED) {
-            float srun = 0.f;
-            if (nblk > 0) srun = staged_item_fixed<HP>(m, lds, cring, loader, aoff, row0, blk0, nblk, wave, lane, g);
-            srun += __shfl_xor(srun, 32, 64);                 // lanes l and l+32 hold the two halves of a row
-            if (g == 0 && b < B) m.part[(size_t)b * kMaxSplits + split] = make_float2(m.m2_fixed, srun);
-            __syncthreads();                                  // LDS is reused by the next item
-            continue;
+            lse.m = m.m2_fixed;
+            lse.s += s2;
+        } else {
+            lse2_merge(lse.m, lse.s, __shfl_xor(lse.m, 32, 64), s2);
         }
-
-        // Blocks 0 and 1 first, then this wave's rows of d (all k, as MFMA B operands; rows
-        // beyond B hold stale scratch: rows are independent and those lanes' results are dropped).
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            if (i < nblk)
-                loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
-        if (!has_rows) {                                      // the loads and barriers of what follows
-            constexpr int NS = C::kStages;
-            wait_vmcnt<0>();
-            __syncthreads();
-#pragma unroll
-            for (int i = 2; i < NS; ++i)
-                if (i < nblk) loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
-            for (int bi = 1; bi < nblk; ++bi) {
-                if (bi + 2 < nblk) wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();
-                else wait_vmcnt<0>();
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                if (bi + NS - 1 < nblk)
-                    loader.issue(weights, cvec, blk0 + bi + NS - 1, lds0 + (bi + NS - 1) % NS * C::kStageBytes,
-                                 cring0 + ((bi + NS - 1) & 7) * kCSlotBytes);
-            }
-            __syncthreads();
-            continue;
-        }
-        bf16x8 dreg[KS];
-        {
-            // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row
-            const bf16_t *dfr = static_cast<const bf16_t *>(m.dfrag) +
-                                ((size_t)(row0 / 32 + wave) * KS * 64 + lane) * 8;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) dreg[ks] = *reinterpret_cast<const bf16x8 *>(dfr + (size_t)ks * 512);
-        }
-        float mrun = FIXED ? m.m2_fixed : -INFINITY, srun = 0.f;
-        // raw accumulators of the previous block, still to be exponentiated; -inf adds 2^-inf = 0
-        f32x16 pacc;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) pacc[i] = -INFINITY;
-
-        // Blocks 0 and 1 have landed once at most the KS younger loads of d are outstanding; d
-        // itself is awaited operand by operand as the first block's MFMAs consume it.
-        wait_vmcnt<(KS < 64 ? KS : 63)>();
-        __syncthreads();                                      // blocks 0 and 1 are published
-#pragma unroll
-        for (int i = 2; i < C::kStages; ++i)
-            if (i < nblk)
-                loader.issue(weights, cvec, blk0 + i, lds0 + i * C::kStageBytes, cring0 + i * kCSlotBytes);
-
-        bf16x8 a[kPrefetch];
-        if (nblk > 0) {
-#pragma unroll
-            for (int i = 0; i < kPrefetch; ++i) a[i] = RNNLM_A_FRAG(lds, i);
-        }
-        for (int bi = 0; bi < nblk; ++bi) {
-            if (bi > 0) {
-                // Publish block bi+1: my loads of it have landed (the only younger ones are
-                // those of block bi+2), then everybody's.  Everybody is also done with block
-                // bi-1, so its stage takes block bi+3.
-                constexpr int NS = C::kStages;
-                if (bi + 2 < nblk) wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();
-                else wait_vmcnt<0>();
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                if (bi + NS - 1 < nblk)
-                    loader.issue(weights, cvec, blk0 + bi + NS - 1, lds0 + (bi + NS - 1) % NS * C::kStageBytes,
-                                 cring0 + ((bi + NS - 1) & 7) * kCSlotBytes);
-            }
-            const char *stage = lds + bi % C::kStages * C::kStageBytes;
-            const char *next_stage = lds + ((bi + 1 < nblk) ? bi + 1 : bi) % C::kStages * C::kStageBytes;
-            // constants of the previous block (for block 0 any landed slot: its pacc is -inf)
-            const f32x4 *pcn = reinterpret_cast<const f32x4 *>(cring + ((bi ? bi - 1 : 0) & 7) * kCSlotBytes);
-            const f32x4 *ccur = reinterpret_cast<const f32x4 *>(cring + (bi & 7) * kCSlotBytes);
-            staged_block<HP, FIXED>(stage, next_stage, aoff, a, dreg, g, ccur, pacc, pcn, mrun, srun);
-        }
-        if (nblk > 0) {                                       // the last block's exp-and-add
-            float x[16];
-            finish_logits<FIXED, C::kScaledD>(pacc, reinterpret_cast<const f32x4 *>(cring + ((nblk - 1) & 7) * kCSlotBytes), g, x);
-            lse2_fold16<FIXED>(x, mrun, srun);
-        }
-        // lanes l and l+32 hold the two halves of a row
-        const float m2 = __shfl_xor(mrun, 32, 64), s2 = __shfl_xor(srun, 32, 64);
-        if (FIXED) srun += s2;
-        else lse2_merge(mrun, srun, m2, s2);
-        if (g == 0 && b < B) m.part[(size_t)b * kMaxSplits + split] = make_float2(mrun, srun);
+        if (lane_now < 32 && b < B) m.part[(size_t)b * kMaxSplits + split] = make_float2(lse.m, lse.s);
         __syncthreads();                                      // LDS is reused by the next item
     }
 }
