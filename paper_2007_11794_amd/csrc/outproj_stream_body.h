@@ -29,8 +29,12 @@ typedef StreamCursorOf<kStreamWaves> StreamCursor;
 // requested into registers in the same place and written to LDS behind the first weights' requests (V = 20000, H = 128, 20
 // rows: bf16 4.0 us, copied in front of the weights 4.1, fp32, copied behind them, 5.2 -> 4.9; a step at V = 1000000, H = 128, 64
 // rows 51.6 -> 50.8).
-// At the wait at least 16 younger loads of the wave are outstanding (four groups of the ring, which the memory
+// At the wait at least 16 younger loads of a wave with weights of its own are outstanding (four groups of the ring, which the memory
 // clobbers keep between request and wait); operations complete in order, so the block has landed once no more than 12 are.
+// A wave without any requests none and goes round the loop (before, it fetched the first sixteen kilobytes of the weights, for the count's
+// sake, through the same 64 bytes a clock as the others' weights): bf16 V = 20000, H = 256, 32 rows 4.44 -> 3.74 us, 64 rows 4.99 -> 4.36, V =
+// 12000, H = 128, 20 rows 3.95 -> 3.14, V = 5000, H = 512, 40 rows 5.9 -> 5.0; fp32 5.8 -> 5.1, 7.55 -> 6.8, 4.87 -> 3.9, 9.85 -> 8.7; from eight blocks
+// of words per workgroup on no change.  Round it, not past the loads in it: a ring that may not have been requested is awaited whole.
 constexpr int kStreamCopyPieces = 2;                // per wave
 
 // What a lane holds of a small block between its request and its way into LDS.
@@ -48,10 +52,11 @@ __device__ __forceinline__ void stream_block_begin(const char *src, int pieces, 
     }
     for (int p = wave; p < pieces; p += WAVES) lds_dma_16(src + (size_t)p * stride, lane * 16, lds_address(lds) + p * 1024);
 }
-template <int WAVES = kStreamWaves>
+template <bool WEIGHTS, int WAVES = kStreamWaves>
 __device__ __forceinline__ void stream_block_end(int pieces, char *lds, int wave, int lane, const StreamPieces &held) {
     if (pieces > kStreamCopyPieces * WAVES) {
-        asm volatile("s_waitcnt vmcnt(12) ; hidden block" ::: "memory");
+        if constexpr (WEIGHTS) asm volatile("s_waitcnt vmcnt(12) ; hidden block" ::: "memory");
+        else wait_vmcnt<0>();
     } else {
 #pragma unroll
         for (int k = 0; k < kStreamCopyPieces; ++k)
@@ -64,14 +69,15 @@ __device__ __forceinline__ void stream_block_end(int pieces, char *lds, int wave
 // HiddenHere in step_few.hip, which computes it between the same two calls.)
 template <int WAVES = kStreamWaves>
 struct StoredBlock {
-    // its wait counts the loads of the weights behind it: a wave without weights of its own asks for some all the same
-    static constexpr bool kCountsLoads = true;
     const char *src;
     int pieces, stride;
     int B;                                            // rows of it that are valid, > 0
     StreamPieces held;
     __device__ __forceinline__ void begin(char *lds, int wave, int lane) { stream_block_begin<WAVES>(src, pieces, lds, wave, lane, held, stride); }
-    __device__ __forceinline__ void end(char *lds, int wave, int lane) { stream_block_end<WAVES>(pieces, lds, wave, lane, held); }
+    // its wait counts the loads of the weights behind it: a wave that has none calls end_without_weights
+    static constexpr bool kCountsLoads = true;
+    __device__ __forceinline__ void end(char *lds, int wave, int lane) { stream_block_end<true, WAVES>(pieces, lds, wave, lane, held); }
+    __device__ __forceinline__ void end_without_weights(char *lds, int wave, int lane) { stream_block_end<false, WAVES>(pieces, lds, wave, lane, held); }
     __device__ __forceinline__ static void put(float2 *at, float2 v) { *at = v; }             // a partial
 };
 
@@ -96,6 +102,28 @@ __device__ __forceinline__ void outproj_stream_block(const ModelDev &m, Block &b
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)RB * KS * 1024);    // [kStreamWaves][RB * 32]
 
     block.begin(lds, wave, lane);
+    auto merge = [&]() {
+        __syncthreads();
+        if (tid < RB * 32) {
+            float mm = red[tid].x, ss = red[tid].y;
+            for (int w = 1; w < kStreamWaves; ++w) {
+                const float2 p = red[w * (RB * 32) + tid];
+                if (FIXED) ss += p.y;
+                else lse2_merge(mm, ss, p.x, p.y);
+            }
+            if (tid < block.B) block.put(&m.part[(size_t)(row0 + tid) * kMaxSplits + split], make_float2(mm, ss));
+        }
+    };
+    if constexpr (Block::kCountsLoads) {
+        if (blk0 + wave >= blk1) {
+            block.end_without_weights(lds, wave, lane);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                if (g == 0) red[wave * (RB * 32) + rb * 32 + col] = make_float2(FIXED ? m2_fixed : -INFINITY, 0.f);
+            merge();
+            return;
+        }
+    }
     bf16x8 ring[kStreamRing][kStreamGroup];
     StreamCursor in = {blk0 + wave, 0};
     // Always kStreamGroup loads, so that the number of younger loads behind any operand is the same on
@@ -176,16 +204,7 @@ __device__ __forceinline__ void outproj_stream_block(const ModelDev &m, Block &b
         else lse2_merge(mrun[rb], srun[rb], m2, s2);
         if (g == 0) red[wave * (RB * 32) + rb * 32 + col] = make_float2(mrun[rb], srun[rb]);
     }
-    __syncthreads();
-    if (tid < RB * 32) {
-        float mm = red[tid].x, ss = red[tid].y;
-        for (int w = 1; w < kStreamWaves; ++w) {
-            const float2 p = red[w * (RB * 32) + tid];
-            if (FIXED) ss += p.y;
-            else lse2_merge(mm, ss, p.x, p.y);
-        }
-        if (tid < block.B) block.put(&m.part[(size_t)(row0 + tid) * kMaxSplits + split], make_float2(mm, ss));
-    }
+    merge();
 }
 
 template <int RB, bool FIXED, bool SCALED>
@@ -225,6 +244,28 @@ __device__ __forceinline__ void outproj_stream_f32_block(const ModelDev &m, Bloc
     float2 *red = reinterpret_cast<float2 *>(lds + (size_t)kTerms * RB * KS * 1024);
 
     block.begin(lds, wave, lane);
+    auto merge = [&]() {
+        __syncthreads();
+        if (tid < RB * 32) {
+            float mm = red[tid].x, ss = red[tid].y;
+            for (int w = 1; w < WAVES; ++w) {
+                const float2 p = red[w * (RB * 32) + tid];
+                if (FIXED) ss += p.y;
+                else lse2_merge(mm, ss, p.x, p.y);
+            }
+            if (tid < block.B) block.put(&m.part[(size_t)(row0 + tid) * kMaxSplits + split], make_float2(mm, ss));
+        }
+    };
+    if constexpr (Block::kCountsLoads) {
+        if (blk0 + wave >= blk1) {
+            block.end_without_weights(lds, wave, lane);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+                if (g == 0) red[wave * (RB * 32) + rb * 32 + col] = make_float2(FIXED ? m2_fixed : -INFINITY, 0.f);
+            merge();
+            return;
+        }
+    }
     f16x8 ring[kStreamRing][2 * kStreamGroup32], second[kStreamRing][ONE_TERM ? RB * kStreamGroup32 : 1];
     StreamCursorOf<WAVES> in = {blk0 + wave, 0};
     auto issue = [&](int slot) __attribute__((always_inline)) {                  // always as many loads (see above)
@@ -317,16 +358,7 @@ __device__ __forceinline__ void outproj_stream_f32_block(const ModelDev &m, Bloc
         else lse2_merge(mrun[rb], srun[rb], m2, s2);
         if (g == 0) red[wave * (RB * 32) + rb * 32 + col] = make_float2(mrun[rb], srun[rb]);
     }
-    __syncthreads();
-    if (tid < RB * 32) {
-        float mm = red[tid].x, ss = red[tid].y;
-        for (int w = 1; w < WAVES; ++w) {
-            const float2 p = red[w * (RB * 32) + tid];
-            if (FIXED) ss += p.y;
-            else lse2_merge(mm, ss, p.x, p.y);
-        }
-        if (tid < block.B) block.put(&m.part[(size_t)(row0 + tid) * kMaxSplits + split], make_float2(mm, ss));
-    }
+    merge();
 }
 
 template <int RB, bool FIXED, int WAVES = kStreamWaves, bool ONE_TERM = false>
