@@ -439,7 +439,7 @@ int rnnlm_set_option(rnnlm_model *model, int option, int value) {
             if (value == 5 && outproj_stream_max_rows(model->dev) == 0) return RNNLM_EINVAL;
             if (value == 4 && !model->dev.ofac) return RNNLM_EINVAL;
             // (by itself the library takes the staged kernel for every padded size up to 704)
-            if (value == 2 && (!outproj_staged_supported(model->dev) ||
+            if (value == 2 && (model->dev.dtype != RNNLM_BF16 || !outproj_staged_supported(model->dev) ||
                                (model->dev.Hp != 128 && model->dev.Hp != 256 && model->dev.Hp != 512)))
                 return RNNLM_EINVAL;
             model->outproj_kernel = value;

@@ -238,11 +238,13 @@ static Bf16Kernel choose_bf16(const ModelDev &m, int rows, bool fixed_offset, in
     return kBf16Plain;
 }
 
-// The same for fp32 models.  Infinite weights are for the plain kernel.
-enum F32Kernel { kF32Stream, kF32Split2, kF32Tiled, kF32Plain };
+// The same for fp32 models (the first two-term form goes by the second's name).  Infinite weights are for the plain kernel.
+enum F32Kernel { kF32Stream, kF32Staged, kF32Split2, kF32Tiled, kF32Plain };
 static F32Kernel choose_f32(const ModelDev &m, int rows, int kernel_choice) {
     if (stream_choice(m, rows, kernel_choice)) return kF32Stream;
     if (kernel_choice == 3) return kF32Tiled;
+    // the rows in registers wherever both terms fit them (Hp <= 320); figures in outproj_staged.hip
+    if (kernel_choice == 0 && rows >= 64 && !m.infinite_O && outproj_staged_supported(m)) return kF32Staged;
     if (m.ofac && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64 && !m.infinite_O))) return kF32Split2;
     return kF32Plain;
 }
@@ -279,7 +281,7 @@ WeightsAhead outproj_weights_ahead(const ModelDev &m, int rows, bool fixed_offse
         const F32Kernel k = choose_f32(m, rows, kernel_choice);
         a.block_kb *= 2;
         if (k == kF32Split2) a.waves = 4;
-        else if (k != kF32Stream) a.splits = 0;
+        else if (k != kF32Stream && k != kF32Staged) a.splits = 0;
     }
     return a;
 }
@@ -297,6 +299,7 @@ const char *outproj_kernel_name(const ModelDev &m, int rows, bool fixed_offset, 
     }
     switch (choose_f32(m, rows, kernel_choice)) {
         case kF32Stream: return "outproj_stream_kernel";
+        case kF32Staged:
         case kF32Split2: return "outproj_split2_kernel";
         case kF32Tiled: return "outproj_tiled_kernel";
         default: return "outproj_plain_f32_kernel";
@@ -329,6 +332,7 @@ hipError_t launch_outproj(const ModelDev &m, int rows, const int *B_dev, bool fi
         // rows, the tiled two-term kernel from 64 rows on.  The tiled fp32-MFMA kernel only on request.
         const F32Kernel which = choose_f32(m, rows, kernel_choice);
         if (which == kF32Stream) return launch_outproj_stream(m, rows, B_dev, fixed_offset, splits, stream);
+        if (which == kF32Staged) return launch_outproj_staged(m, rows, B_dev, fixed_offset, splits, stream);
         if (which == kF32Tiled) return launch_outproj_tiled(m, rows, B_dev, fixed_offset, splits, stream);
         if (which == kF32Split2) return launch_outproj_split2(m, rows, B_dev, fixed_offset, splits, stream);
         const int row_groups = (rows + kFM - 1) / kFM, col_blocks = m.Vp / kFN;

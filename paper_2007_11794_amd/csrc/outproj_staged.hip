@@ -1,4 +1,4 @@
-// Output projection + log-sum-exp, LDS-staged bf16 MFMA kernel for Hp <= 704 (multiples of 64 from 128 on).
+// Output projection + log-sum-exp, LDS-staged MFMA kernel: bf16 models with Hp <= 704, fp32 models with Hp <= 320 (multiples of 64 from 128 on).
 //
 // What is computed is the same as in the plain kernel (normalising over all words of the
 // vocabulary, Section 2.1 of the paper); this is the fast form for batches of >= 128 rows.
@@ -51,6 +51,15 @@
 // 100 rows 21.2 / 17.0, 513 51.8 / 43.2; V = 30011, H = 650, running maximum, 97, 317 rows 15.6 / 11.9, 21.8 / 20.4 (18.7 as groups of 128:
 // staged_split).  Full groups: the same.
 //
+// fp32 models.  Weights and rows as two fp16 terms in operand order, three products (outproj_split2.hip, whose sums these are); an operand is two
+// kilobytes, a k-step three MFMAs, and a word has a factor beside its constant.  A row's two terms fit the registers up to Hp = 320; the
+// tiles of outproj_split2.hip, which take rows through LDS too, had two k-steps of 16 units on their way and a barrier for each.  Us per
+// launch, tiles / this: V = 20000, H = 256, 100 rows 10.2 / 7.8, 256 12.7 / 11.3, 300 13.8 / 13.9, 2000 58.6 / 49.6; V = 100000, H = 256, 128 rows
+// 34.2 / 22.6, 1024 135 / 113 (running maximum 139 / 115); H = 128, 80 rows 19.9 / 12.7, 500 43.8 / 35.2; V = 60000, H = 192, 200 rows 20.2 /
+// 18.0, 1500 93.5 / 78.8; V = 50000, H = 300, 128 rows 22.4 / 17.0, 1024 94.5 / 71.9; V = 1000, H = 200, 200 rows 9.4 / 5.8.  Up to 64 rows, known on the
+// device only, the streaming body has eight waves here, four there: V = 20000, H = 256, 32 rows 5.1 / 5.4, 64 6.8 / 7.3; V = 50000, H = 300, 50
+// rows 17.7 / 14.7; V = 3000, H = 128, 32 rows 3.9 / 3.7.
+//
 // When the batch turns out to hold at most 64 rows (the count may be known on the device only),
 // the kernel runs the weight-streaming body instead (outproj_stream_body.h): see the top of
 // the kernel.
@@ -69,30 +78,39 @@ namespace rnnlm {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kCSlots = 8;                       // ring of per-block constants (32 floats each)
-constexpr int kCSlotBytes = kStagedWords * 4;
-constexpr int kPrefetch = 4;                     // A operands read this many k-steps ahead
+constexpr int kStagedF32Hp = 320;               // largest padded hidden size of fp32 models whose rows' two terms fit the registers
+constexpr int kCSlots = 8;                       // ring of per-block constants (32 floats each; fp32 models: and 32 factors)
 
-template <int HP>
+// T: type of the weights.  An operand of one k-step (32 words or rows x 16 units) is a kilobyte of bf16, or two of fp16: the two terms.
+template <typename T, int HP>
 struct StagedCfg {
+    static constexpr int kTerms = sizeof(T) / 2;
+    using Operand = std::conditional_t<kTerms == 1, bf16x8, f16x8>;
     static constexpr int KS = HP / 16;                       // MFMA k-steps per block
-    static constexpr bool kRowOrder = HP % 128 == 0 && HP <= 512;       // weights from Ot, else from Ofrag
-    static constexpr bool kScaledD = staged_scaled_d(HP);
-    static constexpr bool kHalves = HP > 512;                           // groups of 128 rows where they pay (staged_split)
+    static constexpr bool kRowOrder = kTerms == 1 && HP % 128 == 0 && HP <= 512;       // weights from Ot, else from Ofrag
+    static constexpr bool kScaledD = kTerms == 1 && staged_scaled_d(HP);
+    static constexpr bool kHalves = kTerms == 1 && HP > 512;            // groups of 128 rows where they pay (staged_split)
     static constexpr int CPR = HP / 8;                                  // 16-byte chunks per word row
-    static constexpr int kStages = HP <= 512 ? 4 : 3;                  // as LDS allows
-    static constexpr int kLoadsPerThread = (KS + 7) / 8;                // weight loads per block: 8 KB each
+    static constexpr int kStages = kTerms * HP <= 512 ? 4 : 3;         // as LDS allows
+    static constexpr int kPrefetch = 4 / kTerms;                        // A operands read this many k-steps ahead
+    static constexpr int kLoadsPerThread = (kTerms * KS + 7) / 8;       // weight loads per block: 8 KB each
     static constexpr int kStageBytes = kLoadsPerThread * 8192;
-    static constexpr int kLoadsPerBlock = kLoadsPerThread + 1;          // + one for the constants
-    static constexpr int kLdsBytes = kStages * kStageBytes + kCSlots * kCSlotBytes;
+    static constexpr int kLoadsPerBlock = kLoadsPerThread + kTerms;     // + one for the constants (+ one for the factors)
+    static constexpr int kSlotBytes = kTerms * kStagedWords * 4;
+    static constexpr int kLdsBytes = kStages * kStageBytes + kCSlots * kSlotBytes;
     static_assert(HP % 64 == 0 && KS >= 8, "");
     static_assert(kLdsBytes <= 160 * 1024, "");
 };
+// Do the logits start from their constants?  Fixed offset, and no factor per word.
+template <typename T, bool FIXED>
+constexpr bool kStartsAtConstants = FIXED && sizeof(T) == 2;
 
 // The block loader.
-template <int HP>
+template <typename T, int HP>
 struct Loader {
-    using C = StagedCfg<HP>;
+    using C = StagedCfg<T, HP>;
+    const char *weights;
+    const float *cvec, *factors;                             // of the words (factors: fp32 models)
     uint32_t wave;                                           // wave index, in an SGPR
     uint32_t voff[C::kRowOrder ? C::kLoadsPerThread : 1];    // this lane's bytes of a piece (row order: of a block)
     int lane;
@@ -112,9 +130,9 @@ struct Loader {
             voff[0] = (uint32_t)lane * 16;
         }
     }
-    // (a block is 64 HP bytes in either order)
-    __device__ __forceinline__ const char *block_of(const char *weights, int block) const {
-        return weights + (size_t)block * (64 * HP);
+    // (a block is 64 HP bytes in either order, times the terms)
+    __device__ __forceinline__ const char *block_of(int block) const {
+        return weights + (size_t)block * (64 * HP * C::kTerms);
     }
     // The loads of a 32-word block into a stage and a slot of constants, in pieces and without branches (the block body is one
     // basic block): weight load q of the block, and its constants.  real = false turns the load into a dummy
@@ -125,19 +143,24 @@ struct Loader {
         if constexpr (C::kRowOrder) {
             lds_dma_16(src, real ? voff[q] : 0u, to);
         } else {
-            const bool mine = real && (HP % 128 == 0 || q + 1 < C::kLoadsPerThread || wave < 4);
+            const bool mine = real && (C::kTerms * HP % 128 == 0 || q + 1 < C::kLoadsPerThread || wave < 4);
             lds_dma_16(mine ? src + (q * 8 + wave) * 1024 : src, mine ? voff[0] : 0u, to);
         }
     }
-    __device__ __forceinline__ void issue_consts(const float *cblk, uint32_t cslot_lds) const {
-        lds_dma_16_lane0(cblk, wave * 16, cslot_lds + wave * 16);
+    // (0: the constants of the block's words, 1: their factors)
+    template <int WHICH>
+    __device__ __forceinline__ void issue_words(int block, uint32_t cslot_lds) const {
+        lds_dma_16_lane0((WHICH ? factors : cvec) + (size_t)block * kStagedWords, wave * 16, cslot_lds + WHICH * (kStagedWords * 4) + wave * 16);
     }
-    __device__ __forceinline__ void issue_all(const char *weights, const float *cvec, int block, uint32_t stage_lds,
-                                              uint32_t cslot_lds) const {
-        const char *src = block_of(weights, block);
+    __device__ __forceinline__ void issue_consts(int block, uint32_t cslot_lds) const {
+        issue_words<0>(block, cslot_lds);
+        if constexpr (C::kTerms == 2) issue_words<1>(block, cslot_lds);
+    }
+    __device__ __forceinline__ void issue_all(int block, uint32_t stage_lds, uint32_t cslot_lds) const {
+        const char *src = block_of(block);
 #pragma unroll
-        for (int q = 0; q < StagedCfg<HP>::kLoadsPerThread; ++q) issue_weights(src, q, true, stage_lds);
-        issue_consts(cvec + (size_t)block * kStagedWords, cslot_lds);
+        for (int q = 0; q < C::kLoadsPerThread; ++q) issue_weights(src, q, true, stage_lds);
+        issue_consts(block, cslot_lds);
     }
 };
 
@@ -147,17 +170,19 @@ struct Loader {
 // would notice).  Running maximum (constants of any size): the constants are added at the end.
 template <bool SCALED>
 __device__ __forceinline__ float base2(float acc) { return SCALED ? acc : acc * kLog2e; }
-template <bool SCALED>
-__device__ __forceinline__ float base2_plus(float acc, float c) { return SCALED ? acc + c : fmaf(acc, kLog2e, c); }
+// fp32 models: f is the word's factor, which brings its powers of two and log2(e) back.
+template <typename T, bool SCALED>
+__device__ __forceinline__ float base2_plus(float acc, float f, float c) { return sizeof(T) == 4 ? fmaf(acc, f, c) : SCALED ? acc + c : fmaf(acc, kLog2e, c); }
 
 // This lane's part of an A operand.  Row order: chunk (2 ks + g) of word `col`, swizzled; only the low 4 bits
 // of the chunk index take part in the swizzle, so eight per-lane offsets plus compile-time constants cover
 // all k-steps.  Operand order: one offset.
-template <int HP>
+template <typename T, int HP>
 struct FragOffsets {
-    int at[StagedCfg<HP>::kRowOrder ? 8 : 1];
+    using C = StagedCfg<T, HP>;
+    int at[C::kRowOrder ? 8 : 1];
     __device__ __forceinline__ void init(int lane) {
-        if constexpr (StagedCfg<HP>::kRowOrder) {
+        if constexpr (C::kRowOrder) {
             const int col = lane & 31, g = lane >> 5;
 #pragma unroll
             for (int j = 0; j < 8; ++j) at[j] = col * (HP * 2) + ((((2 * j) | g) ^ (col & 15)) * 16);
@@ -166,29 +191,16 @@ struct FragOffsets {
         }
     }
     __device__ __forceinline__ int operator()(int ks) const {
-        if constexpr (StagedCfg<HP>::kRowOrder) return at[ks & 7] + (ks >> 3) * 256;
-        else return at[0] + ks * 1024;
+        if constexpr (C::kRowOrder) return at[ks & 7] + (ks >> 3) * 256;
+        else return at[0] + ks * (C::kTerms * 1024);
+    }
+    // read the A operand of k-step ks
+    __device__ __forceinline__ void read(const char *stage, int ks, typename C::Operand (&a)[C::kTerms]) const {
+#pragma unroll
+        for (int t = 0; t < C::kTerms; ++t) a[t] = *reinterpret_cast<const typename C::Operand *>(stage + (*this)(ks) + t * 1024);
     }
 };
-#define RNNLM_A_FRAG(stage, ks) (*reinterpret_cast<const bf16x8 *>((stage) + aoff(ks)))
 
-// One MFMA B operand (this lane's 16 bytes of a 1 KB fragment) requested WITHOUT the compiler
-// knowing that a load is in flight: the register is defined for it at once, and the caller keeps
-// it unread until await_d_operand has waited for the data.  (A load the compiler can see makes
-// it guard the operand with vmcnt waits of its own inside the block loop, and those drain the
-// direct-to-LDS loads, which it cannot see.)
-template <int OFFSET>
-__device__ __forceinline__ void load_d_operand(bf16x8 &dst, const bf16_t *lane_ptr) {
-    static_assert(OFFSET >= 0 && OFFSET < 4096, "immediate offset of a global load");
-    asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(dst) : "v"(lane_ptr), "n"(OFFSET) : "memory");
-}
-// Wait until at most `younger` of this wave's vector-memory operations are outstanding; the
-// operand goes in and out so that its first use cannot move in front of the wait.
-template <int YOUNGER>
-__device__ __forceinline__ void await_d_operand(bf16x8 &op) {
-    static_assert(YOUNGER >= 0 && YOUNGER < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(op) : "n"(YOUNGER));
-}
 // fn(std::integral_constant<int, I>) for I = BEGIN .. END - 1, in order.
 template <int BEGIN, int END, typename Fn>
 __device__ __forceinline__ void static_for(Fn &&fn) {
@@ -198,31 +210,59 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
     }
 }
 
-// Dispatch of load_d_operand on a compile-time operand index: operand j of a wave lies 1 KB behind
-// operand j - 1; one pointer every 4 KB, immediate offsets in between.
-template <int J>
-__device__ __forceinline__ void load_d_operand_at(bf16x8 &dst, const bf16_t *dfr) {
-    load_d_operand<(J % 4) * 1024>(dst, dfr + (size_t)(J / 4) * 2048);
+// One MFMA B operand (this lane's 16 bytes of a 1 KB fragment) requested WITHOUT the compiler
+// knowing that a load is in flight: the register is defined for it at once, and the caller keeps
+// it unread until await_d_operand has waited for the data.  (A load the compiler can see makes
+// it guard the operand with vmcnt waits of its own inside the block loop, and those drain the
+// direct-to-LDS loads, which it cannot see.)
+template <int OFFSET, typename Operand>
+__device__ __forceinline__ void load_d_operand(Operand &dst, const bf16_t *lane_ptr) {
+    static_assert(OFFSET >= 0 && OFFSET < 4096, "immediate offset of a global load");
+    asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(dst) : "v"(lane_ptr), "n"(OFFSET) : "memory");
+}
+// Wait until at most `younger` of this wave's vector-memory operations are outstanding; the
+// operand goes in and out so that its first use cannot move in front of the wait.
+template <int YOUNGER, typename Operand>
+__device__ __forceinline__ void await_d_operand(Operand (&op)[1]) {
+    static_assert(YOUNGER >= 0 && YOUNGER < 64, "vmcnt is a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(op[0]) : "n"(YOUNGER));
+}
+template <int YOUNGER, typename Operand>
+__device__ __forceinline__ void await_d_operand(Operand (&op)[2]) {
+    static_assert(YOUNGER >= 0 && YOUNGER < 64, "vmcnt is a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%2)" : "+v"(op[0]), "+v"(op[1]) : "n"(YOUNGER));
+}
+// Dispatch of load_d_operand on a compile-time k-step: the kilobytes of a wave's operands lie one behind
+// the other; one pointer every 4 KB, immediate offsets in between.
+template <int KSTEP, typename Operand, int TERMS>
+__device__ __forceinline__ void load_d_operand_at(Operand (&dst)[TERMS], const bf16_t *dfr) {
+    static_for<0, TERMS>([&](auto t) __attribute__((always_inline)) {
+        constexpr int J = KSTEP * TERMS + decltype(t)::value;
+        load_d_operand<(J % 4) * 1024>(dst[decltype(t)::value], dfr + (size_t)(J / 4) * 2048);
+    });
 }
 
 // What block 0 of an item issues besides its own work (staged_block<HP, FIXED, true>): the part of
 // d that the prologue has not requested, and blocks 1 and 2.  All loads of a wave are issued in
 // one fixed program order, so the number of loads younger than any given one is a compile-time
 // figure: that is what the vmcnt immediates of block 0 are computed from.
-template <int HP>
+template <typename T, int HP>
 struct FirstBlockSchedule {
-    using C = StagedCfg<HP>;
-    static constexpr int KS = C::KS, HALF = KS / 2, L = C::kLoadsPerBlock, NW = C::kLoadsPerThread;
+    using C = StagedCfg<T, HP>;
+    static constexpr int KS = C::KS, HALF = KS / 2, L = C::kLoadsPerBlock, NW = C::kLoadsPerThread, TERMS = C::kTerms;
     static constexpr int kLoadStep = (HALF - 2) / NW;
-    static constexpr int D0 = KS < 8 ? KS : 8;                 // operands of d requested by the prologue
+    static constexpr int D0 = 8 / TERMS;                       // operands of d requested by the prologue
     static constexpr int kAhead = C::kStages - 2;              // blocks requested in the first half of block 0: 1 and, with four stages, 2
-    static_assert(kAhead * L <= HALF, "");
-    // loads issued in k-step k: before its MFMA an operand of d (e1) and a load of block 1 or 2 (e2),
-    // after its MFMA the regular loads of the block behind them (e3)
-    static constexpr int e1(int k) { return k + D0 < KS ? 1 : 0; }
-    static constexpr int e2(int k) { return k < kAhead * L ? 1 : 0; }
+    static_assert(kAhead * L <= HALF * TERMS, "");
+    // loads issued in k-step k: before its MFMAs an operand of d (e1) and as many loads of block 1 or 2 (e2),
+    // after them the regular loads of the block behind them (e3)
+    static constexpr int e1(int k) { return k + D0 < KS ? TERMS : 0; }
+    static constexpr int e2(int k) {
+        const int left = kAhead * L - k * TERMS;
+        return left <= 0 ? 0 : left < TERMS ? left : TERMS;
+    }
     static constexpr int e3(int k) {
-        int n = (k == KS - 2) ? 1 : 0;
+        int n = (k == KS - 2) ? TERMS : 0;                     // (constants and factors)
         for (int q = 0; q < NW; ++q)
             if (k == HALF + 1 + q * kLoadStep) ++n;
         return n;
@@ -231,7 +271,7 @@ struct FirstBlockSchedule {
     static constexpr int younger_than_d(int ks) {
         int n = 0;
         if (ks < D0) {
-            n = D0 - 1 - ks;
+            n = (D0 - 1 - ks) * TERMS;
             for (int k = 0; k <= ks; ++k) n += e1(k) + e2(k);
             for (int k = 0; k < ks; ++k) n += e3(k);
         } else {
@@ -242,11 +282,12 @@ struct FirstBlockSchedule {
         }
         return n;
     }
-    // loads younger than the last load of block 1 (k-step L - 1) at the barrier on top of k-step HALF
+    // loads younger than the last load of block 1 at the barrier on top of k-step HALF
     static constexpr int younger_than_block1() {
-        int n = 0;
-        for (int k = L; k < HALF; ++k) n += e1(k) + e2(k);
-        for (int k = L - 1; k < HALF; ++k) n += e3(k);
+        const int last = (L - 1) / TERMS;                      // the k-step that issues it
+        int n = e2(last) - 1 - (L - 1) % TERMS;
+        for (int k = last + 1; k < HALF; ++k) n += e1(k) + e2(k);
+        for (int k = last; k < HALF; ++k) n += e3(k);
         return n;
     }
     static constexpr int worst() {
@@ -257,10 +298,16 @@ struct FirstBlockSchedule {
     }
     static_assert(worst() < 64, "vmcnt is a 6-bit counter");
 };
+// The operands a wave holds: its rows of d for the whole reduction length, and the words' next ones.
+template <typename T, int HP>
+struct StagedOperands {
+    using C = StagedCfg<T, HP>;
+    typename C::Operand d[C::KS][C::kTerms], a[C::kPrefetch][C::kTerms];
+};
 struct FirstBlockLoads {
     const bf16_t *dfr;          // this lane's 16 bytes of operand 0 of its wave's rows
     const char *blk[2];         // weights of blocks 1 and 2 (or the dummy source)
-    const float *cst[2];        // their constants
+    int block[2];               // their numbers (0)
     bool real[2];
     uint32_t stage[2], cslot[2];
 };
@@ -271,7 +318,7 @@ struct FirstBlockLoads {
 // 24.3; V = 100000, H = 576, 1000 rows 98.8 / 90.9; V = 65536, H = 512, 1024 rows 63.5 / 57.4 (fixed offset 54), 300 31.7 / 27.9; H = 320, 1229
 // rows 55.7 / 50.1; V = 200000, H = 128, 1000 rows 73.8 / 68.6; with two or three blocks in all V = 20000, H = 192, 200 rows 6.0 / 6.2.
 template <int KS>
-struct RunningMaxSchedule {
+struct FoldSchedule {
     static constexpr int constants(int q) { return q * KS / 16; }
     static constexpr int kRead = KS < 12 ? 1 : KS < 16 ? 2 : 3;    // k-steps for an LDS read
     static constexpr int logits(int q) { return constants(q) + kRead; }
@@ -288,7 +335,7 @@ struct RunningLse {
 // One 32-word block for this wave's 32 rows, as ONE basic block.
 //   acc     on entry the block's constants (fixed offset: the logits start from them) or zero, on return the finished
 //           logits of the block (running maximum: without their constants)
-//   other   on entry the same of the previous block (-inf before the first): their
+//   other   on entry the same of the previous block (unused in front of the first): their
 //           exp-and-add is spread over the k-steps (fixed offset: of the first half); on return the start of
 //           block bi+1 (constants read from the ring in the second half; after the last block: a landed
 //           slot, unused)
@@ -303,29 +350,28 @@ struct RunningLse {
 // k-steps ahead of its use, and blocks 1 and 2 load by load in the first half.  Every MFMA waits
 // for ITS operand of d alone, and the barrier for block 1 alone (FirstBlockSchedule has the
 // counts): the chain runs at the pace at which d arrives instead of starting after all of it.
-template <int HP, bool FIXED, bool FIRST>
-__device__ __forceinline__ void staged_block(const char *lds, const char *cring, uint32_t lds0,
-                                                   uint32_t cring0, const Loader<HP> &loader, const char *weights,
-                                                   const float *cvec, int blk0, int nblk, int bi,
-                                                   const FragOffsets<HP> &aoff, bf16x8 (&a)[kPrefetch],
-                                                   bf16x8 (&dreg)[HP / 16], int g, f32x16 &acc,
-                                                   f32x16 &other, RunningLse &lse, const FirstBlockLoads &first) {
-    using C = StagedCfg<HP>;
-    using F = FirstBlockSchedule<HP>;
-    constexpr int KS = C::KS, HALF = KS / 2, NW = C::kLoadsPerThread;
+template <typename T, int HP, bool FIXED, bool FIRST>
+__device__ __forceinline__ void staged_block(const char *lds, const char *cring, uint32_t lds0, uint32_t cring0,
+                                             const Loader<T, HP> &loader, int blk0, int nblk, int bi,
+                                             const FragOffsets<T, HP> &aoff, StagedOperands<T, HP> &op, int g, f32x16 &acc,
+                                             f32x16 &other, RunningLse &lse, const FirstBlockLoads &first) {
+    using C = StagedCfg<T, HP>;
+    using F = FirstBlockSchedule<T, HP>;
+    constexpr int KS = C::KS, HALF = KS / 2, NW = C::kLoadsPerThread, kPrefetch = C::kPrefetch, TERMS = C::kTerms;
+    constexpr bool kAtConstants = kStartsAtConstants<T, FIXED>;
     constexpr int kLoadStep = (HALF - 2) / NW;                 // k-steps between two weight loads
-    static_assert(KS >= 2 * kPrefetch && kLoadStep >= 1 && HALF + 1 + (NW - 1) * kLoadStep < KS - 2, "");
+    static_assert(KS >= 2 * kPrefetch && kLoadStep >= 1 && HALF + 1 + (NW - 1) * kLoadStep <= KS - 2, "");
     constexpr int NS = C::kStages;
     const char *stage = lds + bi % NS * C::kStageBytes;
     const char *next_stage = lds + ((bi + 1 < nblk) ? bi + 1 : bi) % NS * C::kStageBytes;
-    // fixed offset: the constants the next block starts from; else those of the previous one (in front of the first any landed slot)
-    const f32x4 *cn = reinterpret_cast<const f32x4 *>(cring + (FIXED ? (bi + 1) & 7 : FIRST ? 0 : (bi - 1) & 7) * kCSlotBytes);
-    using R = RunningMaxSchedule<KS>;
-    f32x4 c4[4];                                               // (running maximum: one of them in use at a time)
+    // the constants the next block starts from, or those of the previous one
+    const f32x4 *cn = reinterpret_cast<const f32x4 *>(cring + ((kAtConstants ? bi + 1 : bi - 1) & 7) * C::kSlotBytes);
+    using R = FoldSchedule<KS>;
+    f32x4 c4[4], f4[4];                                        // (those of the previous block: one or two of them in use at a time)
     const bool real = bi + NS - 1 < nblk;
     const int block3 = real ? blk0 + bi + NS - 1 : 0;
-    const char *src3 = loader.block_of(weights, block3);
-    const uint32_t stage3 = lds0 + (bi + NS - 1) % NS * C::kStageBytes, cslot3 = cring0 + ((bi + NS - 1) & 7) * kCSlotBytes;
+    const char *src3 = loader.block_of(block3);
+    const uint32_t stage3 = lds0 + (bi + NS - 1) % NS * C::kStageBytes, cslot3 = cring0 + ((bi + NS - 1) & 7) * C::kSlotBytes;
     // the k-steps as a compile-time loop: every condition below is a constant, and so are the vmcnt
     // immediates
     static_for<0, KS>([&](auto step) __attribute__((always_inline)) {
@@ -337,39 +383,48 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
-        const bf16x8 cur = a[ks % kPrefetch];
-        if constexpr (ks + kPrefetch < KS) a[ks % kPrefetch] = RNNLM_A_FRAG(stage, ks + kPrefetch);
-        else a[ks % kPrefetch] = RNNLM_A_FRAG(next_stage, ks + kPrefetch - KS);
+        typename C::Operand cur[TERMS];
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) cur[t] = op.a[ks % kPrefetch][t];
+        if constexpr (ks + kPrefetch < KS) aoff.read(stage, ks + kPrefetch, op.a[ks % kPrefetch]);
+        else aoff.read(next_stage, ks + kPrefetch - KS, op.a[ks % kPrefetch]);
         if constexpr (FIRST) {
-            if constexpr (ks + F::D0 < KS) load_d_operand_at<ks + F::D0>(dreg[ks + F::D0], first.dfr);
-            if constexpr (ks < F::L) {
-                if constexpr (ks < NW) loader.issue_weights(first.blk[0], ks, first.real[0], first.stage[0]);
-                else loader.issue_consts(first.cst[0], first.cslot[0]);
-            } else if constexpr (ks < F::kAhead * F::L) {
-                if constexpr (ks - F::L < NW) loader.issue_weights(first.blk[1], ks - F::L, first.real[1], first.stage[1]);
-                else loader.issue_consts(first.cst[1], first.cslot[1]);
-            }
-            await_d_operand<F::younger_than_d(ks)>(dreg[ks]);
+            if constexpr (ks + F::D0 < KS) load_d_operand_at<ks + F::D0>(op.d[ks + F::D0], first.dfr);
+            static_for<ks * TERMS, ks * TERMS + F::e2(ks)>([&](auto load) __attribute__((always_inline)) {
+                constexpr int b = decltype(load)::value / F::L, q = decltype(load)::value % F::L;
+                if constexpr (q < NW) loader.issue_weights(first.blk[b], q, first.real[b], first.stage[b]);
+                else loader.template issue_words<q - NW>(first.block[b], first.cslot[b]);
+            });
+            await_d_operand<F::younger_than_d(ks)>(op.d[ks]);
         }
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, dreg[ks], acc, 0, 0, 0);
-        if constexpr (FIXED) {
+        if constexpr (TERMS == 1) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur[0], op.d[ks][0], acc, 0, 0, 0);
+        } else {                                               // smallest cross terms first
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[1], op.d[ks][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[0], op.d[ks][1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[0], op.d[ks][0], acc, 0, 0, 0);
+        }
+        if constexpr (!FIRST && kAtConstants) {
             // the previous block's sixteen logits, over k-steps 1 .. HALF
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 if (1 + (e * HALF) / 16 == ks) lse.s += fast_exp2(base2<C::kScaledD>(other[e]));
-        } else {
+        } else if constexpr (!FIRST) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (ks == R::logits(q)) {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        other[4 * q + i] = base2_plus<C::kScaledD>(other[4 * q + i], c4[q][i]);
-                        lse.offset = q + i == 0 ? other[0] : fmaxf(lse.offset, other[4 * q + i]);
+                        other[4 * q + i] = base2_plus<T, C::kScaledD>(other[4 * q + i], f4[q][i], c4[q][i]);
+                        if (!FIXED) lse.offset = q + i == 0 ? other[0] : fmaxf(lse.offset, other[4 * q + i]);
                     }
                 }
-                if (ks == R::constants(q)) c4[q] = cn[2 * q + g];
+                if (ks == R::constants(q)) {
+                    c4[q] = cn[2 * q + g];
+                    if constexpr (TERMS == 2) f4[q] = cn[kStagedWords / 4 + 2 * q + g];
+                }
             }
-            if constexpr (ks == R::kMaximum) {
+            if constexpr (!FIXED && ks == R::kMaximum) {
                 const float mn = fmaxf(lse.m, lse.offset);
                 lse.offset = mn == -INFINITY ? 0.f : mn;       // (nothing but -inf so far: the terms below are 2^-inf)
                 lse.s *= fast_exp2(lse.m - lse.offset);
@@ -378,21 +433,24 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
             }
 #pragma unroll
             for (int e = 0; e < 16; ++e)
-                if (R::term(e) == ks) lse.terms += fast_exp2(other[e] - lse.offset);
-            if constexpr (ks == KS - 1) {
-                lse.s += lse.terms;
+                if (R::term(e) == ks) {
+                    if constexpr (FIXED) lse.s += fast_exp2(other[e]);             // (the offset is in the constants)
+                    else lse.terms += fast_exp2(other[e] - lse.offset);
+                }
+            if constexpr (!FIXED && ks == KS - 1) lse.s += lse.terms;
+        }
+        if constexpr (!kAtConstants && ks == KS - 1) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) other[i] = 0.f;
-            }
+            for (int i = 0; i < 16; ++i) other[i] = 0.f;
         }
         // second half: loads of block bi+3, with the fixed offset the constants of block bi+1 into the resting accumulators
 #pragma unroll
         for (int q = 0; q < NW; ++q)
             if (ks == HALF + 1 + q * kLoadStep) loader.issue_weights(src3, q, real, stage3);
-        if constexpr (ks == KS - 2) loader.issue_consts(cvec + (size_t)block3 * kStagedWords, cslot3);
+        if constexpr (ks == KS - 2) loader.issue_consts(block3, cslot3);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (FIXED && ks == HALF + 1 + (q * (HALF - 1)) / 4) {
+            if (kAtConstants && ks == HALF + 1 + (q * (HALF - 1)) / 4) {
                 const f32x4 c = cn[2 * q + g];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) other[4 * q + i] = c[i];
@@ -403,72 +461,64 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
     });
 }
 
-template <bool FIXED, bool SCALED>
-__device__ __forceinline__ const float *block_constants(const ModelDev &m) {
-    return !FIXED ? m.cvec2 : SCALED ? m.cvec2_fixed : m.cvec_fixed;
-}
-
 // The exp-and-add of an item's last block.
-template <bool FIXED, bool SCALED>
+template <typename T, int HP, bool FIXED>
 __device__ __forceinline__ void fold_last_block(const f32x16 &acc, const char *cring, int bi, int g, RunningLse &lse) {
-    if constexpr (FIXED) {
+    using C = StagedCfg<T, HP>;
+    if constexpr (kStartsAtConstants<T, FIXED>) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) lse.s += fast_exp2(base2<SCALED>(acc[e]));
+        for (int e = 0; e < 16; ++e) lse.s += fast_exp2(base2<C::kScaledD>(acc[e]));
     } else {
-        const f32x4 *cn = reinterpret_cast<const f32x4 *>(cring + (bi & 7) * kCSlotBytes);
+        const f32x4 *cn = reinterpret_cast<const f32x4 *>(cring + (bi & 7) * C::kSlotBytes);
         float x[16];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const f32x4 c = cn[2 * q + g];
+            const f32x4 c = cn[2 * q + g], f = C::kTerms == 2 ? cn[kStagedWords / 4 + 2 * q + g] : c;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[4 * q + i] = base2_plus<SCALED>(acc[4 * q + i], c[i]);
+            for (int i = 0; i < 4; ++i) x[4 * q + i] = base2_plus<T, C::kScaledD>(acc[4 * q + i], f[i], c[i]);
         }
-        lse2_fold16<false>(x, lse.m, lse.s);
+        lse2_fold16<FIXED>(x, lse.m, lse.s);
     }
 }
 
 // All blocks of one (row group, split) item for this wave's rows: the item's words' part of the log-sum-exp for this lane's half of
 // its row, as (lse.m, lse.s); with the fixed offset the sum of 2^(logit - offset) alone.
-template <int HP, bool FIXED>
-__device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *cring, const Loader<HP> &loader,
-                                                   const FragOffsets<HP> &aoff, int row0, int blk0, int nblk, int wave,
+template <typename T, int HP, bool FIXED>
+__device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *cring, const Loader<T, HP> &loader,
+                                            const FragOffsets<T, HP> &aoff, int row0, int blk0, int nblk, int wave,
                                             int lane, int g, RunningLse &lse) {
-    using C = StagedCfg<HP>;
+    using C = StagedCfg<T, HP>;
     constexpr int KS = C::KS;
-    const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
-    const float *cvec = block_constants<FIXED, C::kScaledD>(m);
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
     // Block 0 and the first operands of this wave's rows of d (all k of 32 rows are MFMA B operands
     // held in registers; rows beyond B hold stale scratch: rows are independent and those lanes'
     // results are dropped).  The rest of d and blocks 1 and 2 are requested by block 0 itself.
-    using F = FirstBlockSchedule<HP>;
-    loader.issue_all(weights, cvec, blk0, lds0, cring0);
-    bf16x8 dreg[KS];
+    using F = FirstBlockSchedule<T, HP>;
+    loader.issue_all(blk0, lds0, cring0);
+    StagedOperands<T, HP> op;
     FirstBlockLoads first;
-    // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row
-    first.dfr = static_cast<const bf16_t *>(m.dfrag) + ((size_t)(row0 / 32 + wave) * KS * 64 + lane) * 8;
+    // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row, a term behind the other
+    first.dfr = static_cast<const bf16_t *>(m.dfrag) + ((size_t)(row0 / 32 + wave) * KS * C::kTerms * 64 + lane) * 8;
     static_for<0, F::D0>([&](auto j) __attribute__((always_inline)) {
-        load_d_operand_at<decltype(j)::value>(dreg[decltype(j)::value], first.dfr);
+        load_d_operand_at<decltype(j)::value>(op.d[decltype(j)::value], first.dfr);
     });
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         first.real[i] = i + 1 < nblk;
-        const int block = first.real[i] ? blk0 + i + 1 : 0;
-        first.blk[i] = loader.block_of(weights, block);
-        first.cst[i] = cvec + (size_t)block * kStagedWords;
+        first.block[i] = first.real[i] ? blk0 + i + 1 : 0;
+        first.blk[i] = loader.block_of(first.block[i]);
         first.stage[i] = lds0 + (i + 1) % C::kStages * C::kStageBytes;
-        first.cslot[i] = cring0 + (i + 1) * kCSlotBytes;
+        first.cslot[i] = cring0 + (i + 1) * C::kSlotBytes;
     }
     // Block 0 has landed once only the younger loads are outstanding: the first operands of d.
-    wait_vmcnt<F::D0>();
+    wait_vmcnt<F::D0 * C::kTerms>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();                             // block 0 is published
     asm volatile("" ::: "memory");
     // From block 1 on every wave has, at the barrier in the middle of block bi, the loads of blocks
     // bi+1 and bi+2 in flight at most.
-    bf16x8 a[kPrefetch];
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i) a[i] = RNNLM_A_FRAG(lds, i);
+    for (int i = 0; i < C::kPrefetch; ++i) aoff.read(lds, i, op.a[i]);
     f32x16 acc0, acc1;
     {
         const f32x4 *c0 = reinterpret_cast<const f32x4 *>(cring);
@@ -476,15 +526,13 @@ __device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *
         for (int q = 0; q < 4; ++q) {
             const f32x4 c = c0[2 * q + g];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc0[4 * q + i] = FIXED ? c[i] : 0.f;
+            for (int i = 0; i < 4; ++i) acc0[4 * q + i] = kStartsAtConstants<T, FIXED> ? c[i] : 0.f;
         }
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc1[i] = -INFINITY;        // "previous block" of block 0: adds 2^-inf = 0
     lse.m = -INFINITY;
     lse.s = 0.f;
 #define RNNLM_BLOCK(FIRST, BI, ACC, OTHER) \
-    staged_block<HP, FIXED, FIRST>(lds, cring, lds0, cring0, loader, weights, cvec, blk0, nblk, BI, aoff, a, dreg, g, ACC, OTHER, lse, first)
+    staged_block<T, HP, FIXED, FIRST>(lds, cring, lds0, cring0, loader, blk0, nblk, BI, aoff, op, g, ACC, OTHER, lse, first)
     RNNLM_BLOCK(true, 0, acc0, acc1);
     int bi = 1;
     for (; bi + 1 < nblk; bi += 2) {
@@ -493,9 +541,9 @@ __device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *
     }
     if (bi < nblk) {
         RNNLM_BLOCK(false, bi, acc1, acc0);
-        fold_last_block<FIXED, C::kScaledD>(acc1, cring, nblk - 1, g, lse);
+        fold_last_block<T, HP, FIXED>(acc1, cring, nblk - 1, g, lse);
     } else {
-        fold_last_block<FIXED, C::kScaledD>(acc0, cring, nblk - 1, g, lse);
+        fold_last_block<T, HP, FIXED>(acc0, cring, nblk - 1, g, lse);
     }
 #undef RNNLM_BLOCK
     // dummy loads may still be in flight into stages the next item fills first
@@ -505,19 +553,17 @@ __device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *
 // A wave without rows in an item: its share of the loads and all barriers, as staged_item has them (block 0 is published by the
 // first barrier; the barrier of block bi publishes block bi + 1 and frees the stage of block bi - 1), and nothing else.  The matrix
 // pipes are left to the waves that have rows: with up to four of them each has one to itself.
-template <int HP, bool FIXED>
-__device__ __forceinline__ void staged_item_loads(const ModelDev &m, uint32_t lds0, uint32_t cring0, const Loader<HP> &loader, int blk0, int nblk) {
-    using C = StagedCfg<HP>;
+template <typename T, int HP>
+__device__ __forceinline__ void staged_item_loads(uint32_t lds0, uint32_t cring0, const Loader<T, HP> &loader, int blk0, int nblk) {
+    using C = StagedCfg<T, HP>;
     constexpr int NS = C::kStages;
-    const char *weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
-    const float *cvec = block_constants<FIXED, C::kScaledD>(m);
     auto issue = [&](int bi) __attribute__((always_inline)) {            // always as many loads
         const bool real = bi < nblk;
         const int block = real ? blk0 + bi : 0;
-        const char *src = loader.block_of(weights, block);
+        const char *src = loader.block_of(block);
 #pragma unroll
         for (int q = 0; q < C::kLoadsPerThread; ++q) loader.issue_weights(src, q, real, lds0 + bi % NS * C::kStageBytes);
-        loader.issue_consts(cvec + (size_t)block * kStagedWords, cring0 + (bi & 7) * kCSlotBytes);
+        loader.issue_consts(block, cring0 + (bi & 7) * C::kSlotBytes);
     };
     issue(0);
     wait_vmcnt<0>();
@@ -536,11 +582,9 @@ __device__ __forceinline__ void staged_item_loads(const ModelDev &m, uint32_t ld
     wait_vmcnt<0>();                                                     // (dummies: the next item fills these stages)
 }
 
-template <int HP, bool FIXED>
-__global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, int rows,
-                                                                  const int *__restrict__ B_dev,
-                                                                  int wg_per_xcd) {
-    using C = StagedCfg<HP>;
+template <typename T, int HP, bool FIXED>
+__device__ __forceinline__ void staged_kernel(const ModelDev &m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
+    using C = StagedCfg<T, HP>;
     constexpr int KS = C::KS;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     char *const cring = lds + C::kStages * C::kStageBytes;
@@ -551,39 +595,47 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
     // them instead.  Same grid, and the same partials come out: with one row group the vocabulary
     // is cut into as many splits as there are workgroups, split = workgroup index.
     static_assert(kThreads == kStreamThreads, "");
-    static_assert(C::kLdsBytes >= 2 * KS * 1024 + kStreamWaves * 64 * 8, "LDS for two row blocks of the streaming form");
+    static_assert(C::kLdsBytes >= C::kTerms * 2 * KS * 1024 + kStreamWaves * 64 * 8, "LDS for two row blocks of the streaming form");
     if (B <= 64 && m.Ofrag && (int)gridDim.x == staged_plan(B, wg_per_xcd).S) {
-        if (B <= 32) outproj_stream_body<1, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-        else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        if constexpr (C::kTerms == 2) {
+            if (B <= 32) outproj_stream_f32_body<1, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            else outproj_stream_f32_body<2, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        } else {
+            if (B <= 32) outproj_stream_body<1, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+        }
         return;
     }
-    const StagedSplit split_of = staged_split(B, wg_per_xcd, C::kHalves);
-    const StagedPlan plan = split_of.plan;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    const int T = m.Vp / kStagedWords;                       // 32-word blocks in the vocabulary
+    const int blocks = m.Vp / kStagedWords;                  // 32-word blocks in the vocabulary
+    const StagedSplit split_of = staged_split(B, wg_per_xcd, C::kHalves);
+    const StagedPlan plan = split_of.plan;
     const int items = plan.RG * plan.Sx;
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
-    Loader<HP> loader;
+    Loader<T, HP> loader;
     loader.init();
-    FragOffsets<HP> aoff;
+    loader.weights = static_cast<const char *>(C::kRowOrder ? m.Ot : m.Ofrag);
+    loader.cvec = !FIXED ? m.cvec2 : C::kTerms == 2 || C::kScaledD ? m.cvec2_fixed : m.cvec_fixed;
+    loader.factors = m.ofac;
+    FragOffsets<T, HP> aoff;
     aoff.init(lane);
 
     for (int item = local; item < items; item += wg_per_xcd) {
         const int rg = item % plan.RG, split = xcd + kXcds * (item / plan.RG);
-        const int blk0 = part_begin(split, T, plan.S);
-        const int nblk = part_begin(split + 1, T, plan.S) - blk0;
+        const int blk0 = part_begin(split, blocks, plan.S);
+        const int nblk = part_begin(split + 1, blocks, plan.S) - blk0;
         const int row0 = rg * split_of.rows;
         const bool has_rows = (int)loader.wave * 32 < min(split_of.rows, B - row0);       // (wave-uniform)
         if (!has_rows) {
-            if (nblk > 0) staged_item_loads<HP, FIXED>(m, lds0, cring0, loader, blk0, nblk);
+            if (nblk > 0) staged_item_loads<T, HP>(lds0, cring0, loader, blk0, nblk);
             __syncthreads();
             continue;
         }
         RunningLse lse;
         lse.m = -INFINITY;
         lse.s = 0.f;
-        if (nblk > 0) staged_item<HP, FIXED>(m, lds, cring, loader, aoff, row0, blk0, nblk, wave, lane, g, lse);
+        if (nblk > 0) staged_item<T, HP, FIXED>(m, lds, cring, loader, aoff, row0, blk0, nblk, wave, lane, g, lse);
         // lanes l and l+32 hold the two halves of a row (the lane asked for anew: with Hp = 704 there is no register to keep it in)
         const int lane_now = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
         const int b = row0 + (int)loader.wave * 32 + (lane_now & 31);                        // this lane's row
@@ -598,30 +650,38 @@ __global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, in
         __syncthreads();                                      // LDS is reused by the next item
     }
 }
-#undef RNNLM_A_FRAG
 
-template <int HP>
+template <int HP, bool FIXED>
+__global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
+    staged_kernel<bf16_t, HP, FIXED>(m, rows, B_dev, wg_per_xcd);
+}
+// (the two-term form of fp32 models goes by one name, whether the rows come through LDS or sit in registers)
+template <int HP, bool FIXED>
+__global__ __launch_bounds__(kThreads) void outproj_split2_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
+    staged_kernel<float, HP, FIXED>(m, rows, B_dev, wg_per_xcd);
+}
+
+template <typename T, int HP>
 hipError_t launch_hp(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset, int wg_per_xcd,
                      hipStream_t stream) {
-    using C = StagedCfg<HP>;
+    using C = StagedCfg<T, HP>;
     static LdsLimit limit[2];
-    const void *fn = fixed_offset ? reinterpret_cast<const void *>(outproj_staged_kernel<HP, true>)
-                                  : reinterpret_cast<const void *>(outproj_staged_kernel<HP, false>);
-    if (hipError_t e = limit[fixed_offset ? 1 : 0].ensure(fn, C::kLdsBytes); e != hipSuccess) return e;
-    dim3 grid(kXcds * wg_per_xcd), block(kThreads);
-    if (fixed_offset)
-        hipLaunchKernelGGL((outproj_staged_kernel<HP, true>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,
-                           wg_per_xcd);
+    auto launch = [&](auto kernel, LdsLimit &l) -> hipError_t {
+        if (hipError_t e = l.ensure(reinterpret_cast<const void *>(kernel), C::kLdsBytes); e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(kXcds * wg_per_xcd), dim3(kThreads), C::kLdsBytes, stream, m, rows, B_dev, wg_per_xcd);
+        return hipGetLastError();
+    };
+    if constexpr (C::kTerms == 2)
+        return fixed_offset ? launch(outproj_split2_kernel<HP, true>, limit[1]) : launch(outproj_split2_kernel<HP, false>, limit[0]);
     else
-        hipLaunchKernelGGL((outproj_staged_kernel<HP, false>), grid, block, C::kLdsBytes, stream, m, rows, B_dev,
-                           wg_per_xcd);
-    return hipGetLastError();
+        return fixed_offset ? launch(outproj_staged_kernel<HP, true>, limit[1]) : launch(outproj_staged_kernel<HP, false>, limit[0]);
 }
 
 }  // namespace
 
 bool outproj_staged_supported(const ModelDev &m) {
-    return m.dtype == RNNLM_BF16 && m.Ofrag && m.Hp >= 128 && m.Hp <= 704 && m.Hp % 64 == 0;
+    if (m.dtype != RNNLM_BF16) return m.ofac && m.Ofrag && m.Hp >= 128 && m.Hp <= kStagedF32Hp && m.Hp % 64 == 0;
+    return m.Ofrag && m.Hp >= 128 && m.Hp <= 704 && m.Hp % 64 == 0;
 }
 
 hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
@@ -629,17 +689,26 @@ hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, 
     // One workgroup per compute unit: 256 CUs in 8 XCDs.
     const int wg_per_xcd = 32;
     *splits = SplitInfo{0, wg_per_xcd, m.Hp > 512 ? 0 : kStagedRows, kMaxSplits / kXcds, 0, 0};
+    if (m.dtype != RNNLM_BF16) {
+        switch (m.Hp) {
+            case 128: return launch_hp<float, 128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 192: return launch_hp<float, 192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 256: return launch_hp<float, 256>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 320: return launch_hp<float, 320>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            default: return hipErrorInvalidValue;
+        }
+    }
     switch (m.Hp) {
-        case 128: return launch_hp<128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 192: return launch_hp<192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 256: return launch_hp<256>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 320: return launch_hp<320>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 384: return launch_hp<384>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 448: return launch_hp<448>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 512: return launch_hp<512>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 576: return launch_hp<576>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 640: return launch_hp<640>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
-        case 704: return launch_hp<704>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 128: return launch_hp<bf16_t, 128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 192: return launch_hp<bf16_t, 192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 256: return launch_hp<bf16_t, 256>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 320: return launch_hp<bf16_t, 320>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 384: return launch_hp<bf16_t, 384>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 448: return launch_hp<bf16_t, 448>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 512: return launch_hp<bf16_t, 512>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 576: return launch_hp<bf16_t, 576>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 640: return launch_hp<bf16_t, 640>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+        case 704: return launch_hp<bf16_t, 704>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -228,7 +228,8 @@ __host__ __device__ inline StagedPlan staged_plan(int B, int wg_per_xcd) {
 // The staged kernel's row groups: 256 rows.  Beyond Hp = 512, three groups of 128 (four of a workgroup's eight waves each, with a
 // matrix pipe to itself) where two of 256 would leave one less than half full.  Us per launch, 256 / 128, V = 30011, H = 650: 257, 300, 384
 // rows 17.4 / 16.3, 17.5 / 16.2, 18.8 / 17.1, running maximum 20.9 / 19.0, 21.1 / 18.6, 21.8 / 19.4.  Not for five groups instead of
-// three (600 rows 24.3 / 24.2) and not below (V = 65536, H = 512, 300 rows 23.1 / 22.7, 600 35.2 / 36.4; V = 20000, H = 256, 300 rows 6.6 / 6.8).
+// three (600 rows 24.3 / 24.2), not for fp32 models (V = 100000, H = 128, 300 rows 30.0 / 31.6; V = 60000, H = 192, 200 rows 18.7 / 20.5; V = 100000,
+// H = 256, 300 rows 53.3 / 51.0) and not below (V = 65536, H = 512, 300 rows 23.1 / 22.7, 600 35.2 / 36.4; V = 20000, H = 256, 300 rows 6.6 / 6.8).
 struct StagedSplit {
     StagedPlan plan;
     int rows;              // of a group
