@@ -186,6 +186,15 @@ __device__ __forceinline__ void lds_dma_16_lane0(const void *sbase, uint32_t vof
                  : "memory");
 }
 
+// The same from lanes 0 and 1, each with its own voff.
+__device__ __forceinline__ void lds_dma_16_lanes01(const void *sbase, uint32_t voff, uint32_t lds_base) {
+    uint64_t saved_exec;
+    asm volatile("s_mov_b64 %0, exec\n\ts_mov_b64 exec, 3\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b64 exec, %0"
+                 : "=&s"(saved_exec)
+                 : "{m0}"(lds_base), "v"(voff), "s"(sbase)
+                 : "memory");
+}
+
 __device__ __forceinline__ uint32_t lds_address(const void *p) {
     return (uint32_t)reinterpret_cast<uintptr_t>(p);         // LDS offsets are the low 32 bits
 }

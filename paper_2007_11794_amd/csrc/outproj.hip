@@ -243,7 +243,7 @@ enum F32Kernel { kF32Stream, kF32Staged, kF32Split2, kF32Tiled, kF32Plain };
 static F32Kernel choose_f32(const ModelDev &m, int rows, int kernel_choice) {
     if (stream_choice(m, rows, kernel_choice)) return kF32Stream;
     if (kernel_choice == 3) return kF32Tiled;
-    // the rows in registers wherever both terms fit them (Hp <= 320); figures in outproj_staged.hip
+    // the rows in registers wherever both terms fit them (Hp <= 576); figures in outproj_staged.hip
     if (kernel_choice == 0 && rows >= 64 && !m.infinite_O && outproj_staged_supported(m)) return kF32Staged;
     if (m.ofac && (kernel_choice == 4 || (kernel_choice == 0 && rows >= 64 && !m.infinite_O))) return kF32Split2;
     return kF32Plain;

@@ -1,4 +1,4 @@
-// Output projection + log-sum-exp, LDS-staged MFMA kernel: bf16 models with Hp <= 704, fp32 models with Hp <= 320 (multiples of 64 from 128 on).
+// Output projection + log-sum-exp, LDS-staged MFMA kernel: bf16 models with Hp <= 704, fp32 models with Hp <= 576 (multiples of 64 from 128 on).
 //
 // What is computed is the same as in the plain kernel (normalising over all words of the
 // vocabulary, Section 2.1 of the paper); this is the fast form for batches of >= 128 rows.
@@ -52,13 +52,17 @@
 // staged_split).  Full groups: the same.
 //
 // fp32 models.  Weights and rows as two fp16 terms in operand order, three products (outproj_split2.hip, whose sums these are); an operand is two
-// kilobytes, a k-step three MFMAs, and a word has a factor beside its constant.  A row's two terms fit the registers up to Hp = 320; the
+// kilobytes, a k-step three MFMAs, and a word has a factor beside its constant.  A row's two terms fit 256 registers up to Hp = 320, and 512 up to
+// Hp = 576, with four waves and 128 rows per workgroup; a block of weights then comes in two chunks, so that three are on their way.  The
 // tiles of outproj_split2.hip, which take rows through LDS too, had two k-steps of 16 units on their way and a barrier for each.  Us per
 // launch, tiles / this: V = 20000, H = 256, 100 rows 10.2 / 7.8, 256 12.7 / 11.3, 300 13.8 / 13.9, 2000 58.6 / 49.6; V = 100000, H = 256, 128 rows
-// 34.2 / 22.6, 1024 135 / 113 (running maximum 139 / 115); H = 128, 80 rows 19.9 / 12.7, 500 43.8 / 35.2; V = 60000, H = 192, 200 rows 20.2 /
-// 18.0, 1500 93.5 / 78.8; V = 50000, H = 300, 128 rows 22.4 / 17.0, 1024 94.5 / 71.9; V = 1000, H = 200, 200 rows 9.4 / 5.8.  Up to 64 rows, known on the
+// 34.2 / 22.6, 1024 136 / 113 (running maximum 139 / 115); H = 128, 80 rows 19.9 / 12.7, 500 43.8 / 35.2; V = 60000, H = 192, 200 rows 20.2 /
+// 18.0, 1500 93.5 / 78.8; V = 50000, H = 300, 128 rows 22.4 / 17.0, 1024 94.5 / 71.9; V = 1000, H = 200, 200 rows 9.4 / 5.8;
+// V = 65536, H = 512, 100 rows 36.0 / 28.2, 300 75 / 60, 1024 162.9 / 158.7; V = 20000, H = 512, 256 rows 21.6 / 18.9; V = 100000, H = 384, 700 155 / 134;
+// V = 60000, H = 448, 4000 566 / 499; V = 50000, H = 570, 300 63 / 53; V = 3000, H = 512, 1000 17.7 / 12.6.  Beyond 576 registers spill.  Up to 64 rows, known on the
 // device only, the streaming body has eight waves here, four there: V = 20000, H = 256, 32 rows 5.1 / 5.4, 64 6.8 / 7.3; V = 50000, H = 300, 50
-// rows 17.7 / 14.7; V = 3000, H = 128, 32 rows 3.9 / 3.7.
+// rows 17.7 / 14.7; V = 3000, H = 128, 32 rows 3.9 / 3.7;
+// V = 65536, H = 512, 32 rows 23.9 / 23.8, 64 31.4 / 26.0; V = 20000, H = 512, 20 rows 9.3 / 9.5.
 //
 // When the batch turns out to hold at most 64 rows (the count may be known on the device only),
 // the kernel runs the weight-streaming body instead (outproj_stream_body.h): see the top of
@@ -77,8 +81,7 @@ namespace rnnlm {
 
 namespace {
 
-constexpr int kThreads = 512;
-constexpr int kStagedF32Hp = 320;               // largest padded hidden size of fp32 models whose rows' two terms fit the registers
+constexpr int kStagedF32Hp = 576;               // largest padded hidden size of fp32 models whose rows' two terms fit the registers
 constexpr int kCSlots = 8;                       // ring of per-block constants (32 floats each; fp32 models: and 32 factors)
 
 // T: type of the weights.  An operand of one k-step (32 words or rows x 16 units) is a kilobyte of bf16, or two of fp16: the two terms.
@@ -87,18 +90,22 @@ struct StagedCfg {
     static constexpr int kTerms = sizeof(T) / 2;
     using Operand = std::conditional_t<kTerms == 1, bf16x8, f16x8>;
     static constexpr int KS = HP / 16;                       // MFMA k-steps per block
+    // A block's weights go through LDS in chunks of KC k-steps: one, or two where a wave needs the registers of two for its rows, so that
+    // a workgroup has four waves and 128 rows.
+    static constexpr int kChunks = kTerms == 2 && HP > 320 ? 2 : 1, KC = KS / kChunks;
+    static constexpr int kWaves = kChunks == 1 ? 8 : 4, kThreads = 64 * kWaves, kRows = 32 * kWaves;
     static constexpr bool kRowOrder = kTerms == 1 && HP % 128 == 0 && HP <= 512;       // weights from Ot, else from Ofrag
     static constexpr bool kScaledD = kTerms == 1 && staged_scaled_d(HP);
     static constexpr bool kHalves = kTerms == 1 && HP > 512;            // groups of 128 rows where they pay (staged_split)
     static constexpr int CPR = HP / 8;                                  // 16-byte chunks per word row
-    static constexpr int kStages = kTerms * HP <= 512 ? 4 : 3;         // as LDS allows
+    static constexpr int kStages = kTerms * HP / kChunks <= (kChunks == 1 ? 512 : 576) ? 4 : 3;      // as LDS allows
     static constexpr int kPrefetch = 4 / kTerms;                        // A operands read this many k-steps ahead
-    static constexpr int kLoadsPerThread = (kTerms * KS + 7) / 8;       // weight loads per block: 8 KB each
-    static constexpr int kStageBytes = kLoadsPerThread * 8192;
-    static constexpr int kLoadsPerBlock = kLoadsPerThread + kTerms;     // + one for the constants (+ one for the factors)
+    static constexpr int kLoadsPerThread = (kTerms * KC + kWaves - 1) / kWaves;      // weight loads per chunk: a kilobyte per wave each
+    static constexpr int kStageBytes = kLoadsPerThread * kWaves * 1024;
+    static constexpr int kLoadsPerChunk = kLoadsPerThread + kTerms;     // + one for the constants (+ one for the factors)
     static constexpr int kSlotBytes = kTerms * kStagedWords * 4;
     static constexpr int kLdsBytes = kStages * kStageBytes + kCSlots * kSlotBytes;
-    static_assert(HP % 64 == 0 && KS >= 8, "");
+    static_assert(HP % 64 == 0 && KC >= 8 && (kChunks == 1 || kTerms * KC % kWaves == 0), "");
     static_assert(kLdsBytes <= 160 * 1024, "");
 };
 // Do the logits start from their constants?  Fixed offset, and no factor per word.
@@ -121,7 +128,7 @@ struct Loader {
         if constexpr (C::kRowOrder) {
 #pragma unroll
             for (int q = 0; q < C::kLoadsPerThread; ++q) {
-                const int f = q * kThreads + tid;            // physical chunk this lane fills
+                const int f = q * C::kThreads + tid;            // physical chunk this lane fills
                 const int r = f / C::CPR, p = f % C::CPR;
                 const int c = p ^ (r & 15);                  // logical chunk that belongs there
                 voff[q] = (uint32_t)(r * HP * 2 + c * 16);
@@ -131,36 +138,39 @@ struct Loader {
         }
     }
     // (a block is 64 HP bytes in either order, times the terms)
-    __device__ __forceinline__ const char *block_of(int block) const {
-        return weights + (size_t)block * (64 * HP * C::kTerms);
+    __device__ __forceinline__ const char *chunk_of(int chunk) const {
+        return weights + (size_t)chunk * (64 * HP * C::kTerms / C::kChunks);
     }
     // The loads of a 32-word block into a stage and a slot of constants, in pieces and without branches (the block body is one
     // basic block): weight load q of the block, and its constants.  real = false turns the load into a dummy
     // that counts like a real one for vmcnt but fetches the first bytes of the weights (always
     // there, one cache line for the whole wave) into the same, free, LDS stage.
     __device__ __forceinline__ void issue_weights(const char *src, int q, bool real, uint32_t stage_lds) const {
-        const uint32_t to = stage_lds + (q * 8 + wave) * 1024;
+        const uint32_t to = stage_lds + (q * C::kWaves + wave) * 1024;
         if constexpr (C::kRowOrder) {
             lds_dma_16(src, real ? voff[q] : 0u, to);
         } else {
-            const bool mine = real && (C::kTerms * HP % 128 == 0 || q + 1 < C::kLoadsPerThread || wave < 4);
-            lds_dma_16(mine ? src + (q * 8 + wave) * 1024 : src, mine ? voff[0] : 0u, to);
+            const bool mine = real && (C::kTerms * C::KC % C::kWaves == 0 || q + 1 < C::kLoadsPerThread || wave < 4);
+            lds_dma_16(mine ? src + (q * C::kWaves + wave) * 1024 : src, mine ? voff[0] : 0u, to);
         }
     }
-    // (0: the constants of the block's words, 1: their factors)
+    // (0: the constants of the chunk's words, 1: their factors; 128 bytes, from one or two lanes of each wave)
     template <int WHICH>
-    __device__ __forceinline__ void issue_words(int block, uint32_t cslot_lds) const {
-        lds_dma_16_lane0((WHICH ? factors : cvec) + (size_t)block * kStagedWords, wave * 16, cslot_lds + WHICH * (kStagedWords * 4) + wave * 16);
+    __device__ __forceinline__ void issue_words(int chunk, uint32_t cslot_lds) const {
+        const float *src = (WHICH ? factors : cvec) + (size_t)(chunk / C::kChunks) * kStagedWords;
+        const uint32_t to = cslot_lds + WHICH * (kStagedWords * 4) + wave * (128 / C::kWaves);
+        if constexpr (C::kWaves == 8) lds_dma_16_lane0(src, wave * 16, to);
+        else lds_dma_16_lanes01(src, wave * 32 + voff[0], to);
     }
-    __device__ __forceinline__ void issue_consts(int block, uint32_t cslot_lds) const {
-        issue_words<0>(block, cslot_lds);
-        if constexpr (C::kTerms == 2) issue_words<1>(block, cslot_lds);
+    __device__ __forceinline__ void issue_consts(int chunk, uint32_t cslot_lds) const {
+        issue_words<0>(chunk, cslot_lds);
+        if constexpr (C::kTerms == 2) issue_words<1>(chunk, cslot_lds);
     }
-    __device__ __forceinline__ void issue_all(int block, uint32_t stage_lds, uint32_t cslot_lds) const {
-        const char *src = block_of(block);
+    __device__ __forceinline__ void issue_all(int chunk, uint32_t stage_lds, uint32_t cslot_lds) const {
+        const char *src = chunk_of(chunk);
 #pragma unroll
         for (int q = 0; q < C::kLoadsPerThread; ++q) issue_weights(src, q, true, stage_lds);
-        issue_consts(block, cslot_lds);
+        issue_consts(chunk, cslot_lds);
     }
 };
 
@@ -242,6 +252,14 @@ __device__ __forceinline__ void load_d_operand_at(Operand (&dst)[TERMS], const b
     });
 }
 
+// In which k-steps of a chunk's second half its NW weight loads of the chunk kStages - 1 ahead are issued: evenly apart, several in
+// one only if there are more loads than k-steps.
+template <int KS, int NW>
+struct LoadSchedule {
+    static constexpr int HALF = KS / 2, kApart = (HALF - 2) / NW;
+    static constexpr int at(int q) { return HALF + 1 + (kApart ? q * kApart : q * (KS - HALF - 2) / NW); }
+};
+
 // What block 0 of an item issues besides its own work (staged_block<HP, FIXED, true>): the part of
 // d that the prologue has not requested, and blocks 1 and 2.  All loads of a wave are issued in
 // one fixed program order, so the number of loads younger than any given one is a compile-time
@@ -249,11 +267,10 @@ __device__ __forceinline__ void load_d_operand_at(Operand (&dst)[TERMS], const b
 template <typename T, int HP>
 struct FirstBlockSchedule {
     using C = StagedCfg<T, HP>;
-    static constexpr int KS = C::KS, HALF = KS / 2, L = C::kLoadsPerBlock, NW = C::kLoadsPerThread, TERMS = C::kTerms;
-    static constexpr int kLoadStep = (HALF - 2) / NW;
+    static constexpr int KS = C::KS, HALF = KS / 2, L = C::kLoadsPerChunk, NW = C::kLoadsPerThread, TERMS = C::kTerms;
     static constexpr int D0 = 8 / TERMS;                       // operands of d requested by the prologue
     static constexpr int kAhead = C::kStages - 2;              // blocks requested in the first half of block 0: 1 and, with four stages, 2
-    static_assert(kAhead * L <= HALF * TERMS, "");
+    static_assert(C::kChunks > 1 || kAhead * L <= HALF * TERMS, "");
     // loads issued in k-step k: before its MFMAs an operand of d (e1) and as many loads of block 1 or 2 (e2),
     // after them the regular loads of the block behind them (e3)
     static constexpr int e1(int k) { return k + D0 < KS ? TERMS : 0; }
@@ -264,7 +281,7 @@ struct FirstBlockSchedule {
     static constexpr int e3(int k) {
         int n = (k == KS - 2) ? TERMS : 0;                     // (constants and factors)
         for (int q = 0; q < NW; ++q)
-            if (k == HALF + 1 + q * kLoadStep) ++n;
+            if (k == LoadSchedule<KS, NW>::at(q)) ++n;
         return n;
     }
     // loads younger than operand ks of d when the MFMA of k-step ks is about to be issued
@@ -296,7 +313,7 @@ struct FirstBlockSchedule {
             if (younger_than_d(ks) > w) w = younger_than_d(ks);
         return w;
     }
-    static_assert(worst() < 64, "vmcnt is a 6-bit counter");
+    static_assert(C::kChunks > 1 || worst() < 64, "vmcnt is a 6-bit counter");
 };
 // The operands a wave holds: its rows of d for the whole reduction length, and the words' next ones.
 template <typename T, int HP>
@@ -350,17 +367,18 @@ struct RunningLse {
 // k-steps ahead of its use, and blocks 1 and 2 load by load in the first half.  Every MFMA waits
 // for ITS operand of d alone, and the barrier for block 1 alone (FirstBlockSchedule has the
 // counts): the chain runs at the pace at which d arrives instead of starting after all of it.
-template <typename T, int HP, bool FIXED, bool FIRST>
+template <typename T, int HP, bool FIXED, bool FIRST, int CHUNK = 0>
 __device__ __forceinline__ void staged_block(const char *lds, const char *cring, uint32_t lds0, uint32_t cring0,
                                              const Loader<T, HP> &loader, int blk0, int nblk, int bi,
                                              const FragOffsets<T, HP> &aoff, StagedOperands<T, HP> &op, int g, f32x16 &acc,
                                              f32x16 &other, RunningLse &lse, const FirstBlockLoads &first) {
     using C = StagedCfg<T, HP>;
     using F = FirstBlockSchedule<T, HP>;
-    constexpr int KS = C::KS, HALF = KS / 2, NW = C::kLoadsPerThread, kPrefetch = C::kPrefetch, TERMS = C::kTerms;
+    constexpr int KS = C::KC, HALF = KS / 2, NW = C::kLoadsPerThread, kPrefetch = C::kPrefetch, TERMS = C::kTerms;
     constexpr bool kAtConstants = kStartsAtConstants<T, FIXED>;
-    constexpr int kLoadStep = (HALF - 2) / NW;                 // k-steps between two weight loads
-    static_assert(KS >= 2 * kPrefetch && kLoadStep >= 1 && HALF + 1 + (NW - 1) * kLoadStep <= KS - 2, "");
+    using W = LoadSchedule<KS, NW>;
+    constexpr bool kLoadsRows = FIRST && C::kChunks == 1;
+    static_assert(KS >= 2 * kPrefetch && W::at(NW - 1) <= KS - 2, "");
     constexpr int NS = C::kStages;
     const char *stage = lds + bi % NS * C::kStageBytes;
     const char *next_stage = lds + ((bi + 1 < nblk) ? bi + 1 : bi) % NS * C::kStageBytes;
@@ -370,15 +388,15 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
     f32x4 c4[4], f4[4];                                        // (those of the previous block: one or two of them in use at a time)
     const bool real = bi + NS - 1 < nblk;
     const int block3 = real ? blk0 + bi + NS - 1 : 0;
-    const char *src3 = loader.block_of(block3);
+    const char *src3 = loader.chunk_of(block3);
     const uint32_t stage3 = lds0 + (bi + NS - 1) % NS * C::kStageBytes, cslot3 = cring0 + ((bi + NS - 1) & 7) * C::kSlotBytes;
     // the k-steps as a compile-time loop: every condition below is a constant, and so are the vmcnt
     // immediates
     static_for<0, KS>([&](auto step) __attribute__((always_inline)) {
         constexpr int ks = decltype(step)::value;
         if constexpr (ks == HALF) {
-            if constexpr (FIRST) wait_vmcnt<F::younger_than_block1()>();
-            else wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();
+            if constexpr (kLoadsRows) wait_vmcnt<F::younger_than_block1()>();
+            else wait_vmcnt<(NS - 3) * C::kLoadsPerChunk>();
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
@@ -388,7 +406,7 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
         for (int t = 0; t < TERMS; ++t) cur[t] = op.a[ks % kPrefetch][t];
         if constexpr (ks + kPrefetch < KS) aoff.read(stage, ks + kPrefetch, op.a[ks % kPrefetch]);
         else aoff.read(next_stage, ks + kPrefetch - KS, op.a[ks % kPrefetch]);
-        if constexpr (FIRST) {
+        if constexpr (kLoadsRows) {
             if constexpr (ks + F::D0 < KS) load_d_operand_at<ks + F::D0>(op.d[ks + F::D0], first.dfr);
             static_for<ks * TERMS, ks * TERMS + F::e2(ks)>([&](auto load) __attribute__((always_inline)) {
                 constexpr int b = decltype(load)::value / F::L, q = decltype(load)::value % F::L;
@@ -400,16 +418,16 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
         if constexpr (TERMS == 1) {
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur[0], op.d[ks][0], acc, 0, 0, 0);
         } else {                                               // smallest cross terms first
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[1], op.d[ks][0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[0], op.d[ks][1], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[0], op.d[ks][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[1], op.d[CHUNK * KS + ks][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[0], op.d[CHUNK * KS + ks][1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(cur[0], op.d[CHUNK * KS + ks][0], acc, 0, 0, 0);
         }
-        if constexpr (!FIRST && kAtConstants) {
+        if constexpr (!FIRST && CHUNK == 0 && kAtConstants) {
             // the previous block's sixteen logits, over k-steps 1 .. HALF
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 if (1 + (e * HALF) / 16 == ks) lse.s += fast_exp2(base2<C::kScaledD>(other[e]));
-        } else if constexpr (!FIRST) {
+        } else if constexpr (!FIRST && CHUNK == 0) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 if (ks == R::logits(q)) {
@@ -439,14 +457,14 @@ __device__ __forceinline__ void staged_block(const char *lds, const char *cring,
                 }
             if constexpr (!FIXED && ks == KS - 1) lse.s += lse.terms;
         }
-        if constexpr (!kAtConstants && ks == KS - 1) {
+        if constexpr (!kAtConstants && CHUNK == 0 && ks == KS - 1) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) other[i] = 0.f;
         }
         // second half: loads of block bi+3, with the fixed offset the constants of block bi+1 into the resting accumulators
 #pragma unroll
         for (int q = 0; q < NW; ++q)
-            if (ks == HALF + 1 + q * kLoadStep) loader.issue_weights(src3, q, real, stage3);
+            if (ks == W::at(q)) loader.issue_weights(src3, q, real, stage3);
         if constexpr (ks == KS - 2) loader.issue_consts(block3, cslot3);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -493,25 +511,44 @@ __device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *
     // Block 0 and the first operands of this wave's rows of d (all k of 32 rows are MFMA B operands
     // held in registers; rows beyond B hold stale scratch: rows are independent and those lanes'
     // results are dropped).  The rest of d and blocks 1 and 2 are requested by block 0 itself.
-    using F = FirstBlockSchedule<T, HP>;
-    loader.issue_all(blk0, lds0, cring0);
     StagedOperands<T, HP> op;
     FirstBlockLoads first;
-    // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row, a term behind the other
-    first.dfr = static_cast<const bf16_t *>(m.dfrag) + ((size_t)(row0 / 32 + wave) * KS * C::kTerms * 64 + lane) * 8;
-    static_for<0, F::D0>([&](auto j) __attribute__((always_inline)) {
-        load_d_operand_at<decltype(j)::value>(op.d[decltype(j)::value], first.dfr);
-    });
+    if constexpr (C::kChunks == 1) {
+        using F = FirstBlockSchedule<T, HP>;
+        loader.issue_all(blk0, lds0, cring0);
+        // fragment (row block, ks) of the fragment-ordered copy: 64 lanes x 16 bytes in a row, a term behind the other
+        first.dfr = static_cast<const bf16_t *>(m.dfrag) + ((size_t)(row0 / 32 + wave) * KS * C::kTerms * 64 + lane) * 8;
+        static_for<0, F::D0>([&](auto j) __attribute__((always_inline)) {
+            load_d_operand_at<decltype(j)::value>(op.d[decltype(j)::value], first.dfr);
+        });
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        first.real[i] = i + 1 < nblk;
-        first.block[i] = first.real[i] ? blk0 + i + 1 : 0;
-        first.blk[i] = loader.block_of(first.block[i]);
-        first.stage[i] = lds0 + (i + 1) % C::kStages * C::kStageBytes;
-        first.cslot[i] = cring0 + (i + 1) * C::kSlotBytes;
+        for (int i = 0; i < 2; ++i) {
+            first.real[i] = i + 1 < nblk;
+            first.block[i] = first.real[i] ? blk0 + i + 1 : 0;
+            first.blk[i] = loader.chunk_of(first.block[i]);
+            first.stage[i] = lds0 + (i + 1) % C::kStages * C::kStageBytes;
+            first.cslot[i] = cring0 + (i + 1) * C::kSlotBytes;
+        }
+        // Block 0 has landed once only the younger loads are outstanding: the first operands of d.
+        wait_vmcnt<F::D0 * C::kTerms>();
+    } else {
+        // the first chunks, then the rows by loads the compiler sees, which may put them into either half of the 512 registers; the
+        // wait is one it sees as well, so that it adds none inside the loop
+#pragma unroll
+        for (int i = 0; i < C::kStages - 1; ++i) {
+            const int chunk = i < nblk ? blk0 + i : 0;
+            const char *src = loader.chunk_of(chunk);
+#pragma unroll
+            for (int q = 0; q < C::kLoadsPerThread; ++q) loader.issue_weights(src, q, i < nblk, lds0 + i * C::kStageBytes);
+            loader.issue_consts(chunk, cring0 + i * C::kSlotBytes);
+        }
+        const auto *dfr = static_cast<const typename C::Operand *>(m.dfrag) + (size_t)(row0 / 32 + wave) * KS * C::kTerms * 64 + lane;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int t = 0; t < C::kTerms; ++t) op.d[ks][t] = dfr[(ks * C::kTerms + t) * 64];
+        __builtin_amdgcn_s_waitcnt(0x0f70);                   // vmcnt(0)
     }
-    // Block 0 has landed once only the younger loads are outstanding: the first operands of d.
-    wait_vmcnt<F::D0 * C::kTerms>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();                             // block 0 is published
     asm volatile("" ::: "memory");
@@ -531,21 +568,25 @@ __device__ __forceinline__ void staged_item(const ModelDev &m, char *lds, char *
     }
     lse.m = -INFINITY;
     lse.s = 0.f;
-#define RNNLM_BLOCK(FIRST, BI, ACC, OTHER) \
-    staged_block<T, HP, FIXED, FIRST>(lds, cring, lds0, cring0, loader, blk0, nblk, BI, aoff, op, g, ACC, OTHER, lse, first)
-    RNNLM_BLOCK(true, 0, acc0, acc1);
+    auto block = [&](auto first_block, int bi, f32x16 &acc, f32x16 &other) __attribute__((always_inline)) {
+        static_for<0, C::kChunks>([&](auto chunk) __attribute__((always_inline)) {
+            constexpr int c = decltype(chunk)::value;
+            staged_block<T, HP, FIXED, decltype(first_block)::value, c>(lds, cring, lds0, cring0, loader, blk0, nblk, C::kChunks * bi + c, aoff, op, g, acc, other, lse, first);
+        });
+    };
+    const int blocks = nblk / C::kChunks;
+    block(std::true_type{}, 0, acc0, acc1);
     int bi = 1;
-    for (; bi + 1 < nblk; bi += 2) {
-        RNNLM_BLOCK(false, bi, acc1, acc0);
-        RNNLM_BLOCK(false, bi + 1, acc0, acc1);
+    for (; bi + 1 < blocks; bi += 2) {
+        block(std::false_type{}, bi, acc1, acc0);
+        block(std::false_type{}, bi + 1, acc0, acc1);
     }
-    if (bi < nblk) {
-        RNNLM_BLOCK(false, bi, acc1, acc0);
+    if (bi < blocks) {
+        block(std::false_type{}, bi, acc1, acc0);
         fold_last_block<T, HP, FIXED>(acc1, cring, nblk - 1, g, lse);
     } else {
         fold_last_block<T, HP, FIXED>(acc0, cring, nblk - 1, g, lse);
     }
-#undef RNNLM_BLOCK
     // dummy loads may still be in flight into stages the next item fills first
     wait_vmcnt<0>();
 }
@@ -560,7 +601,7 @@ __device__ __forceinline__ void staged_item_loads(uint32_t lds0, uint32_t cring0
     auto issue = [&](int bi) __attribute__((always_inline)) {            // always as many loads
         const bool real = bi < nblk;
         const int block = real ? blk0 + bi : 0;
-        const char *src = loader.block_of(block);
+        const char *src = loader.chunk_of(block);
 #pragma unroll
         for (int q = 0; q < C::kLoadsPerThread; ++q) loader.issue_weights(src, q, real, lds0 + bi % NS * C::kStageBytes);
         loader.issue_consts(block, cring0 + (bi & 7) * C::kSlotBytes);
@@ -573,7 +614,7 @@ __device__ __forceinline__ void staged_item_loads(uint32_t lds0, uint32_t cring0
 #pragma unroll
     for (int i = 1; i < NS - 1; ++i) issue(i);
     for (int bi = 0; bi < nblk; ++bi) {
-        wait_vmcnt<(NS - 3) * C::kLoadsPerBlock>();                      // block bi + 1 has landed
+        wait_vmcnt<(NS - 3) * C::kLoadsPerChunk>();                      // block bi + 1 has landed
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -594,12 +635,12 @@ __device__ __forceinline__ void staged_kernel(const ModelDev &m, int rows, const
     // are left): the time is then the time to read the weights once, and the workgroup streams
     // them instead.  Same grid, and the same partials come out: with one row group the vocabulary
     // is cut into as many splits as there are workgroups, split = workgroup index.
-    static_assert(kThreads == kStreamThreads, "");
-    static_assert(C::kLdsBytes >= C::kTerms * 2 * KS * 1024 + kStreamWaves * 64 * 8, "LDS for two row blocks of the streaming form");
-    if (B <= 64 && m.Ofrag && (int)gridDim.x == staged_plan(B, wg_per_xcd).S) {
+    constexpr bool kTwoBlocks = C::kLdsBytes >= C::kTerms * 2 * KS * 1024 + C::kWaves * 64 * 8;      // LDS for two row blocks of the streaming form
+    static_assert(kTwoBlocks || C::kChunks == 2, "");
+    if (B <= (kTwoBlocks ? 64 : 32) && m.Ofrag && (int)gridDim.x == staged_plan(B, wg_per_xcd).S) {
         if constexpr (C::kTerms == 2) {
-            if (B <= 32) outproj_stream_f32_body<1, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-            else outproj_stream_f32_body<2, FIXED>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            if (!kTwoBlocks || B <= 32) outproj_stream_f32_body<1, FIXED, C::kWaves>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            else outproj_stream_f32_body<2, FIXED, C::kWaves>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
         } else {
             if (B <= 32) outproj_stream_body<1, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
             else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
@@ -609,7 +650,7 @@ __device__ __forceinline__ void staged_kernel(const ModelDev &m, int rows, const
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5;
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
     const int blocks = m.Vp / kStagedWords;                  // 32-word blocks in the vocabulary
-    const StagedSplit split_of = staged_split(B, wg_per_xcd, C::kHalves);
+    const StagedSplit split_of = C::kRows == kStagedRows ? staged_split(B, wg_per_xcd, C::kHalves) : StagedSplit{plan_rounds(B, C::kRows, wg_per_xcd, m.Vp), C::kRows};
     const StagedPlan plan = split_of.plan;
     const int items = plan.RG * plan.Sx;
     const uint32_t lds0 = lds_address(lds), cring0 = lds_address(cring);
@@ -623,8 +664,8 @@ __device__ __forceinline__ void staged_kernel(const ModelDev &m, int rows, const
 
     for (int item = local; item < items; item += wg_per_xcd) {
         const int rg = item % plan.RG, split = xcd + kXcds * (item / plan.RG);
-        const int blk0 = part_begin(split, blocks, plan.S);
-        const int nblk = part_begin(split + 1, blocks, plan.S) - blk0;
+        const int blk0 = part_begin(split, blocks, plan.S) * C::kChunks;               // (in chunks, from here on)
+        const int nblk = part_begin(split + 1, blocks, plan.S) * C::kChunks - blk0;
         const int row0 = rg * split_of.rows;
         const bool has_rows = (int)loader.wave * 32 < min(split_of.rows, B - row0);       // (wave-uniform)
         if (!has_rows) {
@@ -652,12 +693,12 @@ __device__ __forceinline__ void staged_kernel(const ModelDev &m, int rows, const
 }
 
 template <int HP, bool FIXED>
-__global__ __launch_bounds__(kThreads) void outproj_staged_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
+__global__ __launch_bounds__((StagedCfg<bf16_t, HP>::kThreads)) void outproj_staged_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
     staged_kernel<bf16_t, HP, FIXED>(m, rows, B_dev, wg_per_xcd);
 }
 // (the two-term form of fp32 models goes by one name, whether the rows come through LDS or sit in registers)
 template <int HP, bool FIXED>
-__global__ __launch_bounds__(kThreads) void outproj_split2_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
+__global__ __launch_bounds__((StagedCfg<float, HP>::kThreads)) void outproj_split2_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
     staged_kernel<float, HP, FIXED>(m, rows, B_dev, wg_per_xcd);
 }
 
@@ -668,7 +709,7 @@ hipError_t launch_hp(const ModelDev &m, int rows, const int *B_dev, bool fixed_o
     static LdsLimit limit[2];
     auto launch = [&](auto kernel, LdsLimit &l) -> hipError_t {
         if (hipError_t e = l.ensure(reinterpret_cast<const void *>(kernel), C::kLdsBytes); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(kXcds * wg_per_xcd), dim3(kThreads), C::kLdsBytes, stream, m, rows, B_dev, wg_per_xcd);
+        hipLaunchKernelGGL(kernel, dim3(kXcds * wg_per_xcd), dim3(C::kThreads), C::kLdsBytes, stream, m, rows, B_dev, wg_per_xcd);
         return hipGetLastError();
     };
     if constexpr (C::kTerms == 2)
@@ -690,11 +731,16 @@ hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, 
     const int wg_per_xcd = 32;
     *splits = SplitInfo{0, wg_per_xcd, m.Hp > 512 ? 0 : kStagedRows, kMaxSplits / kXcds, 0, 0};
     if (m.dtype != RNNLM_BF16) {
+        *splits = m.Hp > 320 ? SplitInfo{0, wg_per_xcd, -kStagedRows / 2, m.Vp, 0, 0} : SplitInfo{0, wg_per_xcd, kStagedRows, kMaxSplits / kXcds, 0, 0};
         switch (m.Hp) {
             case 128: return launch_hp<float, 128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
             case 192: return launch_hp<float, 192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
             case 256: return launch_hp<float, 256>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
             case 320: return launch_hp<float, 320>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 384: return launch_hp<float, 384>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 448: return launch_hp<float, 448>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 512: return launch_hp<float, 512>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
+            case 576: return launch_hp<float, 576>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
             default: return hipErrorInvalidValue;
         }
     }

@@ -225,6 +225,25 @@ typedef RowPlan StagedPlan;
 __host__ __device__ inline StagedPlan staged_plan(int B, int wg_per_xcd) {
     return plan_rows(B, kStagedRows, wg_per_xcd, kMaxSplits / kXcds);
 }
+// Groups of 128 rows that do not divide an XCD's workgroups leave some of them idle (12 groups: 24 of 32 busy): with up to three items per
+// workgroup one after the other the vocabulary is cut finer and fewer are.  A further item costs its rows' way into the registers, some 3 us, which is taken as
+// a tenth of the launch; vocabularies below 16384 words keep to one.  Us per launch, one item / this, fp32: V = 65536, H = 512, 1100 rows 181 / 177, 1300
+// 229 / 219, 1500 248 / 237; V = 20000, H = 512, 1300 78 / 77; V = 17000, H = 512, 2100 116 / 102; V = 50000, H = 576, 2600 383 / 345.  800 rows (7
+// groups, 28 of 32 busy) keep to one: V = 65536, H = 512 134.7 / 134.2, V = 20000 49.6 / 50.6.
+__host__ __device__ inline RowPlan plan_rounds(int B, int group_rows, int wg_per_xcd, int Vp) {
+    RowPlan p = plan_rows(B, group_rows, wg_per_xcd, kMaxSplits / kXcds);
+    if (p.RG < 5 || Vp < 16384) return p;
+    int best = 48 * p.RG * p.Sx / wg_per_xcd;                // busy 48ths
+    for (int r = 2; r <= 3; ++r) {
+        const int Sx = r * wg_per_xcd / p.RG, busy = 48 * p.RG * Sx / (r * wg_per_xcd) - 5 * (r - 1);
+        if (Sx <= kMaxSplits / kXcds && Sx > 0 && busy > best) {
+            best = busy;
+            p.Sx = Sx;
+        }
+    }
+    p.S = kXcds * p.Sx;
+    return p;
+}
 // The staged kernel's row groups: 256 rows.  Beyond Hp = 512, three groups of 128 (four of a workgroup's eight waves each, with a
 // matrix pipe to itself) where two of 256 would leave one less than half full.  Us per launch, 256 / 128, V = 30011, H = 650: 257, 300, 384
 // rows 17.4 / 16.3, 17.5 / 16.2, 18.8 / 17.1, running maximum 20.9 / 19.0, 21.1 / 18.6, 21.8 / 19.4.  Not for five groups instead of
@@ -247,13 +266,14 @@ struct SplitInfo {
     int fixed_splits;      // > 0: that many
     int wg_per_xcd;        // else plan_rows(B, group_rows, wg_per_xcd, sx_cap).S
     int group_rows;        // 0: staged_split(B, wg_per_xcd, true).plan.S
-    int sx_cap;
+    int sx_cap;            // group_rows < 0: plan_rounds(B, -group_rows, wg_per_xcd, sx_cap).S
     int stream_rows;       // 0 < B <= stream_rows: stream_splits instead (0: every workgroup of the grid has one)
     int stream_splits;
 };
 __host__ __device__ inline int splits_of(const SplitInfo &si, int B) {
     if (si.fixed_splits > 0) return si.fixed_splits;
     if (B > 0 && B <= si.stream_rows) return si.stream_splits > 0 ? si.stream_splits : kXcds * si.wg_per_xcd;
+    if (si.group_rows < 0) return plan_rounds(B, -si.group_rows, si.wg_per_xcd, si.sx_cap).S;
     if (si.group_rows == 0) return staged_split(B, si.wg_per_xcd, true).plan.S;
     return plan_rows(B, si.group_rows, si.wg_per_xcd, si.sx_cap).S;
 }

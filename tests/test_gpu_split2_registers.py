@@ -1,5 +1,5 @@
-"""Two-term fp32 output projection with the rows in registers (padded hidden sizes of 128 to 320), against the oracle and the
-form that takes rows through LDS: rows around its groups of 256 and 32, vocabularies that end inside a block, a stage and a split, words many powers of
+"""Two-term fp32 output projection with the rows in registers (padded hidden sizes of 128 to 576), against the oracle and the
+form that takes rows through LDS: rows around its groups of 256 (from 384 on 128) and 32, vocabularies that end inside a block, a stage and a split, words many powers of
 two apart, a maximum that moves from block to block, words of probability 0, row counts known on the device only."""
 import numpy as np
 import pytest
@@ -13,7 +13,8 @@ from test_gpu_split2 import model_of
 pytestmark = pytest.mark.gpu
 
 SIZES = [(3, 70, 65), (255, 128, 128), (16500, 100, 300), (8300, 190, 129), (33000, 150, 255), (700, 200, 257), (25000, 256, 140),
-         (1000, 256, 8300), (513, 257, 100), (12500, 320, 513), (41000, 300, 161)]
+         (1000, 256, 8300), (513, 257, 100), (12500, 320, 513), (41000, 300, 161), (16500, 350, 300), (8300, 448, 129), (25000, 512, 140), (700, 500, 257), (300, 512, 8300),
+         (33000, 570, 65), (17000, 350, 1300), (16400, 450, 2100)]
 
 
 @pytest.mark.parametrize("V,H,B", SIZES)
@@ -49,7 +50,7 @@ def test_against_the_oracle_and_the_other_form(V, H, B):
 
 
 @pytest.mark.parametrize("shape", ["rising", "falling", "jumping"])
-@pytest.mark.parametrize("V,H,B", [(16500, 128, 130), (33000, 190, 200), (3000, 250, 257), (17000, 320, 300)])
+@pytest.mark.parametrize("V,H,B", [(16500, 128, 130), (33000, 190, 200), (3000, 250, 257), (17000, 320, 300), (9000, 500, 200)])
 def test_maximum_moves_between_blocks(V, H, B, shape):
     rng = np.random.default_rng(H * 1009 + V)
     model = {"U": rng.normal(0, 0.3, (V, H)), "W": rng.normal(0, 1 / np.sqrt(H), (H, H)), "O": rng.normal(0, 2 / np.sqrt(H), (H, V))}
