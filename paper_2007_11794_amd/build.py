@@ -29,9 +29,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 
 # These kernels' loops begin at a fetch line.  Staged: V = 60000, H = 128, 4096 rows 60.3 against 59.6 us.  Two-term: left where they fall, the same instructions took 158 to 173 us (V = 65536,
 # H = 512, fp32, 1024 rows) and 32.6 to 34.3 (V = 8000, H = 1200, 40 rows), depending on what stands in front of them.
+# Streaming: V = 1000000, H = 128, 10 rows 39.3 against 38.5 us.
 # Staged: sums of matrix products stay in VGPRs in the kernels that may use 512 registers; in AGPRs each was copied out and
 # back (fp32, 64 rows known on the device only: V = 65536, H = 512 27.2 against 26.0 us, V = 50000, H = 384, 50 rows 19.0 against 17.2).
-FILE_FLAGS = {"outproj_split2.hip": ["-falign-loops=64"], "outproj_staged.hip": ["-falign-loops=64", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+FILE_FLAGS = {"outproj_stream.hip": ["-falign-loops=64"], "outproj_split2.hip": ["-falign-loops=64"], "outproj_staged.hip": ["-falign-loops=64", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def flags_of(src: str) -> list:
