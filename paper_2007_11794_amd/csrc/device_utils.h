@@ -223,13 +223,15 @@ __device__ __forceinline__ void seen_by_all() { asm volatile("s_waitcnt vmcnt(0)
 
 // 64-bit key -> 32 mixed bits for the hash tables of history ids: the high word, multiplied and folded, added to the low one, then
 // a round of folding and multiplying.  Two 32-bit products, which take four slots of a SIMD each: one workgroup that hashes
-// 4096 ids issues little else (a 64-bit finaliser has eight of them, and shifts of 64 bits).
-__device__ __forceinline__ uint32_t id_hash(uint64_t k) {
+// 4096 ids issues little else (a 64-bit finaliser has eight of them, and shifts of 64 bits).  Three different shifts: folded twice by 16, a
+// high word with no low one beside it was itself again, and 4000 ids in their top 19 bits made a chain of 1290 probes in LDS (now 8).
+// On counters at any bit, pairs of counters, floating-point numbers and addresses chains are as long as with the finaliser.
+__host__ __device__ __forceinline__ uint32_t id_hash(uint64_t k) {
     uint32_t x = (uint32_t)(k >> 32) * 0x9E3779B1u;
-    x = (uint32_t)k + (x ^ (x >> 16));
-    x ^= x >> 16;
+    x = (uint32_t)k + (x ^ (x >> 12));
+    x ^= x >> 14;
     x *= 0x7FEB352Du;
-    return x ^ (x >> 15);
+    return x ^ (x >> 16);
 }
 
 // splitmix64 finaliser: 64 well-mixed bits
