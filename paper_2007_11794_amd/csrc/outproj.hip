@@ -281,7 +281,8 @@ WeightsAhead outproj_weights_ahead(const ModelDev &m, int rows, bool fixed_offse
         const F32Kernel k = choose_f32(m, rows, kernel_choice);
         a.block_kb *= 2;
         if (k == kF32Split2) a.waves = 4;
-        else if (k != kF32Stream && k != kF32Staged) a.splits = 0;
+        else if (k == kF32Staged) a.waves = staged_waves(true, m.Hp);
+        else if (k != kF32Stream) a.splits = 0;
     }
     return a;
 }

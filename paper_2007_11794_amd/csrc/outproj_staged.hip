@@ -92,8 +92,8 @@ struct StagedCfg {
     static constexpr int KS = HP / 16;                       // MFMA k-steps per block
     // A block's weights go through LDS in chunks of KC k-steps: one, or two where a wave needs the registers of two for its rows, so that
     // a workgroup has four waves and 128 rows.
-    static constexpr int kChunks = kTerms == 2 && HP > 320 ? 2 : 1, KC = KS / kChunks;
-    static constexpr int kWaves = kChunks == 1 ? 8 : 4, kThreads = 64 * kWaves, kRows = 32 * kWaves;
+    static constexpr int kWaves = staged_waves(kTerms == 2, HP), kChunks = 8 / kWaves, KC = KS / kChunks;
+    static constexpr int kThreads = 64 * kWaves, kRows = 32 * kWaves;
     static constexpr bool kRowOrder = kTerms == 1 && HP % 128 == 0 && HP <= 512;       // weights from Ot, else from Ofrag
     static constexpr bool kScaledD = kTerms == 1 && staged_scaled_d(HP);
     static constexpr bool kHalves = kTerms == 1 && HP > 512;            // groups of 128 rows where they pay (staged_split)
@@ -731,7 +731,7 @@ hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, 
     const int wg_per_xcd = 32;
     *splits = SplitInfo{0, wg_per_xcd, m.Hp > 512 ? 0 : kStagedRows, kMaxSplits / kXcds, 0, 0};
     if (m.dtype != RNNLM_BF16) {
-        *splits = m.Hp > 320 ? SplitInfo{0, wg_per_xcd, -kStagedRows / 2, m.Vp, 0, 0} : SplitInfo{0, wg_per_xcd, kStagedRows, kMaxSplits / kXcds, 0, 0};
+        *splits = staged_waves(true, m.Hp) == 4 ? SplitInfo{0, wg_per_xcd, -kStagedRows / 2, m.Vp, 0, 0} : SplitInfo{0, wg_per_xcd, kStagedRows, kMaxSplits / kXcds, 0, 0};
         switch (m.Hp) {
             case 128: return launch_hp<float, 128>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);
             case 192: return launch_hp<float, 192>(m, rows, B_dev, fixed_offset, wg_per_xcd, stream);

@@ -191,6 +191,8 @@ hipError_t launch_recur_whole(const ModelDev &m, int units, bool vec, int rows, 
 
 constexpr int kStagedRows = 256;   // rows per workgroup of the staged kernel
 constexpr int kStagedWords = 32;   // words per LDS stage
+// Waves of the staged kernel's workgroups, its streaming form included: four where a row's two terms take the registers of two waves.
+constexpr int staged_waves(bool f32, int Hp) { return f32 && Hp > 320 ? 4 : 8; }
 constexpr int kXcds = 8;           // workgroup id modulo 8 = the XCD (L2 domain) it runs on
 constexpr size_t kAllL2s = (size_t)kXcds * 4 << 20;
 

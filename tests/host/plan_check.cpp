@@ -63,8 +63,8 @@ int main() {
     const int blocks_of[] = {256, 257, 2047, 2048, 6250, 31250}, hp_of[] = {64, 128, 192, 512, 704, 1024};
     for (int blocks : blocks_of)
         for (int hp : hp_of)
-            for (int fp32 = 0; fp32 < 2; ++fp32) {
-                const WeightsAhead a = {nullptr, blocks, hp / 16 * (1 + fp32), kMaxSplits, fp32 ? 4 : 8};
+            for (int form = 0; form < 3; ++form) {               // bf16, fp32 with eight waves and with four
+                const WeightsAhead a = {nullptr, blocks, hp / 16 * (form ? 2 : 1), kMaxSplits, form == 2 ? 4 : 8};
                 for (int split : {0, 1, 100, 255}) {
                     const int b0 = part_begin(split, blocks, kMaxSplits), b1 = part_begin(split + 1, blocks, kMaxSplits);
                     const int rounds = (b1 - b0 + a.waves - 1) / a.waves, pieces = rounds * a.waves * (a.block_kb / 4);

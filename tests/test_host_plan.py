@@ -11,15 +11,26 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_work_split_arithmetic_on_the_host(tmp_path):
+def check_on_the_host(tmp_path, name, libraries=()):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not found")
-    exe = str(tmp_path / "plan_check")
+    exe = str(tmp_path / name)
     cmd = [hipcc, "--cuda-host-only", "-std=c++17", "-O1", "-x", "hip",
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_2007_11794_amd", "csrc"),
-           os.path.join(ROOT, "tests", "host", "plan_check.cpp"), "-o", exe]
+           os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe, "-x", "none"] + list(libraries)
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:] + r.stderr[-2000:]
+
+
+def test_work_split_arithmetic_on_the_host(tmp_path):
+    check_on_the_host(tmp_path, "plan_check")
+
+
+def test_weights_read_ahead_in_the_order_of_their_reader(tmp_path):
+    import paper_2007_11794_amd as rn
+    rn.lib()                                   # (there, or it says so)
+    folder, file = os.path.split(rn.lib_path())
+    check_on_the_host(tmp_path, "ahead_check", [rn.lib_path(), "-Wl,-rpath," + folder])
