@@ -232,14 +232,21 @@ __host__ __device__ inline StagedPlan staged_plan(int B, int wg_per_xcd) {
 // a tenth of the launch; vocabularies below 16384 words keep to one.  Us per launch, one item / this, fp32: V = 65536, H = 512, 1100 rows 181 / 177, 1300
 // 229 / 219, 1500 248 / 237; V = 20000, H = 512, 1300 78 / 77; V = 17000, H = 512, 2100 116 / 102; V = 50000, H = 576, 2600 383 / 345.  800 rows (7
 // groups, 28 of 32 busy) keep to one: V = 65536, H = 512 134.7 / 134.2, V = 20000 49.6 / 50.6.
+// Beyond 32 groups one item for every group and XCD takes two rounds by itself, and is counted as that: one split per XCD / this, V = 17000,
+// H = 512, 4200 rows 336 / 290, H = 384, 4600 247 / 211, V = 65536, H = 512, 4200 1096 / 908, 5200 1099 / 931, V = 40000, H = 576, 4100 776 / 642
+// (whole steps, us).
 __host__ __device__ inline RowPlan plan_rounds(int B, int group_rows, int wg_per_xcd, int Vp) {
     RowPlan p = plan_rows(B, group_rows, wg_per_xcd, kMaxSplits / kXcds);
     if (p.RG < 5 || Vp < 16384) return p;
-    int best = 48 * p.RG * p.Sx / wg_per_xcd;                // busy 48ths
+    auto busy_48ths = [&](int Sx) {                          // of the rounds that the items take
+        const int rounds = (p.RG * Sx + wg_per_xcd - 1) / wg_per_xcd;
+        return 48 * p.RG * Sx / (rounds * wg_per_xcd) - 5 * (rounds - 1);
+    };
+    int best = busy_48ths(p.Sx);
     for (int r = 2; r <= 3; ++r) {
-        const int Sx = r * wg_per_xcd / p.RG, busy = 48 * p.RG * Sx / (r * wg_per_xcd) - 5 * (r - 1);
-        if (Sx <= kMaxSplits / kXcds && Sx > 0 && busy > best) {
-            best = busy;
+        const int Sx = r * wg_per_xcd / p.RG;
+        if (Sx <= kMaxSplits / kXcds && Sx > 0 && busy_48ths(Sx) > best) {
+            best = busy_48ths(Sx);
             p.Sx = Sx;
         }
     }

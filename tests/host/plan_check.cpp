@@ -50,6 +50,23 @@ int main() {
         const StagedPlan p = staged_plan(B, 32);
         REQUIRE(p.RG == (B + kStagedRows - 1) / kStagedRows && p.S == kXcds * p.Sx, "staged B=%d", B);
     }
+    // the finer splits of groups of 128 rows: kernel and reader agree, partials fit, and no number of splits is better by the rule's own
+    // count (the busy part of the rounds that the items take, in 48ths, less five for every round behind the first) where it may choose
+    for (int Vp : {256, 16384 - 256, 16384, 65536, 1000192})
+        for (int B = 1; B <= 14000; ++B) {
+            const RowPlan p = plan_rounds(B, 128, 32, Vp), one = plan_rows(B, 128, 32, kMaxSplits / kXcds);
+            const SplitInfo si = {0, 32, -128, Vp, 0, 0};
+            REQUIRE(splits_of(si, B) == p.S && p.S == kXcds * p.Sx && p.Sx >= 1 && p.S <= kMaxSplits, "B=%d Vp=%d: S=%d, reader %d", B, Vp, p.S, splits_of(si, B));
+            REQUIRE(p.RG == one.RG, "B=%d Vp=%d: RG=%d", B, Vp, p.RG);
+            if (p.RG < 5 || Vp < 16384) {
+                REQUIRE(p.Sx == one.Sx, "B=%d Vp=%d: Sx=%d", B, Vp, p.Sx);
+                continue;
+            }
+            auto rounds = [&](int Sx) { return (p.RG * Sx + 31) / 32; };
+            auto busy = [&](int Sx) { return 48 * p.RG * Sx / (32 * rounds(Sx)) - 5 * (rounds(Sx) - 1); };
+            for (int Sx = 1; Sx <= kMaxSplits / kXcds && rounds(Sx) <= 3; ++Sx)
+                REQUIRE(busy(p.Sx) >= busy(Sx), "B=%d Vp=%d: Sx=%d keeps %d of 48 busy, Sx=%d %d", B, Vp, p.Sx, busy(p.Sx), Sx, busy(Sx));
+        }
     // cutting `units` blocks into `parts` splits: the 32-bit form equals floor(index * units / parts)
     const int units_of[] = {1, 7, 63, 64, 255, 256, 257, 2048, 6250, 31251, 1 << 20, (1 << 25) + 3, 0x7FFFFFFF};
     for (int units : units_of)
