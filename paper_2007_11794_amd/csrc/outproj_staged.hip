@@ -634,16 +634,15 @@ __device__ __forceinline__ void staged_kernel(const ModelDev &m, int rows, const
     // Few rows after all (after the grouping or the cache lookup only the device knows how many
     // are left): the time is then the time to read the weights once, and the workgroup streams
     // them instead.  Same grid, and the same partials come out: with one row group the vocabulary
-    // is cut into as many splits as there are workgroups, split = workgroup index.
-    constexpr bool kTwoBlocks = C::kLdsBytes >= C::kTerms * 2 * KS * 1024 + C::kWaves * 64 * 8;      // LDS for two row blocks of the streaming form
-    static_assert(kTwoBlocks || C::kChunks == 2, "");
-    if (B <= (kTwoBlocks ? 64 : 32) && m.Ofrag && (int)gridDim.x == staged_plan(B, wg_per_xcd).S) {
+    // is cut into as many splits as there are workgroups (kMaxSplits), split = workgroup index.
+    static_assert(C::kLdsBytes >= C::kTerms * 2 * KS * 1024 + C::kWaves * 64 * 8, "LDS for two row blocks of the streaming form");
+    if (B <= 64) {
         if constexpr (C::kTerms == 2) {
-            if (!kTwoBlocks || B <= 32) outproj_stream_f32_body<1, FIXED, C::kWaves>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-            else outproj_stream_f32_body<2, FIXED, C::kWaves>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            if (B <= 32) outproj_stream_f32_body<1, FIXED, C::kWaves>(m, B, 0, (int)blockIdx.x, kMaxSplits, lds);
+            else outproj_stream_f32_body<2, FIXED, C::kWaves>(m, B, 0, (int)blockIdx.x, kMaxSplits, lds);
         } else {
-            if (B <= 32) outproj_stream_body<1, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
-            else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, (int)gridDim.x, lds);
+            if (B <= 32) outproj_stream_body<1, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, kMaxSplits, lds);
+            else outproj_stream_body<2, FIXED, C::kScaledD>(m, B, 0, (int)blockIdx.x, kMaxSplits, lds);
         }
         return;
     }
@@ -728,7 +727,8 @@ bool outproj_staged_supported(const ModelDev &m) {
 hipError_t launch_outproj_staged(const ModelDev &m, int rows, const int *B_dev, bool fixed_offset,
                                  SplitInfo *splits, hipStream_t stream) {
     // One workgroup per compute unit: 256 CUs in 8 XCDs.
-    const int wg_per_xcd = 32;
+    constexpr int wg_per_xcd = 32;
+    static_assert(kXcds * wg_per_xcd == kMaxSplits, "splits of the streaming form");
     *splits = SplitInfo{0, wg_per_xcd, m.Hp > 512 ? 0 : kStagedRows, kMaxSplits / kXcds, 0, 0};
     if (m.dtype != RNNLM_BF16) {
         *splits = staged_waves(true, m.Hp) == 4 ? SplitInfo{0, wg_per_xcd, -kStagedRows / 2, m.Vp, 0, 0} : SplitInfo{0, wg_per_xcd, kStagedRows, kMaxSplits / kXcds, 0, 0};
