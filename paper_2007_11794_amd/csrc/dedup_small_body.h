@@ -59,6 +59,21 @@ __device__ __forceinline__ void find_or_insert_lds(KeyPtr tkeys, int cap, const 
     }
 }
 
+// The same for one key of a thread.
+template <typename KeyPtr>
+__device__ __forceinline__ int find_or_insert_lds(KeyPtr tkeys, int cap, uint64_t key) {
+    if (key == kEmpty) return cap;
+    const uint32_t h = id_hash(key);
+    const int step = (int)(h >> 16) | 1;
+    int slot = (int)(h & (uint32_t)(cap - 1));
+    for (int probe = 0; probe < cap; ++probe) {
+        const unsigned long long old = atomicCAS(reinterpret_cast<unsigned long long *>(&tkeys[slot]), (unsigned long long)kEmpty, (unsigned long long)key);
+        if (old == kEmpty || old == key) return slot;
+        slot = (slot + step) & (cap - 1);
+    }
+    return -1;   // unreachable: the table is at most half full
+}
+
 // How many of n things, side by side, a thread of `threads` takes: 1, 2 or 4 (more threads do nothing instead), so that what they
 // read and write goes in whole vectors.  For n <= 4 * threads.
 __device__ __forceinline__ int per_thread(int n, int threads) { return n > 2 * threads ? 4 : n > threads ? 2 : 1; }

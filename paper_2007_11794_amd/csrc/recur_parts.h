@@ -93,41 +93,47 @@ constexpr int kGroupLdsBytes = (4 * kGroupedMax + 4) * 12 + kGroupedMax * 4;
 struct Nothing {
     __device__ __forceinline__ void operator()() const {}
 };
+// PER ids a thread, in code of its own for one: what is left out for the second is branches into lines of the program that are not there
+// yet.  Grouped steps, hierarchical layer, us, one body for both / this: bf16, H = 94, 20 ids 10.22 / 10.00, H = 128, 40 10.24 / 9.89, H = 1200,
+// 100 18.80 / 18.42, H = 512, 200 11.48 / 11.37; fp32, H = 256, 40 10.39 / 10.04; H = 512, 1000 ids 13.11 / 13.07.
 // meanwhile(): requests that do not hang on the groups, once the ids are there.
-template <class Meanwhile = Nothing>
-__device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, int *wsum, const int *&rep_out, Meanwhile meanwhile = Meanwhile()) {
-    constexpr int kPer = kGroupedMax / kRecurThreads, kCap = 4 * kGroupedMax;
+template <int PER, class Meanwhile>
+__device__ __forceinline__ int group_ids_of(const IdGroups &ids, int N, char *lds, int *wsum, const int *&rep_out, Meanwhile meanwhile) {
+    constexpr int kCap = 4 * kGroupedMax;
     uint64_t *tkeys = reinterpret_cast<uint64_t *>(lds);                  // [kCap + 1]
     int *tfirst = reinterpret_cast<int *>(tkeys + kCap + 4);              // [kCap + 1] min raw index, later the group number
     int *rep = tfirst + kCap + 4;                                         // [kGroupedMax]
-    static_assert(kGroupLdsBytes <= 64 * 1024, "fits the smallest ring");
-    const int tid = threadIdx.x, per = per_thread(N, kRecurThreads), n0 = tid * per;
-    uint64_t key[kPer];
-    load_some(ids.key, n0, per, N, key);
+    const int tid = threadIdx.x, n0 = tid * PER;
+    uint64_t key[PER];
+    load_some(ids.key, n0, PER, N, key);
     int cap = 64;                                                         // a power of two, at most half full, many ids a quarter
-    while (cap < (N <= kRecurThreads ? 2 : 4) * N) cap <<= 1;
+    while (cap < (PER == 1 ? 2 : 4) * N) cap <<= 1;
     constexpr u32x4 kFree = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, kNone = {0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu, 0x7FFFFFFFu};
     for (int i = tid; i < (cap + 4) / 2; i += kRecurThreads) reinterpret_cast<u32x4 *>(tkeys)[i] = kFree;      // while the keys are on their way
     for (int i = tid; i < (cap + 4) / 4; i += kRecurThreads) reinterpret_cast<u32x4 *>(tfirst)[i] = kNone;
     __syncthreads();
-    int slot[kPer];
-    find_or_insert_lds(tkeys, cap, key, slot, [&](int i) { return i < per && n0 + i < N; });
+    int slot[PER];
+    if constexpr (PER == 1) {
+        slot[0] = n0 < N ? find_or_insert_lds(tkeys, cap, key[0]) : -1;
+    } else {
+        find_or_insert_lds(tkeys, cap, key, slot, [&](int i) { return n0 + i < N; });
+    }
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
+    for (int i = 0; i < PER; ++i)
         if (slot[i] >= 0) atomicMin(&tfirst[slot[i]], n0 + i);
     __builtin_amdgcn_sched_barrier(0);                                    // (loads are awaited in order, and the ids are there)
     meanwhile();
     __syncthreads();
-    int is_first[kPer], mine = 0;
+    int is_first[PER], mine = 0;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         is_first[i] = (slot[i] >= 0 && tfirst[slot[i]] == n0 + i) ? 1 : 0;
         mine += is_first[i];
     }
     int total;
     int u = block_exclusive_scan(mine, wsum, total);                      // barriers inside: all first indices are read
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         if (is_first[i]) {
             rep[u] = n0 + i;
             tfirst[slot[i]] = u;
@@ -136,15 +142,20 @@ __device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, 
     }
     __syncthreads();
     if (blockIdx.x == 0) {
-        int group[kPer];
+        int group[PER];
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) group[i] = slot[i] >= 0 ? tfirst[slot[i]] : 0;
-        store_some(ids.inverse, n0, per, N, group);
+        for (int i = 0; i < PER; ++i) group[i] = slot[i] >= 0 ? tfirst[slot[i]] : 0;
+        store_some(ids.inverse, n0, PER, N, group);
         for (int i = tid; i < total; i += kRecurThreads) ids.rep[i] = rep[i];
         if (tid == 0) *ids.n_unique = total;
     }
     rep_out = rep;
     return total;
+}
+template <class Meanwhile = Nothing>
+__device__ __forceinline__ int group_ids(const IdGroups &ids, int N, char *lds, int *wsum, const int *&rep_out, Meanwhile meanwhile = Meanwhile()) {
+    static_assert(kGroupedMax == 2 * kRecurThreads && kGroupLdsBytes <= 64 * 1024, "one or two ids a thread; fits the smallest ring");
+    return N <= kRecurThreads ? group_ids_of<1>(ids, N, lds, wsum, rep_out, meanwhile) : group_ids_of<2>(ids, N, lds, wsum, rep_out, meanwhile);
 }
 
 }  // namespace rnnlm
