@@ -410,7 +410,6 @@ constexpr int ring_bytes(int elem, bool half) { return (half ? 64 : elem == 2 ? 
 
 // UNITS > 0 (the count is known on the device only, Hp <= UNITS): the whole form where it would be taken for a count known on the host, 32
 // units a workgroup while those fit the compute units in one round, then 64, bf16 models two workgroups of them side by side.
-__host__ __device__ inline int whole_rows(int Hp, int units, int rounds) { return 32 * kXcds * (rounds * kChipGroups / kXcds / (Hp / units)); }
 template <typename WT, int UNITS, int UB, bool VEC>
 __device__ __forceinline__ void whole_body(const ModelDev &m, int B, int b0, int j0, int source, const int32_t *row_dst,
                                            const int32_t *prev_word, const float *h_in, float *h_out, char *lds) {
@@ -470,7 +469,9 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
     }
     constexpr int kRing = ring_bytes(sizeof(WT), HALF);
     constexpr bool kSmallOnly = sizeof(WT) == 2 && !HALF;          // launches of at most small_rows(Hp, 1) rows
-    if (kSmallOnly || B <= small_rows(m.Hp, 2)) {      // uniform
+    constexpr bool kLargeOnly = sizeof(WT) == 2 && VEC && UNITS > 0;               // small_rows(Hp, 2) is whole_rows(Hp, 64, 2)
+    static_assert(!(kSmallOnly && kLargeOnly), "all rows have the whole form");
+    if (kSmallOnly || (!kLargeOnly && B <= small_rows(m.Hp, 2))) {                 // uniform
         if (bs >= B) return;
         const int j0 = (local % JS) * 64;
         if (m.Hp % 128 == 0)
@@ -513,10 +514,12 @@ template <typename WT, bool VEC, bool HALF>
 hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
                   const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
     auto go = [&](auto fn) { return fn(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream); };
-    if (B_dev && m.Wops && m.Hp <= 512 && (VEC || m.H >= 4)) {
-        if (m.Hp <= 128) return go(launch_ring<WT, VEC, HALF, 128>);
-        if (m.Hp <= 256) return go(launch_ring<WT, VEC, HALF, 256>);
-        return go(launch_ring<WT, VEC, HALF, 512>);
+    if constexpr (sizeof(WT) == 4 || HALF || !VEC) {          // (else all of a launch's rows have the whole form, in a kernel of its own)
+        if (B_dev && m.Wops && m.Hp <= 512 && (VEC || m.H >= 4)) {
+            if (m.Hp <= 128) return go(launch_ring<WT, VEC, HALF, 128>);
+            if (m.Hp <= 256) return go(launch_ring<WT, VEC, HALF, 256>);
+            return go(launch_ring<WT, VEC, HALF, 512>);
+        }
     }
     return go(launch_ring<WT, VEC, HALF, 0>);
 }

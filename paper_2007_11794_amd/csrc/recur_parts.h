@@ -9,7 +9,6 @@
 namespace rnnlm {
 
 constexpr int kRecurThreads = 512;
-constexpr int kChipGroups = 256;                     // workgroups in one round: one per compute unit
 
 struct Finish {                                       // where the results of one row go
     float *h_row;
@@ -87,7 +86,6 @@ __device__ __forceinline__ f32x4 plain_sum4(const float *w, int Hp, int units, c
 // unit and of the round trip of the count and the rows: step at V = 20000, H = 256, fp32, 256 ids 27.0 -> 25.2 us,
 // V = 65536, H = 512, bf16, 1024 ids 67.4 -> 66.9.  Workgroup 0 leaves the result for the kernels behind.
 // Returns the number of groups; representatives in LDS (valid until the ring is filled).
-constexpr int kGroupedMax = 1024;
 constexpr int kGroupLdsBytes = (4 * kGroupedMax + 4) * 12 + kGroupedMax * 4;
 
 struct Nothing {

@@ -1,5 +1,6 @@
 // Hidden update, launches in the whole form: see recur_whole.h.
 #include <algorithm>
+#include <type_traits>
 
 #include "recur_whole.h"
 
@@ -55,13 +56,16 @@ hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *
 template <typename WT, int UNITS>
 hipError_t launch_units(const ModelDev &m, bool wide, bool vec, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
                         const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
-    auto go = [&](auto fn) { return fn(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream); };
-    if (ids.key) {
-        if (wide) return vec ? go(launch<WT, UNITS, 2, true, true>) : go(launch<WT, UNITS, 2, false, true>);
-        return vec ? go(launch<WT, UNITS, 1, true, true>) : go(launch<WT, UNITS, 1, false, true>);
-    }
-    if (wide) return vec ? go(launch<WT, UNITS, 2, true, false>) : go(launch<WT, UNITS, 2, false, false>);
-    return vec ? go(launch<WT, UNITS, 1, true, false>) : go(launch<WT, UNITS, 1, false, false>);
+    auto go = [&](auto ub, auto aligned, auto group) -> hipError_t {
+        constexpr int UB = decltype(ub)::value;
+        constexpr bool VEC = decltype(aligned)::value, GROUP = decltype(group)::value;
+        if constexpr (recur_whole_exists(sizeof(WT) == 2, UNITS, 32 * UB, VEC, GROUP))
+            return launch<WT, UNITS, UB, VEC, GROUP>(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream);
+        else return hipErrorInvalidValue;
+    };
+    auto with_group = [&](auto ub, auto aligned) { return ids.key ? go(ub, aligned, std::true_type{}) : go(ub, aligned, std::false_type{}); };
+    auto with_rows = [&](auto ub) { return vec ? with_group(ub, std::true_type{}) : with_group(ub, std::false_type{}); };
+    return wide ? with_rows(std::integral_constant<int, 2>{}) : with_rows(std::integral_constant<int, 1>{});
 }
 
 }  // namespace
@@ -86,15 +90,21 @@ hipError_t launch_recur_whole(const ModelDev &m, int units, bool vec, int rows, 
                               const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream) {
     auto go = [&](auto fn) { return fn(m, units == 64, vec, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream); };
     if (m.dtype == RNNLM_BF16) {
-        if (m.Hp <= 128) return go(launch_units<bf16_t, 128>);
-        if (m.Hp <= 256) return go(launch_units<bf16_t, 256>);
-        if (m.Hp <= 512) return go(launch_units<bf16_t, 512>);
-        if (m.Hp <= 768) return go(launch_units<bf16_t, 768>);
-        return go(launch_units<bf16_t, 1024>);
+        switch (recur_whole_top(m.Hp)) {
+            case 128: return go(launch_units<bf16_t, 128>);
+            case 256: return go(launch_units<bf16_t, 256>);
+            case 512: return go(launch_units<bf16_t, 512>);
+            case 768: return go(launch_units<bf16_t, 768>);
+            case 1024: return go(launch_units<bf16_t, 1024>);
+            default: return hipErrorInvalidValue;
+        }
     }
-    if (m.Hp <= 128) return go(launch_units<float, 128>);
-    if (m.Hp <= 256) return go(launch_units<float, 256>);
-    return go(launch_units<float, 512>);
+    switch (recur_whole_top(m.Hp)) {
+        case 128: return go(launch_units<float, 128>);
+        case 256: return go(launch_units<float, 256>);
+        case 512: return go(launch_units<float, 512>);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace rnnlm

@@ -179,6 +179,7 @@ struct IdGroups {
     const uint64_t *key;                       // [rows] or null
     int32_t *rep, *inverse, *n_unique;         // as launch_dedup leaves them
 };
+constexpr int kGroupedMax = 1024;          // most of them
 bool recur_groups_ids(const ModelDev &m, int N);
 hipError_t launch_recur(const ModelDev &m, int rows, const int *B_dev, const int32_t *row_src,
                         const int32_t *row_dst, const int32_t *prev_word, const float *h_in,
@@ -188,12 +189,23 @@ bool recur_whole_supported(int dtype, int Hp);            // the model gets Wops
 int recur_whole_units(const ModelDev &m, int rows, bool vec, bool grouped);
 hipError_t launch_recur_whole(const ModelDev &m, int units, bool vec, int rows, const int *B_dev, const int32_t *row_src, const int32_t *row_dst,
                               const int32_t *prev_word, const float *h_in, float *h_out, const IdGroups &ids, hipStream_t stream);
+constexpr int kXcds = 8;           // workgroup id modulo 8 = the XCD (L2 domain) it runs on
+constexpr int kChipGroups = 256;   // workgroups in one round: one per compute unit
+// Rows for which workgroups of 32 rows and `units` units fit the chip in `rounds` rounds, a row block on one XCD.
+__host__ __device__ constexpr int whole_rows(int Hp, int units, int rounds) { return 32 * kXcds * (rounds * kChipGroups / kXcds / (Hp / units)); }
+// The largest padded hidden size of the kernel that takes Hp.
+constexpr int recur_whole_top(int Hp) { return Hp <= 128 ? 128 : Hp <= 256 ? 256 : Hp <= 512 ? 512 : Hp <= 768 ? 768 : 1024; }
+// Its kernels for hidden sizes up to `top`: where recur_whole_units, and the form for few units that comes in front of it, leave them any launch.
+constexpr bool recur_whole_exists(bool bf16, int top, int units, bool vec, bool grouped) {
+    if (units == 64 && !vec && top <= 512) return false;
+    if (grouped) return top > (bf16 ? 128 : 64) && (units == 32 || whole_rows(top, 32, 1) < kGroupedMax);
+    return bf16 || units == 64 || (!vec && top > 256);
+}
 
 constexpr int kStagedRows = 256;   // rows per workgroup of the staged kernel
 constexpr int kStagedWords = 32;   // words per LDS stage
 // Waves of the staged kernel's workgroups, its streaming form included: four where a row's two terms take the registers of two waves.
 constexpr int staged_waves(bool f32, int Hp) { return f32 && Hp > 320 ? 4 : 8; }
-constexpr int kXcds = 8;           // workgroup id modulo 8 = the XCD (L2 domain) it runs on
 constexpr size_t kAllL2s = (size_t)kXcds * 4 << 20;
 
 // Work split of an output-projection kernel for B rows on a grid of kXcds * wg_per_xcd workgroups.

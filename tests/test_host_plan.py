@@ -29,8 +29,9 @@ def test_work_split_arithmetic_on_the_host(tmp_path):
     check_on_the_host(tmp_path, "plan_check")
 
 
-def test_weights_read_ahead_in_the_order_of_their_reader(tmp_path):
+@pytest.mark.parametrize("name", ["ahead_check",      # weights read ahead in the order of their reader
+                                  "whole_check"])     # launches and kernels of the hidden update's whole form
+def test_dispatch_of_the_built_library(tmp_path, name):
     import paper_2007_11794_amd as rn
     rn.lib()                                   # (there, or it says so)
-    folder, file = os.path.split(rn.lib_path())
-    check_on_the_host(tmp_path, "ahead_check", [rn.lib_path(), "-Wl,-rpath," + folder])
+    check_on_the_host(tmp_path, name, [rn.lib_path(), "-Wl,-rpath," + os.path.dirname(rn.lib_path())])
