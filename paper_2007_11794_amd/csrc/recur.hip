@@ -411,12 +411,15 @@ constexpr int ring_bytes(int elem, bool half) { return (half ? 64 : elem == 2 ? 
 // UNITS > 0 (the count is known on the device only, Hp <= UNITS): the whole form where it would be taken for a count known on the host, 32
 // units a workgroup while those fit the compute units in one round, then 64, bf16 models two workgroups of them side by side.
 template <typename WT, int UNITS, int UB, bool VEC>
-__device__ __forceinline__ void whole_body(const ModelDev &m, int B, int b0, int j0, int source, const int32_t *row_dst,
+__device__ __forceinline__ void whole_body(const ModelDev &m, int B, int b0, int j0, const int32_t *row_src, const int32_t *row_dst,
                                            const int32_t *prev_word, const float *h_in, float *h_out, char *lds) {
     if (b0 >= B) return;                               // uniform
     RecurWhole<WT, UNITS, UB, VEC> t(b0, j0);
+    int source = min(b0 + t.col, B - 1);
+    if (row_src) source = row_src[source];
+    __builtin_amdgcn_sched_barrier(0);                 // (loads are awaited in order)
     t.request_weights(m);
-    t.request_rows(m, prev_word, h_in, t.real_rows(source, B));
+    t.request_rows(m, prev_word, h_in, source);
     t.run(m, B, row_dst, h_in, h_out, lds);
 }
 
@@ -435,11 +438,10 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, tid = threadIdx.x;
     const int JS = m.Hp / 64, JL = (m.Hp + 127) / 128;
     const int bs = (xcd + kXcds * (local / JS)) * 32, bl = (xcd + kXcds * (local / JL)) * 64;
-    // The rows to take are requested for all shapes beside the row count, not behind it (entries
-    // between the true count and `rows` are read and not used).  In the whole form by every wave, whose lanes l and l + 32 have row l.
-    const int JW = m.Hp / 32, bw = (xcd + kXcds * (local / JW)) * 32, in_block = UNITS > 0 ? tid & 31 : tid;
-    int source_s = bs + in_block, source_l = bl + tid, source_w = bw + in_block, B;
-    if (UNITS == 0 && ids.key) {                       // uniform
+    // The rows to take are requested for both shapes beside the row count, not behind it (entries
+    // between the true count and `rows` are read and not used).
+    int source_s = bs + tid, source_l = bl + tid, B;
+    if (ids.key) {                                     // uniform
         const int *rep;
         B = __builtin_amdgcn_readfirstlane(group_ids(ids, rows, lds, wsum, rep));
         if (tid < 64) {                                // (read before the barrier in front of the first load into the ring)
@@ -447,23 +449,20 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
             source_l = rep[min(bl + tid, B - 1)];
         }
     } else {
-        if (UNITS > 0 && row_src) {
-            source_w = row_src[min(source_w, rows - 1)];
-            source_s = row_src[min(source_s, rows - 1)];
-        }
         if (row_src && tid < 64) {
-            if (UNITS == 0) source_s = row_src[min(source_s, rows - 1)];
-            source_l = row_src[min(source_l, rows - 1)];
+            source_s = row_src[min(bs + tid, rows - 1)];
+            source_l = row_src[min(bl + tid, rows - 1)];
         }
         B = B_dev ? *B_dev : rows;
     }
     if constexpr (UNITS > 0) {
         if (B <= whole_rows(m.Hp, 32, 1)) {            // uniform
-            whole_body<WT, UNITS, 1, VEC>(m, B, bw, local % JW * 32, source_w, row_dst, prev_word, h_in, h_out, lds);
+            const int JW = m.Hp / 32;
+            whole_body<WT, UNITS, 1, VEC>(m, B, (xcd + kXcds * (local / JW)) * 32, local % JW * 32, row_src, row_dst, prev_word, h_in, h_out, lds);
             return;
         }
         if (VEC && B <= whole_rows(m.Hp, 64, sizeof(WT) == 2 ? 2 : 1)) {
-            whole_body<WT, UNITS, 2, VEC>(m, B, bs, local % JS * 64, source_s, row_dst, prev_word, h_in, h_out, lds);
+            whole_body<WT, UNITS, 2, VEC>(m, B, bs, local % JS * 64, row_src, row_dst, prev_word, h_in, h_out, lds);
             return;
         }
     }

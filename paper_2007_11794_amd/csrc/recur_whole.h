@@ -65,9 +65,6 @@ struct RecurWhole {
         rs = load4(m.half_rowsum_W + je);
     }
 
-    // The rows of the block out of a list whose entries from B > b0 on are stale: the last real one stands for them.
-    __device__ __forceinline__ int real_rows(int source, int B) const { return B - b0 < 32 ? __shfl(source, min(col, B - 1 - b0), 64) : source; }
-
     // source: the row of h_in and prev_word to take for row b0 + col
     __device__ __forceinline__ void request_rows(const ModelDev &m, const int32_t *prev_word, const float *h_in, int source) {
         src = source;

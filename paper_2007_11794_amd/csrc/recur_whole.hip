@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kRecurThreads) void recur_whole_kernel(
         if (t.b0 >= B) return;
         __builtin_amdgcn_sched_barrier(0);                               // (loads are awaited in order)
         t.request_weights(m);
-        source = t.real_rows(source, B);
+        if (row_src && B - t.b0 < 32) source = __shfl(source, min(t.lane & 31, B - 1 - t.b0), 64);   // entries from B on are stale
     }
     t.request_rows(m, prev_word, h_in, source);
     t.run(m, B, row_dst, h_in, h_out, lds);
