@@ -438,10 +438,12 @@ __global__ __launch_bounds__(kThreads) void recur_kernel(
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, tid = threadIdx.x;
     const int JS = m.Hp / 64, JL = (m.Hp + 127) / 128;
     const int bs = (xcd + kXcds * (local / JS)) * 32, bl = (xcd + kXcds * (local / JL)) * 64;
-    // The rows to take are requested for both shapes beside the row count, not behind it (entries
-    // between the true count and `rows` are read and not used).
+    // The ring's rows to take are requested for both shapes beside the row count, not behind it (entries
+    // between the true count and `rows` are read and not used).  The whole form asks for its own behind it: asked by every wave beside
+    // the count, for 32 and 64 units a workgroup, the same launches took as long or longer (steps with the hierarchical layer, us, behind /
+    // beside: 4096 ids, bf16, H = 512, 1229 distinct 21.63 / 21.58, 410 17.35 / 17.41; H = 256, 1229 16.71 / 16.80, fp32 19.12 / 19.27).
     int source_s = bs + tid, source_l = bl + tid, B;
-    if (ids.key) {                                     // uniform
+    if (UNITS == 0 && ids.key) {                       // uniform (with the count on the device the ids are grouped already)
         const int *rep;
         B = __builtin_amdgcn_readfirstlane(group_ids(ids, rows, lds, wsum, rep));
         if (tid < 64) {                                // (read before the barrier in front of the first load into the ring)
