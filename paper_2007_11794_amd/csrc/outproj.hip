@@ -238,7 +238,7 @@ static Bf16Kernel choose_bf16(const ModelDev &m, int rows, bool fixed_offset, in
     return kBf16Plain;
 }
 
-// The same for fp32 models (the first two-term form goes by the second's name).  Infinite weights are for the plain kernel.
+// The same for fp32 models.  Infinite weights are for the plain kernel.
 enum F32Kernel { kF32Stream, kF32Staged, kF32Split2, kF32Tiled, kF32Plain };
 static F32Kernel choose_f32(const ModelDev &m, int rows, int kernel_choice) {
     if (stream_choice(m, rows, kernel_choice)) return kF32Stream;
@@ -300,7 +300,7 @@ const char *outproj_kernel_name(const ModelDev &m, int rows, bool fixed_offset, 
     }
     switch (choose_f32(m, rows, kernel_choice)) {
         case kF32Stream: return "outproj_stream_kernel";
-        case kF32Staged:
+        case kF32Staged: return "outproj_staged_f32_kernel";
         case kF32Split2: return "outproj_split2_kernel";
         case kF32Tiled: return "outproj_tiled_kernel";
         default: return "outproj_plain_f32_kernel";
@@ -330,7 +330,8 @@ hipError_t launch_outproj(const ModelDev &m, int rows, const int *B_dev, bool fi
     } else {
         // fp32 on the fp16 matrix cores through a two-term split of both operands (three fp16 products per
         // fp32 product at sixteen times the fp32 matrix rate, same accuracy): weight streaming for few
-        // rows, the tiled two-term kernel from 64 rows on.  The tiled fp32-MFMA kernel only on request.
+        // rows; from 64 rows on the staged kernel, its rows in registers, for 128 to 576 padded units, and the tiles of the
+        // two-term kernel for the others.  The tiled fp32-MFMA kernel only on request.
         const F32Kernel which = choose_f32(m, rows, kernel_choice);
         if (which == kF32Stream) return launch_outproj_stream(m, rows, B_dev, fixed_offset, splits, stream);
         if (which == kF32Staged) return launch_outproj_staged(m, rows, B_dev, fixed_offset, splits, stream);

@@ -695,9 +695,8 @@ template <int HP, bool FIXED>
 __global__ __launch_bounds__((StagedCfg<bf16_t, HP>::kThreads)) void outproj_staged_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
     staged_kernel<bf16_t, HP, FIXED>(m, rows, B_dev, wg_per_xcd);
 }
-// (the two-term form of fp32 models goes by one name, whether the rows come through LDS or sit in registers)
 template <int HP, bool FIXED>
-__global__ __launch_bounds__((StagedCfg<float, HP>::kThreads)) void outproj_split2_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
+__global__ __launch_bounds__((StagedCfg<float, HP>::kThreads)) void outproj_staged_f32_kernel(ModelDev m, int rows, const int *__restrict__ B_dev, int wg_per_xcd) {
     staged_kernel<float, HP, FIXED>(m, rows, B_dev, wg_per_xcd);
 }
 
@@ -712,7 +711,7 @@ hipError_t launch_hp(const ModelDev &m, int rows, const int *B_dev, bool fixed_o
         return hipGetLastError();
     };
     if constexpr (C::kTerms == 2)
-        return fixed_offset ? launch(outproj_split2_kernel<HP, true>, limit[1]) : launch(outproj_split2_kernel<HP, false>, limit[0]);
+        return fixed_offset ? launch(outproj_staged_f32_kernel<HP, true>, limit[1]) : launch(outproj_staged_f32_kernel<HP, false>, limit[0]);
     else
         return fixed_offset ? launch(outproj_staged_kernel<HP, true>, limit[1]) : launch(outproj_staged_kernel<HP, false>, limit[0]);
 }

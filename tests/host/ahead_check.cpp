@@ -27,11 +27,9 @@ int main() {
                         const WeightsAhead a = outproj_weights_ahead(m, rows, fixed != 0, choice);
                         int want = 0;                          // 0: nothing is read ahead
                         if ((size_t)m.Vp * Hp * (dtype == RNNLM_BF16 ? 2 : 4) > kAllL2s) {
-                            const bool tiles = strcmp(kernel, "outproj_split2_kernel") == 0 && (choice == 4 || Hp < 128 || Hp > 576);
-                            const bool staged = !tiles && (strcmp(kernel, "outproj_split2_kernel") == 0 || strncmp(kernel, "outproj_staged", 14) == 0);
                             if (strcmp(kernel, "outproj_stream_kernel") == 0 || strcmp(kernel, "outproj_rowstream_kernel") == 0) want = 8;
-                            if (tiles) want = 4;
-                            if (staged) want = staged_waves(dtype != RNNLM_BF16, Hp);
+                            if (strcmp(kernel, "outproj_split2_kernel") == 0) want = 4;
+                            if (strncmp(kernel, "outproj_staged", 14) == 0) want = staged_waves(dtype != RNNLM_BF16, Hp);
                         }
                         if ((a.splits > 0) != (want > 0) || (want > 0 && (a.waves != want || a.splits != kMaxSplits || a.block_kb * 1024 != 32 * Hp * (dtype == RNNLM_BF16 ? 2 : 4)))) {
                             printf("FAILED dtype %d Hp %d rows %d fixed %d choice %d (%s): %d waves in %d splits, blocks of %d KB; %d waves wanted\n", dtype, Hp, rows, fixed, choice,

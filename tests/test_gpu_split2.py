@@ -76,8 +76,8 @@ def test_a_word_masked_by_an_infinite_weight(V, H, B):
     m.close()
 
 
-# both terms of 64 and of 32 rows in LDS, one term of 32 rows, neither; rows around what each takes; a vocabulary of fewer
-# blocks of 32 words than there are workgroups, one with a remainder
+# The tiles (on request where the rows fit the registers): both terms of 64 and of 32 rows in LDS, one term of 32 rows, neither; rows
+# around what each takes; a vocabulary of fewer blocks of 32 words than there are workgroups, one with a remainder
 @pytest.mark.parametrize("V,H,N,unique", [(300, 64, 300, 1), (9000, 256, 1024, 64), (9000, 256, 1024, 65), (20011, 320, 513, 32),
                                           (20011, 320, 513, 33), (9000, 576, 300, 31), (9000, 640, 300, 32), (9000, 832, 300, 20),
                                           (9000, 832, 300, 40), (3000, 1024, 300, 9), (66000, 900, 513, 32), (3000, 1300, 300, 9)])
@@ -90,18 +90,21 @@ def test_few_rows_known_on_the_device_only(V, H, N, unique):
     query = rng.integers(0, V, (N, 2)).astype(np.int32)
     ref = oracle.step(model, prev[:unique], h_in[:unique], query, row_of_query=src.astype(np.int32))
     tol = 1e-5 + 2.0 ** -24 * np.sqrt(H) * 0.5 * np.abs(model["O"]).sum(0).max()                 # as above
-    assert m.outproj_kernel_name(N) == "outproj_split2_kernel"
-    for lse_mode in (0, 1):
-        m.set_option(rn.OPT_LSE_MODE, lse_mode)
-        out = gpu_step_dedup(m, src.astype(np.uint64) + 5, prev, h_in, query)
-        assert out["n_unique"] == unique and np.max(np.abs(out["logprob"] - ref["logprob"])) <= tol
+    for kernel in (0, 4):
+        m.set_option(rn.OPT_OUTPROJ_KERNEL, kernel)
+        in_registers = kernel == 0 and 64 < H <= 576
+        assert m.outproj_kernel_name(N) == ("outproj_staged_f32_kernel" if in_registers else "outproj_split2_kernel")
+        for lse_mode in (0, 1):
+            m.set_option(rn.OPT_LSE_MODE, lse_mode)
+            out = gpu_step_dedup(m, src.astype(np.uint64) + 5, prev, h_in, query)
+            assert out["n_unique"] == unique and np.max(np.abs(out["logprob"] - ref["logprob"])) <= tol
     assert m.last_error() == 0
     m.close()
 
 
 @pytest.mark.parametrize("V", [2, 300, 1100])
 def test_more_row_groups_than_workgroups(V):
-    """Workgroups take several row groups, of vocabulary splits that hold no word at all where there are few."""
+    """Workgroups take several row groups, of vocabulary splits that hold no word at all where there are few (64 units: the tiles)."""
     H, B = 64, 9000
     rng = np.random.default_rng(V)
     model = model_of(rng, V, H, 1.0)

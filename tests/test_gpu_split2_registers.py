@@ -32,6 +32,7 @@ def test_against_the_oracle_and_the_other_form(V, H, B):
         by_form = []
         for kernel in (0, 4):
             m.set_option(rn.OPT_OUTPROJ_KERNEL, kernel)
+            assert m.outproj_kernel_name(B) == ("outproj_split2_kernel" if kernel else "outproj_staged_f32_kernel")
             h, lp = gpu_step(m, prev, h_in, query)
             assert np.max(np.abs(h - ref["h_out"])) <= 1e-5
             assert np.max(np.abs(lp - ref["logprob"])) <= tol, (kernel, lse_mode)
@@ -63,6 +64,7 @@ def test_maximum_moves_between_blocks(V, H, B, shape):
     model["bias"] = bias
     m = load_model(model, "f32", B)
     m.set_option(rn.OPT_LSE_MODE, 1)
+    assert m.outproj_kernel_name(B) == "outproj_staged_f32_kernel"
     prev, h_in = rng.integers(0, V, B).astype(np.int32), rng.uniform(0, 1, (B, H)).astype(np.float32)
     query = rng.choice(np.flatnonzero(~masked), (B, 2)).astype(np.int32)
     h, lp = gpu_step(m, prev, h_in, query)
