@@ -21,12 +21,15 @@ constexpr int kSplit2Operand = 2048;           // bytes of one two-term fp16 ope
 constexpr int kSplit2DExp = 14;                // fp32 models: the centred hidden vector times 2^14 in dfrag
 constexpr float kLn2 = 0.6931471805599453f;
 
-// Device-side view of a loaded model (all pointers are device pointers).
+// Device-side view of a loaded model (all pointers are device pointers).  It is an argument of every kernel, which fetches from it in front
+// of everything else, by lines of 64 bytes: no holes but behind single floats, and the weights of the hidden update in the first line.  With a
+// pointer more in front of half_rowsum_W, us: tree of 1000000 words, H = 128, 64 rows 7.72 -> 7.84; 109192 words, H = 92, 143 rows 7.31 -> 7.45.
 struct ModelDev {
     int V, H;
     int Hp;            // H rounded up to a multiple of 64; padded weights are zero
     int Vp;            // V rounded up to a multiple of 256; padded rows of Ot are zero
     int dtype;
+    int hs_max_len;    // hierarchical output layer: longest path
     const void *U;     // [V][Hp]
     const void *W;     // [Hp rounded up to 128][Hp], W[j][i]
     const void *Ot;    // [Vp][Hp], Ot[v][j] = O[j][v]
@@ -34,9 +37,6 @@ struct ModelDev {
     // 32 g + c of fragment (blk, ks) holds unit 32 blk + c, inputs 16 ks + 8 g .. + 7; fp32: [Hp / 32][Hp / 16][2][64 lanes][4], the
     // first and the last four of those eight.
     const void *Wfrag;
-    // W in MFMA-operand order as bf16 terms (one of bf16 models, the same as Wfrag there; three of fp32 models) for the whole form of the
-    // hidden update (recur_whole_supported), else null: [Hp / 32][Hp / 16][terms][64 lanes][8].
-    const void *Wops;
     const float *half_rowsum_W;   // [Hp]  0.5 * sum_i W[j][i]
     const float *bias;            // [V]
     const float *half_colsum_O;   // [V]   0.5 * sum_j O[j][v]
@@ -58,7 +58,9 @@ struct ModelDev {
     const void *Theta;            // [V-1][Hp] node vectors, weights' type, zero-padded
     const int32_t *path_off;      // [V+1]
     const int32_t *path_entry;    // [path_off[V]] node | code bit << 31, root first
-    int hs_max_len;               // longest path
+    // W in MFMA-operand order as bf16 terms (one of bf16 models, the same as Wfrag there; three of fp32 models) for the whole form of the
+    // hidden update (recur_whole_supported), else null: [Hp / 32][Hp / 16][terms][64 lanes][8].
+    const void *Wops;
     // scratch
     void *d;           // [max_Bp][Hp]  h' - 0.5 in the weights' type
     // The same block in the order the output projection reads it as an MFMA operand.  bf16 models: times

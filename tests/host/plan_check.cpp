@@ -1,6 +1,7 @@
 // Host-side check of the work-split arithmetic the output-projection kernels and the kernels behind
 // them share (plan_rows, splits_of in the library's internal header): compiled for the host only and
 // run by tests/test_host_plan.py.  Prints "ok" or the first violated property.
+#include <stddef.h>
 #include <stdio.h>
 
 #include <vector>
@@ -96,6 +97,9 @@ int main() {
                     for (int n : seen) REQUIRE(n == 1, "blocks=%d hp=%d split=%d: a piece is left out", blocks, hp, split);
                 }
             }
+    // the model as an argument of the kernels: what the hidden update asks for first in the first line, nothing in lines further on than it has to be
+    REQUIRE(offsetof(ModelDev, half_rowsum_W) + sizeof(void *) <= 64, "half_rowsum_W at %d", (int)offsetof(ModelDev, half_rowsum_W));
+    REQUIRE(sizeof(ModelDev) == 8 * sizeof(int) + 2 * 2 * sizeof(float) + 21 * sizeof(void *), "ModelDev has %d bytes", (int)sizeof(ModelDev));
     printf("ok\n");
     return 0;
 }
