@@ -517,9 +517,12 @@ hipError_t launch(const ModelDev &m, int rows, const int *B_dev, const int32_t *
     auto go = [&](auto fn) { return fn(m, rows, B_dev, row_src, row_dst, prev_word, h_in, h_out, ids, stream); };
     if constexpr (sizeof(WT) == 4 || HALF || !VEC) {          // (else all of a launch's rows have the whole form, in a kernel of its own)
         if (B_dev && m.Wops && m.Hp <= 512 && (VEC || m.H >= 4)) {
-            if (m.Hp <= 128) return go(launch_ring<WT, VEC, HALF, 128>);
-            if (m.Hp <= 256) return go(launch_ring<WT, VEC, HALF, 256>);
-            return go(launch_ring<WT, VEC, HALF, 512>);
+            switch (recur_whole_top(m.Hp)) {
+                case 128: return go(launch_ring<WT, VEC, HALF, 128>);
+                case 256: return go(launch_ring<WT, VEC, HALF, 256>);
+                case 384: return go(launch_ring<WT, VEC, HALF, 384>);
+                default: return go(launch_ring<WT, VEC, HALF, 512>);
+            }
         }
     }
     return go(launch_ring<WT, VEC, HALF, 0>);

@@ -93,8 +93,11 @@ hipError_t launch_recur_whole(const ModelDev &m, int units, bool vec, int rows, 
         switch (recur_whole_top(m.Hp)) {
             case 128: return go(launch_units<bf16_t, 128>);
             case 256: return go(launch_units<bf16_t, 256>);
+            case 384: return go(launch_units<bf16_t, 384>);
             case 512: return go(launch_units<bf16_t, 512>);
+            case 640: return go(launch_units<bf16_t, 640>);
             case 768: return go(launch_units<bf16_t, 768>);
+            case 896: return go(launch_units<bf16_t, 896>);
             case 1024: return go(launch_units<bf16_t, 1024>);
             default: return hipErrorInvalidValue;
         }
@@ -102,6 +105,7 @@ hipError_t launch_recur_whole(const ModelDev &m, int units, bool vec, int rows, 
     switch (recur_whole_top(m.Hp)) {
         case 128: return go(launch_units<float, 128>);
         case 256: return go(launch_units<float, 256>);
+        case 384: return go(launch_units<float, 384>);
         case 512: return go(launch_units<float, 512>);
         default: return hipErrorInvalidValue;
     }

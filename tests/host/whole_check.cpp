@@ -31,7 +31,8 @@ int main() {
                         const bool one_round = (Hp / 32) * ((rows + 31) / 32) <= kChipGroups;
                         if (!grouped && one_round && (bf16 ? Hp == 128 && !vec : Hp <= 256 || vec || rows <= 16)) continue;
                         const int top = recur_whole_top(Hp);
-                        if (top < Hp) return printf("FAILED Hp %d: kernels up to %d\n", Hp, top), 1;
+                        // (a kernel requests the weights of all k-steps up to its largest size)
+                        if (top < Hp || top >= Hp + 128) return printf("FAILED Hp %d: kernels up to %d\n", Hp, top), 1;
                         if (!recur_whole_exists(bf16, top, units, vec, grouped))
                             return printf("FAILED %s Hp %d rows %d vec %d grouped %d: no kernel with %d units\n", bf16 ? "bf16" : "fp32", Hp, rows, vec, grouped, units), 1;
                         met.insert({bf16, top, units, vec, grouped});

@@ -22,8 +22,8 @@ def check(m, model, dtype, H, prev, h_in, out, rows):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("H,B", [(1, 5), (3, 40), (4, 33), (5, 31), (6, 64), (7, 65), (129, 97), (254, 1025), (256, 1024), (256, 1025), (257, 32), (320, 700),
-                                 (509, 513), (511, 1), (512, 513), (512, 1025), (512, 2048), (512, 2049), (513, 260), (766, 257), (767, 300), (768, 512),
+@pytest.mark.parametrize("H,B", [(1, 5), (3, 40), (4, 33), (5, 31), (6, 64), (7, 65), (129, 97), (254, 1025), (256, 1024), (256, 1025), (257, 32), (320, 700), (384, 512), (384, 641),
+                                 (509, 513), (511, 1), (512, 513), (512, 1025), (512, 2048), (512, 2049), (513, 260), (766, 257), (767, 300), (768, 512), (640, 256), (638, 769), (640, 768), (770, 513), (896, 250),
                                  (1021, 129), (1024, 257), (1024, 513)])
 def test_rows_known_on_the_host(H, B, dtype):
     rng = np.random.default_rng(H * 5000 + B)
