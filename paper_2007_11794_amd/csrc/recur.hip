@@ -419,7 +419,7 @@ __device__ __forceinline__ void whole_body(const ModelDev &m, int B, int b0, int
     if (row_src) source = row_src[source];
     __builtin_amdgcn_sched_barrier(0);                 // (loads are awaited in order)
     t.request_weights(m);
-    t.request_rows(m, prev_word, h_in, source);
+    t.request_rows(m, prev_word, h_in, source, B);
     t.run(m, B, row_dst, h_in, h_out, lds);
 }
 

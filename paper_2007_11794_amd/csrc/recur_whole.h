@@ -65,21 +65,35 @@ struct RecurWhole {
         rs = load4(m.half_rowsum_W + je);
     }
 
-    // source: the row of h_in and prev_word to take for row b0 + col
-    __device__ __forceinline__ void request_rows(const ModelDev &m, const int32_t *prev_word, const float *h_in, int source) {
+    __device__ __forceinline__ void request_row(const ModelDev &m, const float *h_in, int r) {
+        const float *row = h_in + (size_t)__builtin_amdgcn_readlane(src, wave + 8 * r) * m.H;
+#pragma unroll
+        for (int q = 0; q < kPieces; ++q) {
+            const int k = 256 * q + 4 * lane;
+            if (256 * q < m.H) {                                         // uniform
+                if (VEC) x[r][q] = *reinterpret_cast<const f32x4 *>(row + (k < m.H ? k : 0));
+                else __builtin_memcpy(&x[r][q], row + min(k, m.H - 4), 16);
+            }
+        }
+    }
+    // source: the row of h_in and prev_word to take for row b0 + col, of B > b0.  Rows that are not there are not requested: a request
+    // takes its time on the compute unit's way to its caches, whatever it hits.  Us, 32 rows requested / those there are, steps with the
+    // hierarchical layer, bf16, 1 row: H = 256 7.05 / 6.93, 384 7.74 / 7.41, 512 8.59 / 8.32, 640 10.44 / 9.75, 768 10.60 / 9.99, 1024 11.44 / 10.77; 8
+    // rows, H = 512 9.11 / 8.86.
+    __device__ __forceinline__ void request_rows(const ModelDev &m, const int32_t *prev_word, const float *h_in, int source, int B) {
         src = source;
         prev = prev_word[src];
+        if (b0 + wave + 8 * (kRows - 1) < B) {                                                // uniform
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const float *row = h_in + (size_t)__builtin_amdgcn_readlane(src, wave + 8 * r) * m.H;
+            for (int r = 0; r < kRows; ++r) request_row(m, h_in, r);
+        } else {
 #pragma unroll
-            for (int q = 0; q < kPieces; ++q) {
-                const int k = 256 * q + 4 * lane;
-                if (256 * q < m.H) {                                     // uniform
-                    if (VEC) x[r][q] = *reinterpret_cast<const f32x4 *>(row + (k < m.H ? k : 0));
-                    else __builtin_memcpy(&x[r][q], row + min(k, m.H - 4), 16);
-                }
+            for (int r = 0; r < kRows; ++r) {
+#pragma unroll
+                for (int q = 0; q < kPieces; ++q) x[r][q] = f32x4{};
+                if (b0 + wave + 8 * r < B) request_row(m, h_in, r);
             }
+            __builtin_amdgcn_s_waitcnt(0x0f70);                          // vmcnt(0), seen by the compiler: what it counts below are the loads above
         }
     }
 

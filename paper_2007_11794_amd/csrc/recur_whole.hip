@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kRecurThreads) void recur_whole_kernel(
         t.request_weights(m);
         if (row_src && B - t.b0 < 32) source = __shfl(source, min(t.lane & 31, B - 1 - t.b0), 64);   // entries from B on are stale
     }
-    t.request_rows(m, prev_word, h_in, source);
+    t.request_rows(m, prev_word, h_in, source, B);
     t.run(m, B, row_dst, h_in, h_out, lds);
 }
 
