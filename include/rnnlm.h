@@ -70,11 +70,13 @@ enum rnnlm_option {
     /* Which output-projection kernel: 0 = automatic (default), 1 = the plain any-shape
      * kernel, 2 = the LDS-staged kernel with the hidden block held in registers (bf16;
      * on request only for H up to 128, 193 to 256 and 449 to 512; by itself the library takes it for
-     * every H up to 704, from 128 rows on), 3 = the LDS-tiled kernel for any hidden size and both types,
+     * every H up to 704, from 128 rows on, and its form for fp32 models, which no value asks for, for H from
+     * 65 to 576, from 64 rows on), 3 = the LDS-tiled kernel for any hidden size and both types,
      * 4 = (fp32 models) the LDS-tiled kernel on a two-term fp16 split of both operands (every word's weights scaled by a
      * power of two; operands good to 2^-23, a product to 2^-21 of itself, sums in fp32: errors as of fp32
      * products unless a sum is dominated by one term) at fp16 matrix-core speed: the automatic choice for fp32 from 64 rows
-     * on unless an output weight is infinite (then 1 is, at any number of rows), 5 = the weight-streaming kernel for few rows, which reads the operand-ordered copy of the
+     * on for H up to 64 and beyond 576 (between them the staged kernel computes the same sums), unless an output weight is
+     * infinite (then 1 is, at any H and number of rows), 5 = the weight-streaming kernel for few rows, which reads the operand-ordered copy of the
      * output weights once per launch at memory speed (fp32 models: the same two fp16 terms):
      * the automatic choice up to 64 rows when two launches suffice (the staged, row-streaming,
      * eight-wave tiled and two-term kernels also take it on the device, when a grouped or

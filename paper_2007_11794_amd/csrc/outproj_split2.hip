@@ -17,7 +17,8 @@
 // Bound by the matrix pipe at the clock the chip holds under it: 308 -> 163 to 173 us,
 // as the clock allows (1.26 PFLOP/s of fp16 products), V = 20000, H = 256, 256 rows 20.5 -> 12.3 us.
 //
-// Padded hidden sizes of 128 to 576 take the form in outproj_staged.hip, rows in registers (figures there); this one on request.
+// Padded hidden sizes of 128 to 576 take the form in outproj_staged.hip, rows in registers (figures there); this one on request, so
+// the figures of such sizes here and below are of option 4.
 //
 // Layout: both operands are kept as MFMA operands (ModelDev::Ofrag, dfrag), so 32 words x 16 units x 2
 // terms are 2 KB contiguous, global memory -> LDS -> register without any rearrangement, and every LDS

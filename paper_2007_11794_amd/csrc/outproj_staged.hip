@@ -1,12 +1,12 @@
 // Output projection + log-sum-exp, LDS-staged MFMA kernel: bf16 models with Hp <= 704, fp32 models with Hp <= 576 (multiples of 64 from 128 on).
 //
 // What is computed is the same as in the plain kernel (normalising over all words of the
-// vocabulary, Section 2.1 of the paper); this is the fast form for batches of >= 128 rows.
+// vocabulary, Section 2.1 of the paper); this is the fast form for batches of >= 128 rows (fp32 models: >= 64).
 //
 // Shape of the work.  The hidden block d = h' - 1/2 is tiny (rows x Hp bf16, 1 MB at
 // 1024 x 512) and the output weights are large (64 MB at V = 65536), so the
 // weights are streamed exactly once per row group and the hidden block never moves:
-//   - a workgroup (8 waves) owns 256 rows; each wave keeps ITS 32 rows of d for the whole
+//   - a workgroup (8 waves; fp32 models beyond Hp = 320 four, and half of the rows) owns 256 rows; each wave keeps ITS 32 rows of d for the whole
 //     reduction length in registers (Hp/16 MFMA B-operands, 128 VGPRs at Hp = 512), loaded from
 //     the fragment-ordered copy of the block (one operand = 1 KB contiguous);
 //   - the weights of 32 words (32 x Hp bf16, 32 KB at Hp = 512) form one LDS stage; four
@@ -62,7 +62,8 @@
 // V = 60000, H = 448, 4000 566 / 499; V = 50000, H = 570, 300 63 / 53; V = 3000, H = 512, 1000 17.7 / 12.6.  Beyond 576 registers spill.  Up to 64 rows, known on the
 // device only, the streaming body has eight waves here, four there: V = 20000, H = 256, 32 rows 5.1 / 5.4, 64 6.8 / 7.3; V = 50000, H = 300, 50
 // rows 17.7 / 14.7; V = 3000, H = 128, 32 rows 3.9 / 3.7;
-// V = 65536, H = 512, 32 rows 23.9 / 23.8, 64 31.4 / 26.0; V = 20000, H = 512, 20 rows 9.3 / 9.5.
+// V = 65536, H = 512, 32 rows 23.9 / 23.8, 64 31.4 / 26.0; V = 20000, H = 512, 20 rows 9.3 / 9.5.  (Beyond the L2s at Hp = 128 too: whole steps of 130
+// ids, 4 of them distinct, V = 80000 19.6 / 20.0, V = 150000 25.2 / 25.5.  With four of the eight waves here it was the same or slower.)
 //
 // When the batch turns out to hold at most 64 rows (the count may be known on the device only),
 // the kernel runs the weight-streaming body instead (outproj_stream_body.h): see the top of

@@ -28,8 +28,8 @@
 //          once for two blocks of units, and reading, converting and multiplying overlap between the waves
 //          (with 32 x 32 per wave over the whole reduction H = 1024, 3000 rows took 43 us instead of 30).
 // Models of few units have a third, in kernels of its own (recur_few_units_f32_kernel, recur_few_units_bf16_kernel), and where the
-// whole of a workgroup's operands fits registers and LDS and its workgroups the compute units there is a fourth (recur_whole.h): the
-// figures below are of sizes some of which it has taken over.
+// whole of a workgroup's operands fits registers and LDS and its workgroups the compute units there is a fourth (recur_whole.h), which of
+// the sizes below has taken over bf16 H = 512, H = 650 and fp32 H = 512 with 1024 rows: what stands there are the ring's times.
 // Launches of bf16 models that fit one small workgroup per compute unit use a whole unit's LDS as the ring (128 KB, all
 // but one stage in flight), larger ones half of it, two workgroups per unit; fp32 models always the whole one.
 // Measured, us per launch (rows in brackets), before and after, the kernels before being one tiled and one

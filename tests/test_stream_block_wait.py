@@ -33,7 +33,7 @@ def test_the_scan_counts():
 
 
 # source, waits in it: one per instance of the streaming form
-@pytest.mark.parametrize("source,waits", [("outproj_stream.hip", 12), ("outproj_staged.hip", 40), ("outproj_tiled.hip", 8),
+@pytest.mark.parametrize("source,waits", [("outproj_stream.hip", 12), ("outproj_staged.hip", 72), ("outproj_tiled.hip", 8),
                                           ("outproj_rowstream.hip", 2), ("outproj_split2.hip", 12)])
 def test_enough_younger_loads(source, waits, tmp_path):
     out = str(tmp_path / "kernel.s")
